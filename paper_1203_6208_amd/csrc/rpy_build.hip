@@ -1,6 +1,7 @@
 // rpy_build.hip -- wrapping, Fourier phase tables and the real-space tiles
 // of the diffusion matrix (eq. DF / DFmodified of arXiv:1203.6208).
 #include "rpy_internal.h"
+#include "rpy_pairs.h"
 
 namespace rpy {
 
@@ -77,6 +78,8 @@ __device__ inline uint16_t to_bf16(double d)
     return (uint16_t)(u >> 16);
 }
 
+// The erfc / exp form, for parameters outside the polynomial form's range
+// (make_smooth_coef).
 // One workgroup per stored tile (I <= J).  Wave w takes the bead rows
 // bi = w + 4 s (s = 0..15), its 64 lanes the bead columns bj, so each step
 // computes 64 pair blocks (I*64 + bi, J*64 + bj) over their periodic images.
@@ -216,10 +219,91 @@ __global__ __launch_bounds__(256) void k_build_tiles(int N, const int2 *__restri
     }
 }
 
+// The same tiles by the polynomial pair form (rpy_pairs.h): workgroup b takes
+// the row part b % nsplit of tile b / nsplit, its 4 waves ngroups groups of
+// rows each (4 ngroups PAIR_GROUP nsplit = 64).  N = 4000, FP64: 202 -> 93 us
+// against the erfc form, of which the 396 MB of tiles take about 80 us at the
+// rate of a large fill; the vector units are no longer what bounds it.
+// STREAM: non-temporal FP64 stores, for arrays past TILE_CACHE_BYTES (with an
+// FP32 copy 128 -> 108 us at N = 4000; the copy's own stores allocate, since
+// the products read it back from the Infinity Cache).
+template <int LOWP, int NP, int NF, bool STREAM>
+__global__ __launch_bounds__(256) void k_build_smooth(int N, int nsplit, int ngroups,
+                                                      const int2 *__restrict__ tile_ij,
+                                                      const double *__restrict__ rt, PairConst p,
+                                                      const double *coef,
+                                                      double *__restrict__ d64,
+                                                      float *__restrict__ p32,
+                                                      uint16_t *__restrict__ p16)
+{
+    __shared__ double sI[TS], sJ[TS];
+    __shared__ double qa[4][pair_queue<NF>()], qb[4][pair_queue<NF>()];
+    const int t = blockIdx.x / nsplit, part = blockIdx.x % nsplit;
+    const int2 ij = tile_ij[t];
+    const int I = ij.x, J = ij.y;
+    const int nI = N - I * TB, nJ = N - J * TB;   // valid beads (may exceed TB)
+    if (threadIdx.x < TS) {
+        const int e = threadIdx.x;
+        sI[e] = e / 3 < nI ? rt[3 * (size_t)I * TB + e] : 0.0;
+        sJ[e] = e / 3 < nJ ? rt[3 * (size_t)J * TB + e] : 0.0;
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row0 = (4 * part + w) * ngroups * PAIR_GROUP;
+    build_rows<TB, NP, NF>(p, smooth_ptr(coef), sI, sJ, nI, nJ, I == J, lane, row0, ngroups, qa[w],
+                           qb[w], [&](int bi, int bj, const double (&b)[6]) {
+        // packed planes: a wave writes 512 contiguous bytes per FP64 plane
+        const size_t o6 = (size_t)t * TILE6 + (size_t)bi * 6 * TB + bj;
+#pragma unroll
+        for (int e = 0; e < 6; ++e) {
+            if (STREAM) __builtin_nontemporal_store(b[e], &d64[o6 + (size_t)e * TB]);
+            else d64[o6 + (size_t)e * TB] = b[e];
+            if (LOWP == 1) p32[o6 + (size_t)e * TB] = (float)b[e];
+            if (LOWP == 2) p16[o6 + (size_t)e * TB] = to_bf16(b[e]);
+        }
+    });
+}
+
+template <int LOWP, int NP, int NF> static void build_smooth(const Ctx &c, hipStream_t s)
+{
+    // a tile's rows over enough workgroups to fill the device: with few tiles
+    // a workgroup per tile leaves most of it idle (N = 100: 45 -> 5 us)
+    int nsplit = 1;
+    while (nsplit < 16 / PAIR_GROUP && c.ntiles * nsplit < 1024) nsplit *= 2;
+    const int ngroups = TB / (4 * nsplit * PAIR_GROUP);
+    const dim3 g(c.ntiles * nsplit), b(256);
+    if ((size_t)c.ntiles * TILE6 * sizeof(double) > TILE_CACHE_BYTES)
+        hipLaunchKernelGGL((k_build_smooth<LOWP, NP, NF, true>), g, b, 0, s, c.N, nsplit, ngroups,
+                           c.tile_ij, c.rt, c.pc, c.smooth, c.d64, c.p32, c.p16);
+    else
+        hipLaunchKernelGGL((k_build_smooth<LOWP, NP, NF, false>), g, b, 0, s, c.N, nsplit, ngroups,
+                           c.tile_ij, c.rt, c.pc, c.smooth, c.d64, c.p32, c.p16);
+}
+
+template <int LOWP> static void build_smooth_np(const Ctx &c, hipStream_t s)
+{
+    // one moved component at most while the reach is below L / sqrt 2: two
+    // moved components are each at least L / 2 long
+    const bool single = c.pc.reach * c.pc.reach < 0.5 * c.L * c.L;
+    if (c.smooth_np == SMOOTH_NP[0]) {
+        if (single) build_smooth<LOWP, SMOOTH_NP[0], 3>(c, s);
+        else build_smooth<LOWP, SMOOTH_NP[0], 7>(c, s);
+    } else {
+        if (single) build_smooth<LOWP, SMOOTH_NP[1], 3>(c, s);
+        else build_smooth<LOWP, SMOOTH_NP[1], 7>(c, s);
+    }
+}
+
 void launch_build_tiles(const Ctx &c, hipStream_t s)
 {
     if (c.lma) {   // low-memory form: only the cell list and sorted positions
         launch_lma_build(c, s);
+        return;
+    }
+    if (c.smooth_np) {
+        if (c.lowp == RPY_PREC_F32) build_smooth_np<1>(c, s);
+        else if (c.lowp == RPY_PREC_BF16) build_smooth_np<2>(c, s);
+        else build_smooth_np<0>(c, s);
         return;
     }
     const dim3 g(c.ntiles), b(256);

@@ -105,6 +105,89 @@ PairConst make_pair_const(double L, double a, double alpha, double rc)
     return p;
 }
 
+// S1, S2 at x^2 = u in extended precision: the power series below x = 0.75
+// (as make_pair_const), the closed form above.
+static void smooth_exact(long double u, const PairConst &p, long double &s1, long double &s2)
+{
+    const long double x = sqrtl(u), isp = 1.0L / sqrtl(acosl(-1.0L));
+    const long double A1 = (long double)p.a * p.alpha, A3 = A1 * A1 * A1;
+    if (x < 0.75L) {
+        long double f1 = 0, g1 = 0, f2 = 0, g2 = 0, un = 1, fact = 1;   // u^n, n!
+        for (int n = 0; n < 30; ++n) {
+            if (n > 0) fact *= n;
+            const long double q = ((n & 1) ? -un : un) / fact, i1 = 1.0L / (n + 1);
+            f1 += q * (3.0L / (2 * (2 * n + 1)) + 4.5L + 3 * n);
+            g1 += q * (i1 - i1 / (2 * n + 3) - (14 + 20 * n + 4 * n * (n - 1)));
+            f2 += q * (3.0L / (2 * (2 * n + 1)) - 1.5L - 3 * n);
+            g2 += q * (3 * i1 / (2 * n + 3) - 3 * i1 + (2 + 16 * n + 4 * n * (n - 1)));
+            un *= u;
+        }
+        s1 = (A1 * f1 + A3 * g1) * isp;
+        s2 = (A1 * f2 + A3 * g2) * isp;
+        return;
+    }
+    const long double e = erfl(x), g = expl(-u) * isp, e1 = e / x, e3 = e / (x * u), iu = 1.0L / u;
+    s1 = A1 * (0.75L * e1 - (3 * u - 4.5L) * g) + A3 * (0.5L * e3 - ((4 * u - 20) * u + 14 + iu) * g);
+    s2 = A1 * (0.75L * e1 - (1.5L - 3 * u) * g) +
+         A3 * (-1.5L * e3 - ((16 - 4 * u) * u - 2 - 3 * iu) * g);
+}
+
+// Coefficients for smooth_images, highest power of z = 2 r^2 / r_c^2 - 1
+// first, from the Chebyshev series of S1 and S2 at 48 nodes.  Returns the
+// number of terms: the smallest of SMOOTH_NP (at least np_min) past which the
+// series' tails sum to less than 2e-17 max |S| (below the rounding of one
+// FP64 operation; 30 terms reach alpha r_c = 3.5, 38 terms 4.6), or 0 where
+// the form does not apply: longer series, 2a > r_c (images below 2a beyond
+// r_c carry no S) or max(r_c, 2a) >= L (more than two images per axis).
+int make_smooth_coef(const PairConst &p, int np_min, double coef[2 * SMOOTH_MAX])
+{
+    constexpr int NN = 48;
+    // cos(pi i / (2 NN)), one period
+    static const std::vector<long double> cs = [] {
+        std::vector<long double> v(4 * NN);
+        for (int i = 0; i < 4 * NN; ++i) v[i] = cosl(acosl(-1.0L) * i / (2 * NN));
+        return v;
+    }();
+    if (!(2.0 * p.a <= p.rc) || !(p.reach < p.L)) return 0;
+    const long double um = (long double)p.alpha * p.alpha * p.rc * p.rc;
+    long double f[2][NN], c[2][NN], top[2] = {0, 0};
+    for (int j = 0; j < NN; ++j) {
+        smooth_exact(0.5L * um * (cs[2 * j + 1] + 1), p, f[0][j], f[1][j]);
+        for (int w = 0; w < 2; ++w) top[w] = fmaxl(top[w], fabsl(f[w][j]));
+    }
+    for (int w = 0; w < 2; ++w)
+        for (int k = 0; k < NN; ++k) {
+            long double s = 0;
+            for (int j = 0; j < NN; ++j) s += f[w][j] * cs[k * (2 * j + 1) % (4 * NN)];
+            c[w][k] = (k ? 2.0L : 1.0L) * s / NN;
+        }
+    for (int np : SMOOTH_NP) {
+        if (np < np_min) continue;
+        bool ok = true;
+        for (int w = 0; w < 2; ++w) {
+            long double tail = 0;
+            for (int k = np; k < NN; ++k) tail += fabsl(c[w][k]);
+            ok = ok && tail < 2e-17L * top[w];
+        }
+        if (!ok) continue;
+        for (int w = 0; w < 2; ++w) {
+            // powers of z from the Chebyshev polynomials T_k = 2 z T_{k-1} - T_{k-2}
+            long double t0[SMOOTH_MAX] = {1}, t1[SMOOTH_MAX] = {0, 1}, m[SMOOTH_MAX] = {};
+            m[0] = c[w][0];
+            for (int k = 1; k < np; ++k) {
+                for (int i = 0; i <= k; ++i) m[i] += c[w][k] * t1[i];
+                long double t2[SMOOTH_MAX];
+                for (int i = 0; i < SMOOTH_MAX; ++i) t2[i] = (i ? 2 * t1[i - 1] : 0) - t0[i];
+                memcpy(t0, t1, sizeof t0);
+                memcpy(t1, t2, sizeof t1);
+            }
+            for (int i = 0; i < np; ++i) coef[2 * (np - 1 - i) + w] = (double)m[i];
+        }
+        return np;
+    }
+    return 0;
+}
+
 }  // namespace rpy
 
 static int validate(const rpy_params *p, int *n2max_out)
@@ -208,7 +291,7 @@ extern "C" void rpy_destroy(rpy_ctx *x)
     if (!x) return;
     (void)hipDeviceSynchronize();
     Ctx &c = x->c;
-    void *bufs[] = {c.rt, c.rt_ev, c.eph, c.etab, c.kvec, c.kcoef, c.tile_ij, c.d64,
+    void *bufs[] = {c.rt, c.rt_ev, c.smooth, c.eph, c.etab, c.kvec, c.kcoef, c.tile_ij, c.d64,
                     c.p32, c.p16, c.part, c.xpk, c.ypart,
                     c.vpk, c.bpart, c.tkm,
                     c.sfpart, c.tk, c.sfr, c.work, c.scal, c.red, c.flags, c.cell_start, c.lanc,
@@ -267,6 +350,8 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
             c.lds_max = lds;
     }
     c.pc = make_pair_const(c.L, c.a, c.alpha, c.rc);
+    double smooth[2 * SMOOTH_MAX];
+    c.smooth_np = make_smooth_coef(c.pc, 0, smooth);
     c.nbt = (c.N + TB - 1) / TB;
     c.ntiles = c.nbt * (c.nbt + 1) / 2;
     c.n3pad = c.nbt * TS;
@@ -316,7 +401,7 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     const int ncell_cap = 64;
     const size_t ncells_cap = (size_t)ncell_cap * ncell_cap * ncell_cap;
     if ((rc = dalloc(&c.rt, nv)) || (rc = dalloc(&c.rt_ev, nv)) || (rc = dalloc(&c.etab, nv * (c.nmax + 1))) ||
-        (rc = dalloc(&c.kvec, kv.size())) || (rc = dalloc(&c.kcoef, kc.size())) ||
+        (rc = dalloc(&c.smooth, 2 * SMOOTH_MAX)) || (rc = dalloc(&c.kvec, kv.size())) || (rc = dalloc(&c.kcoef, kc.size())) ||
         (rc = dalloc(&c.tile_ij, tij.size())) || (!c.lma && (rc = dalloc(&c.d64, te6))) ||
         (c.lma && ((rc = dalloc(&c.lma_start, 2 * lcells + 1)) ||
                    (rc = dalloc(&c.lma_beads, (size_t)c.N)) ||
@@ -364,6 +449,8 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     for (size_t i = 0; i < nv; ++i) um[i] = (i & 1) ? -1.0 : 1.0;
     hipError_t e;
     if ((e = hipMemcpy(c.kvec, kv.data(), kv.size() * sizeof(KVec), hipMemcpyHostToDevice)) ||
+        (c.smooth_np && (e = hipMemcpy(c.smooth, smooth, 2 * c.smooth_np * sizeof(double),
+                                       hipMemcpyHostToDevice))) ||
         (e = hipMemcpy(x->Um, um.data(), nv * sizeof(double), hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(c.kcoef, kc.data(), kc.size() * sizeof(KCoef), hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(c.tile_ij, tij.data(), tij.size() * sizeof(int2), hipMemcpyHostToDevice)) ||

@@ -207,6 +207,13 @@ RPY_HD inline void pair_block(double d0x, double d0y, double d0z, bool self,
 
 PairConst make_pair_const(double L, double a, double alpha, double rc);
 
+// The smooth part S = Omega_A - M1 as polynomials in r^2 over [0, r_c^2]
+// (rpy_pairs.h): terms used per coefficient, 0 where the polynomial form does
+// not apply (make_smooth_coef states the rule).
+constexpr int SMOOTH_NP[2] = {30, 38};
+constexpr int SMOOTH_MAX = 38;
+int make_smooth_coef(const PairConst &p, int np_min, double coef[2 * SMOOTH_MAX]);
+
 // ------------------------------------------------------- pair derivatives
 // d/dx of the M1 coefficients (eq. M1 differentiated, x = alpha r), with the
 // values: c1 = erfc(x) A + g B, c2 = erfc(x) A2 + g B2, g = e^{-x^2}/sqrt(pi),
@@ -395,6 +402,8 @@ struct Ctx {
     int lowp, max_rhs;
     int rhs_cap;       // stride of the per-RHS work buffers: max(max_rhs, 3)
     PairConst pc;
+    int smooth_np = 0;           // terms of the polynomial pair form (0: erfc / exp form)
+    double *smooth = nullptr;    // [smooth_np][2] its coefficients
     // tiling
     int nbt;           // bead tiles per side
     int ntiles;        // stored tiles

@@ -8,6 +8,7 @@
 // bead any of whose images is within reach (each pair then has one such image
 // at most).
 #include "rpy_internal.h"
+#include "rpy_pairs.h"
 #include "rpy_sf.h"
 
 namespace rpy {
@@ -59,18 +60,36 @@ __device__ inline void lma_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The block of one queued pair.  With max(r_c, 2a) < L/3 only the minimum
+// The block of one queued pair, NP > 0: by the polynomial pair form with NP
+// terms (rpy_pairs.h), else by erfc and exp.  With max(r_c, 2a) < L/3 only the minimum
 // image of a pair can be within reach (any other is farther than 2L/3), and
 // a bead has no image of itself within reach: the block is add_image of the
 // minimum image (the term pair_block would sum), or the self term.
-template <int M>
+template <int M, int NP>
 __device__ inline void lma_pair(double hx, double hy, double hz, int k, int h,
-                                const PairConst &p, const double *__restrict__ rt_s,
+                                const PairConst &p, SmoothCoef coef, const double *__restrict__ rt_s,
                                 const double *__restrict__ vs, int n3, int j0,
                                 double acc[M][3])
 {
     double b[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (k == h) {
+    if constexpr (NP > 0) {
+        double dx = hx - rt_s[3 * (size_t)k], dy = hy - rt_s[3 * (size_t)k + 1],
+               dz = hz - rt_s[3 * (size_t)k + 2];
+        dx -= p.L * rint(dx * p.invL);
+        dy -= p.L * rint(dy * p.invL);
+        dz -= p.L * rint(dz * p.invL);
+        const double r2[1] = {dx * dx + dy * dy + dz * dz};
+        double c1[1], w[1];
+        smooth_images<1, NP>(r2, p, coef, c1, w);
+        const double a = k == h ? p.self_coeff : c1[0], v = k == h ? 0.0 : w[0];
+        const double vx = v * dx, vy = v * dy;
+        b[0] = fma(vx, dx, a);
+        b[1] = vx * dy;
+        b[2] = vx * dz;
+        b[3] = fma(vy, dy, a);
+        b[4] = vy * dz;
+        b[5] = fma(v * dz, dz, a);
+    } else if (k == h) {
         b[0] = b[3] = b[5] = p.self_coeff;
     } else {
         double dx = hx - rt_s[3 * (size_t)k], dy = hy - rt_s[3 * (size_t)k + 1],
@@ -90,12 +109,13 @@ __device__ inline void lma_pair(double hx, double hy, double hz, int k, int h,
     }
 }
 
-// Four waves per SIMD (at most 128 VGPRs; the compiler spills a few values
+// Four waves per SIMD (at most 128 VGPRs; the erfc form spills a few values
 // to scratch) ran the N = 32000 product 1.3x faster than the three that 169
 // VGPRs allow; five or six waves were slower.
-template <int M>
+template <int M, int NP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_lma_real(int N, int n3, int n3pad, int rhs_cap, int j0,
                                                   double L, int nc, PairConst p,
+                                                  const double *coef_g,
                                                   const int *__restrict__ start,
                                                   const int *__restrict__ beads,
                                                   const double *__restrict__ rt_s,
@@ -107,6 +127,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     if (gate && *gate) return;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int *q = queue[w];
+    const SmoothCoef coef = smooth_ptr(coef_g);
     const double invL = 1.0 / L;
     for (int i = 0; i < LMA_HOMES / 4; ++i) {
         const int h = blockIdx.x * LMA_HOMES + 4 * w + i;   // wave-uniform
@@ -150,12 +171,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                     lma_wave_sync();
                     if (lane < rest) q[lane] = moved;
                     qn = rest;
-                    lma_pair<M>(hx, hy, hz, kk, h, p, rt_s, vs, n3, j0, acc);
+                    lma_pair<M, NP>(hx, hy, hz, kk, h, p, coef, rt_s, vs, n3, j0, acc);
                 }
             }
         }
         lma_wave_sync();
-        if (lane < qn) lma_pair<M>(hx, hy, hz, q[lane], h, p, rt_s, vs, n3, j0, acc);
+        if (lane < qn) lma_pair<M, NP>(hx, hy, hz, q[lane], h, p, coef, rt_s, vs, n3, j0, acc);
         lma_wave_sync();   // the queue is reused by the next home bead
         const int nu = beads[h];
 #pragma unroll
@@ -175,10 +196,16 @@ void launch_lma_real(const Ctx &c, const double *v, int m, hipStream_t s)
     hipLaunchKernelGGL(k_lma_gather, dim3((m * c.N + 255) / 256), dim3(256), 0, s, c.N, m, c.n3,
                        c.lma_beads, v, c.v_sorted, c.gate);
     const dim3 g((c.N + LMA_HOMES - 1) / LMA_HOMES);
-#define RPY_LMA_REAL(MC)                                                                        \
-    hipLaunchKernelGGL(k_lma_real<MC>, g, dim3(256), 0, s, c.N, c.n3, c.n3pad, c.rhs_cap, j0, \
-                       c.L, c.lma_nc, c.pc, c.lma_start, c.lma_beads, c.rt_sorted, c.v_sorted, \
-                       c.part, c.gate)
+#define RPY_LMA_REAL_NP(MC, NP)                                                                 \
+    hipLaunchKernelGGL((k_lma_real<MC, NP>), g, dim3(256), 0, s, c.N, c.n3, c.n3pad, c.rhs_cap, \
+                       j0, c.L, c.lma_nc, c.pc, c.smooth, c.lma_start, c.lma_beads,             \
+                       c.rt_sorted, c.v_sorted, c.part, c.gate)
+#define RPY_LMA_REAL(MC)                                               \
+    do {                                                               \
+        if (c.smooth_np == SMOOTH_NP[0]) RPY_LMA_REAL_NP(MC, SMOOTH_NP[0]); \
+        else if (c.smooth_np) RPY_LMA_REAL_NP(MC, SMOOTH_NP[1]);       \
+        else RPY_LMA_REAL_NP(MC, 0);                                   \
+    } while (0)
     for (int j0 = 0; j0 < m;) {   // groups of 4, 2, 1 vectors
         const int mc = (m - j0) >= 4 ? 4 : (m - j0) >= 2 ? 2 : 1;
         if (mc == 4) RPY_LMA_REAL(4);
@@ -187,6 +214,7 @@ void launch_lma_real(const Ctx &c, const double *v, int m, hipStream_t s)
         j0 += mc;
     }
 #undef RPY_LMA_REAL
+#undef RPY_LMA_REAL_NP
 }
 
 // Structure-factor partials of the m input vectors (one or two at a time).
