@@ -868,18 +868,20 @@ void launch_trial(const Ctx &c, int m, int n, int nmax, double tol, size_t ps,
                        c.adapt, c.tpart, c.scal, e_f);
 }
 
-void launch_trial_check(const Ctx &c, int m, int n, int nmax, double tol, double *e_f,
+int epi_trial_chunks(int N) { return (N + EPI_BEADS - 1) / EPI_BEADS; }   // its workgroups
+
+void launch_trial_check(const Ctx &c, int m, int nchunk, int n, int nmax, double tol, double *e_f,
                         hipStream_t s)
 {
-    const int nchunk = (c.N + EPI_BEADS - 1) / EPI_BEADS;   // k_kspace_epi workgroups
     hipLaunchKernelGGL(k_trial_check, dim3(1), dim3(1024), 0, s, m, nchunk, n, nmax, tol,
                        c.adapt, c.tpart, c.scal, e_f);
 }
 
 int trial_chunks(int N)
 {
-    const int a = (3 * N + 255) / 256, b = (N + EPI_BEADS - 1) / EPI_BEADS;
-    return a > b ? a : b;
+    const int a = (3 * N + 255) / 256, b = epi_trial_chunks(N);
+    const int r = N <= ROWS_MAX ? rows_trial_chunks(N) : 0;
+    return a > b ? (a > r ? a : r) : (b > r ? b : r);
 }
 
 // E_f = sqrt(|dS.dS - dW.(D dW)| / dW.(D dW)), one workgroup per RHS.

@@ -17,6 +17,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -221,12 +222,15 @@ __global__ __launch_bounds__(256) void k_bbuild_smooth(const int4 *__restrict__ 
     constexpr int rows = TBB / 4, ngroups = rows * TBB / (64 * PAIR_GROUP);
     build_rows<TBB, NP, NF>(d.pc, smooth_ptr(coef + (size_t)box * 2 * SMOOTH_MAX), sI, sJ,
                             d.N - I * TBB, d.N - J * TBB, I == J, lane, w * rows, ngroups, qa[w],
-                            qb[w], [&](int bi, int bj, const double (&b)[6]) {
-        const size_t o6 = (size_t)t * 6 * TBB * TBB + (size_t)bi * 6 * TBB + bj;
+                            qb[w], [&](const int *bi, int bj, const double (*b)[6]) {
 #pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            __builtin_nontemporal_store(b[c], &d64[o6 + (size_t)c * TBB]);
-            if (LOWP) __builtin_nontemporal_store((float)b[c], &d32[o6 + (size_t)c * TBB]);
+        for (int q = 0; q < PAIR_GROUP; ++q) {
+            const size_t o6 = (size_t)t * 6 * TBB * TBB + (size_t)bi[q] * 6 * TBB + bj;
+#pragma unroll
+            for (int c = 0; c < 6; ++c) {
+                __builtin_nontemporal_store(b[q][c], &d64[o6 + (size_t)c * TBB]);
+                if (LOWP) __builtin_nontemporal_store((float)b[q][c], &d32[o6 + (size_t)c * TBB]);
+            }
         }
     });
 }
@@ -1057,16 +1061,23 @@ extern "C" int rpy_batch_create(rpy_batch **out, const rpy_params *bp, int nbox,
 
     // the polynomial pair form, with one number of terms for all boxes
     std::vector<double> smooth((size_t)nbox * 2 * SMOOTH_MAX, 0.0);
+    // (boxes usually share alpha r_c up to rounding, and then the basis: a
+    // relative difference of 1e-14 moves S by less than its rounding)
     std::vector<int> terms(nbox);
     int np = 1;
+    std::unique_ptr<SmoothBasis> basis;
+    auto coefs = [&](int i, int least) {
+        const double um = smooth_um(hb[i].pc);
+        if (!basis || !(fabs(um - basis->um) < 1e-14 * um)) basis.reset(new SmoothBasis(um));
+        return make_smooth_coef(hb[i].pc, *basis, least, &smooth[(size_t)i * 2 * SMOOTH_MAX]);
+    };
     for (int i = 0; i < nbox && np; ++i) {
         const PairConst &pc = hb[i].pc;
-        terms[i] = make_smooth_coef(pc, np, &smooth[(size_t)i * 2 * SMOOTH_MAX]);
-        np = terms[i];   // at least the terms of the boxes before, or 0
+        np = terms[i] = coefs(i, np);   // at least the terms of the boxes before, or 0
         if (!(pc.reach * pc.reach < 0.5 * pc.L * pc.L)) b->smooth_single = false;
     }
     for (int i = 0; i < nbox && np; ++i)
-        if (terms[i] != np) np = make_smooth_coef(hb[i].pc, np, &smooth[(size_t)i * 2 * SMOOTH_MAX]);
+        if (terms[i] != np) np = coefs(i, np);
     b->smooth_np = np;
 
     // half-space wave vectors (one integer set) and per-box weights

@@ -251,15 +251,18 @@ __global__ __launch_bounds__(256) void k_build_smooth(int N, int nsplit, int ngr
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row0 = (4 * part + w) * ngroups * PAIR_GROUP;
     build_rows<TB, NP, NF>(p, smooth_ptr(coef), sI, sJ, nI, nJ, I == J, lane, row0, ngroups, qa[w],
-                           qb[w], [&](int bi, int bj, const double (&b)[6]) {
+                           qb[w], [&](const int *bi, int bj, const double (*b)[6]) {
         // packed planes: a wave writes 512 contiguous bytes per FP64 plane
-        const size_t o6 = (size_t)t * TILE6 + (size_t)bi * 6 * TB + bj;
 #pragma unroll
-        for (int e = 0; e < 6; ++e) {
-            if (STREAM) __builtin_nontemporal_store(b[e], &d64[o6 + (size_t)e * TB]);
-            else d64[o6 + (size_t)e * TB] = b[e];
-            if (LOWP == 1) p32[o6 + (size_t)e * TB] = (float)b[e];
-            if (LOWP == 2) p16[o6 + (size_t)e * TB] = to_bf16(b[e]);
+        for (int q = 0; q < PAIR_GROUP; ++q) {
+            const size_t o6 = (size_t)t * TILE6 + (size_t)bi[q] * 6 * TB + bj;
+#pragma unroll
+            for (int e = 0; e < 6; ++e) {
+                if (STREAM) __builtin_nontemporal_store(b[q][e], &d64[o6 + (size_t)e * TB]);
+                else d64[o6 + (size_t)e * TB] = b[q][e];
+                if (LOWP == 1) p32[o6 + (size_t)e * TB] = (float)b[q][e];
+                if (LOWP == 2) p16[o6 + (size_t)e * TB] = to_bf16(b[q][e]);
+            }
         }
     });
 }

@@ -33,6 +33,12 @@ struct rpy_ctx {
     double *acc = nullptr;    // [max_rhs][3N] scratch accumulator
     // the phase matrix c.eph is valid for wrap generation eph_gen
     uint64_t wrap_gen = 1, eph_gen = 0;
+    // with c.drow the stored tiles and the rows are each formed when a product
+    // needs them; they hold D of the wrap generations tiles_gen and rows_gen.
+    // captured: some call has been captured into a graph, whose replays this
+    // bookkeeping does not see -- from then on the context uses the tiles only
+    uint64_t tiles_gen = 0, rows_gen = 0;
+    bool captured = false;
     // bd_step runs the forces and the noise on a second stream (default
     // priority) beside the tile build: fork after the wrap, join before the
     // drift product
@@ -105,84 +111,94 @@ PairConst make_pair_const(double L, double a, double alpha, double rc)
     return p;
 }
 
-// S1, S2 at x^2 = u in extended precision: the power series below x = 0.75
-// (as make_pair_const), the closed form above.
-static void smooth_exact(long double u, const PairConst &p, long double &s1, long double &s2)
+// S1 = A1 F1 + A3 G1, S2 = A1 F2 + A3 G2 at x^2 = u in extended precision,
+// v = (F1, F2, G1, G2): the power series below x = 0.75 (as make_pair_const),
+// the closed form above.
+static void smooth_exact(long double u, long double v[4])
 {
     const long double x = sqrtl(u), isp = 1.0L / sqrtl(acosl(-1.0L));
-    const long double A1 = (long double)p.a * p.alpha, A3 = A1 * A1 * A1;
     if (x < 0.75L) {
-        long double f1 = 0, g1 = 0, f2 = 0, g2 = 0, un = 1, fact = 1;   // u^n, n!
+        long double un = 1, fact = 1;   // u^n, n!
+        v[0] = v[1] = v[2] = v[3] = 0;
         for (int n = 0; n < 30; ++n) {
             if (n > 0) fact *= n;
-            const long double q = ((n & 1) ? -un : un) / fact, i1 = 1.0L / (n + 1);
-            f1 += q * (3.0L / (2 * (2 * n + 1)) + 4.5L + 3 * n);
-            g1 += q * (i1 - i1 / (2 * n + 3) - (14 + 20 * n + 4 * n * (n - 1)));
-            f2 += q * (3.0L / (2 * (2 * n + 1)) - 1.5L - 3 * n);
-            g2 += q * (3 * i1 / (2 * n + 3) - 3 * i1 + (2 + 16 * n + 4 * n * (n - 1)));
+            const long double q = ((n & 1) ? -un : un) / fact * isp, i1 = 1.0L / (n + 1);
+            v[0] += q * (3.0L / (2 * (2 * n + 1)) + 4.5L + 3 * n);
+            v[1] += q * (3.0L / (2 * (2 * n + 1)) - 1.5L - 3 * n);
+            v[2] += q * (i1 - i1 / (2 * n + 3) - (14 + 20 * n + 4 * n * (n - 1)));
+            v[3] += q * (3 * i1 / (2 * n + 3) - 3 * i1 + (2 + 16 * n + 4 * n * (n - 1)));
             un *= u;
         }
-        s1 = (A1 * f1 + A3 * g1) * isp;
-        s2 = (A1 * f2 + A3 * g2) * isp;
         return;
     }
     const long double e = erfl(x), g = expl(-u) * isp, e1 = e / x, e3 = e / (x * u), iu = 1.0L / u;
-    s1 = A1 * (0.75L * e1 - (3 * u - 4.5L) * g) + A3 * (0.5L * e3 - ((4 * u - 20) * u + 14 + iu) * g);
-    s2 = A1 * (0.75L * e1 - (1.5L - 3 * u) * g) +
-         A3 * (-1.5L * e3 - ((16 - 4 * u) * u - 2 - 3 * iu) * g);
+    v[0] = 0.75L * e1 - (3 * u - 4.5L) * g;
+    v[1] = 0.75L * e1 - (1.5L - 3 * u) * g;
+    v[2] = 0.5L * e3 - ((4 * u - 20) * u + 14 + iu) * g;
+    v[3] = -1.5L * e3 - ((16 - 4 * u) * u - 2 - 3 * iu) * g;
 }
 
-// Coefficients for smooth_images, highest power of z = 2 r^2 / r_c^2 - 1
-// first, from the Chebyshev series of S1 and S2 at 48 nodes.  Returns the
-// number of terms: the smallest of SMOOTH_NP (at least np_min) past which the
-// series' tails sum to less than 2e-17 max |S| (below the rounding of one
-// FP64 operation; 30 terms reach alpha r_c = 3.5, 38 terms 4.6), or 0 where
-// the form does not apply: longer series, 2a > r_c (images below 2a beyond
-// r_c carry no S) or max(r_c, 2a) >= L (more than two images per axis).
-int make_smooth_coef(const PairConst &p, int np_min, double coef[2 * SMOOTH_MAX])
+// The Chebyshev series of F1, F2, G1, G2 on [0, um], um = (alpha r_c)^2, at
+// SMOOTH_NN nodes, and its first SMOOTH_NP[.] terms in powers of z.
+SmoothBasis::SmoothBasis(double um_) : um(um_)
 {
-    constexpr int NN = 48;
-    // cos(pi i / (2 NN)), one period
-    static const std::vector<long double> cs = [] {
-        std::vector<long double> v(4 * NN);
-        for (int i = 0; i < 4 * NN; ++i) v[i] = cosl(acosl(-1.0L) * i / (2 * NN));
-        return v;
-    }();
-    if (!(2.0 * p.a <= p.rc) || !(p.reach < p.L)) return 0;
-    const long double um = (long double)p.alpha * p.alpha * p.rc * p.rc;
-    long double f[2][NN], c[2][NN], top[2] = {0, 0};
+    constexpr int NN = SMOOTH_NN;
+    long double cs[4 * NN], c[4][NN];   // cos(pi i / (2 NN)), one period
+    for (int i = 0; i < 4 * NN; ++i) cs[i] = cosl(acosl(-1.0L) * i / (2 * NN));
     for (int j = 0; j < NN; ++j) {
-        smooth_exact(0.5L * um * (cs[2 * j + 1] + 1), p, f[0][j], f[1][j]);
-        for (int w = 0; w < 2; ++w) top[w] = fmaxl(top[w], fabsl(f[w][j]));
+        long double v[4];
+        smooth_exact(0.5L * um * (cs[2 * j + 1] + 1), v);
+        for (int w = 0; w < 4; ++w) f[w][j] = v[w];
     }
-    for (int w = 0; w < 2; ++w)
+    for (int w = 0; w < 4; ++w)
         for (int k = 0; k < NN; ++k) {
             long double s = 0;
             for (int j = 0; j < NN; ++j) s += f[w][j] * cs[k * (2 * j + 1) % (4 * NN)];
             c[w][k] = (k ? 2.0L : 1.0L) * s / NN;
         }
-    for (int np : SMOOTH_NP) {
+    // powers of z from the Chebyshev polynomials T_k = 2 z T_{k-1} - T_{k-2}
+    long double t0[SMOOTH_MAX] = {1}, t1[SMOOTH_MAX] = {0, 1}, m[4][SMOOTH_MAX] = {};
+    for (int k = 0; k < SMOOTH_MAX; ++k) {
+        for (int w = 0; w < 4; ++w)
+            for (int i = 0; i <= k; ++i) m[w][i] += c[w][k] * t0[i];
+        long double t2[SMOOTH_MAX];
+        for (int i = 0; i < SMOOTH_MAX; ++i) t2[i] = (i ? 2 * t1[i - 1] : 0) - t0[i];
+        memcpy(t0, t1, sizeof t0);
+        memcpy(t1, t2, sizeof t1);
+        for (int n = 0; n < 2; ++n)
+            if (k + 1 == SMOOTH_NP[n]) memcpy(power[n], m, sizeof m);
+    }
+    for (int w = 0; w < 4; ++w)
+        for (int n = 0; n < 2; ++n) {
+            tail[n][w] = 0;
+            for (int k = SMOOTH_NP[n]; k < NN; ++k) tail[n][w] += fabsl(c[w][k]);
+        }
+}
+
+// Coefficients for smooth_images, highest power of z = 2 r^2 / r_c^2 - 1
+// first.  Returns the number of terms: the smallest of SMOOTH_NP (at least
+// np_min) past which the series' tails sum to less than 2e-17 max |S| (below
+// the rounding of one FP64 operation; 30 terms reach alpha r_c = 3.5, 38 terms
+// 4.6), or 0 where the form does not apply: longer series, 2a > r_c (images
+// below 2a beyond r_c carry no S) or max(r_c, 2a) >= L (more than two images
+// per axis).
+int make_smooth_coef(const PairConst &p, const SmoothBasis &b, int np_min, double coef[2 * SMOOTH_MAX])
+{
+    if (!(2.0 * p.a <= p.rc) || !(p.reach < p.L)) return 0;
+    const long double A1 = (long double)p.a * p.alpha, A3 = A1 * A1 * A1;
+    long double top[2] = {0, 0};
+    for (int j = 0; j < SMOOTH_NN; ++j)
+        for (int w = 0; w < 2; ++w) top[w] = fmaxl(top[w], fabsl(A1 * b.f[w][j] + A3 * b.f[2 + w][j]));
+    for (int n = 0; n < 2; ++n) {
+        const int np = SMOOTH_NP[n];
         if (np < np_min) continue;
         bool ok = true;
-        for (int w = 0; w < 2; ++w) {
-            long double tail = 0;
-            for (int k = np; k < NN; ++k) tail += fabsl(c[w][k]);
-            ok = ok && tail < 2e-17L * top[w];
-        }
+        for (int w = 0; w < 2; ++w)
+            ok = ok && A1 * b.tail[n][w] + A3 * b.tail[n][2 + w] < 2e-17L * top[w];
         if (!ok) continue;
-        for (int w = 0; w < 2; ++w) {
-            // powers of z from the Chebyshev polynomials T_k = 2 z T_{k-1} - T_{k-2}
-            long double t0[SMOOTH_MAX] = {1}, t1[SMOOTH_MAX] = {0, 1}, m[SMOOTH_MAX] = {};
-            m[0] = c[w][0];
-            for (int k = 1; k < np; ++k) {
-                for (int i = 0; i <= k; ++i) m[i] += c[w][k] * t1[i];
-                long double t2[SMOOTH_MAX];
-                for (int i = 0; i < SMOOTH_MAX; ++i) t2[i] = (i ? 2 * t1[i - 1] : 0) - t0[i];
-                memcpy(t0, t1, sizeof t0);
-                memcpy(t1, t2, sizeof t1);
-            }
-            for (int i = 0; i < np; ++i) coef[2 * (np - 1 - i) + w] = (double)m[i];
-        }
+        for (int w = 0; w < 2; ++w)
+            for (int i = 0; i < np; ++i)
+                coef[2 * (np - 1 - i) + w] = (double)(A1 * b.power[n][w][i] + A3 * b.power[n][2 + w][i]);
         return np;
     }
     return 0;
@@ -292,7 +308,7 @@ extern "C" void rpy_destroy(rpy_ctx *x)
     (void)hipDeviceSynchronize();
     Ctx &c = x->c;
     void *bufs[] = {c.rt, c.rt_ev, c.smooth, c.eph, c.etab, c.kvec, c.kcoef, c.tile_ij, c.d64,
-                    c.p32, c.p16, c.part, c.xpk, c.ypart,
+                    c.p32, c.p16, c.drow, c.part, c.xpk, c.ypart,
                     c.vpk, c.bpart, c.tkm,
                     c.sfpart, c.tk, c.sfr, c.work, c.scal, c.red, c.flags, c.cell_start, c.lanc,
                     c.adapt, c.tpart,
@@ -350,8 +366,8 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
             c.lds_max = lds;
     }
     c.pc = make_pair_const(c.L, c.a, c.alpha, c.rc);
-    double smooth[2 * SMOOTH_MAX];
-    c.smooth_np = make_smooth_coef(c.pc, 0, smooth);
+    double smooth[2 * SMOOTH_MAX] = {};
+    c.smooth_np = make_smooth_coef(c.pc, SmoothBasis(smooth_um(c.pc)), 0, smooth);
     c.nbt = (c.N + TB - 1) / TB;
     c.ntiles = c.nbt * (c.nbt + 1) / 2;
     c.n3pad = c.nbt * TS;
@@ -397,16 +413,28 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     const size_t lcells = c.lma ? (size_t)c.lma_nc * c.lma_nc * c.lma_nc : 0;
     const size_t nv = (size_t)c.n3;
     const size_t mv = (size_t)c.rhs_cap * nv;
+    std::vector<int> roff;
+    std::vector<double> rwk;
+    const bool rows = !c.lma && c.lowp == RPY_PREC_F64 && c.N <= ROWS_MAX &&
+                      make_rows_weights(c, roff, rwk);
+    c.row_ld = (c.N + 127) / 128 * 128;
+    // one table: the pair polynomials, the octant weights, their offsets
+    std::vector<double> tabs(smooth, smooth + 2 * SMOOTH_MAX);
+    tabs.insert(tabs.end(), rwk.begin(), rwk.end());
+    tabs.resize(tabs.size() + (roff.size() + 1) / 2);
+    if (!roff.empty())
+        memcpy(&tabs[2 * SMOOTH_MAX + rwk.size()], roff.data(), roff.size() * sizeof(int));
     c.work_elems = 3 * nv + nv + 4 * nv + nv + nv + 2 * mv + mv + mv;
     const int ncell_cap = 64;
     const size_t ncells_cap = (size_t)ncell_cap * ncell_cap * ncell_cap;
     if ((rc = dalloc(&c.rt, nv)) || (rc = dalloc(&c.rt_ev, nv)) || (rc = dalloc(&c.etab, nv * (c.nmax + 1))) ||
-        (rc = dalloc(&c.smooth, 2 * SMOOTH_MAX)) || (rc = dalloc(&c.kvec, kv.size())) || (rc = dalloc(&c.kcoef, kc.size())) ||
+        (rc = dalloc(&c.smooth, tabs.size())) || (rc = dalloc(&c.kvec, kv.size())) || (rc = dalloc(&c.kcoef, kc.size())) ||
         (rc = dalloc(&c.tile_ij, tij.size())) || (!c.lma && (rc = dalloc(&c.d64, te6))) ||
         (c.lma && ((rc = dalloc(&c.lma_start, 2 * lcells + 1)) ||
                    (rc = dalloc(&c.lma_beads, (size_t)c.N)) ||
                    (rc = dalloc(&c.rt_sorted, nv)) ||
                    (rc = dalloc(&c.v_sorted, (size_t)c.rhs_cap * nv)))) ||
+        (rows && (rc = dalloc(&c.drow, (size_t)c.N * 6 * c.row_ld))) ||
         (c.lowp == RPY_PREC_F32 && (rc = dalloc(&c.p32, te6))) ||
         (c.lowp == RPY_PREC_BF16 && (rc = dalloc(&c.p16, te6))) ||
         (rc = dalloc(&c.part, (size_t)c.nslot * c.rhs_cap * c.n3pad)) ||
@@ -435,6 +463,8 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
         rpy_destroy(x);
         return rc;
     }
+    c.row_wk = c.smooth + 2 * SMOOTH_MAX;
+    c.row_off = reinterpret_cast<int *>(c.row_wk + rwk.size());
     double *w = c.work;
     x->F = w; w += 3 * nv;
     x->Um = w; w += nv;
@@ -449,14 +479,17 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     for (size_t i = 0; i < nv; ++i) um[i] = (i & 1) ? -1.0 : 1.0;
     hipError_t e;
     if ((e = hipMemcpy(c.kvec, kv.data(), kv.size() * sizeof(KVec), hipMemcpyHostToDevice)) ||
-        (c.smooth_np && (e = hipMemcpy(c.smooth, smooth, 2 * c.smooth_np * sizeof(double),
-                                       hipMemcpyHostToDevice))) ||
+        (e = hipMemcpy(c.smooth, tabs.data(), tabs.size() * sizeof(double), hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(x->Um, um.data(), nv * sizeof(double), hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(c.kcoef, kc.data(), kc.size() * sizeof(KCoef), hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(c.tile_ij, tij.data(), tij.size() * sizeof(int2), hipMemcpyHostToDevice)) ||
         (e = hipMemset(c.flags, 0, 4 * sizeof(int))) ||
         (e = hipMemset(c.adapt, 0, sizeof(AdaptState))) ||
         (te6 && (e = hipMemset(c.d64, 0, te6 * sizeof(double)))) ||
+        // the columns past the tiles are never written
+        (rows && c.row_ld > c.nbt * TB &&
+         (e = hipMemset2D(c.drow + c.nbt * TB, c.row_ld * sizeof(double), 0,
+                          (c.row_ld - c.nbt * TB) * sizeof(double), (size_t)c.N * 6))) ||
         (c.block && (e = hipMemset(c.tkm, 0, (size_t)c.nk4 * 6 * BLOCK_RHS * sizeof(double))))) {
         rc = hip_fail(e, "rpy_create upload");
         rpy_destroy(x);
@@ -512,15 +545,61 @@ struct ProfScope {
     }
 };
 
+// Whether products of `m` vectors, about `products` of them on the present
+// positions, go by rows (rpy_rows.hip).  Forming the rows costs more than the
+// tiles by the octant sums, 10 us at N = 400 and 80 at N = 1400; a product by
+// rows saves 10 and 6 us.  Up to ROWS_EAGER beads they pay from the first.
+constexpr int ROWS_EAGER = 256;
+constexpr int ROWS_PRODUCTS = 8;
+static bool use_rows(rpy_ctx *x, int m, int products, hipStream_t s)
+{
+    const Ctx &c = x->c;
+    if (!c.drow) return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        x->captured = true;
+    }
+    if (st != hipStreamCaptureStatusNone) x->captured = true;
+    return !x->captured && m <= 4 && (c.N <= ROWS_EAGER || products >= ROWS_PRODUCTS);
+}
+
+// D of the present positions in the form that about `products` products of m
+// vectors are to use, unless it is there already.
+static void form_tensor(rpy_ctx *x, int products, hipStream_t s, int m = 1)
+{
+    const Ctx &c = x->c;
+    const bool rows = use_rows(x, m, products, s);
+    // by rows as well where only they are formed and the products can use them
+    if (rows ? x->rows_gen == x->wrap_gen : c.drow && x->tiles_gen == x->wrap_gen) return;
+    if (!rows && m <= 4 && c.drow && !x->captured && x->rows_gen == x->wrap_gen) return;
+    ProfScope ps(x, RPY_PROF_BUILD, s);
+    if (rows) {
+        launch_build_rows(c, s);
+        x->rows_gen = x->wrap_gen;
+    } else {
+        launch_build_tiles(c, s);
+        // a captured build has not run: later calls form the tiles again
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (c.drow && (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone))
+            (void)hipGetLastError();
+        else
+            x->tiles_gen = x->wrap_gen;
+    }
+}
+
+// Whether a product of m vectors runs by rows now.
+static bool by_rows(const rpy_ctx *x, int m)
+{
+    return x->c.drow && m <= 4 && !x->captured && x->rows_gen == x->wrap_gen;
+}
+
 extern "C" int rpy_ewald_build(rpy_ctx *x, const double *pos, void *stream)
 {
     if (!x || !pos) return RPY_EINVAL;
     launch_wrap_tables(x->c, pos, S(stream));
     ++x->wrap_gen;
-    {
-        ProfScope ps(x, RPY_PROF_BUILD, S(stream));
-        launch_build_tiles(x->c, S(stream));
-    }
+    form_tensor(x, 1, S(stream));
     return check_launch("rpy_ewald_build");
 }
 
@@ -574,6 +653,11 @@ static void product(rpy_ctx *x, const double *v, int m, int prec, const EpiArgs 
         launch_block_epi(c, f, s);
         return;
     }
+    if (by_rows(x, m)) {
+        ProfScope ps(x, m == 1 ? RPY_PROF_SYMV : RPY_PROF_SYMV_MULTI, s);
+        launch_row_product(c, v, f, s);
+        return;
+    }
     // the tile-product launches also write T_k of their vectors
     for (int j0 = 0; j0 < m;) {
         const int r = m - j0;
@@ -594,6 +678,7 @@ extern "C" int rpy_apply(rpy_ctx *x, const double *v, double *out, int m, int pr
     f.mode = EPI_APPLY;
     f.m = m;
     f.vout = out;
+    if (x->c.drow) form_tensor(x, 1, S(stream), m);
     product(x, v, m, prec, f, S(stream));
     return check_launch("rpy_apply");
 }
@@ -663,7 +748,9 @@ static void cheb_adapt_run(rpy_ctx *x, int m, int prec, int first, int host_firs
     const int *done = &c.adapt->done;
     auto trial = [&](int n, bool fused) {
         if (n < host_first) return;
-        if (fused) launch_trial_check(c, m, n, nmax, tol, e_f, s);
+        if (fused)
+            launch_trial_check(c, m, by_rows(x, m) ? rows_trial_chunks(c.N) : epi_trial_chunks(c.N),
+                               n, nmax, tol, e_f, s);
         else launch_trial(c, m, n, nmax, tol, ps, x->ddw, out, e_f, s);
     };
     const bool fuse = !(c.block && m >= BLOCK_MIN_RHS);
@@ -722,11 +809,12 @@ extern "C" int chebyshev_sqrt_apply(rpy_ctx *x, const double *dw, double *out, i
         return RPY_EINVAL;
     hipStream_t s = S(stream);
     Ctx &c = x->c;
+    if (tol > 0 && n_cheb > c.cheb_keep) {
+        snprintf(g_err, sizeof g_err, "the adaptive order needs cheb_keep >= n_cheb");
+        return RPY_EINVAL;
+    }
+    if (c.drow) form_tensor(x, n_cheb - 1, s, m);
     if (tol > 0) {
-        if (n_cheb > c.cheb_keep) {
-            snprintf(g_err, sizeof g_err, "the adaptive order needs cheb_keep >= n_cheb");
-            return RPY_EINVAL;
-        }
         launch_copy(c.vhist, dw, (size_t)m * c.n3, s);   // V_0
         launch_cheb_coeffs(c, 0, RPY_BOUNDS_EXPLICIT, 0.0, d_min, d_max, nullptr, s, 0, n_cheb);
         cheb_adapt_run(x, m, prec, 1, adapt_first(0, d_min, d_max, n_cheb), n_cheb, tol, out,
@@ -844,6 +932,7 @@ extern "C" int rpy_lanczos_bounds(rpy_ctx *x, int n_iter, uint64_t seed, const d
     const Ctx &c = x->c;
     const int n3 = c.n3;
     double *qa = x->Bv[0], *qb = x->Bv[1], *w = x->acc;
+    if (c.drow) form_tensor(x, n_iter, s);
     if (!start) {
         launch_noise(x->dW, n3, seed, 0, 1.0, s);
         start = x->dW;
@@ -894,6 +983,7 @@ extern "C" int chebyshev_sqrt_adaptive(rpy_ctx *x, const double *dw, double *out
         return RPY_EINVAL;
     hipStream_t s = S(stream);
     Ctx &c = x->c;
+    if (c.drow) form_tensor(x, n_max - 1, s, m);
     const int floor_n = n_start >= 2 ? n_start : 0;
     launch_copy(c.vhist, dw, (size_t)m * c.n3, s);   // V_0
     launch_cheb_coeffs(c, 0, RPY_BOUNDS_EXPLICIT, 0.0, d_min, d_max, nullptr, s, floor_n, n_max);
@@ -950,7 +1040,7 @@ extern "C" int rpy_u_forward(rpy_ctx *x, const double *pos, const double *F, con
     const size_t nv = (size_t)c.n3;
     launch_wrap_tables(c, pos, s);
     ++x->wrap_gen;
-    launch_build_tiles(c, s);
+    form_tensor(x, n_cheb, s);
     EpiArgs f{};
     f.mode = EPI_APPLY;
     f.m = 1;
@@ -983,7 +1073,7 @@ extern "C" int rpy_u_vjp(rpy_ctx *x, const double *pos, const double *F, const d
     const size_t nv = (size_t)c.n3;
     launch_wrap_tables(c, pos, s);
     ++x->wrap_gen;
-    launch_build_tiles(c, s);
+    form_tensor(x, n_cheb, s);
     launch_cheb_coeffs(c, n_cheb, RPY_BOUNDS_EXPLICIT, 0.0, d_min, d_max, nullptr, s);
     size_t ps = nv;
     if (!vh) {   // recompute V_0 .. V_{n_cheb-1}
@@ -1055,6 +1145,7 @@ extern "C" int rpy_bounds(rpy_ctx *x, int rule, double C, double *d_min, double 
     f.mode = EPI_APPLY;
     f.m = m;
     f.vout = x->Y + nv;
+    if (c.drow) form_tensor(x, 1, s, m);
     product(x, v, m, RPY_PREC_F64, f, s);
     launch_cheb_coeffs(c, 2, rule, C, 0, 0, x->Y + nv, s);
     int rc = check_launch("rpy_bounds");
@@ -1174,10 +1265,7 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
         else launch_copy(w, dw, nv, x->side);
     }
     HIP_TRY(hipEventRecord(x->join, x->side));
-    {
-        ProfScope ps(x, RPY_PROF_BUILD, s);
-        launch_build_tiles(c, s);
-    }
+    form_tensor(x, bp->tol > 0 ? bp->n_max : bp->n_cheb, s);
     HIP_TRY(hipStreamWaitEvent(s, x->join, 0));
     // the drift product: F, then U+ (paper and dilute rules) and U- (dilute),
     // then dW; D.F lands in Y, D.U+ in Y + nv, D.dW last
@@ -1277,6 +1365,7 @@ extern "C" int rpy_real_space_dense(rpy_ctx *x, double *out, void *stream)
         snprintf(g_err, sizeof g_err, "the low-memory form stores no real-space matrix");
         return RPY_EINVAL;
     }
+    if (x->c.drow) form_tensor(x, 1, S(stream), MAX_RHS);   // the tiles hold the real-space part
     launch_dense_copy(x->c, out, S(stream));
     return check_launch("rpy_real_space_dense");
 }

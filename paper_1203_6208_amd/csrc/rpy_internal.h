@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/rpy.h"
 
 #define RPY_HD __host__ __device__
@@ -212,7 +214,15 @@ PairConst make_pair_const(double L, double a, double alpha, double rc);
 // not apply (make_smooth_coef states the rule).
 constexpr int SMOOTH_NP[2] = {30, 38};
 constexpr int SMOOTH_MAX = 38;
-int make_smooth_coef(const PairConst &p, int np_min, double coef[2 * SMOOTH_MAX]);
+constexpr int SMOOTH_NN = 48;
+struct SmoothBasis {   // depends on alpha r_c only: boxes that share it share the basis
+    double um;
+    long double f[4][SMOOTH_NN], power[2][4][SMOOTH_MAX], tail[2][4];
+    explicit SmoothBasis(double um);
+};
+inline double smooth_um(const PairConst &p) { return p.alpha * p.alpha * p.rc2; }
+int make_smooth_coef(const PairConst &p, const SmoothBasis &b, int np_min,
+                     double coef[2 * SMOOTH_MAX]);
 
 // ------------------------------------------------------- pair derivatives
 // d/dx of the M1 coefficients (eq. M1 differentiated, x = alpha r), with the
@@ -403,7 +413,7 @@ struct Ctx {
     int rhs_cap;       // stride of the per-RHS work buffers: max(max_rhs, 3)
     PairConst pc;
     int smooth_np = 0;           // terms of the polynomial pair form (0: erfc / exp form)
-    double *smooth = nullptr;    // [smooth_np][2] its coefficients
+    double *smooth = nullptr;    // [smooth_np][2] its coefficients, then the tables of the rows
     // tiling
     int nbt;           // bead tiles per side
     int ntiles;        // stored tiles
@@ -425,6 +435,11 @@ struct Ctx {
     double *d64 = nullptr;       // [ntiles][TILE6], packed symmetric blocks
     float *p32 = nullptr;        // [ntiles][TILE6] packed planes, lowp FP32
     uint16_t *p16 = nullptr;     // [ntiles][TILE6] packed planes, lowp BF16
+    // complete tensor by rows (rpy_rows.hip; FP64 contexts of at most ROWS_MAX beads)
+    int row_ld = 0;              // columns stored per plane of a row
+    double *drow = nullptr;      // [N][6][row_ld]
+    int *row_off = nullptr;      // octant weights of the reciprocal sum: first chunk per n_x (in smooth)
+    double *row_wk = nullptr;    // their stream (in smooth)
     double *part = nullptr;      // [nbt][rhs_cap][n3pad] tile-column partials
     // block products (5 to 16 vectors on the matrix cores, any tile precision)
     bool block = false;          // enabled: stored tiles and max_rhs >= BLOCK_MIN_RHS
@@ -491,6 +506,15 @@ void launch_wrap_tables(const Ctx &c, const double *pos, hipStream_t s);
 void launch_wrap_positions(const Ctx &c, const double *pos, double *rt, hipStream_t s);
 void launch_build_tiles(const Ctx &c, hipStream_t s);
 void launch_dense_copy(const Ctx &c, double *out, hipStream_t s);
+// complete tensor by rows (rpy_rows.hip): the build from the wrapped positions
+// and phase tables, and a product of up to 4 vectors with its epilogue
+constexpr int ROWS_MAX = 1536;   // beads
+constexpr int rows_nz(int nmax) { return nmax <= 6 ? 7 : 9; }
+bool make_rows_weights(const Ctx &c, std::vector<int> &off, std::vector<double> &w);
+void launch_build_rows(const Ctx &c, hipStream_t s);
+struct EpiArgs;
+void launch_row_product(const Ctx &c, const double *v, const EpiArgs &f, hipStream_t s);
+int rows_trial_chunks(int N);    // its partial sums of a trial per vector
 // products: the tile-product kernel also computes the structure-factor
 // partials of its input; launch_sf_reduce turns them into tk; the final
 // kernel adds the reciprocal back-projection to the tile partials and applies
@@ -551,10 +575,11 @@ void launch_cheb_coeffs(const Ctx &c, int n_cheb, int rule, double C, double dmi
 // written), else puts the coefficients of order n + 1 in place.
 void launch_trial(const Ctx &c, int m, int n, int nmax, double tol, size_t ps,
                   const double *ddw, double *ds, double *e_f, hipStream_t s);
-// The same decision when the back-projection epilogue of the product that
-// completed order n formed the trial (EpiArgs::trial_n): only the check.
-void launch_trial_check(const Ctx &c, int m, int n, int nmax, double tol, double *e_f,
+// The same decision when the epilogue of the product that completed order n
+// formed the trial (EpiArgs::trial_n, nchunk partial sums): only the check.
+void launch_trial_check(const Ctx &c, int m, int nchunk, int n, int nmax, double tol, double *e_f,
                         hipStream_t s);
+int epi_trial_chunks(int N);     // partial sums of a k_kspace_epi trial per vector
 // Partial-sum chunks of a trial per right-hand side: the larger of the
 // separate trial kernel's (256 entries each) and the epilogue's (one per
 // workgroup), which sizes c.tpart.

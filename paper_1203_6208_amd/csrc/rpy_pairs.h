@@ -35,7 +35,9 @@ __device__ inline void smooth_images(const double (&r2)[R], const PairConst &p, 
     }
     // The coefficients of a chunk are loaded while the previous chunk is
     // used; the empty asm ties each load to that chunk's start, since all
-    // of them at once do not fit the scalar registers.
+    // of them at once do not fit the scalar registers.  Scalar loads return
+    // out of order, so a wait is always for all of them: the asm also takes
+    // the current chunk, whose wait then comes before the next chunk's loads.
     double cur[2 * CH], nxt[2 * CH];
 #pragma unroll
     for (int q = 0; q < R; ++q) __asm__ volatile("" : "+s"(coef), "+v"(z[q]));
@@ -44,6 +46,7 @@ __device__ inline void smooth_images(const double (&r2)[R], const PairConst &p, 
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
         if (k + 1 < NC) {
+            __asm__ volatile("" : "+s"(coef), "+s"(cur[0]), "+s"(cur[2 * CH - 1]));
 #pragma unroll
             for (int q = 0; q < R; ++q)
                 __asm__ volatile("" : "+s"(coef), "+v"(s1[q]), "+v"(s2[q]));
@@ -93,9 +96,15 @@ __device__ inline void smooth_images(const double (&r2)[R], const PairConst &p, 
 //     64 pairs have one.
 // Two rows per group: with one the build of N = 4000 beads takes 134 us, with
 // two 97, with four 105 (registers).
-// store(bi, bj, b) receives the 6 entries of each pair (zero for padding).
+// store(bi, bj, b) receives the rows bi[q] of a group and the 6 entries of
+// each pair (zero for padding).
 constexpr int PAIR_GROUP = 2;
-template <int NF> constexpr int pair_queue() { return PAIR_GROUP * 64 * NF; }
+constexpr int PAIR_CAND = 4;   // candidates per row queued at a time
+template <int NF, int G = PAIR_GROUP> constexpr int pair_queue()
+{
+    return G * 64 * (NF < PAIR_CAND ? NF : PAIR_CAND);
+}
+template <int NF> constexpr int pair_code(int f) { return NF == 3 ? 1 << f : f + 1; }
 
 __device__ inline void pair_wave_sync()
 {
@@ -110,25 +119,22 @@ __device__ inline int lanes_below(unsigned long long m)
     return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
 }
 
-template <int TBB, int NP, int NF, typename Store>
+template <int TBB, int NP, int NF, int G = PAIR_GROUP, typename Store>
 __device__ inline void build_rows(const PairConst &p, SmoothCoef coef, const double *sI,
                                   const double *sJ, int nI, int nJ, bool diag, int lane, int row0,
                                   int ngroups, double *qa, double *qb, Store store)
 {
-    constexpr int G = PAIR_GROUP;
     constexpr int RS = 64 / TBB;   // rows per wave step
     const int bj = lane % TBB, sub = lane / TBB;
     const double xj = sJ[3 * bj], yj = sJ[3 * bj + 1], zj = sJ[3 * bj + 2];
     const bool okj = bj < nJ;
     for (int g = 0; g < ngroups; ++g) {
         double d[G][3], e[G][3], r2[G];   // nearest image; its components moved one box length
-        unsigned hit = 0;   // bit q NF + f: candidate f of row q contributes
-        int qn = 0;         // queued candidates (wave-uniform)
+        int rows[G];
 #pragma unroll
         for (int q = 0; q < G; ++q) {
-            const int bi = row0 + (g * G + q) * RS + sub;
+            const int bi = rows[q] = row0 + (g * G + q) * RS + sub;
             const double d0[3] = {sI[3 * bi] - xj, sI[3 * bi + 1] - yj, sI[3 * bi + 2] - zj};
-            const bool live = okj && bi < nI && !(diag && bi == bj);
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 const double n = -rint(d0[a] * p.invL);
@@ -136,65 +142,82 @@ __device__ inline void build_rows(const PairConst &p, SmoothCoef coef, const dou
                 e[q][a] = d0[a] + (n - copysign(1.0, d[q][a])) * p.L;
             }
             r2[q] = d[q][0] * d[q][0] + d[q][1] * d[q][1] + d[q][2] * d[q][2];
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const int code = NF == 3 ? 1 << f : f + 1;
-                const double fx = code & 1 ? e[q][0] : d[q][0], fy = code & 2 ? e[q][1] : d[q][1],
-                             fz = code & 4 ? e[q][2] : d[q][2];
-                const double f2 = fx * fx + fy * fy + fz * fz;
-                const bool in = live && f2 <= p.rc2;
-                const unsigned long long m = __ballot(in);
-                if (in) qa[qn + lanes_below(m)] = f2;
-                qn += __popcll(m);
-                hit |= in ? 1u << (q * NF + f) : 0u;
-            }
         }
-        double c1[G], w[G];
+        double c1[G], w[G], bb[G][6];
         smooth_images<G, NP>(r2, p, coef, c1, w);
-        pair_wave_sync();
-        for (int s = lane; s < qn; s += 64) {
-            const double f2[1] = {qa[s]};
-            double fc[1], fw[1];
-            smooth_images<1, NP>(f2, p, coef, fc, fw);
-            qa[s] = fc[0];
-            qb[s] = fw[0];
-        }
-        pair_wave_sync();
-        int base = 0;
 #pragma unroll
         for (int q = 0; q < G; ++q) {
-            const int bi = row0 + (g * G + q) * RS + sub;
-            const bool live = okj && bi < nI, self = diag && bi == bj;
+            double(&b)[6] = bb[q];
+            const bool live = okj && rows[q] < nI, self = diag && rows[q] == bj;
             const bool in = live && !self && (r2[q] <= p.rc2 || r2[q] < p.a2x4);
             const double a = in ? c1[q] : live && self ? p.self_coeff : 0.0, v = in ? w[q] : 0.0;
             const double vx = v * d[q][0], vy = v * d[q][1];
-            double b[6] = {fma(vx, d[q][0], a), vx * d[q][1], vx * d[q][2],
-                           fma(vy, d[q][1], a), vy * d[q][2], fma(v * d[q][2], d[q][2], a)};
+            b[0] = fma(vx, d[q][0], a);
+            b[1] = vx * d[q][1];
+            b[2] = vx * d[q][2];
+            b[3] = fma(vy, d[q][1], a);
+            b[4] = vy * d[q][2];
+            b[5] = fma(v * d[q][2], d[q][2], a);
+        }
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const bool has = hit & (1u << (q * NF + f));
-                const unsigned long long m = __ballot(has);
-                if (m == 0) continue;   // wave-uniform
-                const int code = NF == 3 ? 1 << f : f + 1;
-                if (has) {
-                    const int s = base + lanes_below(m);
-                    const double fc = qa[s], fw = qb[s];
+        for (int f0 = 0; f0 < NF; f0 += PAIR_CAND) {
+            unsigned hit = 0;   // bit q PAIR_CAND + f: candidate f0 + f of row q contributes
+            int qn = 0;         // queued candidates (wave-uniform)
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const bool live = okj && rows[q] < nI && !(diag && rows[q] == bj);
+#pragma unroll
+                for (int f = 0; f < PAIR_CAND && f0 + f < NF; ++f) {
+                    const int code = pair_code<NF>(f0 + f);
                     const double fx = code & 1 ? e[q][0] : d[q][0],
                                  fy = code & 2 ? e[q][1] : d[q][1],
                                  fz = code & 4 ? e[q][2] : d[q][2];
-                    const double ux = fw * fx, uy = fw * fy;
-                    b[0] += fma(ux, fx, fc);
-                    b[1] += ux * fy;
-                    b[2] += ux * fz;
-                    b[3] += fma(uy, fy, fc);
-                    b[4] += uy * fz;
-                    b[5] += fma(fw * fz, fz, fc);
+                    const double f2 = fx * fx + fy * fy + fz * fz;
+                    const bool in = live && f2 <= p.rc2;
+                    const unsigned long long m = __ballot(in);
+                    if (in) qa[qn + lanes_below(m)] = f2;
+                    qn += __popcll(m);
+                    hit |= in ? 1u << (q * PAIR_CAND + f) : 0u;
                 }
-                base += __popcll(m);
             }
-            store(bi, bj, b);
+            pair_wave_sync();
+            for (int s = lane; s < qn; s += 64) {
+                const double f2[1] = {qa[s]};
+                double fc[1], fw[1];
+                smooth_images<1, NP>(f2, p, coef, fc, fw);
+                qa[s] = fc[0];
+                qb[s] = fw[0];
+            }
+            pair_wave_sync();
+            int base = 0;
+#pragma unroll
+            for (int q = 0; q < G; ++q)
+#pragma unroll
+                for (int f = 0; f < PAIR_CAND && f0 + f < NF; ++f) {
+                    const bool has = hit & (1u << (q * PAIR_CAND + f));
+                    const unsigned long long m = __ballot(has);
+                    if (m == 0) continue;   // wave-uniform
+                    const int code = pair_code<NF>(f0 + f);
+                    double(&b)[6] = bb[q];
+                    if (has) {
+                        const int s = base + lanes_below(m);
+                        const double fc = qa[s], fw = qb[s];
+                        const double fx = code & 1 ? e[q][0] : d[q][0],
+                                     fy = code & 2 ? e[q][1] : d[q][1],
+                                     fz = code & 4 ? e[q][2] : d[q][2];
+                        const double ux = fw * fx, uy = fw * fy;
+                        b[0] += fma(ux, fx, fc);
+                        b[1] += ux * fy;
+                        b[2] += ux * fz;
+                        b[3] += fma(uy, fy, fc);
+                        b[4] += uy * fz;
+                        b[5] += fma(fw * fz, fz, fc);
+                    }
+                    base += __popcll(m);
+                }
+            pair_wave_sync();   // the queue is rewritten
         }
-        pair_wave_sync();   // the queue is rewritten by the next group
+        store(rows, bj, bb);
     }
 }
 
