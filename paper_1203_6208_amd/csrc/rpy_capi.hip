@@ -39,6 +39,10 @@ struct rpy_ctx {
     // bookkeeping does not see -- from then on the context uses the tiles only
     uint64_t tiles_gen = 0, rows_gen = 0;
     bool captured = false;
+    // series kernel: number of its next call's first term, bound of its waits
+    // (10 ms; a wait is microseconds unless the kernel is not fully resident)
+    uint32_t series_epoch = 1;
+    long long series_limit = 1000000;
     // bd_step runs the forces and the noise on a second stream (default
     // priority) beside the tile build: fork after the wrap, join before the
     // drift product
@@ -308,7 +312,7 @@ extern "C" void rpy_destroy(rpy_ctx *x)
     (void)hipDeviceSynchronize();
     Ctx &c = x->c;
     void *bufs[] = {c.rt, c.rt_ev, c.smooth, c.eph, c.etab, c.kvec, c.kcoef, c.tile_ij, c.d64,
-                    c.p32, c.p16, c.drow, c.part, c.xpk, c.ypart,
+                    c.p32, c.p16, c.drow, c.series, c.part, c.xpk, c.ypart,
                     c.vpk, c.bpart, c.tkm,
                     c.sfpart, c.tk, c.sfr, c.work, c.scal, c.red, c.flags, c.cell_start, c.lanc,
                     c.adapt, c.tpart,
@@ -418,6 +422,12 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     const bool rows = !c.lma && c.lowp == RPY_PREC_F64 && c.N <= ROWS_MAX &&
                       make_rows_weights(c, roff, rwk);
     c.row_ld = (c.N + 127) / 128 * 128;
+    const bool series = rows && c.N <= SERIES_MAX;
+    // coefficients, ring, vector words, partial-sum words, record, flag
+    constexpr size_t SW = 2 * 2 * 3 * SERIES_MAX, SP = 2 * 2 * 2 * 64;
+    constexpr size_t SC = (SERIES_ORDERS + 1) * SERIES_ORDERS, SR = 3 * 3 * SERIES_MAX;
+    constexpr size_t SERIES_DOUBLES = SC + SR + SW + SP + 2 + 1;
+    static_assert(sizeof(SeriesRec) == 2 * sizeof(double), "the record is two doubles");
     // one table: the pair polynomials, the octant weights, their offsets
     std::vector<double> tabs(smooth, smooth + 2 * SMOOTH_MAX);
     tabs.insert(tabs.end(), rwk.begin(), rwk.end());
@@ -435,6 +445,7 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
                    (rc = dalloc(&c.rt_sorted, nv)) ||
                    (rc = dalloc(&c.v_sorted, (size_t)c.rhs_cap * nv)))) ||
         (rows && (rc = dalloc(&c.drow, (size_t)c.N * 6 * c.row_ld))) ||
+        (series && (rc = dalloc(&c.series, SERIES_DOUBLES))) ||
         (c.lowp == RPY_PREC_F32 && (rc = dalloc(&c.p32, te6))) ||
         (c.lowp == RPY_PREC_BF16 && (rc = dalloc(&c.p16, te6))) ||
         (rc = dalloc(&c.part, (size_t)c.nslot * c.rhs_cap * c.n3pad)) ||
@@ -463,6 +474,14 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
         rpy_destroy(x);
         return rc;
     }
+    if (series) {
+        c.series_coef = c.series;
+        c.series_ring = c.series + SC;
+        c.series_words = reinterpret_cast<unsigned long long *>(c.series + SC + SR);
+        c.series_part = c.series_words + SW;
+        c.series_rec = reinterpret_cast<SeriesRec *>(c.series_part + SP);
+        c.series_abort = reinterpret_cast<int *>(c.series_rec + 1);
+    }
     c.row_wk = c.smooth + 2 * SMOOTH_MAX;
     c.row_off = reinterpret_cast<int *>(c.row_wk + rwk.size());
     double *w = c.work;
@@ -487,6 +506,7 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
         (e = hipMemset(c.adapt, 0, sizeof(AdaptState))) ||
         (te6 && (e = hipMemset(c.d64, 0, te6 * sizeof(double)))) ||
         // the columns past the tiles are never written
+        (series && (e = hipMemset(c.series + SC, 0, (SERIES_DOUBLES - SC) * sizeof(double)))) ||
         (rows && c.row_ld > c.nbt * TB &&
          (e = hipMemset2D(c.drow + c.nbt * TB, c.row_ld * sizeof(double), 0,
                           (c.row_ld - c.nbt * TB) * sizeof(double), (size_t)c.N * 6))) ||
@@ -713,6 +733,47 @@ static void cheb_run(rpy_ctx *x, const double *dw, double *out, int m, int n_che
     }
 }
 
+// Whether the series of one vector up to order nmax runs in one launch.
+static bool by_series(const rpy_ctx *x, int m, int nmax)
+{
+    return x->c.series && m == 1 && nmax <= SERIES_ORDERS && by_rows(x, 1);
+}
+
+// The arguments of such a series on V_0 = dw into out, n terms or, with st,
+// orders up to n.
+static SeriesArgs series_args(rpy_ctx *x, const double *dw, double *out, int n, AdaptState *st,
+                              double tol)
+{
+    const Ctx &c = x->c;
+    SeriesArgs a{};
+    a.N = c.N;
+    a.ld = c.row_ld;
+    a.n = n;
+    a.drow = c.drow;
+    a.dw = dw;
+    a.ud = x->Y;
+    a.ddw = x->ddw;
+    a.out = out;
+    a.scal = c.scal;
+    a.coef = st ? c.series_coef : c.series_coef + (size_t)n * SERIES_ORDERS;
+    a.st = st;
+    a.tol = tol;
+    a.words = c.series_words;
+    a.part = c.series_part;
+    a.epoch = x->series_epoch;
+    x->series_epoch += (uint32_t)n + 2;   // terms 1 .. n and the last sums
+    a.limit = x->series_limit;
+    a.abort_flag = c.series_abort;
+    a.rec = c.series_rec;
+    a.vh = st ? c.vhist : c.series_ring;
+    a.ps = st ? (size_t)c.rhs_cap * c.n3 : (size_t)3 * SERIES_MAX;
+    return a;
+}
+
+// For tests: the bound of the series kernel's waits, in 100 MHz ticks (negative:
+// every wait gives up at once, so that the finishing kernel runs the series).
+extern "C" void rpy_series_wait(rpy_ctx *x, int64_t ticks) { x->series_limit = ticks; }
+
 // First order of an adaptive call as the device computes it from the
 // interval (eq. nint, rounded half away from zero) or the caller's start.
 static int adapt_first(int floor_n, double d_min, double d_max, int nmax)
@@ -799,6 +860,23 @@ static int adapt_result(rpy_ctx *x, int *n_used, hipStream_t s)
     return st.last_etol ? RPY_ETOL : RPY_OK;
 }
 
+// The series on an explicit interval: n0 terms (tol <= 0, n0 = n) or the orders
+// n0 .. n.
+static void series_explicit(rpy_ctx *x, const double *dw, double *out, int n0, int n, double d_min,
+                            double d_max, double tol, double *e_f, hipStream_t s)
+{
+    const Ctx &c = x->c;
+    AdaptState *st = tol > 0 ? c.adapt : nullptr;
+    launch_series_coeffs(c, n0, n, 1, d_min, d_max, st, s);
+    SeriesArgs a = series_args(x, dw, out, n, st, tol);
+    a.want_ef = e_f != nullptr;
+    {
+        ProfScope ps(x, RPY_PROF_SYMV, s);
+        launch_series(a, s);
+    }
+    launch_series_finish(a, nullptr, 0.0, nullptr, nullptr, e_f ? e_f : c.red, s);
+}
+
 extern "C" int chebyshev_sqrt_apply(rpy_ctx *x, const double *dw, double *out, int m,
                                     int n_cheb, double d_min, double d_max, double tol, int prec,
                                     int *n_used, double *e_f, void *stream)
@@ -815,6 +893,12 @@ extern "C" int chebyshev_sqrt_apply(rpy_ctx *x, const double *dw, double *out, i
     }
     if (c.drow) form_tensor(x, n_cheb - 1, s, m);
     if (tol > 0) {
+        if (by_series(x, m, n_cheb)) {
+            series_explicit(x, dw, out, adapt_first(0, d_min, d_max, n_cheb), n_cheb, d_min, d_max,
+                            tol, e_f, s);
+            int rc = check_launch("chebyshev_sqrt_apply");
+            return rc || !n_used ? rc : adapt_result(x, n_used, s);
+        }
         launch_copy(c.vhist, dw, (size_t)m * c.n3, s);   // V_0
         launch_cheb_coeffs(c, 0, RPY_BOUNDS_EXPLICIT, 0.0, d_min, d_max, nullptr, s, 0, n_cheb);
         cheb_adapt_run(x, m, prec, 1, adapt_first(0, d_min, d_max, n_cheb), n_cheb, tol, out,
@@ -822,6 +906,11 @@ extern "C" int chebyshev_sqrt_apply(rpy_ctx *x, const double *dw, double *out, i
         int rc = check_launch("chebyshev_sqrt_apply");
         if (rc || !n_used) return rc;
         return adapt_result(x, n_used, s);
+    }
+    if (by_series(x, m, n_cheb)) {
+        series_explicit(x, dw, out, n_cheb, n_cheb, d_min, d_max, 0.0, e_f, s);
+        if (n_used) *n_used = n_cheb;
+        return check_launch("chebyshev_sqrt_apply");
     }
     launch_cheb_coeffs(c, n_cheb, RPY_BOUNDS_EXPLICIT, 0.0, d_min, d_max, nullptr, s);
     cheb_run(x, dw, out, m, n_cheb, prec, s);
@@ -985,6 +1074,12 @@ extern "C" int chebyshev_sqrt_adaptive(rpy_ctx *x, const double *dw, double *out
     Ctx &c = x->c;
     if (c.drow) form_tensor(x, n_max - 1, s, m);
     const int floor_n = n_start >= 2 ? n_start : 0;
+    if (by_series(x, m, n_max)) {
+        series_explicit(x, dw, out, adapt_first(floor_n, d_min, d_max, n_max), n_max, d_min, d_max,
+                        tol, e_f, s);
+        int rc = check_launch("chebyshev_sqrt_adaptive");
+        return rc ? rc : adapt_result(x, n_used, s);
+    }
     launch_copy(c.vhist, dw, (size_t)m * c.n3, s);   // V_0
     launch_cheb_coeffs(c, 0, RPY_BOUNDS_EXPLICIT, 0.0, d_min, d_max, nullptr, s, floor_n, n_max);
     cheb_adapt_run(x, m, prec, 1, adapt_first(floor_n, d_min, d_max, n_max), n_max, tol, out,
@@ -1270,6 +1365,24 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
     // the drift product: F, then U+ (paper and dilute rules) and U- (dilute),
     // then dW; D.F lands in Y, D.U+ in Y + nv, D.dW last
     const int nb = rule == RPY_BOUNDS_PAPER ? 1 : rule == RPY_BOUNDS_DILUTE ? 2 : 0;
+    const int floor_n = adapt ? (bp->n_cheb >= 2 ? bp->n_cheb : 0) : -1;
+    const int nmax = adapt ? bp->n_max : bp->n_cheb;
+    const bool series = by_series(x, 1, nmax);
+    if (series && rule == RPY_BOUNDS_EXPLICIT) {
+        // the interval needs no product: drift, series and update in two launches
+        AdaptState *st = adapt ? c.adapt : nullptr;
+        launch_series_coeffs(c, adapt ? adapt_first(floor_n, bp->d_min, bp->d_max, nmax) : nmax, nmax,
+                             1, bp->d_min, bp->d_max, st, s);
+        SeriesArgs a = series_args(x, w, x->dS, nmax, st, bp->tol);
+        a.F = x->F;
+        a.want_ef = e_f != nullptr;
+        {
+            ProfScope ps(x, RPY_PROF_SYMV, s);
+            launch_series(a, s);
+        }
+        launch_series_finish(a, pos, bp->dt / 4.0, drift, noise, e_f ? e_f : c.red, s);
+        return check_launch("bd_step");
+    }
     EpiArgs f{};
     f.mode = EPI_APPLY;
     f.vout = x->Y;
@@ -1287,13 +1400,10 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
         product(x, g, f.m, RPY_PREC_F64, f, s);
     }
     const double *du = x->Y + nv;
-    const int floor_n = adapt ? (bp->n_cheb >= 2 ? bp->n_cheb : 0) : -1;
-    const int nmax = adapt ? bp->n_max : bp->n_cheb;
     launch_cheb_coeffs(c, bp->n_cheb, rule, bp->bounds_C, bp->d_min, bp->d_max,
                        nb ? du : nullptr, s, floor_n, nmax);
-    if (adapt) {
+    if (adapt || series) {
         const size_t ps = (size_t)c.rhs_cap * nv;
-        launch_copy(c.vhist, w, nv, s);   // V_0
         // The first order the device can start from.  Explicit interval: the
         // device's own value.  The paper's rule fixes d_max / d_min = C N^0.6
         // whatever D is, so eq. nint is known up to the rounding of that
@@ -1306,6 +1416,21 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
             const int k = adapt_first(0, 1.0, bp->bounds_C * pow((double)c.N, 0.6), nmax) - 1;
             host_first = k < 2 ? 2 : k;
         }
+        if (series) {
+            if (adapt) launch_series_coeffs(c, host_first, nmax, 0, 0.0, 0.0, c.adapt, s);
+            SeriesArgs a = series_args(x, w, x->dS, nmax, adapt ? c.adapt : nullptr, bp->tol);
+            a.have_ddw = 1;
+            a.ddw = x->Y + (1 + nb) * nv;
+            if (!adapt) a.coef = c.scal + 8;
+            a.want_ef = e_f != nullptr;
+            {
+                ProfScope pf(x, RPY_PROF_SYMV, s);
+                launch_series(a, s);
+            }
+            launch_series_finish(a, pos, bp->dt / 4.0, drift, noise, e_f ? e_f : c.red, s);
+            return check_launch("bd_step");
+        }
+        launch_copy(c.vhist, w, nv, s);   // V_0
         launch_cheb_first(c, x->Y + (1 + nb) * nv, w, c.vhist + ps, x->acc, x->ddw, s);
         cheb_adapt_run(x, 1, bp->prec, 2, host_first, nmax, bp->tol, x->dS,
                        e_f ? e_f : c.red, s);

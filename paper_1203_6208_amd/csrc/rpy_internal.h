@@ -440,6 +440,13 @@ struct Ctx {
     double *drow = nullptr;      // [N][6][row_ld]
     int *row_off = nullptr;      // octant weights of the reciprocal sum: first chunk per n_x (in smooth)
     double *row_wk = nullptr;    // their stream (in smooth)
+    // series in one launch (rpy_series.hip; rows of at most SERIES_MAX beads)
+    double *series = nullptr;        // one allocation: the buffers below
+    double *series_coef = nullptr;   // [SERIES_ORDERS + 1][SERIES_ORDERS] c_p per order
+    double *series_ring = nullptr;   // [3][3 SERIES_MAX]
+    unsigned long long *series_words = nullptr, *series_part = nullptr;
+    struct SeriesRec *series_rec = nullptr;
+    int *series_abort = nullptr;
     double *part = nullptr;      // [nbt][rhs_cap][n3pad] tile-column partials
     // block products (5 to 16 vectors on the matrix cores, any tile precision)
     bool block = false;          // enabled: stored tiles and max_rhs >= BLOCK_MIN_RHS
@@ -515,6 +522,38 @@ void launch_build_rows(const Ctx &c, hipStream_t s);
 struct EpiArgs;
 void launch_row_product(const Ctx &c, const double *v, const EpiArgs &f, hipStream_t s);
 int rows_trial_chunks(int N);    // its partial sums of a trial per vector
+// The Chebyshev series of one vector in one launch (rpy_series.hip).
+constexpr int SERIES_MAX = 512;      // beads
+constexpr int SERIES_ORDERS = 128;   // largest order
+struct SeriesRec {
+    double ef;
+    int n, pad;
+};
+struct SeriesArgs {
+    int N, ld;
+    int n;                    // terms; with st the largest order
+    int have_ddw;             // ddw holds D dW
+    int want_ef;              // fixed order: E_f wanted
+    const double *drow, *dw;  // rows of D, V_0
+    const double *F;          // with F: ud = D F as well
+    double *ud, *ddw, *out;   // D F, D dW, dS
+    const double *scal;       // interval scalars
+    const double *coef;       // fixed order: c_p; with st [order][SERIES_ORDERS]
+    AdaptState *st;           // adaptive order, null: fixed
+    double tol;
+    unsigned long long *words, *part;   // the vectors and partial sums in flight
+    uint32_t epoch;           // first of the numbers this call marks its words with
+    long long limit;          // bound of a wait (100 MHz ticks)
+    int *abort_flag;
+    SeriesRec *rec;
+    double *vh;               // for the finishing kernel alone: terms at vh + p ps
+    size_t ps;
+};
+void launch_series_coeffs(const Ctx &c, int n0, int n1, int explicit_, double dmin, double dmax,
+                          AdaptState *st, hipStream_t s);
+void launch_series(const SeriesArgs &a, hipStream_t s);
+void launch_series_finish(const SeriesArgs &a, double *pos, double dt4, double *drift, double *noise,
+                          double *e_f, hipStream_t s);
 // products: the tile-product kernel also computes the structure-factor
 // partials of its input; launch_sf_reduce turns them into tk; the final
 // kernel adds the reciprocal back-projection to the tile partials and applies

@@ -113,6 +113,19 @@ __device__ inline void pair_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Components 0..2 summed over the wave: lane l receives component l & 3 (0 in
+// lane 3).
+__device__ inline double wave_sum3(double a0, double a1, double a2, int lane)
+{
+    const bool b0 = lane & 1, b1 = lane & 2;
+    const double r0 = (b0 ? a1 : a0) + __shfl_xor(b0 ? a0 : a1, 1);
+    const double r1 = (b0 ? 0.0 : a2) + __shfl_xor(b0 ? a2 : 0.0, 1);
+    double r = (b1 ? r1 : r0) + __shfl_xor(b1 ? r0 : r1, 2);
+#pragma unroll
+    for (int o = 4; o <= 32; o <<= 1) r += __shfl_xor(r, o);
+    return r;
+}
+
 // Lanes below this one that are set in a wave mask.
 __device__ inline int lanes_below(unsigned long long m)
 {

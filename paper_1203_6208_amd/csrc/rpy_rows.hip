@@ -307,19 +307,6 @@ constexpr int ROW_U = 4;
 constexpr int ROW_BEADS = 4;
 typedef double row2 __attribute__((ext_vector_type(2)));
 
-// Components 0..2 summed over the wave: lane l receives component l & 3 (0 in
-// lane 3).
-__device__ inline double wave_sum3(double a0, double a1, double a2, int lane)
-{
-    const bool b0 = lane & 1, b1 = lane & 2;
-    const double r0 = (b0 ? a1 : a0) + __shfl_xor(b0 ? a0 : a1, 1);
-    const double r1 = (b0 ? 0.0 : a2) + __shfl_xor(b0 ? a2 : 0.0, 1);
-    double r = (b1 ? r1 : r0) + __shfl_xor(b1 ? r0 : r1, 2);
-#pragma unroll
-    for (int o = 4; o <= 32; o <<= 1) r += __shfl_xor(r, o);
-    return r;
-}
-
 template <int M, int WPR>
 __global__ __launch_bounds__(64 * ROW_BEADS * WPR) void k_row(int N, int n3, int ld, int j0,
                                                               int flip, const double *drow,

@@ -1,0 +1,465 @@
+// rpy_series.hip -- the whole Chebyshev series of one vector in one launch, for
+// boxes of at most SERIES_MAX beads whose tensor is stored by rows
+// (rpy_rows.hip).
+//
+// Such a product is about a microsecond of work behind four of launch.  Here a
+// term takes 2.0 us at N = 100 and, with the trials of the adaptive order, 3.0
+// at N = 400 (one launch per term: 3.9 and 5.6, plus the check of each order),
+// bound by the round trip of the new vector through memory:
+// every wave keeps its bead row of D in registers for the whole series, and the
+// workgroups pass each new vector to each other through memory: every double
+// travels as two 8-byte words that carry half of it and the number of the
+// term, so a reader polls the words themselves until all of them are of the
+// term it waits for -- no barrier, no fence, no separate flag, only relaxed
+// atomic accesses at device scope.  Two slots suffice: a workgroup writes V_{p+2}
+// after it has read all of V_{p+1}, so every workgroup has read all of V_p by then.
+//
+// The wait needs all workgroups on the device at once (one per 8 beads, 64 at
+// most).  They are, unless enough other such kernels run at the same time that
+// some are only partly resident; so every wait is bounded: a workgroup that has
+// waited for its limit raises a flag, all of them leave, and the finishing
+// kernel, one workgroup that waits for nobody, then runs the series alone.
+#include "rpy_internal.h"
+#include "rpy_pairs.h"
+
+namespace rpy {
+
+constexpr int SR_BEADS = 8;                 // beads (waves) per workgroup
+constexpr int SR_NT = 64 * SR_BEADS;
+constexpr int SR_NB = SERIES_MAX / 128;     // column blocks of a row
+static_assert(SERIES_MAX / SR_BEADS <= 64, "one lane per workgroup in the partial sums");
+typedef double sr2 __attribute__((ext_vector_type(2)));
+typedef unsigned long long word_t;
+
+__device__ inline void put(word_t *p, double v, uint32_t ep)
+{
+    const word_t b = (word_t)__double_as_longlong(v), e = (word_t)ep << 32;
+    __hip_atomic_store(p, e | (b & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + 1, e | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Polls the n <= NW doubles q, q + stride, ... of this thread until all carry
+// ep.  False if the wait ran out or another workgroup's did.
+template <int NW>
+__device__ inline bool take(const word_t *src, int q, int stride, int n, uint32_t ep, double *v,
+                            int *abort_flag, long long limit)
+{
+    const long long t0 = wall_clock64();
+    if (limit < 0) {   // tests: no wait is granted
+        __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
+    }
+    for (int it = 0;; ++it) {
+        word_t w[NW][2];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            const int e = q + k * stride;
+            if (e < n) {
+                w[k][0] = __hip_atomic_load(src + 2 * e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                w[k][1] = __hip_atomic_load(src + 2 * e + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                w[k][0] = w[k][1] = (word_t)ep << 32;
+            }
+        }
+        bool all = true;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            all = all && (uint32_t)(w[k][0] >> 32) == ep && (uint32_t)(w[k][1] >> 32) == ep;
+            v[k] = __longlong_as_double((long long)((w[k][1] << 32) | (w[k][0] & 0xffffffffull)));
+        }
+        if (all) return true;
+        if ((it & 15) == 15 &&
+            (__hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
+             wall_clock64() - t0 > limit)) {
+            __hip_atomic_store(abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return false;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+
+// y += the lane's two columns of a column block times their vector entries x.
+__device__ inline void row_block(const sr2 (&d)[6], const double *x, double &y0, double &y1, double &y2)
+{
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const double x0 = x[3 * q], x1 = x[3 * q + 1], x2 = x[3 * q + 2];
+        y0 += d[0][q] * x0 + d[1][q] * x1 + d[2][q] * x2;
+        y1 += d[1][q] * x0 + d[3][q] * x1 + d[4][q] * x2;
+        y2 += d[2][q] * x0 + d[4][q] * x1 + d[5][q] * x2;
+    }
+}
+
+// The row's product with the staged vector x: component l & 3 in lane l.
+__device__ inline double row_dot(const sr2 (&d)[SR_NB][6], int nb, const double *x, int lane)
+{
+    double y0 = 0.0, y1 = 0.0, y2 = 0.0;
+#pragma unroll
+    for (int u = 0; u < SR_NB; ++u)
+        if (u < nb) row_block(d[u], x + 6 * (lane + 64 * u), y0, y1, y2);
+    return wave_sum3(y0, y1, y2, lane);
+}
+
+// dS of order n from the history lanes (V_q in lane q & 63, set q >> 6).
+__device__ inline double trial_sum(const double (&h)[2][3], int n, const double *ct, int lane)
+{
+    double t0 = 0.0, t1 = 0.0, t2 = 0.0;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int q = 64 * s + lane;
+        const double c = q < n ? (q ? ct[q] : 0.5 * ct[0]) : 0.0;
+        t0 += c * h[s][0];
+        t1 += c * h[s][1];
+        t2 += c * h[s][2];
+    }
+    return wave_sum3(t0, t1, t2, lane);
+}
+
+__device__ inline bool settles(double a, double b, int n, int nmax, double tol, double &ef)
+{
+    ef = sqrt(fabs(a - b) / b);
+    return (ef > 0.0 ? ef : 0.0) < tol || n >= nmax;   // as k_trial_check
+}
+
+__global__ __launch_bounds__(SR_NT) void k_series(SeriesArgs a)
+{
+    __shared__ double sx[2][3 * SERIES_MAX];
+    __shared__ double tred[SR_BEADS][2], pr[2 * 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int i = blockIdx.x * SR_BEADS + w, ic = min(i, a.N - 1), n3 = 3 * a.N;
+    const int nb = a.ld / 128, G = gridDim.x;
+    const bool eth = i < a.N && lane < 3;   // lanes 0..2 own the row's entries
+    const size_t o = 3 * (size_t)ic + min(lane, 2);
+    const double *row = a.drow + (size_t)ic * 6 * a.ld + 2 * lane;
+    sr2 d[SR_NB][6];
+#pragma unroll
+    for (int u = 0; u < SR_NB; ++u)
+#pragma unroll
+        for (int e = 0; e < 6; ++e)
+            d[u][e] = u < nb ? *reinterpret_cast<const sr2 *>(row + (size_t)e * a.ld + 128 * u)
+                             : sr2{0.0, 0.0};
+    for (int z = threadIdx.x; z < 3 * SERIES_MAX; z += SR_NT) {
+        sx[0][z] = z < n3 ? a.dw[z] : 0.0;
+        sx[1][z] = a.F && z < n3 ? a.F[z] : 0.0;
+    }
+    const double ya = a.scal[2], yb = a.scal[3];
+    const bool adapt = a.st != nullptr;
+    const int nmax = a.n, nst = adapt ? a.st->n_start : 0;
+    __syncthreads();
+    const double v0 = sx[0][o];
+    double dd;   // D dW
+    if (a.have_ddw) dd = a.ddw[o];
+    else dd = row_dot(d, nb, sx[0], lane);
+    if (a.F) {
+        const double f = row_dot(d, nb, sx[1], lane);
+        if (eth) a.ud[o] = f;
+    }
+    if (!a.have_ddw && eth) a.ddw[o] = dd;
+    double vp = v0, v = ya * dd - yb * v0;   // V_0, V_1
+    if (eth && nmax > 2) put(a.words + 2 * o, v, a.epoch + 1);
+    __syncthreads();
+    for (int z = threadIdx.x; z < 3 * SERIES_MAX; z += SR_NT) sx[1][z] = 0.0;   // zero past 3N
+    double acc = 0.0, h[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}}, t = 0.0;
+    const double *ct = a.coef;   // fixed order: its coefficients
+    auto keep = [&](int p, double x) {   // V_p into its history lane
+        const double x0 = __shfl(x, 0), x1 = __shfl(x, 1), x2 = __shfl(x, 2);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+            if (p == 64 * s + lane) {
+                h[s][0] = x0;
+                h[s][1] = x1;
+                h[s][2] = x2;
+            }
+    };
+    // this workgroup's share of dS.dS and dW.D dW, to every workgroup
+    auto share = [&](double s, uint32_t ep) {
+        const double q = eth ? s * s : 0.0, r = eth ? v0 * dd : 0.0;
+        const double q3 = __shfl(q, 0) + __shfl(q, 1) + __shfl(q, 2);
+        const double r3 = __shfl(r, 0) + __shfl(r, 1) + __shfl(r, 2);
+        if (lane == 0) {
+            tred[w][0] = q3;
+            tred[w][1] = r3;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            double z = tred[0][threadIdx.x];
+#pragma unroll
+            for (int k = 1; k < SR_BEADS; ++k) z += tred[k][threadIdx.x];
+            put(a.part + 2 * ((ep & 1) * 2 * 64 + 2 * blockIdx.x + threadIdx.x), z, ep);
+        }
+    };
+    // the sums over all workgroups, in their order; false: the wait ran out
+    auto collect = [&](uint32_t ep, double &sa, double &sb) {
+        double z[1] = {0.0};
+        bool ok = true;
+        if ((int)threadIdx.x < 2 * G)
+            ok = take<1>(a.part + 2 * (ep & 1) * 2 * 64, threadIdx.x, 0, 2 * G, ep, z, a.abort_flag,
+                         a.limit);
+        if (threadIdx.x < 2 * 64) pr[threadIdx.x] = (int)threadIdx.x < 2 * G ? z[0] : 0.0;
+        if (__syncthreads_or(!ok)) return false;
+        sa = pr[2 * lane];
+        sb = pr[2 * lane + 1];
+#pragma unroll
+        for (int x = 32; x >= 1; x >>= 1) {
+            sa += __shfl_xor(sa, x);
+            sb += __shfl_xor(sb, x);
+        }
+        return true;
+    };
+    if (adapt) {
+        keep(0, v0);
+        keep(1, v);
+        if (2 >= nst) {
+            t = trial_sum(h, 2, a.coef + 2 * SERIES_ORDERS, lane);
+            share(t, a.epoch + 2);
+        }
+    } else {
+        acc = 0.5 * ct[0] * v0 + ct[1] * v;
+    }
+    int n = 2;   // order of the last trial
+    bool done = false;
+    double ef = 0.0;
+    for (int p = 2; p < nmax && !done; ++p) {
+        // V_{p-1} from all workgroups
+        double *x = sx[p & 1];
+        double z[3];
+        const bool ok = take<3>(a.words + (size_t)((p - 1) & 1 ? 0 : 1) * 2 * 3 * SERIES_MAX,
+                                threadIdx.x, SR_NT, n3, a.epoch + p - 1, z, a.abort_flag, a.limit);
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if ((int)threadIdx.x + SR_NT * k < n3) x[threadIdx.x + SR_NT * k] = z[k];
+        if (__syncthreads_or(!ok)) return;
+        const double y = row_dot(d, nb, x, lane);
+        const double vn = 2.0 * (ya * y - yb * v) - vp;
+        if (adapt && p >= nst) {   // the trial of order p, formed before this product
+            double sa, sb;
+            if (!collect(a.epoch + p, sa, sb)) return;
+            n = p;
+            done = settles(sa, sb, p, nmax, a.tol, ef);
+            if (done) break;
+        }
+        vp = v;
+        v = vn;
+        if (eth && p + 1 < nmax)
+            put(a.words + (size_t)(p & 1 ? 0 : 1) * 2 * 3 * SERIES_MAX + 2 * o, v, a.epoch + p);
+        if (adapt) {
+            keep(p, v);
+            if (p + 1 >= nst) {
+                t = trial_sum(h, p + 1, a.coef + (size_t)(p + 1) * SERIES_ORDERS, lane);
+                share(t, a.epoch + p + 1);
+            }
+        } else {
+            acc += ct[p] * v;
+        }
+    }
+    if (adapt && !done) {   // the trial of the largest order
+        double sa, sb;
+        if (!collect(a.epoch + nmax, sa, sb)) return;
+        n = nmax;
+        settles(sa, sb, n, nmax, a.tol, ef);
+    }
+    if (eth) a.out[o] = adapt ? t : acc;
+    if (!adapt && a.want_ef) {
+        share(acc, a.epoch + nmax + 1);
+        if (blockIdx.x == 0) {
+            double sa, sb;
+            if (!collect(a.epoch + nmax + 1, sa, sb)) return;
+            settles(sa, sb, 0, 1, 0.0, ef);
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.rec->n = n;
+        a.rec->ef = ef;
+    }
+}
+
+// One workgroup.  If the series above gave up, all of it again, alone: the rows
+// from memory, the terms in vh (adaptive order: all; else a ring of three).
+// Then what follows the series: the adaptive state as k_trial_check leaves it,
+// E_f, the Euler update and the copies of drift and noise.
+constexpr int SF_NT = 1024;
+__global__ __launch_bounds__(SF_NT) void k_series_finish(SeriesArgs a, double *pos, double dt4,
+                                                         double *drift, double *noise, double *e_f)
+{
+    __shared__ double sx[3 * SERIES_MAX];
+    __shared__ double red[2][SF_NT / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, n3 = 3 * a.N;
+    const bool adapt = a.st != nullptr;
+    int n = a.rec->n;
+    double ef = a.rec->ef;
+    const bool redo = *a.abort_flag != 0;   // uniform
+    if (redo) {
+        const int nb = a.ld / 128, nmax = a.n, nst = adapt ? a.st->n_start : 0;
+        const double ya = a.scal[2], yb = a.scal[3];
+        // y = D x for the vector x in memory, into memory
+        auto product = [&](const double *x, double *y) {
+            __syncthreads();
+            for (int z = threadIdx.x; z < 3 * SERIES_MAX; z += SF_NT) sx[z] = z < n3 ? x[z] : 0.0;
+            __syncthreads();
+            for (int i = w; i < a.N; i += SF_NT / 64) {
+                const double *row = a.drow + (size_t)i * 6 * a.ld + 2 * lane;
+                double y0 = 0.0, y1 = 0.0, y2 = 0.0;
+                for (int u = 0; u < nb; ++u) {
+                    sr2 d[6];
+#pragma unroll
+                    for (int e = 0; e < 6; ++e)
+                        d[e] = *reinterpret_cast<const sr2 *>(row + (size_t)e * a.ld + 128 * u);
+                    row_block(d, sx + 6 * (lane + 64 * u), y0, y1, y2);
+                }
+                const double s = wave_sum3(y0, y1, y2, lane);
+                if (lane < 3) y[3 * i + lane] = s;
+            }
+            __syncthreads();
+        };
+        auto sums = [&](double &sa, double &sb) {   // out.out and dW.D dW
+            double p = 0.0, q = 0.0;
+            for (int z = threadIdx.x; z < n3; z += SF_NT) {
+                p += a.out[z] * a.out[z];
+                q += a.dw[z] * a.ddw[z];
+            }
+#pragma unroll
+            for (int x = 32; x >= 1; x >>= 1) {
+                p += __shfl_xor(p, x);
+                q += __shfl_xor(q, x);
+            }
+            if (lane == 0) {
+                red[0][w] = p;
+                red[1][w] = q;
+            }
+            __syncthreads();
+            sa = sb = 0.0;
+            for (int k = 0; k < SF_NT / 64; ++k) {
+                sa += red[0][k];
+                sb += red[1][k];
+            }
+            __syncthreads();
+        };
+        auto term = [&](int p) { return a.vh + (size_t)(adapt ? p : p % 3) * a.ps; };
+        if (!a.have_ddw) product(a.dw, a.ddw);
+        if (a.F) product(a.F, a.ud);
+        for (int z = threadIdx.x; z < n3; z += SF_NT) {
+            term(0)[z] = a.dw[z];
+            term(1)[z] = ya * a.ddw[z] - yb * a.dw[z];
+            if (!adapt) a.out[z] = 0.5 * a.coef[0] * a.dw[z] + a.coef[1] * term(1)[z];
+        }
+        bool done = false;
+        for (int p = 1; p < nmax && !done; ++p) {
+            if (p > 1) {
+                product(term(p - 1), term(p));
+                for (int z = threadIdx.x; z < n3; z += SF_NT) {
+                    const double v = 2.0 * (ya * term(p)[z] - yb * term(p - 1)[z]) - term(p - 2)[z];
+                    term(p)[z] = v;
+                    if (!adapt) a.out[z] += a.coef[p] * v;
+                }
+            }
+            n = p + 1;
+            if (adapt && n >= nst) {
+                const double *ct = a.coef + (size_t)n * SERIES_ORDERS;
+                for (int z = threadIdx.x; z < n3; z += SF_NT) {
+                    double s = 0.5 * ct[0] * term(0)[z];
+                    for (int q = 1; q < n; ++q) s += ct[q] * term(q)[z];
+                    a.out[z] = s;
+                }
+                __syncthreads();
+                double sa, sb;
+                sums(sa, sb);
+                done = settles(sa, sb, n, nmax, a.tol, ef);
+            }
+        }
+        if (!adapt) {
+            __syncthreads();
+            double sa, sb;
+            sums(sa, sb);
+            settles(sa, sb, 0, 1, 0.0, ef);
+        }
+        __syncthreads();
+    }
+    for (int z = threadIdx.x; z < n3; z += SF_NT) {
+        const double s = a.out[z];
+        if (noise) noise[z] = s;
+        if (drift) drift[z] = a.ud[z];
+        if (pos) pos[z] = pos[z] + dt4 * a.ud[z] + s / 1.4142135623730951;
+    }
+    if (threadIdx.x == 0) {
+        if (e_f) *e_f = ef;
+        if (redo) *a.abort_flag = 0;
+        if (adapt) {
+            AdaptState *st = a.st;
+            const bool ok = (ef > 0.0 ? ef : 0.0) < a.tol;
+            st->done = 1;
+            st->n_used = n;
+            st->last_etol = ok ? 0 : 1;
+            if (!ok) {
+                st->etol += 1;
+                st->missed += 1;
+            }
+            st->calls += 1;
+            st->sum_orders += n;
+            if (n > st->max_order) st->max_order = n;
+        }
+    }
+}
+
+// The interval and, per workgroup, the coefficients of one order: n0 +
+// blockIdx.x into ctab[order][SERIES_ORDERS].  explicit_: [dmin, dmax] given,
+// and workgroup 0 writes the scalars and, with st, the adaptive state (as
+// k_cheb_coeffs); otherwise both are there already.
+__global__ __launch_bounds__(256) void k_series_coeffs(int n0, int explicit_, double dmin, double dmax,
+                                                       double *__restrict__ scal,
+                                                       double *__restrict__ ctab,
+                                                       AdaptState *__restrict__ st, int n_start)
+{
+    const double lo = explicit_ ? dmin : scal[0], hi = explicit_ ? dmax : scal[1];
+    const int n = n0 + blockIdx.x;
+    if (explicit_ && blockIdx.x == 0 && threadIdx.x == 0) {
+        scal[0] = lo;
+        scal[1] = hi;
+        scal[2] = 2.0 / (hi - lo);
+        scal[3] = (hi + lo) / (hi - lo);
+        if (st) {
+            st->done = 0;
+            st->n_used = 0;
+            st->n_start = n_start;
+            st->last_etol = 0;
+        }
+    }
+    const double h = 0.5 * (hi - lo), mid = 0.5 * (hi + lo);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double f[2];   // sqrt at the nodes of this lane
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int j = 1 + lane + 64 * k;
+        f[k] = j <= n ? sqrt(h * cospi((j - 0.5) / n) + mid) : 0.0;
+    }
+    for (int p = w; p < n; p += 4) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int j = 1 + lane + 64 * k;
+            if (j <= n) s += f[k] * cospi(p * ((j - 0.5) / n));
+        }
+#pragma unroll
+        for (int x = 32; x >= 1; x >>= 1) s += __shfl_xor(s, x);
+        if (lane == 0) ctab[(size_t)n * SERIES_ORDERS + p] = 2.0 * s / n;
+    }
+}
+
+void launch_series_coeffs(const Ctx &c, int n0, int n1, int explicit_, double dmin, double dmax,
+                          AdaptState *st, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_series_coeffs, dim3(n1 - n0 + 1), dim3(256), 0, s, n0, explicit_, dmin, dmax,
+                       c.scal, c.series_coef, st, n0);
+}
+
+void launch_series(const SeriesArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_series, dim3((a.N + SR_BEADS - 1) / SR_BEADS), dim3(SR_NT), 0, s, a);
+}
+
+void launch_series_finish(const SeriesArgs &a, double *pos, double dt4, double *drift, double *noise,
+                          double *e_f, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_series_finish, dim3(1), dim3(SF_NT), 0, s, a, pos, dt4, drift, noise, e_f);
+}
+
+}  // namespace rpy

@@ -117,3 +117,72 @@ def test_forms_and_capture():
             b.build(pos)
             _close(a.apply(v1), b.apply(v1))
             s.synchronize()
+
+
+@pytest.mark.parametrize("size", [(1, 5), (10, 10), (5, 13), (16, 16), (9, 43), (64, 8)])
+@pytest.mark.parametrize("alone", [False, True])
+def test_series(size, alone):
+    """The series kernel (every order, rule and optional output) and, with waits
+    that give up at once, the finishing kernel that then runs the series alone,
+    against products by tiles; calls in a row, so that a term number of an
+    earlier call is never taken for one of this."""
+    import ctypes
+    w, pos, a, b = _pair(*size, cheb_keep=140)
+    if alone:
+        rpy._lib.rpy_series_wait(a.handle, ctypes.c_int64(-1))
+    v = _vec(w, 1) * 0.03
+    a.build(pos)
+    b.build(pos)
+    for n in (2, 3, 4, 17, 40, 128):
+        got, want = a.sqrt_apply(v, n, 0.04, 40.0, want_ef=True), b.sqrt_apply(v, n, 0.04, 40.0, want_ef=True)
+        _close(got[0], want[0])
+        # E_f^2 is a difference of sums over 3N terms, rounded to about 1e-13
+        assert abs(got[1].item() ** 2 - want[1].item() ** 2) < 1e-12
+    for tol, start, nmax in ((1e-2, 0, 64), (1e-3, 2, 100), (1e-14, 3, 7), (1e-2, 0, 2), (1e-6, 30, 128)):
+        got = a.sqrt_adaptive(v, 0.04, 40.0, tol, nmax, n_start=start, allow_etol=True)
+        want = b.sqrt_adaptive(v, 0.04, 40.0, tol, nmax, n_start=start, allow_etol=True)
+        assert got[2] == want[2]
+        _close(got[0], want[0])
+    assert a.order_stats() == b.order_stats()
+    assert a.status() == b.status()
+    # in a box of a few beads the paper's rule can lie below the spectrum: the
+    # series then diverges (T_p grows past 1e10) and two roundings of it differ freely
+    rule_holds = b.bounds(60.0)[1] > 1.1 * b.lanczos_bounds(min(40, 3 * w.n), margin=0.0)[1]
+    for kw in (dict(n_cheb=2, d_min=0.04, d_max=40.0), dict(n_cheb=20, d_min=0.04, d_max=40.0),
+               dict(n_cheb=20, bounds_rule=rpy.BOUNDS_PAPER, bounds_C=60.0),
+               dict(n_cheb=0, d_min=0.04, d_max=40.0, tol=1e-2, n_max=60),
+               dict(n_cheb=0, bounds_rule=rpy.BOUNDS_PAPER, bounds_C=60.0, tol=1e-2, n_max=100)):
+        if "bounds_rule" in kw and not rule_holds:
+            continue
+        bp = rpy.make_bd_params(dt=1e-3, **kw)
+        p, q = pos.clone(), pos.clone()
+        for step in range(3):
+            if step == 1:
+                a.step(p, bp, seed=3, step=step)
+                b.step(q, bp, seed=3, step=step)
+                continue
+            x, y = (c.step(r, bp, seed=3, step=step, want=True) for c, r in ((a, p), (b, q)))
+            _close(x[0], y[0], 1e-11)
+            _close(x[1], y[1], 1e-11)
+        _close(p, q)
+    assert a.order_stats()[:3] == b.order_stats()[:3]
+
+
+def test_series_on_streams():
+    """Four contexts stepping on four streams at once, as one after the other."""
+    jobs = [_pair(n, 16)[:3] for n in (6, 12, 24, 32)]
+    bp = rpy.make_bd_params(dt=1e-3, n_cheb=20, d_min=0.03, d_max=40.0)
+    streams = [torch.cuda.Stream() for _ in jobs]
+    res = []
+    for together in (False, True):
+        ps = [pos.clone() for _, pos, _ in jobs]
+        torch.cuda.synchronize()
+        for step in range(20):
+            for (w, _, c), p, s in zip(jobs, ps, streams):
+                c.step(p, bp, seed=4, step=step, stream=s)
+                if not together:
+                    s.synchronize()
+        torch.cuda.synchronize()
+        res.append(ps)
+    for x, y in zip(*res):
+        assert torch.equal(x, y)
