@@ -19,11 +19,20 @@ namespace rpy {
     }
 
 // ------------------------------------------------------------------ SYMV
-template <typename A> __device__ inline A sum16(A x)
+// Sums over 16 lanes, in a fixed order: lane q receives that of component
+// min(q & 3, 2).  Two exchanges that halve the components, then two rotations, all
+// on the vector unit: four shuffles per component through LDS instead take
+// 50.3 against 44.6 us for three FP64 vectors at N = 2000, 18.4 against 16.6 us for
+// one on FP32 tiles.
+__device__ inline double sum16x3(double r0, double r1, double r2, int q)
 {
-#pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) x += __shfl_xor(x, o, 16);
-    return x;
+    const bool b0 = q & 1, b1 = q & 2;
+    const double a = (b0 ? r1 : r0) + dpp<DPP_XOR1>(b0 ? r0 : r1);
+    const double b = r2 + dpp<DPP_XOR1>(r2);
+    double r = (b1 ? b : a) + dpp<DPP_XOR2>(b1 ? a : b);
+    r += dpp<DPP_ROR4>(r);
+    r += dpp<DPP_ROR8>(r);
+    return r;
 }
 
 // Loads of a packed plane row (64 values of one bead row and one entry of
@@ -92,9 +101,10 @@ template <> struct P6<uint16_t> {
 };
 
 // Product on the packed tiles (6 planes per bead row, tile[t][i][c][j]),
-// FP64, FP32 or BF16 entries, FP64 arithmetic.  nsf workgroups (at the
-// front of the launch or spread through it) compute T_k of v for a few wave
-// vectors each (sf_direct_block); each further workgroup (NW waves) takes
+// FP64, FP32 or BF16 entries, FP64 arithmetic.  The first nsf
+// workgroups compute T_k of one vector for a column of wave vectors each
+// (sf_column; spread through an FP64 launch instead, two vectors take 80.5 against
+// 78.4 us at N = 4000, one vector the same); each further workgroup (NW waves) takes
 // one stored tile (I, J), in stored order or, when `flip`, in reverse order
 // (each tile's results go to its own slots, so the order changes no value).
 // Wave w, row group g (16 lanes), lane q: bead rows i = 4 NW it + 4 w + g
@@ -110,19 +120,20 @@ template <> struct P6<uint16_t> {
 // Three and four vectors run at two waves per SIMD.
 // Waves per tile workgroup: 4, or 2 for BF16 tiles with one vector.  Those
 // short, cache-resident rows are latency-bound: two waves of 32 rows each,
-// every next row loaded while the current one is used, take 28.5 us at
-// N = 4000 against 32.3 us for four waves with all of a lane's rows loaded
-// at once (one wave: 41.6 us, eight: 38.6 us).  FP32 tiles keep four waves
-// (37.6 us; two: 38.1 us).
+// every next row loaded while the current one is used, take 24.4 us at
+// N = 4000 against 26.2 us for four waves with all of a lane's rows loaded
+// at once (eight: 44.4 us).  FP32 tiles keep four waves (34.4 us; eight 47.3).
 template <typename T, int M> constexpr int symv_waves() { return sizeof(T) == 2 && M == 1 ? 2 : 4; }
+
+// n_z values per structure-factor workgroup of the launch (rpy_sf.h).
+template <typename T> constexpr int symv_nz() { return sizeof(T) == 8 ? 4 : 2; }
 
 template <typename T, int M, bool CACHED, int NW = symv_waves<T, M>()>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(M >= 3 ? 2 : 1, 8))) void k_symv6(int N, int n3, int n3pad, int rhs_cap, int j0,
-                                               int nsf, int sfr, int flip, int nk,
-                                               double invL,
-                                               const KVec *__restrict__ kvec,
+                                               int nsf, int flip, int nm1,
+                                               const SfCol *__restrict__ cols,
                                                const KCoef *__restrict__ kcoef,
-                                               const double *__restrict__ rt,
+                                               const double2 *__restrict__ axt,
                                                double *__restrict__ tk,
                                                const int2 *__restrict__ tile_ij,
                                                const T *__restrict__ tiles,
@@ -132,20 +143,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(M >= 3 
 {
     extern __shared__ double smem[];
     if (gate && *gate) return;   // a product past the settled adaptive order
-    // workgroup b is structure-factor workgroup b / sfr when b is a multiple
-    // of sfr below nsf sfr, else tile ordinal b - (structure-factor
-    // workgroups up to b): sfr = 1 puts them at the front of the launch,
-    // larger sfr spreads them through it
     const int bid = blockIdx.x, ntl = (int)gridDim.x - nsf;
-    if (bid % sfr == 0 && bid / sfr < nsf) {
-        sf_direct_block<M, NW>(bid / sfr, N, nk, rhs_cap, j0, invL, n3, kvec, kcoef, rt, v, tk, smem);
+    if (bid < nsf) {
+        sf_column<NW, symv_nz<T>()>(cols, bid / M, N, nm1, rhs_cap, j0 + bid % M, n3, kcoef, axt,
+                                    v, tk, smem);
         return;
     }
     double(*sx)[TS] = reinterpret_cast<double(*)[TS]>(smem);                    // [M][TS]
     double(*scol)[M][TS] = reinterpret_cast<double(*)[M][TS]>(smem + M * TS);  // [NW][M][TS]
     constexpr int NT = 64 * NW, RPI = 4 * NW, NIT = TB / RPI;   // threads, rows per pass, passes
     constexpr bool HOIST = P6<T>::hoist && NW == 4;
-    const int ord = bid - min(nsf, bid / sfr + 1);
+    const int ord = bid - nsf;
     const int t = flip ? ntl - 1 - ord : ord;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int g = lane >> 4, q = lane & 15;
@@ -243,12 +251,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(M >= 3 
                 r1 += b[1][e] * x0 + b[3][e] * x1 + b[4][e] * x2;
                 r2 += b[2][e] * x0 + b[4][e] * x1 + b[5][e] * x2;
             }
-            r0 = sum16(r0);
-            r1 = sum16(r1);
-            r2 = sum16(r2);
-            if (q < 3)
-                part[((size_t)J * rhs_cap + j0 + j) * n3pad + I * TS + 3 * i + q] =
-                    q == 0 ? r0 : q == 1 ? r1 : r2;
+            const double r = sum16x3(r0, r1, r2, q);
+            if (q < 3) part[((size_t)J * rhs_cap + j0 + j) * n3pad + I * TS + 3 * i + q] = r;
             if (offd) {
                 const double y0 = sx[j][3 * i], y1 = sx[j][3 * i + 1], y2 = sx[j][3 * i + 2];
 #pragma unroll
@@ -285,23 +289,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(M >= 3 
 
 template <typename T, int M> static size_t symv_lds(const Ctx &)
 {
-    // sx occupies M*TS double slots (whatever A is), then scol[NW][M][TS];
-    // the structure-factor workgroups use NW x 6 KPW M doubles
-    constexpr int NW = symv_waves<T, M>();
-    const size_t tile = sizeof(double) * M * TS + sizeof(double) * NW * M * TS;
-    const size_t sf = sizeof(double) * NW * 6 * sf_kpw<M>() * M;
-    return tile > sf ? tile : sf;
+    // sx occupies M*TS doubles, then scol[NW][M][TS]; or the structure factors
+    constexpr int NW = symv_waves<T, M>(), tile = M * TS + NW * M * TS, sf = sf_lds<NW, symv_nz<T>()>();
+    return sizeof(double) * (tile > sf ? tile : sf);
 }
 
 template <typename T, int M>
 static void symv_launch(const Ctx &c, const T *tiles, const double *v, int j0, hipStream_t s)
 {
-    const int nsf = (c.nk + sf_kpw<M>() - 1) / sf_kpw<M>();
-    // The structure-factor workgroups' sincospi work: spread through the FP64
-    // tile stream it overlaps best (68.7 against 70.0 us at the front, N =
-    // 4000); the shorter, cache-resident FP32 / BF16 streams do better with
-    // it at the front (BF16 32.2 against 35.1 us spread)
-    const int sfr = sizeof(T) == 8 ? (nsf + c.ntiles) / nsf : 1;
+    const SfCols &cols = symv_nz<T>() == 4 ? c.sf4 : c.sf2;
+    const int nsf = cols.n * M;
     const size_t lds = symv_lds<T, M>(c);
     // Allocating loads, with the tile order reversed on every other launch,
     // for arrays that fit the Infinity Cache (each product then starts on the
@@ -317,12 +314,12 @@ static void symv_launch(const Ctx &c, const T *tiles, const double *v, int j0, h
     if (cached)
         hipExtLaunchKernelGGL((k_symv6<T, M, true>), dim3(nsf + c.ntiles), dim3(64 * symv_waves<T, M>()),
                               (uint32_t)lds, s, e0, e1, 0u, c.N, c.n3, c.n3pad, c.rhs_cap, j0, nsf,
-                              sfr, flip, c.nk, c.pc.invL, c.kvec, c.kcoef, c.rt, c.tk, c.tile_ij,
+                              flip, c.nmax + 1, cols.d, c.kcoef, c.axt, c.tk, c.tile_ij,
                               tiles, v, c.part, c.gate);
     else
         hipExtLaunchKernelGGL((k_symv6<T, M, false>), dim3(nsf + c.ntiles), dim3(64 * symv_waves<T, M>()),
                               (uint32_t)lds, s, e0, e1, 0u, c.N, c.n3, c.n3pad, c.rhs_cap, j0, nsf,
-                              sfr, flip, c.nk, c.pc.invL, c.kvec, c.kcoef, c.rt, c.tk, c.tile_ij,
+                              flip, c.nmax + 1, cols.d, c.kcoef, c.axt, c.tk, c.tile_ij,
                               tiles, v, c.part, c.gate);
 }
 
@@ -346,72 +343,24 @@ void launch_symv(const Ctx &c, int prec, const double *v, int j0, int mc, hipStr
         symv_group<double>(c, c.d64, v, j0, mc, s);
 }
 
-// ------------------------------------------------- structure-factor reduction
-// Workgroup (16 wave vectors) x (64 chunk groups: 16 waves x 4 lane quarters);
-// grid (k blocks, 2 M): y = (rhs j, cos or sin half).  Lane quarter `sub` of
-// wave g sums the chunks 4 g + sub, +64, ...; an xor tree over the quarters
-// and the 16 waves in LDS combine them in a fixed order, then
-//   T_k = 2 m(k) (I - khat khat) C_k  (or S_k)
-// goes to tk[k][j][3 half + c].
-__global__ __launch_bounds__(1024) void k_sf_reduce(int nk, int nsfc, int rhs_cap, int j0,
-                                                    const KCoef *__restrict__ kcoef,
-                                                    const double *__restrict__ sfpart,
-                                                    double *__restrict__ tk,
-                                                    const int *__restrict__ gate)
+// ------------------------------------------------------- structure factors
+// Grid (columns of wave vectors, vectors).
+__global__ __launch_bounds__(256) void k_sf(int N, int nm1, int rhs_cap, int n3,
+                                            const SfCol *__restrict__ cols,
+                                            const KCoef *__restrict__ kcoef,
+                                            const double2 *__restrict__ axt,
+                                            const double *__restrict__ v, double *__restrict__ tk,
+                                            const int *__restrict__ gate)
 {
-    __shared__ double red[16][3][16];
+    __shared__ double smem[sf_lds<4, 4>()];
     if (gate && *gate) return;
-    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int kk = lane & 15, sub = lane >> 4;
-    const int k = blockIdx.x * 16 + kk;
-    const int j = blockIdx.y >> 1, half = blockIdx.y & 1;
-    // the projection of the 16 threads that finish, loaded with the
-    // partials (after the barrier it would be a second memory round trip)
-    KCoef kc = {0.0, 0.0, 0.0, 0.0};
-    if (threadIdx.x < 16 && k < nk) kc = kcoef[k];
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    if (k < nk) {
-        const size_t cstride = (size_t)6 * rhs_cap * nk;
-        const double *o = sfpart + (size_t)(6 * (j0 + j) + 3 * half) * nk + k;
-        for (int ch = 4 * g + sub; ch < nsfc; ch += 64) {
-            s0 += o[ch * cstride];
-            s1 += o[ch * cstride + nk];
-            s2 += o[ch * cstride + 2 * (size_t)nk];
-        }
-    }
-    s0 += __shfl_xor(s0, 16);
-    s0 += __shfl_xor(s0, 32);
-    s1 += __shfl_xor(s1, 16);
-    s1 += __shfl_xor(s1, 32);
-    s2 += __shfl_xor(s2, 16);
-    s2 += __shfl_xor(s2, 32);
-    if (sub == 0) {
-        red[g][0][kk] = s0;
-        red[g][1][kk] = s1;
-        red[g][2][kk] = s2;
-    }
-    __syncthreads();
-    if (threadIdx.x >= 16 || k >= nk) return;
-    double t[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        double a = 0.0;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) a += red[w][c][kk];
-        t[c] = a;
-    }
-    const double h = kc.hx * t[0] + kc.hy * t[1] + kc.hz * t[2];
-    double *o = tk + ((size_t)k * rhs_cap + j0 + j) * 6 + 3 * half;
-    o[0] = kc.w * (t[0] - kc.hx * h);
-    o[1] = kc.w * (t[1] - kc.hy * h);
-    o[2] = kc.w * (t[2] - kc.hz * h);
+    sf_column<4, 4>(cols, blockIdx.x, N, nm1, rhs_cap, blockIdx.y, n3, kcoef, axt, v, tk, smem);
 }
 
-void launch_sf_reduce(const Ctx &c, int m, hipStream_t s)
+void launch_sf(const Ctx &c, const double *v, int m, hipStream_t s)
 {
-    RPY_RHS_GROUPS(m, hipLaunchKernelGGL(k_sf_reduce, dim3((c.nk + 15) / 16, 2 * MC), dim3(1024),
-                                         0, s, c.nk, c.nsfc, c.rhs_cap, j0, c.kcoef, c.sfpart,
-                                         c.tk, c.gate));
+    hipLaunchKernelGGL(k_sf, dim3(c.sf4.n, m), dim3(256), 0, s, c.N, c.nmax + 1, c.rhs_cap, c.n3,
+                       c.sf4.d, c.kcoef, c.axt, v, c.tk, c.gate);
 }
 
 // ------------------------------------- reciprocal back-projection + epilogue

@@ -5,42 +5,42 @@
 
 namespace rpy {
 
-// One thread per bead: wrapped position rt = L (r/L - floor(r/L)) and the
-// phase table e^{i 2 pi j s_a}, j = 0..nmax, for each axis a (s = r/L wrapped).
-// A non-finite coordinate raises flags[0] and is replaced by 0 so that every
-// later kernel still runs on finite data.
+// One thread per bead and axis (axis-major): wrapped position rt = L (r/L -
+// floor(r/L)) and the phases e^{i 2 pi j s}, j = 0..nmax (s = r/L wrapped), by
+// bead (etab) and bead-contiguous (axt).  A non-finite coordinate raises
+// flags[0] and is replaced by 0 so that every later kernel still runs on
+// finite data.
 __global__ void k_wrap_tables(int N, double L, int nmax, const double *__restrict__ pos,
                               double *__restrict__ rt, double *__restrict__ sfr,
-                              double2 *__restrict__ etab, int *__restrict__ flags)
+                              double2 *__restrict__ etab, double2 *__restrict__ axt,
+                              int *__restrict__ flags)
 {
-    const int nu = blockIdx.x * blockDim.x + threadIdx.x;
-    if (nu >= N) return;
-    bool bad = false;
-    for (int i = 0; i < 3; ++i) {
-        double r = pos[3 * nu + i];
-        if (!isfinite(r)) {
-            bad = true;
-            r = 0.0;
-        }
-        double s = r / L;
-        s = s - floor(s);
-        rt[3 * nu + i] = L * s;
-        sfr[3 * nu + i] = s;
-        double2 *tab = etab + (size_t)(3 * nu + i) * (nmax + 1);
-        for (int j = 0; j <= nmax; ++j) {
-            double sn, cs;
-            sincospi(2.0 * j * s, &sn, &cs);
-            tab[j] = make_double2(cs, sn);
-        }
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= 3 * N) return;
+    const int i = t / N, nu = t - i * N, nm1 = nmax + 1;
+    double r = pos[3 * (size_t)nu + i];
+    if (!isfinite(r)) {
+        atomicOr(flags, 1);
+        r = 0.0;
     }
-    if (bad) atomicOr(flags, 1);
+    double s = r / L;
+    s = s - floor(s);
+    rt[3 * (size_t)nu + i] = L * s;
+    sfr[3 * (size_t)nu + i] = s;
+    double2 *tab = etab + ((size_t)3 * nu + i) * nm1;
+    for (int j = 0; j < nm1; ++j) {
+        double sn, cs;
+        sincospi(2.0 * j * s, &sn, &cs);
+        tab[j] = make_double2(cs, sn);
+        axt[(size_t)(i * nm1 + j) * N + nu] = make_double2(cs, sn);
+    }
 }
 
 void launch_wrap_tables(const Ctx &c, const double *pos, hipStream_t s)
 {
-    const int bs = 256;
-    hipLaunchKernelGGL(k_wrap_tables, dim3((c.N + bs - 1) / bs), dim3(bs), 0, s, c.N, c.L,
-                       c.nmax, pos, c.rt, c.sfr, c.etab, c.flags);
+    const int bs = 128;
+    hipLaunchKernelGGL(k_wrap_tables, dim3((3 * c.N + bs - 1) / bs), dim3(bs), 0, s, c.N, c.L,
+                       c.nmax, pos, c.rt, c.sfr, c.etab, c.axt, c.flags);
 }
 
 // Wrapped positions only; a non-finite coordinate raises flags[0] as above.

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "rpy_internal.h"
+#include "rpy_sf.h"
 
 using namespace rpy;
 
@@ -284,13 +285,10 @@ void set_error(const char *msg) { snprintf(g_err, sizeof g_err, "%s", msg); }
 int hip_error(hipError_t e, const char *what) { return hip_fail(e, what); }
 }  // namespace rpy
 
-// Structure-factor partials: [nsfc][6 rhs_cap][nk] for the vector-unit
-// product, [nk/16 blocks][nchb][6 x 16][16] for the block product.
+// Structure-factor partials of the block product: [nk/16 blocks][nchb][6 x 16][16].
 static size_t sfpart_elems(const Ctx &c)
 {
-    const size_t a = (size_t)c.nsfc * 6 * c.rhs_cap * c.nk;
-    const size_t b = c.block ? (size_t)((c.nk + 15) / 16) * c.nchb * 6 * BLOCK_RHS * 16 : 0;
-    return a > b ? a : b;
+    return c.block ? (size_t)((c.nk + 15) / 16) * c.nchb * 6 * BLOCK_RHS * 16 : 0;
 }
 
 template <typename T> static int dalloc(T **p, size_t n)
@@ -311,7 +309,7 @@ extern "C" void rpy_destroy(rpy_ctx *x)
     if (!x) return;
     (void)hipDeviceSynchronize();
     Ctx &c = x->c;
-    void *bufs[] = {c.rt, c.rt_ev, c.smooth, c.eph, c.etab, c.kvec, c.kcoef, c.tile_ij, c.d64,
+    void *bufs[] = {c.rt, c.rt_ev, c.smooth, c.eph, c.etab, c.tile_ij, c.d64,
                     c.p32, c.p16, c.drow, c.series, c.part, c.xpk, c.ypart,
                     c.vpk, c.bpart, c.tkm,
                     c.sfpart, c.tk, c.sfr, c.work, c.scal, c.red, c.flags, c.cell_start, c.lanc,
@@ -406,6 +404,20 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
             }
     c.nk = (int)kv.size();
     c.nk4 = (c.nk + 3) / 4 * 4;
+    // columns (n_x, n_y) of the half space; kv holds each one's n_z in order
+    std::vector<SfCol> cols;
+    for (int nz = 2; nz <= 4; nz += 2) {
+        for (int k = 0; k < c.nk;) {
+            int e = k;
+            while (e < c.nk && kv[e].nx == kv[k].nx && kv[e].ny == kv[k].ny) ++e;
+            const int top = kv[e - 1].nz;   // n_z = -top .. top, or 1 .. top at n_x = n_y = 0
+            for (int z = 0; z <= top; z += nz)
+                cols.push_back(SfCol{kv[k].nx, kv[k].ny, z, top + 1 - z < nz ? top + 1 - z : nz,
+                                     e - 1 - top, kv[k].nz < 0 ? 1 : 0, 0, 0});
+            k = e;
+        }
+        (nz == 2 ? c.sf2 : c.sf4).n = (int)cols.size() - (nz == 2 ? 0 : c.sf2.n);
+    }
     c.nchb = c.nsfc < 16 ? c.nsfc : 16;
 
     std::vector<int2> tij;
@@ -428,17 +440,25 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     constexpr size_t SC = (SERIES_ORDERS + 1) * SERIES_ORDERS, SR = 3 * 3 * SERIES_MAX;
     constexpr size_t SERIES_DOUBLES = SC + SR + SW + SP + 2 + 1;
     static_assert(sizeof(SeriesRec) == 2 * sizeof(double), "the record is two doubles");
-    // one table: the pair polynomials, the octant weights, their offsets
+    // one table: the pair polynomials, the octant weights, their offsets, the
+    // wave vectors, their coefficients and columns
     std::vector<double> tabs(smooth, smooth + 2 * SMOOTH_MAX);
     tabs.insert(tabs.end(), rwk.begin(), rwk.end());
     tabs.resize(tabs.size() + (roff.size() + 1) / 2);
     if (!roff.empty())
         memcpy(&tabs[2 * SMOOTH_MAX + rwk.size()], roff.data(), roff.size() * sizeof(int));
+    tabs.resize((tabs.size() + 3) / 4 * 4);
+    const size_t t_kc = tabs.size(), t_col = t_kc + 4 * kc.size(), t_kv = t_col + 4 * cols.size();
+    static_assert(sizeof(KCoef) == 32 && sizeof(SfCol) == 32 && sizeof(KVec) == 16, "table layout");
+    tabs.resize(t_kv + 2 * kv.size());
+    memcpy(&tabs[t_kc], kc.data(), kc.size() * sizeof(KCoef));
+    memcpy(&tabs[t_col], cols.data(), cols.size() * sizeof(SfCol));
+    memcpy(&tabs[t_kv], kv.data(), kv.size() * sizeof(KVec));
     c.work_elems = 3 * nv + nv + 4 * nv + nv + nv + 2 * mv + mv + mv;
     const int ncell_cap = 64;
     const size_t ncells_cap = (size_t)ncell_cap * ncell_cap * ncell_cap;
-    if ((rc = dalloc(&c.rt, nv)) || (rc = dalloc(&c.rt_ev, nv)) || (rc = dalloc(&c.etab, nv * (c.nmax + 1))) ||
-        (rc = dalloc(&c.smooth, tabs.size())) || (rc = dalloc(&c.kvec, kv.size())) || (rc = dalloc(&c.kcoef, kc.size())) ||
+    if ((rc = dalloc(&c.rt, nv)) || (rc = dalloc(&c.rt_ev, nv)) || (rc = dalloc(&c.etab, 2 * nv * (c.nmax + 1))) ||
+        (rc = dalloc(&c.smooth, tabs.size())) ||
         (rc = dalloc(&c.tile_ij, tij.size())) || (!c.lma && (rc = dalloc(&c.d64, te6))) ||
         (c.lma && ((rc = dalloc(&c.lma_start, 2 * lcells + 1)) ||
                    (rc = dalloc(&c.lma_beads, (size_t)c.N)) ||
@@ -494,13 +514,16 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     x->Bv[1] = w; w += mv;
     x->ddw = w; w += mv;
     x->acc = w; w += mv;
+    c.axt = c.etab + nv * (c.nmax + 1);
+    c.kcoef = reinterpret_cast<KCoef *>(c.smooth + t_kc);
+    c.sf2.d = reinterpret_cast<SfCol *>(c.smooth + t_col);
+    c.sf4.d = c.sf2.d + c.sf2.n;
+    c.kvec = reinterpret_cast<KVec *>(c.smooth + t_kv);
     std::vector<double> um(nv);
     for (size_t i = 0; i < nv; ++i) um[i] = (i & 1) ? -1.0 : 1.0;
     hipError_t e;
-    if ((e = hipMemcpy(c.kvec, kv.data(), kv.size() * sizeof(KVec), hipMemcpyHostToDevice)) ||
-        (e = hipMemcpy(c.smooth, tabs.data(), tabs.size() * sizeof(double), hipMemcpyHostToDevice)) ||
+    if ((e = hipMemcpy(c.smooth, tabs.data(), tabs.size() * sizeof(double), hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(x->Um, um.data(), nv * sizeof(double), hipMemcpyHostToDevice)) ||
-        (e = hipMemcpy(c.kcoef, kc.data(), kc.size() * sizeof(KCoef), hipMemcpyHostToDevice)) ||
         (e = hipMemcpy(c.tile_ij, tij.data(), tij.size() * sizeof(int2), hipMemcpyHostToDevice)) ||
         (e = hipMemset(c.flags, 0, 4 * sizeof(int))) ||
         (e = hipMemset(c.adapt, 0, sizeof(AdaptState))) ||
@@ -649,8 +672,7 @@ static void product(rpy_ctx *x, const double *v, int m, int prec, const EpiArgs 
         }
         {
             ProfScope ps(x, RPY_PROF_KSPACE, s);
-            launch_lma_sf(c, v, m, s);
-            launch_sf_reduce(c, m, s);
+            launch_sf(c, v, m, s);
         }
         ProfScope ps(x, RPY_PROF_EPI, s);
         launch_kspace_epi(c, f, s);
@@ -1208,8 +1230,7 @@ extern "C" int rpy_u_vjp(rpy_ctx *x, const double *pos, const double *F, const d
     const int qg = c.rhs_cap / 2;
     for (int q0 = 0; q0 < P; q0 += qg) {
         const int nq = P - q0 < qg ? P - q0 : qg;
-        launch_grad_sf(c, xy + 2 * q0 * nv, 2 * nq, s);
-        launch_sf_reduce(c, 2 * nq, s);
+        launch_sf(c, xy + 2 * q0 * nv, 2 * nq, s);
         launch_grad_kspace(c, xy + 2 * q0 * nv, nq, q0 > 0, s);
     }
     launch_grad_sum(c, g_pos, s);

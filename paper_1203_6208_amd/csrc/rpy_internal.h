@@ -403,6 +403,11 @@ struct AdaptState {
 };
 
 // -------------------------------------------------------------- context
+struct SfCols {
+    const struct SfCol *d = nullptr;
+    int n = 0;
+};
+
 struct Ctx {
     // problem
     int N, n3, nchains, bpc;
@@ -429,6 +434,8 @@ struct Ctx {
     double *rt_ev = nullptr;     // wrapped positions for stand-alone force calls
     double *sfr = nullptr;       // fractional coordinates s = r/L - floor(r/L) [N][3]
     double2 *etab = nullptr;     // phases [N][3][nmax+1]
+    double2 *axt = nullptr;      // the same phases bead-contiguous, [3 (nmax + 1)][N] (behind etab)
+    SfCols sf2, sf4;             // columns of wave vectors (rpy_sf.h), cut after 2 and after 4 n_z
     KVec *kvec = nullptr;        // [nk]
     KCoef *kcoef = nullptr;      // [nk]
     int2 *tile_ij = nullptr;     // [ntiles]
@@ -554,8 +561,7 @@ void launch_series_coeffs(const Ctx &c, int n0, int n1, int explicit_, double dm
 void launch_series(const SeriesArgs &a, hipStream_t s);
 void launch_series_finish(const SeriesArgs &a, double *pos, double dt4, double *drift, double *noise,
                           double *e_f, hipStream_t s);
-// products: the tile-product kernel also computes the structure-factor
-// partials of its input; launch_sf_reduce turns them into tk; the final
+// products: the tile-product kernel also computes tk of its input; the final
 // kernel adds the reciprocal back-projection to the tile partials and applies
 // the epilogue of `mode`.
 enum EpiMode { EPI_APPLY = 0, EPI_CHEB_FIRST = 1, EPI_CHEB_NEXT = 2, EPI_ADJ = 3 };
@@ -599,7 +605,9 @@ void launch_block_sf(const Ctx &c, int m, int prec, hipStream_t s);
 void launch_block_epi(const Ctx &c, const EpiArgs &f, hipStream_t s);
 constexpr int BLOCK_MIN_RHS = 5;   // products with at least this many vectors use it
 constexpr int BLOCK_RHS = 16;
-void launch_sf_reduce(const Ctx &c, int m, hipStream_t s);
+// T_k of m vectors into tk (a launch of its own, for the low-memory form and
+// the reverse mode; the tile products carry theirs)
+void launch_sf(const Ctx &c, const double *v, int m, hipStream_t s);
 void launch_kspace_epi(const Ctx &c, const EpiArgs &f, hipStream_t s);
 // Interval (explicit, or the paper's rule from du = D.U+), the scalars of Y
 // and the coefficients of order n_cheb.  With adapt_floor >= 0 the order is
@@ -639,7 +647,6 @@ void launch_adj_init(const Ctx &c, int p, double xs, const double *g, double *mu
 void launch_add(double *out, const double *a, const double *b, size_t n, hipStream_t s);
 void launch_grad_wtiles(const Ctx &c, int nq, hipStream_t s);
 void launch_grad_real(const Ctx &c, hipStream_t s);
-void launch_grad_sf(const Ctx &c, const double *v, int nv, hipStream_t s);
 void launch_grad_kspace(const Ctx &c, const double *xy, int nq, int accumulate, hipStream_t s);
 void launch_grad_sum(const Ctx &c, double *gpos, hipStream_t s);
 // step
@@ -652,7 +659,6 @@ void launch_cell_list_into(int N, double L, int nc, const double *rt, int *start
 // partials of the product's input
 void launch_lma_build(const Ctx &c, hipStream_t s);
 void launch_lma_real(const Ctx &c, const double *v, int m, hipStream_t s);
-void launch_lma_sf(const Ctx &c, const double *v, int m, hipStream_t s);
 void launch_ev_forces(const Ctx &c, const double *rt, double zstar, double dstar, double rcut,
                       double *F, hipStream_t s);
 // g_pos += sum_mu J(d)(gF_nu - gF_mu): transpose of the excluded-volume Jacobian

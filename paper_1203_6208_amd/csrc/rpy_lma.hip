@@ -9,7 +9,6 @@
 // at most).
 #include "rpy_internal.h"
 #include "rpy_pairs.h"
-#include "rpy_sf.h"
 
 namespace rpy {
 
@@ -215,35 +214,6 @@ void launch_lma_real(const Ctx &c, const double *v, int m, hipStream_t s)
     }
 #undef RPY_LMA_REAL
 #undef RPY_LMA_REAL_NP
-}
-
-// Structure-factor partials of the m input vectors (one or two at a time).
-__global__ __launch_bounds__(256) void k_lma_sf(int N, int n3, int nk, int nmax, int rhs_cap,
-                                                int nkb, int m, const KVec *__restrict__ kvec,
-                                                const double2 *__restrict__ etab,
-                                                const double *__restrict__ v,
-                                                double *__restrict__ sfpart,
-                                                const int *__restrict__ gate)
-{
-    extern __shared__ double smem[];
-    if (gate && *gate) return;
-    for (int j0 = 0; j0 < m; j0 += 2) {
-        if (j0 > 0) __syncthreads();   // the vector slots are rewritten
-        if (m - j0 >= 2)
-            sf_partial_block<2>(blockIdx.x, nkb, N, n3, nk, nmax, rhs_cap, j0, kvec, etab, v,
-                                sfpart, smem, j0 == 0);
-        else
-            sf_partial_block<1>(blockIdx.x, nkb, N, n3, nk, nmax, rhs_cap, j0, kvec, etab, v,
-                                sfpart, smem, j0 == 0);
-    }
-}
-
-void launch_lma_sf(const Ctx &c, const double *v, int m, hipStream_t s)
-{
-    const int nkb = (c.nk + 255) / 256;
-    const size_t lds = sizeof(double) * (size_t)(2 * SF_BEADS * 3 * (c.nmax + 1) + SF_BEADS * 2 * 3);
-    hipLaunchKernelGGL(k_lma_sf, dim3(c.nsfc * nkb), dim3(256), lds, s, c.N, c.n3, c.nk, c.nmax,
-                       c.rhs_cap, nkb, m, c.kvec, c.etab, v, c.sfpart, c.gate);
 }
 
 }  // namespace rpy

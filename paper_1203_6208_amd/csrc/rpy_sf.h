@@ -1,5 +1,5 @@
-// rpy_sf.h -- structure-factor partials of a product's input vectors, shared
-// by the tile-product kernels (arXiv:1203.6208, eq. DF, reciprocal sum taken
+// rpy_sf.h -- structure factors of a product's input vectors, shared by the
+// tile-product kernels (arXiv:1203.6208, eq. DF, reciprocal sum taken
 // per product as S_k = sum_mu {cos, sin}(k.r_mu) v_mu).
 #pragma once
 #include "rpy_internal.h"
@@ -18,146 +18,138 @@ __device__ inline double2 kphase(const KVec &kv, const double2 *tab, int nm1)
     return make_double2(xy.x * ez.x - xy.y * ez.y, xy.x * ez.y + xy.y * ez.x);
 }
 
-// Structure-factor partials of the product's input vector, carried by the
-// first `nsf` workgroups of the product kernel (they only read v, so they
-// run beside the tile stream).  Workgroup b: bead chunk b / nkb (SF_BEADS
-// beads), wave-vector block b % nkb; one thread per wave vector:
-//   sfpart[chunk][6 j + c][k] = sum_mu {cos, sin}(k.r_mu) v_mu,c.
-template <int M>
-__device__ inline void sf_partial_block(int b, int nkb, int N, int n3, int nk, int nmax,
-                                        int rhs_cap, int j0, const KVec *__restrict__ kvec,
-                                        const double2 *__restrict__ etab,
-                                        const double *__restrict__ v, double *__restrict__ sfpart,
-                                        double *smem, bool load_tab = true)
-{
-    const int nm1 = nmax + 1;
-    const int chunk = b / nkb, kb = b % nkb;
-    const int b0 = chunk * SF_BEADS;
-    const int nb = min(SF_BEADS, N - b0);
-    double2 *stab = reinterpret_cast<double2 *>(smem);          // [SF_BEADS][3*nm1]
-    double *sv = smem + 2 * SF_BEADS * 3 * nm1;                  // [SF_BEADS][M][3]
-    if (load_tab)  // else still in LDS from the previous group of vectors
-        for (int e = threadIdx.x; e < nb * 3 * nm1; e += blockDim.x)
-            stab[e] = etab[(size_t)b0 * 3 * nm1 + e];
-    for (int e = threadIdx.x; e < nb * 3 * M; e += blockDim.x) {
-        const int bl = e / (3 * M), r = e % (3 * M), j = r / 3, c = r % 3;
-        sv[e] = v[(size_t)(j0 + j) * n3 + 3 * (b0 + bl) + c];
-    }
-    __syncthreads();
-    const int k = kb * blockDim.x + threadIdx.x;
-    if (k >= nk) return;  // no barrier follows inside this function
-    const KVec kv = kvec[k];
-    double acc[M][6];
-#pragma unroll
-    for (int j = 0; j < M; ++j)
-#pragma unroll
-        for (int c = 0; c < 6; ++c) acc[j][c] = 0.0;
-#pragma unroll 4
-    for (int bl = 0; bl < nb; ++bl) {
-        const double2 e = kphase(kv, stab + bl * 3 * nm1, nm1);
-#pragma unroll
-        for (int j = 0; j < M; ++j)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const double x = sv[bl * 3 * M + 3 * j + c];
-                acc[j][c] += e.x * x;
-                acc[j][3 + c] += e.y * x;
-            }
-    }
-    double *o = sfpart + ((size_t)chunk * 6 * rhs_cap + 6 * j0) * nk + k;
-#pragma unroll
-    for (int j = 0; j < M; ++j)
-#pragma unroll
-        for (int c = 0; c < 6; ++c) o[(size_t)(6 * j + c) * nk] = acc[j][c];
-}
-
-// Structure factors of the product's input vectors by wave vector, carried
-// by the first workgroups of the tile-product kernel (they read only the
-// positions and v, so they run beside the tile stream).  Workgroup b owns the
-// KPW wave vectors KPW b .. KPW b + KPW - 1 and sums over every bead,
+// The T_k of one input vector for a column of wave vectors (n_x, n_y, *), summed
+// over every bead by one workgroup of NW waves:
 //   C_k = sum_mu cos(k.r_mu) v_mu,   S_k = sum_mu sin(k.r_mu) v_mu,
-// with k.r_mu = 2 pi n.s_mu (s = r/L of the wrapped position) from sincospi;
-// thread t takes the beads t, t + 64 NW, ... and the sums are combined in a
-// fixed order (an xor tree inside each wave, then the NW waves in LDS).  The
-// workgroup then applies 2 m(k) (I - khat khat) (eq. DF, third term) and
-// writes tk[k][j0 + j] = (T^C_k, T^S_k): the sum over beads is complete, so
-// no reduction over bead chunks follows.
-template <int M> constexpr int sf_kpw() { return M <= 2 ? 2 : 1; }
+//   T_k = 2 m(k) (I - khat khat) (C_k, S_k)   -> tk[k][j]        (eq. DF, third term).
+// Thread t takes the beads t, t + 64 NW, ...  With E = e^{i 2 pi (n_x s_x + n_y s_y)}
+// from the axis tables, a bead's share of n_z and of -n_z is built from the
+// four products of (Re E, Im E) v with cos and sin of 2 pi n_z s_z: 12
+// multiply-adds per pair of wave vectors.  A workgroup takes NZ values of n_z
+// (12 NZ sums per thread); it is bound by the latency of its loads and of its
+// reduction (DPP inside 4 lanes, then LDS, in a fixed order), and re-reads the tables of
+// (n_x, n_y) and v from L2 for every NZ wave vectors and their mirrors.  NZ = 4 beside
+// FP64 tiles and alone (N = 16000, 7947 wave vectors: 92 us, with 2: 134 us; N = 2000,
+// two vectors per pair of the reverse mode: 25 us), NZ = 2 beside the shorter FP32
+// and BF16 streams, whose workgroups need the wave slots more than the
+// bandwidth (FP32, N = 2000: 13.2 against 15.1 us).
+// One wave vector per thread group with sincospi of every bead instead: FP32 37.9 ->
+// 34.3 us at N = 4000 and 18.4 -> 13.2 us at N = 2000, FP64 22.9 -> 18.7 us at
+// N = 2000; alone, with a launch that sums partials, 180 -> 92 us at N = 16000.
+// axt[axis (nmax + 1) + j][N] = e^{i 2 pi j s_axis}: bead-contiguous.
+constexpr int SF_AHEAD = 2;   // beads whose loads go out together
+struct SfCol {
+    int nx, ny, nz0, cnt;   // the column, the first n_z and how many (at most NZ)
+    int k0, both;           // index of n_z = 0 among the wave vectors; -n_z is one too
+    int pad0, pad1;
+};
 
-template <int M, int NW = 4>
-__device__ inline void sf_direct_block(int b, int N, int nk, int rhs_cap, int j0, double invL,
-                                       int n3, const KVec *__restrict__ kvec,
-                                       const KCoef *__restrict__ kcoef,
-                                       const double *__restrict__ rt,
-                                       const double *__restrict__ v, double *__restrict__ tk,
-                                       double *smem)
+// x of the lane CTRL names (a DPP control: a permutation inside 16 lanes, on
+// the vector unit and not through LDS).
+template <int CTRL> __device__ inline double dpp(double x)
 {
-    constexpr int KPW = sf_kpw<M>();
-    constexpr int NV = KPW * M * 6;   // sums per thread
-    double nxs[KPW], nys[KPW], nzs[KPW];
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;
+
+// LDS: sf_lds<NW, NZ>() doubles.
+template <int NW, int NZ> constexpr int sf_lds() { return 12 * NZ * (17 * NW + 1); }
+template <int NW, int NZ>
+__device__ __forceinline__ void sf_column(const SfCol *__restrict__ cols, int b, int N, int nm1,
+                                          int rhs_cap, int j, int n3,
+                                          const KCoef *__restrict__ kcoef, const double2 *axt,
+                                          const double *v, double *__restrict__ tk, double *smem)
+{
+    constexpr int NT = 64 * NW, NS = 12 * NZ;
+    const SfCol col = cols[b];
+    const double2 *tx = axt + (size_t)col.nx * N, *ty = axt + (size_t)(nm1 + abs(col.ny)) * N;
+    const double2 *tz = axt + (size_t)(2 * nm1 + col.nz0) * N, *t1 = axt + (size_t)(2 * nm1 + 1) * N;
+    v += (size_t)j * n3;
+    const double sy = col.ny < 0 ? -1.0 : 1.0;
+    double a[NS];
 #pragma unroll
-    for (int q = 0; q < KPW; ++q) {
-        const KVec kv = kvec[min(KPW * b + q, nk - 1)];
-        nxs[q] = 2.0 * kv.nx;
-        nys[q] = 2.0 * kv.ny;
-        nzs[q] = 2.0 * kv.nz;
-    }
-    double acc[NV];
+    for (int i = 0; i < NS; ++i) a[i] = 0.0;
+#pragma unroll 1
+    for (int m0 = threadIdx.x; m0 < N; m0 += SF_AHEAD * NT) {
+        double2 ex[SF_AHEAD], ey[SF_AHEAD], z[SF_AHEAD], z1[SF_AHEAD];
+        double x[SF_AHEAD][3];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) acc[i] = 0.0;
-    for (int mu = threadIdx.x; mu < N; mu += blockDim.x) {
-        const double sx = rt[3 * mu] * invL, sy = rt[3 * mu + 1] * invL,
-                     sz = rt[3 * mu + 2] * invL;
-        double x[M][3];
+        for (int u = 0; u < SF_AHEAD; ++u) {
+            const int mu = min(m0 + u * NT, N - 1);
+            ex[u] = tx[mu];
+            ey[u] = ty[mu];
+            z[u] = tz[mu];
+            z1[u] = t1[mu];
+            x[u][0] = v[3 * mu];
+            x[u][1] = v[3 * mu + 1];
+            x[u][2] = v[3 * mu + 2];
+        }
+        __asm__ volatile("" ::: "memory");   // the loads of all beads before any use
 #pragma unroll
-        for (int j = 0; j < M; ++j)
+        for (int u = 0; u < SF_AHEAD; ++u) {
+            const double on = m0 + u * NT < N ? 1.0 : 0.0;
+            const double eyi = sy * ey[u].y;
+            const double er = on * (ex[u].x * ey[u].x - ex[u].y * eyi);
+            const double ei = on * (ex[u].x * eyi + ex[u].y * ey[u].x);
+            double zr = z[u].x, zi = z[u].y;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) x[j][c] = v[(size_t)(j0 + j) * n3 + 3 * mu + c];
-#pragma unroll
-        for (int q = 0; q < KPW; ++q) {
-            double sn, cs;
-            sincospi(nxs[q] * sx + nys[q] * sy + nzs[q] * sz, &sn, &cs);
-#pragma unroll
-            for (int j = 0; j < M; ++j)
+            for (int q = 0; q < NZ; ++q) {
+                double *s = a + 12 * q;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    acc[(q * M + j) * 6 + c] += cs * x[j][c];
-                    acc[(q * M + j) * 6 + 3 + c] += sn * x[j][c];
+                    const double w = er * x[u][c], y = ei * x[u][c];
+                    s[c] = fma(w, zr, s[c]);
+                    s[3 + c] = fma(y, zi, s[3 + c]);
+                    s[6 + c] = fma(y, zr, s[6 + c]);
+                    s[9 + c] = fma(w, zi, s[9 + c]);
                 }
+                const double t = zr * z1[u].x - zi * z1[u].y;
+                zi = zr * z1[u].y + zi * z1[u].x;
+                zr = t;
+            }
         }
     }
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        double a = acc[i];
+    for (int i = 0; i < NS; ++i) {
+        a[i] += dpp<DPP_XOR1>(a[i]);
+        a[i] += dpp<DPP_XOR2>(a[i]);
+    }
+    // [sum][17 NW]: the 16 groups of 4 lanes of each wave, padded
+    constexpr int LD = 17 * NW;
+    if ((lane & 3) == 0) {
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) a += __shfl_xor(a, o);
-        if (lane == 0) smem[w * NV + i] = a;
+        for (int i = 0; i < NS; ++i) smem[i * LD + 17 * w + (lane >> 2)] = a[i];
     }
     __syncthreads();
-    // thread (q, j, half) of the first 2 KPW M: the NW waves in order, then
-    // the projection
-    if (threadIdx.x < 2 * KPW * M) {
-        const int half = threadIdx.x & 1, qj = threadIdx.x >> 1, q = qj / M, j = qj % M;
-        const int k = KPW * b + q;
-        if (k < nk) {
-            double t[3];
+    double *sum = smem + NS * LD;
+    for (int e = threadIdx.x; e < NS * 4; e += NT) {   // 4 threads per sum
+        const int i = e >> 2, p = e & 3;
+        double s = 0.0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const int i = qj * 6 + 3 * half + c;
-                double a = smem[i];
-#pragma unroll
-                for (int w2 = 1; w2 < NW; ++w2) a += smem[w2 * NV + i];
-                t[c] = a;
-            }
-            const KCoef kc = kcoef[k];
-            const double h = kc.hx * t[0] + kc.hy * t[1] + kc.hz * t[2];
-            double *o = tk + ((size_t)k * rhs_cap + j0 + j) * 6 + 3 * half;
-            o[0] = kc.w * (t[0] - kc.hx * h);
-            o[1] = kc.w * (t[1] - kc.hy * h);
-            o[2] = kc.w * (t[2] - kc.hz * h);
-        }
+        for (int k = 0; k < 4 * NW; ++k) s += smem[i * LD + 17 * (k >> 2) + 4 * p + (k & 3)];
+        s += dpp<DPP_XOR1>(s);
+        s += dpp<DPP_XOR2>(s);
+        if (p == 0) sum[i] = s;
     }
+    __syncthreads();
+    // thread (n_z, its sign, cos or sin half)
+    const int q = threadIdx.x >> 2, neg = threadIdx.x >> 1 & 1, half = threadIdx.x & 1;
+    if (q >= col.cnt) return;
+    const int nz = col.nz0 + q, k = col.k0 + (neg ? -nz : nz);
+    if (neg ? nz == 0 || !col.both : k < 0) return;   // n_z = 0 once; n = 0 never
+    const double sg = (half != 0) == (neg != 0) ? -1.0 : 1.0;   // C: A1 -/+ A2, S: A3 +/- A4
+    const double *s = sum + 12 * q + 6 * half;
+    const double s0 = s[0] + sg * s[3], s1 = s[1] + sg * s[4], s2 = s[2] + sg * s[5];
+    const KCoef kc = kcoef[k];
+    const double h = kc.hx * s0 + kc.hy * s1 + kc.hz * s2;
+    double *o = tk + ((size_t)k * rhs_cap + j) * 6 + 3 * half;
+    o[0] = kc.w * (s0 - kc.hx * h);
+    o[1] = kc.w * (s1 - kc.hy * h);
+    o[2] = kc.w * (s2 - kc.hz * h);
 }
 
 }  // namespace rpy

@@ -1,0 +1,63 @@
+"""The structure factors by columns of wave vectors, beside the FP32, BF16 and
+FP64 tiles and in a launch of their own (low-memory form): products against
+the oracle at bead counts around the workgroups' strides and at wave-vector
+sets whose columns end in every remainder of the four n_z per workgroup, one
+to four vectors."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1203_6208_amd import inputs, rpy
+
+pytestmark = pytest.mark.gpu
+# every product, with the entries it stores: 1e-12
+TOL = 1e-12
+
+
+def _entries(dense, prec):
+    """The stored real-space entries as the product of `prec` reads them."""
+    if prec == "f64":
+        return dense
+    d = dense.to(torch.float32)
+    return (d if prec == "f32" else d.to(torch.bfloat16)).to(torch.float64)
+
+
+def _run(chains, bpc, alphaL, M, m, lowp, lma):
+    w = inputs.Workload("sf", chains, bpc, 1.0, alphaL=alphaL, M=M, seed=91)
+    pos = torch.from_numpy(w.positions()).cuda()
+    ctx = rpy.context_for(w, lowp=lowp, max_rhs=m, lma=lma)
+    ctx.build(pos)
+    v = np.random.default_rng(3).standard_normal((m, w.n, 3))
+    vc = torch.from_numpy(v).cuda()
+    p = pos.cpu().numpy()
+    recip = oracle.recip_space_matrix(p, w.L, w.a, w.alpha, w.n2max)
+    if lma:
+        dense = torch.from_numpy(oracle.real_space_matrix(p, w.L, w.a, w.alpha, w.rc))
+    else:
+        dense = ctx.real_space_dense().cpu().reshape(3 * w.n, 3 * w.n)
+    for prec in {"f64", lowp}:
+        want = ((_entries(dense, prec).numpy() + recip) @ v.reshape(m, -1).T).T
+        got = ctx.apply(vc, prec=prec).cpu().numpy().reshape(m, -1)
+        assert np.abs(got - want).max() <= TOL * np.abs(want).max(), prec
+    ctx.close()
+
+
+@pytest.mark.parametrize("size", [(1, 5), (1, 127), (8, 16), (3, 43), (1, 257), (27, 19)])
+@pytest.mark.parametrize("lowp", ["f32", "bf16"])
+def test_beside_tiles(size, lowp):
+    for m in (1, 4):
+        _run(*size, 6.0, 3.5, m, lowp, 0)
+
+
+@pytest.mark.parametrize("form", [(4.0, 3.5), (5.0, 3.5), (6.0, 4.6), (8.0, 3.5)])
+def test_wave_vector_sets(form):
+    for m in (1, 2, 3):
+        _run(5, 27, *form, m, "f32", 0)
+
+
+@pytest.mark.parametrize("size", [(8, 25), (1, 255), (2, 128), (3, 171)])
+@pytest.mark.parametrize("alphaL", [12.0, 14.0])
+def test_alone(size, alphaL):
+    for m in (1, 3):
+        _run(*size, alphaL, 3.5, m, "f64", 1)
