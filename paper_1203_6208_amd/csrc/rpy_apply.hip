@@ -130,7 +130,7 @@ template <typename T> constexpr int symv_nz() { return sizeof(T) == 8 ? 4 : 2; }
 
 template <typename T, int M, bool CACHED, int NW = symv_waves<T, M>()>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(M >= 3 ? 2 : 1, 8))) void k_symv6(int N, int n3, int n3pad, int rhs_cap, int j0,
-                                               int nsf, int flip, int nm1,
+                                               int nsf, int flip, int nm1, int fold,
                                                const SfCol *__restrict__ cols,
                                                const KCoef *__restrict__ kcoef,
                                                const double2 *__restrict__ axt,
@@ -145,8 +145,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(M >= 3 
     if (gate && *gate) return;   // a product past the settled adaptive order
     const int bid = blockIdx.x, ntl = (int)gridDim.x - nsf;
     if (bid < nsf) {
-        sf_column<NW, symv_nz<T>()>(cols, bid / M, N, nm1, rhs_cap, j0 + bid % M, n3, kcoef, axt,
-                                    v, tk, smem);
+        sf_column<NW, symv_nz<T>()>(cols, bid / M, N, nm1, rhs_cap, j0 + bid % M, n3, fold, kcoef,
+                                    axt, v, tk, smem);
         return;
     }
     double(*sx)[TS] = reinterpret_cast<double(*)[TS]>(smem);                    // [M][TS]
@@ -314,12 +314,12 @@ static void symv_launch(const Ctx &c, const T *tiles, const double *v, int j0, h
     if (cached)
         hipExtLaunchKernelGGL((k_symv6<T, M, true>), dim3(nsf + c.ntiles), dim3(64 * symv_waves<T, M>()),
                               (uint32_t)lds, s, e0, e1, 0u, c.N, c.n3, c.n3pad, c.rhs_cap, j0, nsf,
-                              flip, c.nmax + 1, cols.d, c.kcoef, c.axt, c.tk, c.tile_ij,
+                              flip, c.nmax + 1, c.fold, cols.d, c.kcoef, c.axt, c.fold ? c.tkf : c.tk, c.tile_ij,
                               tiles, v, c.part, c.gate);
     else
         hipExtLaunchKernelGGL((k_symv6<T, M, false>), dim3(nsf + c.ntiles), dim3(64 * symv_waves<T, M>()),
                               (uint32_t)lds, s, e0, e1, 0u, c.N, c.n3, c.n3pad, c.rhs_cap, j0, nsf,
-                              flip, c.nmax + 1, cols.d, c.kcoef, c.axt, c.tk, c.tile_ij,
+                              flip, c.nmax + 1, c.fold, cols.d, c.kcoef, c.axt, c.fold ? c.tkf : c.tk, c.tile_ij,
                               tiles, v, c.part, c.gate);
 }
 
@@ -345,7 +345,7 @@ void launch_symv(const Ctx &c, int prec, const double *v, int j0, int mc, hipStr
 
 // ------------------------------------------------------- structure factors
 // Grid (columns of wave vectors, vectors).
-__global__ __launch_bounds__(256) void k_sf(int N, int nm1, int rhs_cap, int n3,
+__global__ __launch_bounds__(256) void k_sf(int N, int nm1, int rhs_cap, int n3, int fold,
                                             const SfCol *__restrict__ cols,
                                             const KCoef *__restrict__ kcoef,
                                             const double2 *__restrict__ axt,
@@ -354,13 +354,13 @@ __global__ __launch_bounds__(256) void k_sf(int N, int nm1, int rhs_cap, int n3,
 {
     __shared__ double smem[sf_lds<4, 4>()];
     if (gate && *gate) return;
-    sf_column<4, 4>(cols, blockIdx.x, N, nm1, rhs_cap, blockIdx.y, n3, kcoef, axt, v, tk, smem);
+    sf_column<4, 4>(cols, blockIdx.x, N, nm1, rhs_cap, blockIdx.y, n3, fold, kcoef, axt, v, tk, smem);
 }
 
-void launch_sf(const Ctx &c, const double *v, int m, hipStream_t s)
+void launch_sf(const Ctx &c, const double *v, int m, int fold, hipStream_t s)
 {
     hipLaunchKernelGGL(k_sf, dim3(c.sf4.n, m), dim3(256), 0, s, c.N, c.nmax + 1, c.rhs_cap, c.n3,
-                       c.sf4.d, c.kcoef, c.axt, v, c.tk, c.gate);
+                       fold, c.sf4.d, c.kcoef, c.axt, v, fold ? c.tkf : c.tk, c.gate);
 }
 
 // ------------------------------------- reciprocal back-projection + epilogue
@@ -379,6 +379,55 @@ void launch_sf(const Ctx &c, const double *v, int m, hipStream_t s)
 //   EPI_ADJ        adjoint step mu_p = c_p g + 2 (ya y - yb mu_{p+1}) - mu_{p+2}
 //                  (g = acc, read only; mu_{p+2} = 0 when vprev2 is null),
 //                  dv = xs ya mu_p
+// The epilogue of `mode` for one entry: bead-component index o of the vector
+// block, y the product's value, (pv, pv2, pa) the recurrence operands; with
+// `trial` the entry's terms of the fused trial's dot products.
+__device__ __forceinline__ void epi_entry(const EpiArgs &f, size_t o, double yy, double pv, double pv2,
+                                          double pa, bool trial, double &ta, double &tb2)
+{
+    const double ya = f.scal ? f.scal[2] : 0.0, yb = f.scal ? f.scal[3] : 0.0;
+    double vnew = 0.0;   // the vector this epilogue produces
+    if (f.mode == EPI_APPLY) {
+        f.vout[o] = yy;
+    } else if (f.mode == EPI_CHEB_FIRST) {
+        const double v1 = ya * yy - yb * pv;
+        f.vout[o] = v1;
+        f.acc[o] = 0.5 * f.scal[8] * pv + f.scal[9] * v1;
+        if (f.dv) f.dv[o] = yy;
+        vnew = v1;
+    } else if (f.mode == EPI_CHEB_NEXT) {
+        const double vp = 2.0 * (ya * yy - yb * pv) - pv2;
+        f.vout[o] = vp;
+        f.acc[o] = pa + f.scal[8 + f.p] * vp;
+        vnew = vp;
+    } else {
+        const double mp = f.scal[8 + f.p] * pa + 2.0 * (ya * yy - yb * pv) - pv2;
+        f.vout[o] = mp;
+        f.dv[o] = f.xs * ya * mp;
+    }
+    if (!trial) return;
+    // the terms in k_trial_sum's order; V_p from the register
+    const double *vh = f.vhist + o;
+    const double v0 = vh[0];
+    double d = -0.5 * f.scal[8] * v0;
+    // eight stored terms loaded at a time (a load per term
+    // in turn left each trial's epilogue at about 18 us)
+    for (int q0 = 0; q0 < f.trial_n; q0 += 8) {
+        double t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int q = q0 + u;
+            t[u] = q < f.trial_n && q != f.p ? vh[(size_t)q * f.ps] : vnew;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q0 + u < f.trial_n) d += f.scal[8 + q0 + u] * t[u];
+    }
+    f.ds[o] = d;
+    ta = d * d;
+    tb2 = v0 * f.ddw[o];
+}
+
 constexpr int EPI_BEADS = 16;
 constexpr int EPI_SLICES = 64;
 // When `staged` (nk <= 1024, at most epi_stage_per<M>() x 1024 values of tk,
@@ -498,7 +547,6 @@ __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, i
         kloop(reinterpret_cast<const KVec *>(stage), stage + 2 * (nk + 1), 6 * M);
     else
         kloop(kvec, tk_g + (size_t)j0 * 6, 6 * rhs_cap);
-    const double ya = f.scal ? f.scal[2] : 0.0, yb = f.scal ? f.scal[3] : 0.0;
     // the fused trial, as k_trial_sum: skipped once the order is settled or
     // below the call's first order
     const bool trial = f.trial_n > 0 && (f.mode == EPI_CHEB_FIRST || f.mode == EPI_CHEB_NEXT) &&
@@ -518,48 +566,8 @@ __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, i
             double yy = 0.0;
 #pragma unroll
             for (int ww = 0; ww < 16; ++ww) yy += red[ww][ec][eb];
-            const size_t o = (size_t)(j0 + j) * n3 + 3 * (size_t)ebead + ec;
-            double vnew = 0.0;   // the vector this epilogue produces
-            if (f.mode == EPI_APPLY) {
-                f.vout[o] = yy;
-            } else if (f.mode == EPI_CHEB_FIRST) {
-                const double v0 = pv[j];
-                const double v1 = ya * yy - yb * v0;
-                f.vout[o] = v1;
-                f.acc[o] = 0.5 * f.scal[8] * v0 + f.scal[9] * v1;
-                if (f.dv) f.dv[o] = yy;
-                vnew = v1;
-            } else if (f.mode == EPI_CHEB_NEXT) {
-                const double vp = 2.0 * (ya * yy - yb * pv[j]) - pv2[j];
-                f.vout[o] = vp;
-                f.acc[o] = pa[j] + f.scal[8 + f.p] * vp;
-                vnew = vp;
-            } else {
-                const double mp = f.scal[8 + f.p] * pa[j] + 2.0 * (ya * yy - yb * pv[j]) - pv2[j];
-                f.vout[o] = mp;
-                f.dv[o] = f.xs * ya * mp;
-            }
-            if (trial) {   // the terms in k_trial_sum's order; V_p from the register
-                const double *vh = f.vhist + o;
-                const double v0 = vh[0];
-                double d = -0.5 * f.scal[8] * v0;
-                // eight stored terms loaded at a time (a load per term
-                // in turn left each trial's epilogue at about 18 us)
-                for (int q0 = 0; q0 < f.trial_n; q0 += 8) {
-                    double t[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int q = q0 + u;
-                        t[u] = q < f.trial_n && q != f.p ? vh[(size_t)q * f.ps] : vnew;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (q0 + u < f.trial_n) d += f.scal[8 + q0 + u] * t[u];
-                }
-                f.ds[o] = d;
-                ta = d * d;
-                tb2 = v0 * f.ddw[o];
-            }
+            epi_entry(f, (size_t)(j0 + j) * n3 + 3 * (size_t)ebead + ec, yy, pv[j], pv2[j], pa[j], trial,
+                      ta, tb2);
         }
         if (trial && w == 0) {   // the 3 EPI_BEADS entries are lanes of the first wave
 #pragma unroll
@@ -577,9 +585,125 @@ __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, i
     }
 }
 
+// The same by columns of wave vectors, for wave-vector sets past the staged limit.  Workgroup:
+// 64 beads (lane = bead), 16 waves that share the columns (n_x, n_y, *) in
+// contiguous parts of about equal numbers of pairs +-n_z (wsplit).  Every T is
+// the same for all lanes and is read through the scalar cache; with b = 2 pi n_z s_z
+//   X += cos b A + sin b B,   Y += cos b C + sin b D
+// over a column's pairs (12 multiply-adds and a rotation per two wave vectors), then
+//   y += Re E X + Im E Y,   E = e^{i 2 pi (n_x s_x + n_y s_y)}.
+// Bound by the latency of the scalar loads (about twice the time of the
+// multiply-adds; four waves per SIMD).  N = 16000, 7947 wave vectors: 62 us where
+// the form above, unstaged, took 230 (each vector a workgroup row of its
+// own: four in one pass over the columns 305 us, in four rows 251; N = 2000: 207 and 46).  With
+// the 618 wave vectors of alpha L = 6 the staged form stays ahead: 7.2 against 9.5 us at
+// N = 2000, 8.2 against 10.0 us at N = 4000.
+constexpr int COL_BEADS = 64;
+static_assert(3 * COL_BEADS / 64 <= COL_BEADS / EPI_BEADS, "trial_chunks covers both");
+constexpr int COL_TRIAL = 3 * COL_BEADS / 64;   // waves that hold entries
+__global__ __launch_bounds__(1024) void k_kspace_cols(int N, int n3, int n3pad, int nbt, int nm1,
+                                                      int rhs_cap,
+                                                      const int *__restrict__ wsplit,
+                                                      const FoldCol *__restrict__ cols,
+                                                      const double2 *__restrict__ axt,
+                                                      const double *__restrict__ part,
+                                                      const double *__restrict__ fold, EpiArgs f,
+                                                      const int *__restrict__ gate)
+{
+    __shared__ double red[16][3][COL_BEADS];
+    if (gate && *gate) return;
+    const int j = blockIdx.y, lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nu = min((int)blockIdx.x * COL_BEADS + lane, N - 1);
+    const int c0 = wsplit[w], c1 = wsplit[w + 1];
+    const double2 *tx = axt + nu, *ty = tx + (size_t)nm1 * N;
+    const double2 e1 = tx[(size_t)(2 * nm1 + 1) * N];   // e^{i 2 pi s_z}
+    FoldCol nxt = cols[c0];
+    double2 nex = tx[(size_t)nxt.nx * N], ney = ty[(size_t)abs(nxt.ny) * N];
+    double y[3] = {0.0, 0.0, 0.0};
+    for (int K = w; K < nbt; K += 16) {
+        const double *pp = part + ((size_t)K * rhs_cap + j) * n3pad + 3 * (size_t)nu;
+        y[0] += pp[0];
+        y[1] += pp[1];
+        y[2] += pp[2];
+    }
+    const int eb = (int)threadIdx.x / 3, ec = (int)threadIdx.x % 3;
+    const int ebead = blockIdx.x * COL_BEADS + eb;
+    const bool eth = threadIdx.x < 3 * COL_BEADS && ebead < N;
+    for (int c = c0; c < c1; ++c) {
+        const FoldCol col = nxt;
+        const double2 ex = nex, ey = ney;
+        nxt = cols[min(c + 1, c1 - 1)];
+        nex = tx[(size_t)nxt.nx * N];
+        ney = ty[(size_t)abs(nxt.ny) * N];
+        double X[3] = {0.0, 0.0, 0.0}, Y[3] = {0.0, 0.0, 0.0};
+        double zr = 1.0, zi = 0.0;
+        const double *t = fold + ((size_t)col.p0 * rhs_cap + j) * 12;
+#pragma unroll 1
+        for (int p = 0; p < col.len; p += FOLD_STEP, t += (size_t)FOLD_STEP * 12 * rhs_cap) {
+#pragma unroll
+            for (int u = 0; u < FOLD_STEP; ++u) {
+                const double *s = t + (size_t)u * 12 * rhs_cap;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    X[i] = fma(zr, s[i], X[i]);
+                    X[i] = fma(zi, s[3 + i], X[i]);
+                    Y[i] = fma(zr, s[6 + i], Y[i]);
+                    Y[i] = fma(zi, s[9 + i], Y[i]);
+                }
+                const double r = zr * e1.x - zi * e1.y;
+                zi = zr * e1.y + zi * e1.x;
+                zr = r;
+            }
+        }
+        const double eyi = col.ny < 0 ? -ey.y : ey.y;
+        const double er = ex.x * ey.x - ex.y * eyi, ei = ex.x * eyi + ex.y * ey.x;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            y[i] = fma(er, X[i], y[i]);
+            y[i] = fma(ei, Y[i], y[i]);
+        }
+    }
+    // as k_kspace_epi: the fused trial is skipped once the order is settled
+    const bool trial = f.trial_n > 0 && (f.mode == EPI_CHEB_FIRST || f.mode == EPI_CHEB_NEXT) &&
+                       !f.adapt->done && f.trial_n >= f.adapt->n_start;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) red[w][i][lane] = y[i];
+    __syncthreads();
+    if (w >= COL_TRIAL) return;   // the 3 COL_BEADS entries are the lanes of three waves
+    double ta = 0.0, tb2 = 0.0;
+    if (eth) {
+        const size_t o = (size_t)j * n3 + 3 * (size_t)ebead + ec;
+        const bool next = f.mode == EPI_CHEB_NEXT || f.mode == EPI_ADJ;
+        const double pv = f.mode != EPI_APPLY ? f.vprev[o] : 0.0;
+        const double pv2 = next && f.vprev2 ? f.vprev2[o] : 0.0, pa = next ? f.acc[o] : 0.0;
+        double yy = 0.0;
+#pragma unroll
+        for (int ww = 0; ww < 16; ++ww) yy += red[ww][ec][eb];
+        epi_entry(f, o, yy, pv, pv2, pa, trial, ta, tb2);
+    }
+    if (trial) {
+#pragma unroll
+        for (int o2 = 32; o2 >= 1; o2 >>= 1) {
+            ta += __shfl_xor(ta, o2);
+            tb2 += __shfl_xor(tb2, o2);
+        }
+        if (lane == 0) {
+            double *tp = f.tpart + (((size_t)j * gridDim.x + blockIdx.x) * COL_TRIAL + w) * 2;
+            tp[0] = ta;
+            tp[1] = tb2;
+        }
+    }
+}
+
 void launch_kspace_epi(const Ctx &c, const EpiArgs &f, hipStream_t s)
 {
     const dim3 g((c.N + EPI_BEADS - 1) / EPI_BEADS), b(1024);
+    if (c.fold) {
+        hipLaunchKernelGGL(k_kspace_cols, dim3((c.N + COL_BEADS - 1) / COL_BEADS, f.m), b, 0, s, c.N,
+                           c.n3, c.n3pad, c.nslot, c.nmax + 1, c.rhs_cap, c.fold_split, c.fold_cols,
+                           c.axt, c.part, c.tkf, f, c.gate);
+        return;
+    }
     const size_t tabs = sizeof(double) * 2 * EPI_BEADS * 3 * (size_t)(c.nmax + 1);
     RPY_RHS_GROUPS(f.m, {
         const size_t lds = sizeof(double) * ((size_t)c.nk * (2 + 6 * MC) + 3);
@@ -817,7 +941,10 @@ void launch_trial(const Ctx &c, int m, int n, int nmax, double tol, size_t ps,
                        c.adapt, c.tpart, c.scal, e_f);
 }
 
-int epi_trial_chunks(int N) { return (N + EPI_BEADS - 1) / EPI_BEADS; }   // its workgroups
+int epi_trial_chunks(const Ctx &c)
+{
+    return c.fold ? (c.N + COL_BEADS - 1) / COL_BEADS * COL_TRIAL : (c.N + EPI_BEADS - 1) / EPI_BEADS;
+}
 
 void launch_trial_check(const Ctx &c, int m, int nchunk, int n, int nmax, double tol, double *e_f,
                         hipStream_t s)
@@ -828,7 +955,7 @@ void launch_trial_check(const Ctx &c, int m, int nchunk, int n, int nmax, double
 
 int trial_chunks(int N)
 {
-    const int a = (3 * N + 255) / 256, b = epi_trial_chunks(N);
+    const int a = (3 * N + 255) / 256, b = (N + COL_BEADS - 1) / COL_BEADS * (COL_BEADS / EPI_BEADS);
     const int r = N <= ROWS_MAX ? rows_trial_chunks(N) : 0;
     return a > b ? (a > r ? a : r) : (b > r ? b : r);
 }

@@ -406,18 +406,40 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     c.nk4 = (c.nk + 3) / 4 * 4;
     // columns (n_x, n_y) of the half space; kv holds each one's n_z in order
     std::vector<SfCol> cols;
+    std::vector<FoldCol> fcols;
+    int npair = 0;   // pairs +-n_z, each column's number rounded up to FOLD_STEP
     for (int nz = 2; nz <= 4; nz += 2) {
+        size_t nc = 0;
         for (int k = 0; k < c.nk;) {
             int e = k;
             while (e < c.nk && kv[e].nx == kv[k].nx && kv[e].ny == kv[k].ny) ++e;
             const int top = kv[e - 1].nz;   // n_z = -top .. top, or 1 .. top at n_x = n_y = 0
+            if (nz == 2) {
+                const int len = (top + FOLD_STEP) / FOLD_STEP * FOLD_STEP;
+                fcols.push_back(FoldCol{kv[k].nx, kv[k].ny, npair, len});
+                npair += len;
+            }
+            const int p0 = fcols[nc++].p0;
             for (int z = 0; z <= top; z += nz)
                 cols.push_back(SfCol{kv[k].nx, kv[k].ny, z, top + 1 - z < nz ? top + 1 - z : nz,
-                                     e - 1 - top, kv[k].nz < 0 ? 1 : 0, 0, 0});
+                                     e - 1 - top, kv[k].nz < 0 ? 1 : 0, p0 + z, 0});
             k = e;
         }
         (nz == 2 ? c.sf2 : c.sf4).n = (int)cols.size() - (nz == 2 ? 0 : c.sf2.n);
     }
+    // the columns of the 16 waves of the back-projection: contiguous, about
+    // equal numbers of pairs (a column counts for two more)
+    std::vector<int> split(17 + 3, (int)fcols.size());
+    {
+        const long all = npair + 2 * (long)fcols.size();
+        long at = 0;
+        int w = 0;
+        for (size_t q = 0; q < fcols.size(); ++q) {
+            while (w < 16 && at * 16 >= all * w) split[w++] = (int)q;
+            at += fcols[q].len + 2;
+        }
+    }
+    c.fold = c.nk > FOLD_MIN_NK;
     c.nchb = c.nsfc < 16 ? c.nsfc : 16;
 
     std::vector<int2> tij;
@@ -450,7 +472,11 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     tabs.resize((tabs.size() + 3) / 4 * 4);
     const size_t t_kc = tabs.size(), t_col = t_kc + 4 * kc.size(), t_kv = t_col + 4 * cols.size();
     static_assert(sizeof(KCoef) == 32 && sizeof(SfCol) == 32 && sizeof(KVec) == 16, "table layout");
-    tabs.resize(t_kv + 2 * kv.size());
+    const size_t t_fc = t_kv + 2 * kv.size(), t_sp = t_fc + 2 * fcols.size();
+    static_assert(sizeof(FoldCol) == 16, "table layout");
+    tabs.resize(t_sp + split.size() / 2);
+    memcpy(&tabs[t_fc], fcols.data(), fcols.size() * sizeof(FoldCol));
+    memcpy(&tabs[t_sp], split.data(), split.size() * sizeof(int));
     memcpy(&tabs[t_kc], kc.data(), kc.size() * sizeof(KCoef));
     memcpy(&tabs[t_col], cols.data(), cols.size() * sizeof(SfCol));
     memcpy(&tabs[t_kv], kv.data(), kv.size() * sizeof(KVec));
@@ -478,7 +504,7 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
                      (rc = dalloc(&c.ypart, (size_t)BLOCK_RHS * c.n3)) ||
                      (rc = dalloc(&c.eph, (size_t)(c.N + 3) / 4 * ((c.nk + 15) / 16 * 16) * 4)))) ||
         (rc = dalloc(&c.sfpart, sfpart_elems(c))) ||
-        (rc = dalloc(&c.tk, (size_t)6 * c.rhs_cap * c.nk)) ||
+        (rc = dalloc(&c.tk, (size_t)6 * c.rhs_cap * (c.nk + (c.fold ? 2 * npair : 0)))) ||
         (rc = dalloc(&c.sfr, nv)) ||
         (rc = dalloc(&c.work, c.work_elems)) || (rc = dalloc(&c.scal, 8 + MAX_NCHEB)) ||
         (rc = dalloc(&c.red, 64)) || (rc = dalloc(&c.flags, 4)) ||
@@ -519,6 +545,9 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     c.sf2.d = reinterpret_cast<SfCol *>(c.smooth + t_col);
     c.sf4.d = c.sf2.d + c.sf2.n;
     c.kvec = reinterpret_cast<KVec *>(c.smooth + t_kv);
+    c.fold_cols = reinterpret_cast<FoldCol *>(c.smooth + t_fc);
+    c.fold_split = reinterpret_cast<int *>(c.smooth + t_sp);
+    c.tkf = c.tk + (size_t)6 * c.rhs_cap * c.nk;
     std::vector<double> um(nv);
     for (size_t i = 0; i < nv; ++i) um[i] = (i & 1) ? -1.0 : 1.0;
     hipError_t e;
@@ -528,6 +557,8 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
         (e = hipMemset(c.flags, 0, 4 * sizeof(int))) ||
         (e = hipMemset(c.adapt, 0, sizeof(AdaptState))) ||
         (te6 && (e = hipMemset(c.d64, 0, te6 * sizeof(double)))) ||
+        // the pairs that only round a column up are never written
+        (c.fold && (e = hipMemset(c.tkf, 0, (size_t)12 * c.rhs_cap * npair * sizeof(double)))) ||
         // the columns past the tiles are never written
         (series && (e = hipMemset(c.series + SC, 0, (SERIES_DOUBLES - SC) * sizeof(double)))) ||
         (rows && c.row_ld > c.nbt * TB &&
@@ -672,7 +703,7 @@ static void product(rpy_ctx *x, const double *v, int m, int prec, const EpiArgs 
         }
         {
             ProfScope ps(x, RPY_PROF_KSPACE, s);
-            launch_sf(c, v, m, s);
+            launch_sf(c, v, m, c.fold, s);
         }
         ProfScope ps(x, RPY_PROF_EPI, s);
         launch_kspace_epi(c, f, s);
@@ -832,7 +863,7 @@ static void cheb_adapt_run(rpy_ctx *x, int m, int prec, int first, int host_firs
     auto trial = [&](int n, bool fused) {
         if (n < host_first) return;
         if (fused)
-            launch_trial_check(c, m, by_rows(x, m) ? rows_trial_chunks(c.N) : epi_trial_chunks(c.N),
+            launch_trial_check(c, m, by_rows(x, m) ? rows_trial_chunks(c.N) : epi_trial_chunks(c),
                                n, nmax, tol, e_f, s);
         else launch_trial(c, m, n, nmax, tol, ps, x->ddw, out, e_f, s);
     };
@@ -1230,7 +1261,7 @@ extern "C" int rpy_u_vjp(rpy_ctx *x, const double *pos, const double *F, const d
     const int qg = c.rhs_cap / 2;
     for (int q0 = 0; q0 < P; q0 += qg) {
         const int nq = P - q0 < qg ? P - q0 : qg;
-        launch_sf(c, xy + 2 * q0 * nv, 2 * nq, s);
+        launch_sf(c, xy + 2 * q0 * nv, 2 * nq, 0, s);
         launch_grad_kspace(c, xy + 2 * q0 * nv, nq, q0 > 0, s);
     }
     launch_grad_sum(c, g_pos, s);

@@ -436,6 +436,12 @@ struct Ctx {
     double2 *etab = nullptr;     // phases [N][3][nmax+1]
     double2 *axt = nullptr;      // the same phases bead-contiguous, [3 (nmax + 1)][N] (behind etab)
     SfCols sf2, sf4;             // columns of wave vectors (rpy_sf.h), cut after 2 and after 4 n_z
+    // the back-projection by columns (k_kspace_cols), for more wave vectors than
+    // k_kspace_epi stages
+    bool fold = false;
+    const struct FoldCol *fold_cols = nullptr;
+    const int *fold_split = nullptr;   // [17] the columns of each wave
+    double *tkf = nullptr;       // folded T_k [pair][rhs_cap][12], behind tk
     KVec *kvec = nullptr;        // [nk]
     KCoef *kcoef = nullptr;      // [nk]
     int2 *tile_ij = nullptr;     // [ntiles]
@@ -607,7 +613,8 @@ constexpr int BLOCK_MIN_RHS = 5;   // products with at least this many vectors u
 constexpr int BLOCK_RHS = 16;
 // T_k of m vectors into tk (a launch of its own, for the low-memory form and
 // the reverse mode; the tile products carry theirs)
-void launch_sf(const Ctx &c, const double *v, int m, hipStream_t s);
+void launch_sf(const Ctx &c, const double *v, int m, int fold, hipStream_t s);
+constexpr int FOLD_MIN_NK = 1024;   // more wave vectors take the folded form
 void launch_kspace_epi(const Ctx &c, const EpiArgs &f, hipStream_t s);
 // Interval (explicit, or the paper's rule from du = D.U+), the scalars of Y
 // and the coefficients of order n_cheb.  With adapt_floor >= 0 the order is
@@ -626,7 +633,7 @@ void launch_trial(const Ctx &c, int m, int n, int nmax, double tol, size_t ps,
 // formed the trial (EpiArgs::trial_n, nchunk partial sums): only the check.
 void launch_trial_check(const Ctx &c, int m, int nchunk, int n, int nmax, double tol, double *e_f,
                         hipStream_t s);
-int epi_trial_chunks(int N);     // partial sums of a k_kspace_epi trial per vector
+int epi_trial_chunks(const Ctx &c);   // partial sums of a back-projection's trial per vector
 // Partial-sum chunks of a trial per right-hand side: the larger of the
 // separate trial kernel's (256 entries each) and the epilogue's (one per
 // workgroup), which sizes c.tpart.

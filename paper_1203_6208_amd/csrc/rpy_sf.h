@@ -36,13 +36,22 @@ __device__ inline double2 kphase(const KVec &kv, const double2 *tab, int nm1)
 // One wave vector per thread group with sincospi of every bead instead: FP32 37.9 ->
 // 34.3 us at N = 4000 and 18.4 -> 13.2 us at N = 2000, FP64 22.9 -> 18.7 us at
 // N = 2000; alone, with a launch that sums partials, 180 -> 92 us at N = 16000.
+// With `fold`, T of a pair (n_x, n_y, +-n_z) is stored as the four vectors the
+// back-projection by columns multiplies with cos and sin of 2 pi n_z s_z:
+//   [pair][j][A, B, C, D] = Tc+ + Tc-, Ts+ - Ts-, Ts+ + Ts-, Tc- - Tc+.
 // axt[axis (nmax + 1) + j][N] = e^{i 2 pi j s_axis}: bead-contiguous.
 constexpr int SF_AHEAD = 2;   // beads whose loads go out together
 struct SfCol {
     int nx, ny, nz0, cnt;   // the column, the first n_z and how many (at most NZ)
     int k0, both;           // index of n_z = 0 among the wave vectors; -n_z is one too
-    int pad0, pad1;
+    int p0, pad;            // index of the pair (n_x, n_y, +-nz0) in the folded layout
 };
+// A column of the folded T_k: its pairs (n_x, n_y, +-n_z), n_z = 0, 1, ..., stand at p0,
+// p0 + 1, ...; `len` is their number, rounded up to FOLD_STEP with zeros.
+struct FoldCol {
+    int nx, ny, p0, len;
+};
+constexpr int FOLD_STEP = 2;
 
 // x of the lane CTRL names (a DPP control: a permutation inside 16 lanes, on
 // the vector unit and not through LDS).
@@ -59,7 +68,7 @@ constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_ROR4 = 0x124, DPP_ROR8 = 0x1
 template <int NW, int NZ> constexpr int sf_lds() { return 12 * NZ * (17 * NW + 1); }
 template <int NW, int NZ>
 __device__ __forceinline__ void sf_column(const SfCol *__restrict__ cols, int b, int N, int nm1,
-                                          int rhs_cap, int j, int n3,
+                                          int rhs_cap, int j, int n3, int fold,
                                           const KCoef *__restrict__ kcoef, const double2 *axt,
                                           const double *v, double *__restrict__ tk, double *smem)
 {
@@ -140,16 +149,34 @@ __device__ __forceinline__ void sf_column(const SfCol *__restrict__ cols, int b,
     const int q = threadIdx.x >> 2, neg = threadIdx.x >> 1 & 1, half = threadIdx.x & 1;
     if (q >= col.cnt) return;
     const int nz = col.nz0 + q, k = col.k0 + (neg ? -nz : nz);
-    if (neg ? nz == 0 || !col.both : k < 0) return;   // n_z = 0 once; n = 0 never
-    const double sg = (half != 0) == (neg != 0) ? -1.0 : 1.0;   // C: A1 -/+ A2, S: A3 +/- A4
-    const double *s = sum + 12 * q + 6 * half;
-    const double s0 = s[0] + sg * s[3], s1 = s[1] + sg * s[4], s2 = s[2] + sg * s[5];
-    const KCoef kc = kcoef[k];
-    const double h = kc.hx * s0 + kc.hy * s1 + kc.hz * s2;
-    double *o = tk + ((size_t)k * rhs_cap + j) * 6 + 3 * half;
-    o[0] = kc.w * (s0 - kc.hx * h);
-    o[1] = kc.w * (s1 - kc.hy * h);
-    o[2] = kc.w * (s2 - kc.hz * h);
+    // n_z = 0 once; n = 0 never
+    const bool have = neg ? nz != 0 && col.both : k >= 0;
+    double o0 = 0.0, o1 = 0.0, o2 = 0.0;
+    if (have) {
+        const double sg = (half != 0) == (neg != 0) ? -1.0 : 1.0;   // C: A1 -/+ A2, S: A3 +/- A4
+        const double *s = sum + 12 * q + 6 * half;
+        const double s0 = s[0] + sg * s[3], s1 = s[1] + sg * s[4], s2 = s[2] + sg * s[5];
+        const KCoef kc = kcoef[k];
+        const double h = kc.hx * s0 + kc.hy * s1 + kc.hz * s2;
+        o0 = kc.w * (s0 - kc.hx * h);
+        o1 = kc.w * (s1 - kc.hy * h);
+        o2 = kc.w * (s2 - kc.hz * h);
+    }
+    if (!fold) {
+        if (!have) return;
+        double *o = tk + ((size_t)k * rhs_cap + j) * 6 + 3 * half;
+        o[0] = o0;
+        o[1] = o1;
+        o[2] = o2;
+        return;
+    }
+    // own and mirrored T: half 0: Tc+ + Tc- and Tc- - Tc+, half 1: Ts+ + Ts- and Ts+ - Ts-
+    const double p0 = dpp<DPP_XOR2>(o0), p1 = dpp<DPP_XOR2>(o1), p2 = dpp<DPP_XOR2>(o2);
+    const double so = neg && half ? -1.0 : 1.0, sp = neg && !half ? -1.0 : 1.0;
+    double *o = tk + ((size_t)(col.p0 + q) * rhs_cap + j) * 12 + 3 * (neg ? (half ? 1 : 3) : (half ? 2 : 0));
+    o[0] = so * o0 + sp * p0;
+    o[1] = so * o1 + sp * p1;
+    o[2] = so * o2 + sp * p2;
 }
 
 }  // namespace rpy

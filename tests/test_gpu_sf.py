@@ -61,3 +61,41 @@ def test_wave_vector_sets(form):
 def test_alone(size, alphaL):
     for m in (1, 3):
         _run(*size, alphaL, 3.5, m, "f64", 1)
+
+
+@pytest.mark.parametrize("size", [(8, 25), (3, 64), (2, 65), (1, 255)])
+@pytest.mark.parametrize("lma", [0, 1])
+def test_back_projection_by_columns(size, lma):
+    """More wave vectors than the staged limit: every epilogue, the fused
+    trials and, with stored tiles (an FP32 copy keeps the FP64 products on
+    them), the reverse mode between products."""
+    w = inputs.Workload("cols", *size, 1.0, alphaL=12.0, M=3.5, seed=93)
+    p = w.positions()
+    pos = torch.from_numpy(p).cuda()
+    kw = dict(lma=1) if lma else dict(lowp="f32", grad=1)
+    ctx = rpy.context_for(w, max_rhs=3, cheb_keep=64, **kw)
+    ctx.build(pos)
+    D = oracle.diffusion_matrix(p, w.L, w.a, w.alpha, w.rc, w.n2max)
+    lam = np.linalg.eigvalsh(D)
+    lo, hi = 0.8 * lam[0], 1.2 * lam[-1]
+    for m in (1, 3):
+        dw = w.noise(m=m)
+        ds = ctx.sqrt_apply(torch.from_numpy(dw).cuda(), 14, lo, hi)
+        want = oracle.cheb_sqrt(D, dw.reshape(m, -1), 14, lo, hi)
+        assert np.abs(ds.cpu().numpy().reshape(m, -1) - want).max() <= TOL * np.abs(want).max()
+        if not lma:
+            rng = np.random.default_rng(4)
+            F, g = rng.standard_normal((w.n, 3)), rng.standard_normal((w.n, 3))
+            f1 = dw[:1].reshape(w.n, 3)
+            gp, gF = torch.empty_like(pos), torch.empty_like(pos)
+            c = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (F, f1, g)]
+            rpy.rpy_u_vjp(ctx.handle, pos, *c, 8, lo, hi, gp, gF, None)
+            wp, wF = oracle.u_vjp(p, w.L, w.a, w.alpha, w.rc, w.n2max, F, f1, g, 8, lo, hi)
+            # dL/dR: a sum of terms of both signs, as every test of the reverse mode
+            assert np.abs(gp.cpu().numpy() - wp).max() <= 1e-10 * np.abs(wp).max()
+            assert np.abs(gF.cpu().numpy() - wF).max() <= TOL * np.abs(wF).max()
+        ds, ef, n = ctx.sqrt_adaptive(torch.from_numpy(dw).cuda(), lo, hi, 1e-3, 64)
+        n_o, want = oracle.cheb_adaptive(D, dw.reshape(m, -1), lo, hi, 1e-3, 64)
+        assert n == n_o
+        assert np.abs(ds.cpu().numpy().reshape(m, -1) - want).max() <= TOL * np.abs(want).max()
+    ctx.close()
