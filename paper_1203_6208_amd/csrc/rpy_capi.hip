@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -44,12 +45,75 @@ struct rpy_ctx {
     // (10 ms; a wait is microseconds unless the kernel is not fully resident)
     uint32_t series_epoch = 1;
     long long series_limit = 1000000;
+    int series_dev = -1;      // device whose SeriesGate this context is counted in
     // bd_step runs the forces and the noise on a second stream (default
     // priority) beside the tile build: fork after the wrap, join before the
     // drift product
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
 };
+
+// The series kernel of a box past SERIES_SMALL beads takes nearly every compute
+// unit, and two of them (or one and a small one) started together from two
+// streams could each become resident in part and wait for the bound of their
+// waits.  So while a device has such a context and any other that
+// runs series, their series kernels are ordered one after the other, by an event
+// recorded behind each; the calls around them overlap as before.  With one
+// context, or small boxes only (64 workgroups each, at most four hardware queues), nothing is
+// recorded.
+struct SeriesGate {
+    std::mutex m;
+    int all = 0, big = 0;
+    hipEvent_t ev = nullptr;
+    hipStream_t last = nullptr;
+    bool set = false;
+};
+constexpr int GATE_DEVICES = 64;
+static SeriesGate g_gate[GATE_DEVICES];
+
+static hipError_t gate_enter(rpy_ctx *x)   // before the device synchronisation of rpy_create
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    dev %= GATE_DEVICES;
+    SeriesGate &g = g_gate[dev];
+    std::lock_guard<std::mutex> lock(g.m);
+    if (!g.ev && (e = hipEventCreateWithFlags(&g.ev, hipEventDisableTiming)) != hipSuccess) {
+        g.ev = nullptr;
+        return e;
+    }
+    x->series_dev = dev;
+    ++g.all;
+    g.big += x->c.N > SERIES_SMALL;
+    return hipSuccess;
+}
+
+static void gate_leave(rpy_ctx *x)   // after the device synchronisation of rpy_destroy
+{
+    if (x->series_dev < 0) return;
+    SeriesGate &g = g_gate[x->series_dev];
+    std::lock_guard<std::mutex> lock(g.m);
+    g.big -= x->c.N > SERIES_SMALL;
+    if (--g.all == 0) {
+        (void)hipEventDestroy(g.ev);
+        g.ev = nullptr;
+        g.set = false;
+    }
+}
+
+static void run_series(rpy_ctx *x, const SeriesArgs &a, hipStream_t s)
+{
+    SeriesGate &g = g_gate[x->series_dev];
+    std::lock_guard<std::mutex> lock(g.m);
+    const bool order = g.big > 0 && g.all > 1;
+    if (order && g.set && g.last != s) (void)hipStreamWaitEvent(s, g.ev, 0);
+    launch_series(a, s);
+    if (order) {
+        g.set = hipEventRecord(g.ev, s) == hipSuccess;
+        g.last = s;
+    }
+}
 
 static thread_local char g_err[256];
 
@@ -308,6 +372,7 @@ extern "C" void rpy_destroy(rpy_ctx *x)
 {
     if (!x) return;
     (void)hipDeviceSynchronize();
+    gate_leave(x);
     Ctx &c = x->c;
     void *bufs[] = {c.rt, c.rt_ev, c.smooth, c.eph, c.etab, c.tile_ij, c.d64,
                     c.p32, c.p16, c.drow, c.series, c.part, c.xpk, c.ypart,
@@ -458,7 +523,7 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     c.row_ld = (c.N + 127) / 128 * 128;
     const bool series = rows && c.N <= SERIES_MAX;
     // coefficients, ring, vector words, partial-sum words, record, flag
-    constexpr size_t SW = 2 * 2 * 3 * SERIES_MAX, SP = 2 * 2 * 2 * 64;
+    constexpr size_t SW = 2 * 2 * 3 * SERIES_MAX, SP = 2 * 2 * 2 * SERIES_GROUPS;
     constexpr size_t SC = (SERIES_ORDERS + 1) * SERIES_ORDERS, SR = 3 * 3 * SERIES_MAX;
     constexpr size_t SERIES_DOUBLES = SC + SR + SW + SP + 2 + 1;
     static_assert(sizeof(SeriesRec) == 2 * sizeof(double), "the record is two doubles");
@@ -577,7 +642,7 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
         return rc;
     }
     launch_fill(x->F + nv, 1.0, nv, 0);   // U+ = (1, 1, ..., 1)
-    if ((e = hipDeviceSynchronize()) != hipSuccess) {
+    if ((series && (e = gate_enter(x)) != hipSuccess) || (e = hipDeviceSynchronize()) != hipSuccess) {
         rc = hip_fail(e, "rpy_create sync");
         rpy_destroy(x);
         return rc;
@@ -925,7 +990,7 @@ static void series_explicit(rpy_ctx *x, const double *dw, double *out, int n0, i
     a.want_ef = e_f != nullptr;
     {
         ProfScope ps(x, RPY_PROF_SYMV, s);
-        launch_series(a, s);
+        run_series(x, a, s);
     }
     launch_series_finish(a, nullptr, 0.0, nullptr, nullptr, e_f ? e_f : c.red, s);
 }
@@ -1430,7 +1495,7 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
         a.want_ef = e_f != nullptr;
         {
             ProfScope ps(x, RPY_PROF_SYMV, s);
-            launch_series(a, s);
+            run_series(x, a, s);
         }
         launch_series_finish(a, pos, bp->dt / 4.0, drift, noise, e_f ? e_f : c.red, s);
         return check_launch("bd_step");
@@ -1477,7 +1542,7 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
             a.want_ef = e_f != nullptr;
             {
                 ProfScope pf(x, RPY_PROF_SYMV, s);
-                launch_series(a, s);
+                run_series(x, a, s);
             }
             launch_series_finish(a, pos, bp->dt / 4.0, drift, noise, e_f ? e_f : c.red, s);
             return check_launch("bd_step");

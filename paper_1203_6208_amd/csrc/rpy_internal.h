@@ -536,7 +536,9 @@ struct EpiArgs;
 void launch_row_product(const Ctx &c, const double *v, const EpiArgs &f, hipStream_t s);
 int rows_trial_chunks(int N);    // its partial sums of a trial per vector
 // The Chebyshev series of one vector in one launch (rpy_series.hip).
-constexpr int SERIES_MAX = 512;      // beads
+constexpr int SERIES_MAX = 1024;     // beads
+constexpr int SERIES_SMALL = 512;    // up to this many take eight beads per workgroup
+constexpr int SERIES_GROUPS = 256;   // workgroups at most
 constexpr int SERIES_ORDERS = 128;   // largest order
 struct SeriesRec {
     double ef;

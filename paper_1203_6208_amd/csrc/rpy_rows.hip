@@ -299,7 +299,7 @@ void launch_build_rows(const Ctx &c, hipStream_t s)
 // are combined by a fixed xor tree that leaves component c in lane c, then the
 // waves of a row in order.
 // One vector, per product with its recurrence step: N = 100 3.8 us, 400 5.6,
-// 1000 11.0 (48 MB), 1400 19.8 (94 MB), against 15.5, 15.9, 24 (at 618 wave
+// 1000 11.4 (48 MB), 1400 19.8 (94 MB), against 15.5, 15.9, 24 (at 618 wave
 // vectors) and 26 us in two launches by tiles.
 // flip: workgroups in reverse order (keeping blockIdx mod 8, the XCD), so that
 // a product starts on the rows its XCD's L2 read last.

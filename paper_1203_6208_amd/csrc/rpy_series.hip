@@ -2,9 +2,10 @@
 // boxes of at most SERIES_MAX beads whose tensor is stored by rows
 // (rpy_rows.hip).
 //
-// Such a product is about a microsecond of work behind four of launch.  Here a
-// term takes 2.0 us at N = 100 and, with the trials of the adaptive order, 3.0
-// at N = 400 (one launch per term: 3.9 and 5.6, plus the check of each order),
+// Such a product is a few microseconds of work behind four of launch.  Here a
+// term takes 2.0 us at N = 100, with the trials of the adaptive order 3.0
+// at N = 400, and 4.8 at N = 1000 (one launch per term: 3.9, 5.6 plus the check of each
+// order, and 12.3),
 // bound by the round trip of the new vector through memory:
 // every wave keeps its bead row of D in registers for the whole series, and the
 // workgroups pass each new vector to each other through memory: every double
@@ -15,7 +16,8 @@
 // after it has read all of V_{p+1}, so every workgroup has read all of V_p by then.
 //
 // The wait needs all workgroups on the device at once (one per 8 beads, 64 at
-// most).  They are, unless enough other such kernels run at the same time that
+// most; past 512 beads one per 4, 256 at most, which the host keeps from starting
+// beside another).  They are, unless enough other kernels run at the same time that
 // some are only partly resident; so every wait is bounded: a workgroup that has
 // waited for its limit raises a flag, all of them leave, and the finishing
 // kernel, one workgroup that waits for nobody, then runs the series alone.
@@ -24,10 +26,15 @@
 
 namespace rpy {
 
-constexpr int SR_BEADS = 8;                 // beads (waves) per workgroup
-constexpr int SR_NT = 64 * SR_BEADS;
-constexpr int SR_NB = SERIES_MAX / 128;     // column blocks of a row
-static_assert(SERIES_MAX / SR_BEADS <= 64, "one lane per workgroup in the partial sums");
+// Bead rows per workgroup (B), waves per row (WPR), column blocks of 128 per wave
+// (NB; 24 registers each): (8, 1, 4) up to SERIES_SMALL beads, else (SR_B, SR_WPR, SR_NBW).
+// N = 1000, per term: (4, 4, 2) 4.8 us; (4, 2, 4) 8.6 and (8, 2, 4) 8.2, whose
+// rows spill; (8, 1, 8) 13.3.
+constexpr int SR_SMALL = SERIES_SMALL;
+constexpr int SR_B = 4, SR_WPR = 4, SR_NBW = 2;
+static_assert(SR_WPR * SR_NBW * 128 == SERIES_MAX, "a row in registers");
+static_assert((SERIES_MAX + SR_B - 1) / SR_B <= SERIES_GROUPS && SR_SMALL / 8 <= SERIES_GROUPS,
+              "workgroups in the partial sums");
 typedef double sr2 __attribute__((ext_vector_type(2)));
 typedef unsigned long long word_t;
 
@@ -90,12 +97,14 @@ __device__ inline void row_block(const sr2 (&d)[6], const double *x, double &y0,
     }
 }
 
-// The row's product with the staged vector x: component l & 3 in lane l.
-__device__ inline double row_dot(const sr2 (&d)[SR_NB][6], int nb, const double *x, int lane)
+// A wave's part of its row's product with its columns x of the staged vector:
+// component l & 3 in lane l.
+template <int NB>
+__device__ inline double row_dot(const sr2 (&d)[NB][6], int nb, const double *x, int lane)
 {
     double y0 = 0.0, y1 = 0.0, y2 = 0.0;
 #pragma unroll
-    for (int u = 0; u < SR_NB; ++u)
+    for (int u = 0; u < NB; ++u)
         if (u < nb) row_block(d[u], x + 6 * (lane + 64 * u), y0, y1, y2);
     return wave_sum3(y0, y1, y2, lane);
 }
@@ -121,27 +130,45 @@ __device__ inline bool settles(double a, double b, int n, int nmax, double tol, 
     return (ef > 0.0 ? ef : 0.0) < tol || n >= nmax;   // as k_trial_check
 }
 
-__global__ __launch_bounds__(SR_NT) void k_series(SeriesArgs a)
+template <int B, int WPR, int NB>
+__global__ __launch_bounds__(64 * B * WPR) void k_series(SeriesArgs a)
 {
-    __shared__ double sx[2][3 * SERIES_MAX];
-    __shared__ double tred[SR_BEADS][2], pr[2 * 64];
+    constexpr int NT = 64 * B * WPR, X = 3 * 128 * NB * WPR, NW = (X + NT - 1) / NT;
+    static_assert(2 * SERIES_GROUPS <= NT, "a thread per partial sum");
+    __shared__ double sx[2][X];
+    __shared__ double tred[B][2], pr[2 * SERIES_GROUPS];
+    __shared__ double pd[2][WPR > 1 ? WPR : 1][B][4];   // the row parts of its waves
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int i = blockIdx.x * SR_BEADS + w, ic = min(i, a.N - 1), n3 = 3 * a.N;
-    const int nb = a.ld / 128, G = gridDim.x;
-    const bool eth = i < a.N && lane < 3;   // lanes 0..2 own the row's entries
+    const int r = w % B, h0 = w / B;   // row of the workgroup, wave of the row
+    const int i = blockIdx.x * B + r, ic = min(i, a.N - 1), n3 = 3 * a.N;
+    const int nb = min(max(a.ld / 128 - NB * h0, 0), NB), G = gridDim.x;
+    const bool eth = i < a.N && h0 == 0 && lane < 3;   // lanes that own the row's entries
     const size_t o = 3 * (size_t)ic + min(lane, 2);
-    const double *row = a.drow + (size_t)ic * 6 * a.ld + 2 * lane;
-    sr2 d[SR_NB][6];
+    const double *row = a.drow + (size_t)ic * 6 * a.ld + 128 * NB * h0 + 2 * lane;
+    sr2 d[NB][6];
 #pragma unroll
-    for (int u = 0; u < SR_NB; ++u)
+    for (int u = 0; u < NB; ++u)
 #pragma unroll
         for (int e = 0; e < 6; ++e)
             d[u][e] = u < nb ? *reinterpret_cast<const sr2 *>(row + (size_t)e * a.ld + 128 * u)
                              : sr2{0.0, 0.0};
-    for (int z = threadIdx.x; z < 3 * SERIES_MAX; z += SR_NT) {
+    for (int z = threadIdx.x; z < X; z += NT) {
         sx[0][z] = z < n3 ? a.dw[z] : 0.0;
         sx[1][z] = a.F && z < n3 ? a.F[z] : 0.0;
     }
+    // the row's product with sx[s]: the waves' parts in order, in every wave of the row (q: the
+    // two buffers of the parts alternate between products with no barrier between)
+    auto dot = [&](int s, int q) {
+        double y = row_dot<NB>(d, nb, sx[s] + 3 * 128 * NB * h0, lane);
+        if constexpr (WPR > 1) {
+            if (lane < 4) pd[q][h0][r][lane] = y;
+            __syncthreads();
+            y = pd[q][0][r][lane & 3];
+#pragma unroll
+            for (int k = 1; k < WPR; ++k) y += pd[q][k][r][lane & 3];
+        }
+        return y;
+    };
     const double ya = a.scal[2], yb = a.scal[3];
     const bool adapt = a.st != nullptr;
     const int nmax = a.n, nst = adapt ? a.st->n_start : 0;
@@ -149,16 +176,16 @@ __global__ __launch_bounds__(SR_NT) void k_series(SeriesArgs a)
     const double v0 = sx[0][o];
     double dd;   // D dW
     if (a.have_ddw) dd = a.ddw[o];
-    else dd = row_dot(d, nb, sx[0], lane);
+    else dd = dot(0, 0);
     if (a.F) {
-        const double f = row_dot(d, nb, sx[1], lane);
+        const double f = dot(1, 1);
         if (eth) a.ud[o] = f;
     }
     if (!a.have_ddw && eth) a.ddw[o] = dd;
     double vp = v0, v = ya * dd - yb * v0;   // V_0, V_1
     if (eth && nmax > 2) put(a.words + 2 * o, v, a.epoch + 1);
     __syncthreads();
-    for (int z = threadIdx.x; z < 3 * SERIES_MAX; z += SR_NT) sx[1][z] = 0.0;   // zero past 3N
+    for (int z = threadIdx.x; z < X; z += NT) sx[1][z] = 0.0;   // zero past 3N
     double acc = 0.0, h[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}}, t = 0.0;
     const double *ct = a.coef;   // fixed order: its coefficients
     auto keep = [&](int p, double x) {   // V_p into its history lane
@@ -173,19 +200,19 @@ __global__ __launch_bounds__(SR_NT) void k_series(SeriesArgs a)
     };
     // this workgroup's share of dS.dS and dW.D dW, to every workgroup
     auto share = [&](double s, uint32_t ep) {
-        const double q = eth ? s * s : 0.0, r = eth ? v0 * dd : 0.0;
+        const double q = eth ? s * s : 0.0, t = eth ? v0 * dd : 0.0;
         const double q3 = __shfl(q, 0) + __shfl(q, 1) + __shfl(q, 2);
-        const double r3 = __shfl(r, 0) + __shfl(r, 1) + __shfl(r, 2);
-        if (lane == 0) {
-            tred[w][0] = q3;
-            tred[w][1] = r3;
+        const double r3 = __shfl(t, 0) + __shfl(t, 1) + __shfl(t, 2);
+        if (lane == 0 && h0 == 0) {
+            tred[r][0] = q3;
+            tred[r][1] = r3;
         }
         __syncthreads();
         if (threadIdx.x < 2) {
             double z = tred[0][threadIdx.x];
 #pragma unroll
-            for (int k = 1; k < SR_BEADS; ++k) z += tred[k][threadIdx.x];
-            put(a.part + 2 * ((ep & 1) * 2 * 64 + 2 * blockIdx.x + threadIdx.x), z, ep);
+            for (int k = 1; k < B; ++k) z += tred[k][threadIdx.x];
+            put(a.part + 2 * ((ep & 1) * 2 * SERIES_GROUPS + 2 * blockIdx.x + threadIdx.x), z, ep);
         }
     };
     // the sums over all workgroups, in their order; false: the wait ran out
@@ -193,12 +220,16 @@ __global__ __launch_bounds__(SR_NT) void k_series(SeriesArgs a)
         double z[1] = {0.0};
         bool ok = true;
         if ((int)threadIdx.x < 2 * G)
-            ok = take<1>(a.part + 2 * (ep & 1) * 2 * 64, threadIdx.x, 0, 2 * G, ep, z, a.abort_flag,
+            ok = take<1>(a.part + 2 * (ep & 1) * 2 * SERIES_GROUPS, threadIdx.x, 0, 2 * G, ep, z, a.abort_flag,
                          a.limit);
-        if (threadIdx.x < 2 * 64) pr[threadIdx.x] = (int)threadIdx.x < 2 * G ? z[0] : 0.0;
+        if (threadIdx.x < 2 * SERIES_GROUPS) pr[threadIdx.x] = (int)threadIdx.x < 2 * G ? z[0] : 0.0;
         if (__syncthreads_or(!ok)) return false;
         sa = pr[2 * lane];
         sb = pr[2 * lane + 1];
+        for (int g = 64; g < G; g += 64) {
+            sa += pr[2 * (g + lane)];
+            sb += pr[2 * (g + lane) + 1];
+        }
 #pragma unroll
         for (int x = 32; x >= 1; x >>= 1) {
             sa += __shfl_xor(sa, x);
@@ -222,14 +253,14 @@ __global__ __launch_bounds__(SR_NT) void k_series(SeriesArgs a)
     for (int p = 2; p < nmax && !done; ++p) {
         // V_{p-1} from all workgroups
         double *x = sx[p & 1];
-        double z[3];
-        const bool ok = take<3>(a.words + (size_t)((p - 1) & 1 ? 0 : 1) * 2 * 3 * SERIES_MAX,
-                                threadIdx.x, SR_NT, n3, a.epoch + p - 1, z, a.abort_flag, a.limit);
+        double z[NW];
+        const bool ok = take<NW>(a.words + (size_t)((p - 1) & 1 ? 0 : 1) * 2 * 3 * SERIES_MAX,
+                                threadIdx.x, NT, n3, a.epoch + p - 1, z, a.abort_flag, a.limit);
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-            if ((int)threadIdx.x + SR_NT * k < n3) x[threadIdx.x + SR_NT * k] = z[k];
+        for (int k = 0; k < NW; ++k)
+            if ((int)threadIdx.x + NT * k < n3) x[threadIdx.x + NT * k] = z[k];
         if (__syncthreads_or(!ok)) return;
-        const double y = row_dot(d, nb, x, lane);
+        const double y = dot(p & 1, 0);
         const double vn = 2.0 * (ya * y - yb * v) - vp;
         if (adapt && p >= nst) {   // the trial of order p, formed before this product
             double sa, sb;
@@ -453,7 +484,11 @@ void launch_series_coeffs(const Ctx &c, int n0, int n1, int explicit_, double dm
 
 void launch_series(const SeriesArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_series, dim3((a.N + SR_BEADS - 1) / SR_BEADS), dim3(SR_NT), 0, s, a);
+    if (a.N <= SR_SMALL)
+        hipLaunchKernelGGL((k_series<8, 1, 4>), dim3((a.N + 7) / 8), dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_series<SR_B, SR_WPR, SR_NBW>), dim3((a.N + SR_B - 1) / SR_B),
+                           dim3(64 * SR_B * SR_WPR), 0, s, a);
 }
 
 void launch_series_finish(const SeriesArgs &a, double *pos, double dt4, double *drift, double *noise,

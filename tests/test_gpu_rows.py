@@ -186,3 +186,75 @@ def test_series_on_streams():
         res.append(ps)
     for x, y in zip(*res):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("alone", [False, True])
+@pytest.mark.parametrize("size", [(27, 19), (43, 15), (5, 129), (24, 32), (7, 127), (25, 41), (32, 32)])
+def test_series_of_larger_boxes(size, alone):
+    """As test_series, past the 512 beads of a row in one wave: the edges of the
+    column blocks and of the four rows per workgroup, fixed and adaptive orders,
+    steps with and without products before the series, and with the waits
+    denied the finishing kernel alone."""
+    import ctypes
+    w, pos, a, b = _pair(*size, cheb_keep=140)
+    if alone:
+        rpy._lib.rpy_series_wait(a.handle, ctypes.c_int64(-1))
+    v = _vec(w, 1) * 0.03
+    a.build(pos)
+    b.build(pos)
+    for n in (2, 3, 17, 40):
+        got, want = (c.sqrt_apply(v, n, 0.04, 40.0, want_ef=True) for c in (a, b))
+        _close(got[0], want[0])
+        assert abs(got[1].item() ** 2 - want[1].item() ** 2) < 1e-12
+    for tol, nmax in ((1e-2, 64), (1e-14, 9)):
+        got, want = (c.sqrt_adaptive(v, 0.04, 40.0, tol, nmax, allow_etol=True) for c in (a, b))
+        assert got[2] == want[2]
+        _close(got[0], want[0])
+    for kw in (dict(n_cheb=20, d_min=0.04, d_max=40.0),
+               dict(n_cheb=20, bounds_rule=rpy.BOUNDS_PAPER, bounds_C=60.0),
+               dict(n_cheb=0, d_min=0.04, d_max=40.0, tol=1e-2, n_max=60)):
+        bp = rpy.make_bd_params(dt=1e-3, **kw)
+        p, q = pos.clone(), pos.clone()
+        for step in range(2):
+            x, y = (c.step(r, bp, seed=3, step=step, want=True) for c, r in ((a, p), (b, q)))
+            _close(x[0], y[0], 1e-11)
+            _close(x[1], y[1], 1e-11)
+        _close(p, q)
+
+
+def test_larger_series_on_streams():
+    """Four contexts, three of them past 512 beads, stepping from four threads on
+    four streams at once, as one after the other; one of them is destroyed and made
+    anew in between."""
+    import threading
+    sizes = [(40, 16), (24, 16), (60, 16), (40, 25)]
+    bp = rpy.make_bd_params(dt=1e-3, n_cheb=20, d_min=0.03, d_max=40.0)
+    streams = [torch.cuda.Stream() for _ in sizes]
+    jobs = [_pair(*z)[:3] for z in sizes]
+    res = []
+    for together in (False, True):
+        ps = [pos.clone() for _, pos, _ in jobs]
+        torch.cuda.synchronize()
+
+        def run(k, sync):
+            for step in range(20):
+                jobs[k][2].step(ps[k], bp, seed=4, step=step, stream=streams[k])
+                if sync:
+                    streams[k].synchronize()
+
+        if together:
+            th = [threading.Thread(target=run, args=(k, False)) for k in range(len(jobs))]
+            for t in th:
+                t.start()
+            for t in th:
+                t.join()
+        else:
+            for k in range(len(jobs)):
+                run(k, True)
+        torch.cuda.synchronize()
+        res.append(ps)
+        w = jobs[0][0]
+        jobs[0][2].close()
+        jobs[0] = (w, jobs[0][1], rpy.context_for(w))
+    for x, y in zip(*res):
+        assert torch.equal(x, y)
