@@ -378,8 +378,8 @@ enum {
     RPY_PROF_BUILD = 1,     /* real-space tile build */
     RPY_PROF_KSPACE = 2,    /* structure-factor reduction */
     RPY_PROF_EPI = 3,       /* reciprocal back-projection + recurrence epilogue */
-    RPY_PROF_OTHER = 4,     /* bd_step's forces + noise (on an internal
-                               second stream, beside the tile build) */
+    RPY_PROF_OTHER = 4,     /* bd_step's wrap, phase tables, spring forces and noise
+                               (one launch) */
     RPY_PROF_SYMV_MULTI = 5, /* packed tile products of 2-4 vectors */
     RPY_PROF_KINDS = 6
 };

@@ -1,46 +1,21 @@
 // rpy_build.hip -- wrapping, Fourier phase tables and the real-space tiles
 // of the diffusion matrix (eq. DF / DFmodified of arXiv:1203.6208).
 #include "rpy_internal.h"
+#include "rpy_prelude.h"
 #include "rpy_pairs.h"
 
 namespace rpy {
 
-// One thread per bead and axis (axis-major): wrapped position rt = L (r/L -
-// floor(r/L)) and the phases e^{i 2 pi j s}, j = 0..nmax (s = r/L wrapped), by
-// bead (etab) and bead-contiguous (axt).  A non-finite coordinate raises
-// flags[0] and is replaced by 0 so that every later kernel still runs on
-// finite data.
-__global__ void k_wrap_tables(int N, double L, int nmax, const double *__restrict__ pos,
-                              double *__restrict__ rt, double *__restrict__ sfr,
-                              double2 *__restrict__ etab, double2 *__restrict__ axt,
-                              int *__restrict__ flags)
+// The tables of one bead, axis and index per thread (wrap_entry).
+__global__ void k_wrap_tables(WrapArgs a)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 3 * N) return;
-    const int i = t / N, nu = t - i * N, nm1 = nmax + 1;
-    double r = pos[3 * (size_t)nu + i];
-    if (!isfinite(r)) {
-        atomicOr(flags, 1);
-        r = 0.0;
-    }
-    double s = r / L;
-    s = s - floor(s);
-    rt[3 * (size_t)nu + i] = L * s;
-    sfr[3 * (size_t)nu + i] = s;
-    double2 *tab = etab + ((size_t)3 * nu + i) * nm1;
-    for (int j = 0; j < nm1; ++j) {
-        double sn, cs;
-        sincospi(2.0 * j * s, &sn, &cs);
-        tab[j] = make_double2(cs, sn);
-        axt[(size_t)(i * nm1 + j) * N + nu] = make_double2(cs, sn);
-    }
+    wrap_entry(a, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 void launch_wrap_tables(const Ctx &c, const double *pos, hipStream_t s)
 {
-    const int bs = 128;
-    hipLaunchKernelGGL(k_wrap_tables, dim3((3 * c.N + bs - 1) / bs), dim3(bs), 0, s, c.N, c.L,
-                       c.nmax, pos, c.rt, c.sfr, c.etab, c.axt, c.flags);
+    const int bs = 256, n = wrap_threads(c);
+    hipLaunchKernelGGL(k_wrap_tables, dim3((n + bs - 1) / bs), dim3(bs), 0, s, wrap_args(c, pos));
 }
 
 // Wrapped positions only; a non-finite coordinate raises flags[0] as above.

@@ -46,7 +46,7 @@ struct rpy_ctx {
     uint32_t series_epoch = 1;
     long long series_limit = 1000000;
     int series_dev = -1;      // device whose SeriesGate this context is counted in
-    // bd_step runs the forces and the noise on a second stream (default
+    // bd_step runs the excluded-volume forces on a second stream (default
     // priority) beside the tile build: fork after the wrap, join before the
     // drift product
     hipStream_t side = nullptr;
@@ -1302,9 +1302,7 @@ extern "C" int rpy_u_vjp(rpy_ctx *x, const double *pos, const double *F, const d
     // pairs: x_0 = g, y_0 = F, y_q = V_{q-1}; x_q from the adjoint recurrence
     double *xy = c.xy;
     const int P = n_cheb;
-    launch_copy(xy, g, nv, s);
-    launch_copy(xy + nv, F, nv, s);
-    for (int q = 1; q < P; ++q) launch_copy(xy + (2 * q + 1) * nv, vh + (q - 1) * ps, nv, s);
+    launch_grad_pairs(c, P, g, F, vh, ps, s);
     double *mu[3] = {c.mur, c.mur + nv, c.mur + 2 * nv};
     launch_adj_init(c, P - 1, P - 1 == 1 ? 1.0 : 2.0, g, mu[(P - 1) % 3], xy + 2 * (P - 1) * nv, s);
     for (int p = P - 2; p >= 1; --p) {
@@ -1373,18 +1371,15 @@ extern "C" int rpy_bounds(rpy_ctx *x, int rule, double C, double *d_min, double 
 }
 
 // Springs plus excluded volume; `rt` holds the wrapped positions of `pos`.
-static int forces(rpy_ctx *x, const double *pos, const double *rt, double zstar, double dstar,
-                  double rcut, double *F, hipStream_t s)
+// F += the excluded-volume forces at the wrapped positions rt.
+static void ev_forces(rpy_ctx *x, const double *rt, double zstar, double dstar, double rcut, double *F,
+                      hipStream_t s)
 {
     Ctx &c = x->c;
-    launch_spring_forces(c, pos, F, s);
-    if (zstar > 0) {
-        const int nc = (int)floor(c.L / rcut);
-        c.ncell = nc >= 3 ? (nc > 64 ? 64 : nc) : 0;
-        launch_cell_list(c, rt, rcut, s);
-        launch_ev_forces(c, rt, zstar, dstar, rcut, F, s);
-    }
-    return RPY_OK;
+    const int nc = (int)floor(c.L / rcut);
+    c.ncell = nc >= 3 ? (nc > 64 ? 64 : nc) : 0;
+    launch_cell_list(c, rt, rcut, s);
+    launch_ev_forces(c, rt, zstar, dstar, rcut, F, s);
 }
 
 static int check_ev(const Ctx &c, double zstar, double dstar, double rcut)
@@ -1404,9 +1399,12 @@ extern "C" int rpy_forces(rpy_ctx *x, const double *pos, double zstar, double ds
     int rc = check_ev(x->c, zstar, dstar, rcut);
     if (rc) return rc;
     hipStream_t s = S(stream);
-    // its own wrapped copy: the tables of the built D stay untouched
-    if (zstar > 0) launch_wrap_positions(x->c, pos, x->c.rt_ev, s);
-    forces(x, pos, x->c.rt_ev, zstar, dstar, rcut, out, s);
+    launch_spring_forces(x->c, pos, out, s);
+    if (zstar > 0) {
+        // its own wrapped copy: the tables of the built D stay untouched
+        launch_wrap_positions(x->c, pos, x->c.rt_ev, s);
+        ev_forces(x, x->c.rt_ev, zstar, dstar, rcut, out, s);
+    }
     return check_launch("rpy_forces");
 }
 
@@ -1460,36 +1458,51 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
     if (rc) return rc;
     hipStream_t s = S(stream);
     const size_t nv = (size_t)c.n3;
-    launch_wrap_tables(c, pos, s);
-    ++x->wrap_gen;
+    const int floor_n = adapt ? (bp->n_cheb >= 2 ? bp->n_cheb : 0) : -1;
+    const int nmax = adapt ? bp->n_max : bp->n_cheb;
     // The first Chebyshev product rides with the drift product: one FP64
     // pass over D for [F, U+, (U-,) dW], then the coefficients, then V_1
     // from D.dW; the products from V_1 on take bp->prec.  D.dW in FP64 also
     // makes E_f measure the square root against the FP64 quadratic form.
     double *w = x->F + 2 * nv;
-    // forces and noise on the side stream, beside the build
-    HIP_TRY(hipEventRecord(x->fork, s));
-    HIP_TRY(hipStreamWaitEvent(x->side, x->fork, 0));
-    {
-        ProfScope ps(x, RPY_PROF_OTHER, x->side);
-        forces(x, pos, c.rt, bp->ev_zstar, bp->ev_dstar, bp->ev_rcut, x->F, x->side);
-        if (!dw) launch_noise(w, (int64_t)nv, seed, step, bp->dt, x->side);
-        else launch_copy(w, dw, nv, x->side);
+    PreludeArgs pre{};
+    pre.wrap = wrap_args(c, pos);
+    pre.bpc = c.bpc;
+    pre.dw = dw;
+    pre.w = w;
+    pre.F = x->F;
+    pre.seed = seed;
+    pre.step = step;
+    pre.sdt = sqrt(bp->dt);
+    // an explicit interval's coefficients, where the series kernel will take them
+    const bool coef = c.series && rule == RPY_BOUNDS_EXPLICIT && nmax <= SERIES_ORDERS &&
+                      use_rows(x, 1, nmax, s);
+    if (coef) {
+        const int n0 = adapt ? adapt_first(floor_n, bp->d_min, bp->d_max, nmax) : nmax;
+        pre.coef = series_coef_args(c, n0, 1, bp->d_min, bp->d_max, adapt ? c.adapt : nullptr);
+        pre.ncoef = nmax - n0 + 1;
     }
-    HIP_TRY(hipEventRecord(x->join, x->side));
-    form_tensor(x, bp->tol > 0 ? bp->n_max : bp->n_cheb, s);
-    HIP_TRY(hipStreamWaitEvent(s, x->join, 0));
+    {
+        ProfScope ps(x, RPY_PROF_OTHER, s);
+        launch_prelude(c, pre, s);
+    }
+    ++x->wrap_gen;
+    const bool ev = bp->ev_zstar > 0;
+    if (ev) {   // the excluded-volume forces on the side stream, beside the build
+        HIP_TRY(hipEventRecord(x->fork, s));
+        HIP_TRY(hipStreamWaitEvent(x->side, x->fork, 0));
+        ev_forces(x, c.rt, bp->ev_zstar, bp->ev_dstar, bp->ev_rcut, x->F, x->side);
+        HIP_TRY(hipEventRecord(x->join, x->side));
+    }
+    form_tensor(x, nmax, s);
+    if (ev) HIP_TRY(hipStreamWaitEvent(s, x->join, 0));
     // the drift product: F, then U+ (paper and dilute rules) and U- (dilute),
     // then dW; D.F lands in Y, D.U+ in Y + nv, D.dW last
     const int nb = rule == RPY_BOUNDS_PAPER ? 1 : rule == RPY_BOUNDS_DILUTE ? 2 : 0;
-    const int floor_n = adapt ? (bp->n_cheb >= 2 ? bp->n_cheb : 0) : -1;
-    const int nmax = adapt ? bp->n_max : bp->n_cheb;
     const bool series = by_series(x, 1, nmax);
-    if (series && rule == RPY_BOUNDS_EXPLICIT) {
+    if (coef) {
         // the interval needs no product: drift, series and update in two launches
         AdaptState *st = adapt ? c.adapt : nullptr;
-        launch_series_coeffs(c, adapt ? adapt_first(floor_n, bp->d_min, bp->d_max, nmax) : nmax, nmax,
-                             1, bp->d_min, bp->d_max, st, s);
         SeriesArgs a = series_args(x, w, x->dS, nmax, st, bp->tol);
         a.F = x->F;
         a.want_ef = e_f != nullptr;

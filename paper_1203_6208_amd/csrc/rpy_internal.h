@@ -521,6 +521,19 @@ int hip_error(hipError_t e, const char *what);   // records and returns RPY_EHIP
 
 // ------------------------------------------------------------ launchers
 // build
+struct WrapArgs {
+    int N, nmax;
+    double L;
+    const double *pos;
+    double *rt, *sfr;
+    double2 *etab, *axt;
+    int *flags;
+};
+inline WrapArgs wrap_args(const Ctx &c, const double *pos)
+{
+    return {c.N, c.nmax, c.L, pos, c.rt, c.sfr, c.etab, c.axt, c.flags};
+}
+inline int wrap_threads(const Ctx &c) { return c.n3 * (c.nmax + 1); }
 void launch_wrap_tables(const Ctx &c, const double *pos, hipStream_t s);
 // wrapped positions only (into `rt`), for forces of positions other than D's
 void launch_wrap_positions(const Ctx &c, const double *pos, double *rt, hipStream_t s);
@@ -564,6 +577,13 @@ struct SeriesArgs {
     double *vh;               // for the finishing kernel alone: terms at vh + p ps
     size_t ps;
 };
+struct CoefArgs {
+    int n0, explicit_;
+    double dmin, dmax;
+    double *scal, *ctab;
+    AdaptState *st;
+};
+CoefArgs series_coef_args(const Ctx &c, int n0, int explicit_, double dmin, double dmax, AdaptState *st);
 void launch_series_coeffs(const Ctx &c, int n0, int n1, int explicit_, double dmin, double dmax,
                           AdaptState *st, hipStream_t s);
 void launch_series(const SeriesArgs &a, hipStream_t s);
@@ -654,11 +674,24 @@ void launch_copy(double *dst, const double *src, size_t n, hipStream_t s);
 void launch_adj_init(const Ctx &c, int p, double xs, const double *g, double *mu, double *xq,
                      hipStream_t s);
 void launch_add(double *out, const double *a, const double *b, size_t n, hipStream_t s);
+void launch_grad_pairs(const Ctx &c, int P, const double *g, const double *F, const double *vh,
+                       size_t ps, hipStream_t s);
 void launch_grad_wtiles(const Ctx &c, int nq, hipStream_t s);
 void launch_grad_real(const Ctx &c, hipStream_t s);
 void launch_grad_kspace(const Ctx &c, const double *xy, int nq, int accumulate, hipStream_t s);
 void launch_grad_sum(const Ctx &c, double *gpos, hipStream_t s);
 // step
+struct PreludeArgs {
+    WrapArgs wrap;
+    CoefArgs coef;
+    int ncoef, bwrap, bnoise;   // workgroups of each part (ncoef orders from coef.n0; 0: none)
+    int bpc;
+    const double *dw;           // given dW, or null: noise of (seed, step)
+    double *w, *F;
+    uint64_t seed, step;
+    double sdt;                 // sqrt(dt)
+};
+void launch_prelude(const Ctx &c, PreludeArgs a, hipStream_t s);
 void launch_spring_forces(const Ctx &c, const double *pos, double *F, hipStream_t s);
 void launch_cell_list(const Ctx &c, const double *rt, double rcut, hipStream_t s);
 void launch_cell_list_into(int N, double L, int nc, const double *rt, int *start, int *beads,

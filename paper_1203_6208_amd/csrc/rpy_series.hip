@@ -23,6 +23,7 @@
 // kernel, one workgroup that waits for nobody, then runs the series alone.
 #include "rpy_internal.h"
 #include "rpy_pairs.h"
+#include "rpy_prelude.h"
 
 namespace rpy {
 
@@ -431,55 +432,18 @@ __global__ __launch_bounds__(SF_NT) void k_series_finish(SeriesArgs a, double *p
     }
 }
 
-// The interval and, per workgroup, the coefficients of one order: n0 +
-// blockIdx.x into ctab[order][SERIES_ORDERS].  explicit_: [dmin, dmax] given,
-// and workgroup 0 writes the scalars and, with st, the adaptive state (as
-// k_cheb_coeffs); otherwise both are there already.
-__global__ __launch_bounds__(256) void k_series_coeffs(int n0, int explicit_, double dmin, double dmax,
-                                                       double *__restrict__ scal,
-                                                       double *__restrict__ ctab,
-                                                       AdaptState *__restrict__ st, int n_start)
+__global__ __launch_bounds__(256) void k_series_coeffs(CoefArgs a) { series_coeffs_order(a, blockIdx.x); }
+
+CoefArgs series_coef_args(const Ctx &c, int n0, int explicit_, double dmin, double dmax, AdaptState *st)
 {
-    const double lo = explicit_ ? dmin : scal[0], hi = explicit_ ? dmax : scal[1];
-    const int n = n0 + blockIdx.x;
-    if (explicit_ && blockIdx.x == 0 && threadIdx.x == 0) {
-        scal[0] = lo;
-        scal[1] = hi;
-        scal[2] = 2.0 / (hi - lo);
-        scal[3] = (hi + lo) / (hi - lo);
-        if (st) {
-            st->done = 0;
-            st->n_used = 0;
-            st->n_start = n_start;
-            st->last_etol = 0;
-        }
-    }
-    const double h = 0.5 * (hi - lo), mid = 0.5 * (hi + lo);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    double f[2];   // sqrt at the nodes of this lane
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int j = 1 + lane + 64 * k;
-        f[k] = j <= n ? sqrt(h * cospi((j - 0.5) / n) + mid) : 0.0;
-    }
-    for (int p = w; p < n; p += 4) {
-        double s = 0.0;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int j = 1 + lane + 64 * k;
-            if (j <= n) s += f[k] * cospi(p * ((j - 0.5) / n));
-        }
-#pragma unroll
-        for (int x = 32; x >= 1; x >>= 1) s += __shfl_xor(s, x);
-        if (lane == 0) ctab[(size_t)n * SERIES_ORDERS + p] = 2.0 * s / n;
-    }
+    return CoefArgs{n0, explicit_, dmin, dmax, c.scal, c.series_coef, st};
 }
 
 void launch_series_coeffs(const Ctx &c, int n0, int n1, int explicit_, double dmin, double dmax,
                           AdaptState *st, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_series_coeffs, dim3(n1 - n0 + 1), dim3(256), 0, s, n0, explicit_, dmin, dmax,
-                       c.scal, c.series_coef, st, n0);
+    hipLaunchKernelGGL(k_series_coeffs, dim3(n1 - n0 + 1), dim3(256), 0, s,
+                       series_coef_args(c, n0, explicit_, dmin, dmax, st));
 }
 
 void launch_series(const SeriesArgs &a, hipStream_t s)
