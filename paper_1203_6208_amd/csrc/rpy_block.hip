@@ -44,7 +44,7 @@ typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 
 constexpr int SF_WAVES = 4;    // waves per structure-factor workgroup
-constexpr int SF_U = 16;       // unrolled steps per block (quads per wave at N = 4000)
+constexpr int SF_U[2] = {8, 16};   // unrolled steps per block: quads per wave up to N = 2048, above
 constexpr int SF_PF = 3;       // steps loaded ahead
 constexpr int EPI_U = 10;      // the same for the back-projection (two blocks at 618 k)
 constexpr int EPI_PF = 3;
@@ -202,8 +202,10 @@ template <typename T> struct alignas(32) BlkLds {
 // tile go to bpart[K][row][j] (K = J, rows of I for the row product; K = I,
 // rows of J for the column product), every (K, row) written by exactly one
 // tile.
+// FP32: at most 128 VGPRs, two workgroups per compute unit (132 leave one: 64.4
+// against 60.0 us at N = 4000).
 template <typename T, bool CACHED>
-__global__ __launch_bounds__(64 * BK<T>::NWAVE) void k_block_tiles(int ntiles, int npad, int n3pad,
+__global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1, 8))) void k_block_tiles(int ntiles, int npad, int n3pad,
                                                      const int2 *__restrict__ tile_ij,
                                                      const T *tiles,
                                                      const typename BK<T>::x_t *__restrict__ xs,
@@ -225,9 +227,34 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) void k_block_tiles(int ntiles, i
     const int n = lane & 15, g = lane >> 4;
     const int row = 16 * rg + n;   // this lane's bead row of a plane stripe (column of P^T)
     const int step = gridDim.x;
+    // The vectors of J (row product), then of I (column product), in pieces of 16
+    // bytes, loaded during the previous tile: N = 2000 FP64 48.8 -> 45.3 us, BF16 17.4 -> 15.4.
+    // FP32 tiles load them at the tile's start: their registers would cost the second
+    // workgroup of a compute unit (N = 4000: 62 -> 68 us).
+    constexpr bool XAHEAD = sizeof(T) != 4;
+    constexpr int NC = BlkLds<T>::XW * (int)sizeof(X) / 16, NX = 2 * NC / (64 * NW);
+    static_assert(2 * NC % (64 * NW) == 0, "whole pieces per thread");
+    u4v xr[NX];
+    auto fetch_x = [&](int2 ij) {
+#pragma unroll
+        for (int u = 0; u < NX; ++u) {
+            const int q = threadIdx.x + 64 * NW * u, B = q < NC ? ij.y : ij.x, r = q < NC ? q : q - NC;
+            size_t o;   // entry
+            if constexpr (BF) {
+                constexpr int PR = TB / 8;   // pieces per vector and component
+                const int hl = r / (48 * PR), cj = r / PR % 48;
+                o = ((size_t)hl * 48 + cj) * npad + (size_t)B * TB + 8 * (r % PR);
+            } else {
+                constexpr int PC = TB * BLOCK_RHS * (int)sizeof(X) / 16;   // pieces per component
+                o = ((size_t)(r / PC) * npad + (size_t)B * TB) * BLOCK_RHS + 16 / sizeof(X) * (r % PC);
+            }
+            xr[u] = *reinterpret_cast<const u4v *>(xs + o);
+        }
+    };
     Stripe<T> ring[3];
     int t = blockIdx.x;
     if (t < ntiles) {
+        if (XAHEAD) fetch_x(tile_ij[t]);
         load_stripe<T, CACHED>(tiles, t, 0, row, g, h, ring[0]);
         load_stripe<T, CACHED>(tiles, t, 1, row, g, h, ring[1]);
     }
@@ -235,34 +262,25 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) void k_block_tiles(int ntiles, i
         const int2 ij = tile_ij[t];
         const int I = ij.x, J = ij.y;
         const bool offd = I != J;
+        if (!XAHEAD) fetch_x(ij);
         __syncthreads();   // the previous tile's readers of L are done
-        // stage the vectors of J (row product) and I (column product)
-        if constexpr (BF) {
-            const X *xh = xs, *xl = xs + (size_t)3 * npad * BLOCK_RHS;
-            for (int e = threadIdx.x; e < 2 * XN; e += 64 * NW) {
-                const int hl = e / XN, r = e % XN, cj = r / TB, bead = r % TB;
-                const size_t o = (size_t)cj * npad + bead;
-                L.xj[e] = (hl ? xl : xh)[o + (size_t)J * TB];
-                L.xi[e] = (hl ? xl : xh)[o + (size_t)I * TB];
-            }
-        } else {
-            for (int e = threadIdx.x; e < XN; e += 64 * NW) {
-                const int c = e / (TB * BLOCK_RHS), r = e % (TB * BLOCK_RHS);
-                const size_t o = (size_t)c * npad * BLOCK_RHS + r;
-                L.xj[e] = xs[o + (size_t)J * TB * BLOCK_RHS];
-                L.xi[e] = xs[o + (size_t)I * TB * BLOCK_RHS];
-            }
+#pragma unroll
+        for (int u = 0; u < NX; ++u) {
+            const int q = threadIdx.x + 64 * NW * u;
+            reinterpret_cast<u4v *>(q < NC ? L.xj : L.xi)[q < NC ? q : q - NC] = xr[u];
         }
         A dacc[3], tacc[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) dacc[a] = tacc[a] = A{};
         __syncthreads();
-        const int tn = t + step;   // the tile whose first planes are loaded at the end
+        const int tn = t + step;   // the tile whose vectors and first planes are loaded meanwhile
+        const int2 ijn = tile_ij[min(tn, ntiles - 1)];
 #pragma unroll
         for (int c = 0; c < 6; ++c) {
             // two planes ahead; planes 4 and 5 fetch planes 0 and 1 of the next tile
             if (c + 2 < 6) load_stripe<T, CACHED>(tiles, t, c + 2, row, g, h, ring[(c + 2) % 3]);
             else if (tn < ntiles) load_stripe<T, CACHED>(tiles, tn, c - 4, row, g, h, ring[(c + 2) % 3]);
+            if (XAHEAD && c == 2 && tn < ntiles) fetch_x(ijn);
             __asm__ volatile("" ::: "memory");
             const Stripe<T> &st = ring[c % 3];
             const int a = plane_a(c), b = plane_b(c);
@@ -535,7 +553,8 @@ __device__ inline void block_part_sum(int b, int n3, int n3pad, int m, int nslot
     ypart[(size_t)j * n3 + row] = y;
 }
 
-__global__ __launch_bounds__(256) void k_block_sf(int nk, int nk16, int nq, int cq, int nkb,
+template <int U>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(U > 8 ? 4 : 3, 8))) void k_block_sf(int nk, int nk16, int nq, int cq, int nkb,
                                                   int N, int n3, int n3pad, int m, int nslot,
                                                   const double2 *eph, const double *vpk,
                                                   double *sfpart,
@@ -587,23 +606,25 @@ __global__ __launch_bounds__(256) void k_block_sf(int nk, int nk16, int nq, int 
         acc[5] = __builtin_amdgcn_mfma_f64_16x16x4f64(sn, d.x[2], acc[5], 0, 0, 0);
     };
     constexpr int S = SF_WAVES;
-    // Blocks of SF_U steps, each fully unrolled: the prefetches stay inside
+    // Blocks of U steps (a step past the last is loaded and multiplied by zero:
+    // 8 where a wave has no more, 16 beyond; N = 2000 21.3 against 27.2 us with 16,
+    // N = 4000 30.9 with 8 against 30.1), each fully unrolled: the prefetches stay inside
     // a block, so no load is in flight across a loop back edge (the
     // compiler then waits for all of them at the loop head) and every wait
     // leaves the next SF_PF steps' loads outstanding.
     const int qa = q0 + w;
     const int nsteps = q1 > qa ? (q1 - qa + S - 1) / S : 0;
-    for (int t0 = 0; t0 < nsteps; t0 += SF_U) {
+    for (int t0 = 0; t0 < nsteps; t0 += U) {
         const int qb = qa + t0 * S;
         SfLd b[SF_PF + 1];
 #pragma unroll
         for (int t = 0; t < SF_PF; ++t) fetch(qb + t * S, b[t]);
 #pragma unroll
-        for (int t = 0; t < SF_U; ++t) {
+        for (int t = 0; t < U; ++t) {
             // compiler-only barrier: keeps each prefetch where it is written
             // (the loaded values are otherwise forwarded and the loads
             // re-issued where they are consumed)
-            if (t + SF_PF < SF_U) fetch(qb + (t + SF_PF) * S, b[(t + SF_PF) % (SF_PF + 1)]);
+            if (t + SF_PF < U) fetch(qb + (t + SF_PF) * S, b[(t + SF_PF) % (SF_PF + 1)]);
             __asm__ volatile("" ::: "memory");
             use(b[t % (SF_PF + 1)], qb + t * S);
         }
@@ -643,12 +664,19 @@ __global__ void k_block_sf_reduce(int nk, int nch, const KCoef *__restrict__ kco
     const int j = q2 >> 1, half = q2 & 1;
     const size_t cst = (size_t)6 * BLOCK_RHS * 16;
     const double *src = sfpart + (size_t)kb * nch * cst + (6 * j + 3 * half) * 16 + kk;
+    // all chunks (at most 16) loaded at once: a chunk past the last re-reads it
+    // and is left out
+    double v[BLOCK_CHUNKS][3];
+#pragma unroll
+    for (int ch = 0; ch < BLOCK_CHUNKS; ++ch)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) v[ch][c] = src[min(ch, nch - 1) * cst + 16 * c];
     double t0 = 0.0, t1 = 0.0, t2 = 0.0;
-#pragma unroll 4
-    for (int ch = 0; ch < nch; ++ch) {
-        t0 += src[ch * cst];
-        t1 += src[ch * cst + 16];
-        t2 += src[ch * cst + 32];
+#pragma unroll
+    for (int ch = 0; ch < BLOCK_CHUNKS; ++ch) {
+        t0 += ch < nch ? v[ch][0] : 0.0;
+        t1 += ch < nch ? v[ch][1] : 0.0;
+        t2 += ch < nch ? v[ch][2] : 0.0;
     }
     const KCoef kc = kcoef[k];
     const double h = kc.hx * t0 + kc.hy * t1 + kc.hz * t2;
@@ -667,31 +695,42 @@ void launch_block_sf(const Ctx &c, int m, int prec, hipStream_t s)
     // workgroups per grid row (npg = groups of 16 rows)
     const int npg = (c.n3 + 15) / 16;
     const int px = (npg + c.nchb - 1) / c.nchb;
-    hipLaunchKernelGGL(k_block_sf, dim3(nkb + px, c.nchb), dim3(64 * SF_WAVES), 0, s, c.nk,
-                       (c.nk + 15) / 16 * 16, nq, cq, nkb, c.N, c.n3, c.n3pad, m, c.nbt, c.eph,
-                       c.vpk, c.sfpart, (const void *)c.bpart, prec == RPY_PREC_F64 ? 1 : 0,
-                       c.ypart, c.gate);
+#define RPY_BSF(U)                                                                              \
+    hipLaunchKernelGGL(k_block_sf<U>, dim3(nkb + px, c.nchb), dim3(64 * SF_WAVES), 0, s, c.nk,  \
+                       (c.nk + 15) / 16 * 16, nq, cq, nkb, c.N, c.n3, c.n3pad, m, c.nbt, c.eph, \
+                       c.vpk, c.sfpart, (const void *)c.bpart, prec == RPY_PREC_F64 ? 1 : 0,    \
+                       c.ypart, c.gate)
+    if (cq <= SF_U[0] * SF_WAVES) RPY_BSF(SF_U[0]);
+    else RPY_BSF(SF_U[1]);
+#undef RPY_BSF
     const int nt = (c.nk + 15) / 16 * 2 * BLOCK_RHS * 16;
     hipLaunchKernelGGL(k_block_sf_reduce, dim3((nt + 255) / 256), dim3(256), 0, s, c.nk, c.nchb,
                        c.kcoef, c.sfpart, c.tkm, c.gate);
 }
 
 // ------------------------------ back-projection + partial sum + epilogue
-// Workgroup: 16 beads nu0 .. nu0 + 15, EPI_W waves; wave w takes the
+// Workgroup: 16 beads nu0 .. nu0 + 15 and NC of the components, EPI_W waves; wave w takes the
 // wave-vector steps w, w + EPI_W, ... (4 wave vectors each).  Lane (g, i)
 // holds the phase of bead nu0 + i and k = 4 step + g (A operand: row =
 // bead, inner = k) and T[k][3 half + c][j = i] (B operand; tkm rows >= nk are
-// zero), loaded EPI_PF steps ahead; six FP64 MFMAs per step add
-//   sum_k cos(k.r) Tc + sin(k.r) Ts,  c = 0..2.
+// zero), loaded EPI_PF steps ahead; 2 NC FP64 MFMAs per step add
+//   sum_k cos(k.r) Tc + sin(k.r) Ts,  c of the workgroup.
 // The waves are summed in a fixed order in LDS; thread (j, bead) adds the
 // summed tile partials ypart and applies the epilogue of f.mode (as in
 // k_kspace_epi); with f.pack it also writes V_p in the packed layouts, so the
 // next product of the series needs no packing launch.
+// NC = 1 while three components per workgroup would leave most compute units without one
+// (the three of the same beads then on the same XCD, which reads their phases once): N = 500
+// 10.0 against 14.8 us, N = 2000 14.4 against 15.0, N = 4000 19 against 16.
+// Forming the phases from the axis tables instead of reading the stored
+// matrix (as in the structure factors) loses: 16.6 and 18.2 us at N = 2000 and 4000.
 constexpr int EPI_W = 8;
-struct EpiLd {
+constexpr int EPI_SPLIT_MAX = 2048;
+template <int NC> struct EpiLd {
     double2 e;
-    double t[6];
+    double t[2 * NC];
 };
+template <int NC>
 __global__ __launch_bounds__(64 * EPI_W) void k_block_epi(int N, int n3, int nk4, int nk16,
                                                           const double2 *eph, const double *tkm,
                                                           const double *__restrict__ ypart,
@@ -700,45 +739,64 @@ __global__ __launch_bounds__(64 * EPI_W) void k_block_epi(int N, int n3, int nk4
                                                           double *__restrict__ vpk,
                                                           const int *__restrict__ gate)
 {
-    __shared__ double red[EPI_W][3][16][17];
+    __shared__ double red[EPI_W][NC][16][17];
     if (gate && *gate) return;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int i = lane & 15, g = lane >> 4;
-    const int nu0 = blockIdx.x * 16;
+    int c0 = 0, blk = blockIdx.x;
+    if constexpr (NC == 1) {
+        c0 = (blk >> 3) % 3;
+        blk = 8 * (blk / 24) + (blk & 7);
+    }
+    const int nu0 = 16 * blk;
+    if (nu0 >= N) return;
+    // the epilogue's operands (one bead and vector per thread) and the tile sums
+    const int j = threadIdx.x >> 4, bl = threadIdx.x & 15, bead = nu0 + bl;
+    const bool eth = threadIdx.x < 256 && bead < N && j < f.m;
+    const size_t o = (size_t)j * n3 + 3 * bead + c0;
+    double yt[NC], pv[NC], pv2[NC], pa[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        yt[c] = eth ? ypart[o + c] : 0.0;
+        pv[c] = eth && f.mode != EPI_APPLY ? f.vprev[o + c] : 0.0;
+        pv2[c] = eth && f.mode == EPI_CHEB_NEXT ? f.vprev2[o + c] : 0.0;
+        pa[c] = eth && f.mode == EPI_CHEB_NEXT ? f.acc[o + c] : 0.0;
+    }
     // dead lanes read a zero entry of the last quad (phases of mu >= N are 0)
     const int nus = min(nu0 + i, ((N + 3) / 4) * 4 - 1);
     const double2 *ep = eph + (size_t)(nus >> 2) * nk16 * 4 + (nus & 3);
-    d4v acc[3];
+    d4v acc[2 * NC];   // the cos products, then the sin products: no MFMA waits on the one just issued
 #pragma unroll
-    for (int c = 0; c < 3; ++c) acc[c] = d4v{0.0, 0.0, 0.0, 0.0};
+    for (int q = 0; q < 2 * NC; ++q) acc[q] = d4v{0.0, 0.0, 0.0, 0.0};
     const int nst = nk4 / 4;
     // Branch-free (see k_block_sf): a step past the end is loaded from a
     // valid row and consumes a zero phase; phases of k >= nk are zero.
-    auto fetch = [&](int st, EpiLd &d) {
+    auto fetch = [&](int st, EpiLd<NC> &d) {
         const int k = 4 * min(st, nst - 1) + g;
         d.e = ep[(size_t)k * 4];
-        const double *tr = tkm + (size_t)k * 6 * BLOCK_RHS + i;
+        const double *tr = tkm + ((size_t)k * 6 + c0) * BLOCK_RHS + i;
 #pragma unroll
-        for (int q = 0; q < 6; ++q) d.t[q] = tr[q * BLOCK_RHS];
+        for (int c = 0; c < NC; ++c) {
+            d.t[c] = tr[c * BLOCK_RHS];
+            d.t[NC + c] = tr[(3 + c) * BLOCK_RHS];
+        }
     };
-    auto use = [&](const EpiLd &d, int st) {
+    auto use = [&](const EpiLd<NC> &d, int st) {
         const bool on = st < nst;
-        const double c = on ? d.e.x : 0.0, sn = on ? d.e.y : 0.0;
-        // the three cos products, then the three sin products: no MFMA waits
-        // on the one just issued
+        const double cs = on ? d.e.x : 0.0, sn = on ? d.e.y : 0.0;
 #pragma unroll
-        for (int cc = 0; cc < 3; ++cc)
-            acc[cc] = __builtin_amdgcn_mfma_f64_16x16x4f64(c, d.t[cc], acc[cc], 0, 0, 0);
+        for (int c = 0; c < NC; ++c)
+            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(cs, d.t[c], acc[c], 0, 0, 0);
 #pragma unroll
-        for (int cc = 0; cc < 3; ++cc)
-            acc[cc] = __builtin_amdgcn_mfma_f64_16x16x4f64(sn, d.t[3 + cc], acc[cc], 0, 0, 0);
+        for (int c = 0; c < NC; ++c)
+            acc[NC + c] = __builtin_amdgcn_mfma_f64_16x16x4f64(sn, d.t[NC + c], acc[NC + c], 0, 0, 0);
     };
     constexpr int S = EPI_W;
     // blocks of EPI_U fully unrolled steps, as in k_block_sf
     const int nsteps = (nst - w + S - 1) / S;
     for (int t0 = 0; t0 < nsteps; t0 += EPI_U) {
         const int sb = w + t0 * S;
-        EpiLd b[EPI_PF + 1];
+        EpiLd<NC> b[EPI_PF + 1];
 #pragma unroll
         for (int t = 0; t < EPI_PF; ++t) fetch(sb + t * S, b[t]);
 #pragma unroll
@@ -750,45 +808,44 @@ __global__ __launch_bounds__(64 * EPI_W) void k_block_epi(int N, int n3, int nk4
     }
     // FP64 MFMA output: lane holds beads g + 4e of vector i
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) red[w][c][g + 4 * e][i] = acc[c][e];
+        for (int e = 0; e < 4; ++e) red[w][c][g + 4 * e][i] = acc[c][e] + acc[NC + c][e];
     __syncthreads();
-    if (threadIdx.x >= 256) return;
-    const int j = threadIdx.x >> 4, bl = threadIdx.x & 15;
-    const int bead = nu0 + bl;
-    if (bead >= N || j >= f.m) return;
+    if (!eth) return;
     const double ya = f.scal ? f.scal[2] : 0.0, yb = f.scal ? f.scal[3] : 0.0;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
+    for (int c = 0; c < NC; ++c) {
         double yk = 0.0;
 #pragma unroll
         for (int ww = 0; ww < EPI_W; ++ww) yk += red[ww][c][bl][j];
-        const size_t o = (size_t)j * n3 + 3 * bead + c;
-        const double yy = yk + ypart[o];
+        const double yy = yk + yt[c];
         if (f.mode == EPI_APPLY) {
-            f.vout[o] = yy;
+            f.vout[o + c] = yy;
         } else if (f.mode == EPI_CHEB_FIRST) {
-            const double v0 = f.vprev[o];
-            const double v1 = ya * yy - yb * v0;
-            f.vout[o] = v1;
-            f.acc[o] = 0.5 * f.scal[8] * v0 + f.scal[9] * v1;
-            if (f.dv) f.dv[o] = yy;
-            if (f.pack) pack_entry(f.pack_prec, npad, bead, c, j, v1, xs, vpk);
+            const double v1 = ya * yy - yb * pv[c];
+            f.vout[o + c] = v1;
+            f.acc[o + c] = 0.5 * f.scal[8] * pv[c] + f.scal[9] * v1;
+            if (f.dv) f.dv[o + c] = yy;
+            if (f.pack) pack_entry(f.pack_prec, npad, bead, c0 + c, j, v1, xs, vpk);
         } else {
-            const double vp = 2.0 * (ya * yy - yb * f.vprev[o]) - f.vprev2[o];
-            f.vout[o] = vp;
-            f.acc[o] += f.scal[8 + f.p] * vp;
-            if (f.pack) pack_entry(f.pack_prec, npad, bead, c, j, vp, xs, vpk);
+            const double vp = 2.0 * (ya * yy - yb * pv[c]) - pv2[c];
+            f.vout[o + c] = vp;
+            f.acc[o + c] = pa[c] + f.scal[8 + f.p] * vp;
+            if (f.pack) pack_entry(f.pack_prec, npad, bead, c0 + c, j, vp, xs, vpk);
         }
     }
 }
 
 void launch_block_epi(const Ctx &c, const EpiArgs &f, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_block_epi, dim3((c.N + 15) / 16), dim3(64 * EPI_W), 0, s, c.N, c.n3,
-                       c.nk4, (c.nk + 15) / 16 * 16, c.eph, c.tkm, c.ypart, f, c.nbt * TB, c.xpk,
-                       c.vpk, c.gate);
+#define RPY_BEPI(NC, G)                                                                       \
+    hipLaunchKernelGGL(k_block_epi<NC>, dim3(G), dim3(64 * EPI_W), 0, s, c.N, c.n3, c.nk4,      \
+                       (c.nk + 15) / 16 * 16, c.eph, c.tkm, c.ypart, f, c.nbt * TB, c.xpk,      \
+                       c.vpk, c.gate)
+    if (c.N <= EPI_SPLIT_MAX) RPY_BEPI(1, (c.N + 127) / 128 * 24);
+    else RPY_BEPI(3, (c.N + 15) / 16);
+#undef RPY_BEPI
 }
 
 }  // namespace rpy

@@ -505,7 +505,7 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
         }
     }
     c.fold = c.nk > FOLD_MIN_NK;
-    c.nchb = c.nsfc < 16 ? c.nsfc : 16;
+    c.nchb = c.nsfc < BLOCK_CHUNKS ? c.nsfc : BLOCK_CHUNKS;
 
     std::vector<int2> tij;
     for (int I = 0; I < c.nbt; ++I)

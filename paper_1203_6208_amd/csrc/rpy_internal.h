@@ -633,6 +633,7 @@ void launch_block_sf(const Ctx &c, int m, int prec, hipStream_t s);
 void launch_block_epi(const Ctx &c, const EpiArgs &f, hipStream_t s);
 constexpr int BLOCK_MIN_RHS = 5;   // products with at least this many vectors use it
 constexpr int BLOCK_RHS = 16;
+constexpr int BLOCK_CHUNKS = 16;   // bead chunks of the structure factors at most
 // T_k of m vectors into tk (a launch of its own, for the low-memory form and
 // the reverse mode; the tile products carry theirs)
 void launch_sf(const Ctx &c, const double *v, int m, int fold, hipStream_t s);

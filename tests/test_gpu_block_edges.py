@@ -1,0 +1,35 @@
+"""Edges of the block product's launches (5 to 16 vectors)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover - CPU container
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_1203_6208_amd import inputs, rpy  # noqa: E402
+
+
+def _cuda(x):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.float64)).cuda()
+
+
+@pytest.mark.parametrize("size", [(1, 17), (1, 127), (3, 43), (1, 257), (32, 64), (3, 683), (41, 51)])
+@pytest.mark.parametrize("m", [5, 16])
+def test_block_edges(size, m):
+    """FP64 block products and a short series at bead counts around the groups of
+    beads, chunks and workgroups of the reciprocal sum (one component per
+    workgroup up to 2048 beads, three above; 8 or 16 quads per wave), against
+    the vector-unit path four vectors at a time: both agree with the oracle to
+    1e-12 of the largest entry."""
+    w = inputs.Workload("bedge", *size, 1.0, seed=55)
+    pos = _cuda(w.positions())
+    a, b = (rpy.context_for(w, lowp="bf16", max_rhs=r) for r in (16, 4))
+    a.build(pos)
+    b.build(pos)
+    v = _cuda(np.random.default_rng(8).standard_normal((m, w.n, 3)))
+    for f in (lambda c, x: c.apply(x), lambda c, x: c.sqrt_apply(x, 6, 0.05, 12.0)):
+        got = f(a, v)
+        want = torch.cat([f(b, v[j:j + 4]) for j in range(0, m, 4)])
+        assert (got - want).abs().max().item() <= 1e-12 * want.abs().max().item()
