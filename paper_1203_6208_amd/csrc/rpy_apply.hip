@@ -19,22 +19,6 @@ namespace rpy {
     }
 
 // ------------------------------------------------------------------ SYMV
-// Sums over 16 lanes, in a fixed order: lane q receives that of component
-// min(q & 3, 2).  Two exchanges that halve the components, then two rotations, all
-// on the vector unit: four shuffles per component through LDS instead take
-// 50.3 against 44.6 us for three FP64 vectors at N = 2000, 18.4 against 16.6 us for
-// one on FP32 tiles.
-__device__ inline double sum16x3(double r0, double r1, double r2, int q)
-{
-    const bool b0 = q & 1, b1 = q & 2;
-    const double a = (b0 ? r1 : r0) + dpp<DPP_XOR1>(b0 ? r0 : r1);
-    const double b = r2 + dpp<DPP_XOR1>(r2);
-    double r = (b1 ? b : a) + dpp<DPP_XOR2>(b1 ? a : b);
-    r += dpp<DPP_ROR4>(r);
-    r += dpp<DPP_ROR8>(r);
-    return r;
-}
-
 // Loads of a packed plane row (64 values of one bead row and one entry of
 // the 3 x 3 blocks): lane q (0..15) of a 16-lane row group owns the bead
 // columns col(q, e), e = 0..3, read with 16-byte (FP64, FP32) or 8-byte

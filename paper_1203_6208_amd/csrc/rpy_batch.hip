@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "rpy_internal.h"
+#include "rpy_sf.h"
 #include "rpy_pairs.h"
 
 namespace rpy {
@@ -388,13 +389,12 @@ __global__ __launch_bounds__(256) void k_bsymv(int G3, int nsf, int sfr, int nsp
     const int g = lane >> 4, q = lane & 15;
     // The tile's address needs only t: the first bead row's loads go out
     // before the vector loads, which wait on the tile table and the box
-    // record.  With one vector the loop then loads each next row while the
-    // current one is used (three waves per SIMD instead of four; 256 FP32
-    // boxes: 6531 -> 6655 box-steps per second).  Two tiles per workgroup,
+    // record.  The other rows are loaded as they are used, at four waves per SIMD: each
+    // next row loaded while the current one is used takes three, and 33.6 against
+    // 33.3 ms for the step of 256 FP32 boxes.  Two tiles per workgroup,
     // the second one's first row loaded during the first one's column
-    // combine, lost (5899, and 6263 without that load).
+    // combine, lost (5899 against 6531 box-steps per second, and 6263 without that load).
     const T *tile = tiles + (size_t)t * 6 * TBB * TBB;
-    constexpr bool PF = M == 1;
     typename BLd<T, TBB>::raw_t rw[TBB / 16][6];
 #pragma unroll
     for (int c = 0; c < 6; ++c)
@@ -435,17 +435,7 @@ __global__ __launch_bounds__(256) void k_bsymv(int G3, int nsf, int sfr, int nsp
 #pragma unroll
     for (int it = 0; it < TBB / 16; ++it) {
         const int i = 16 * it + 4 * w + g;
-        if constexpr (PF) {
-            if (it + 1 < TBB / 16) {
-#pragma unroll
-                for (int c = 0; c < 6; ++c)
-                    rw[it + 1][c] = BLd<T, TBB>::template raw<CACHED>(
-                        tile + (size_t)(i + 16) * 6 * TBB + c * TBB, q);
-            }
-            // compiler-only barrier: keeps the next row's loads ahead of this
-            // row's arithmetic
-            __asm__ volatile("" ::: "memory");
-        } else if (it > 0) {
+        if (it > 0) {
 #pragma unroll
             for (int c = 0; c < 6; ++c)
                 rw[it][c] = BLd<T, TBB>::template raw<CACHED>(tile + (size_t)i * 6 * TBB + c * TBB, q);
@@ -480,15 +470,8 @@ __global__ __launch_bounds__(256) void k_bsymv(int G3, int nsf, int sfr, int nsp
         }
 #pragma unroll
         for (int j = 0; j < M; ++j) {
-            double r0 = r[j][0], r1 = r[j][1], r2 = r[j][2];
-#pragma unroll
-            for (int o = 8; o >= 1; o >>= 1) {
-                r0 += __shfl_xor(r0, o, 16);
-                r1 += __shfl_xor(r1, o, 16);
-                r2 += __shfl_xor(r2, o, 16);
-            }
-            if (q < 3)
-                part[((size_t)J * BRC + j) * G3 + rowI + 3 * i + q] = q == 0 ? r0 : q == 1 ? r1 : r2;
+            const double s = sum16x3(r[j][0], r[j][1], r[j][2], q);
+            if (q < 3) part[((size_t)J * BRC + j) * G3 + rowI + 3 * i + q] = s;
         }
     }
     if (!offd) return;
