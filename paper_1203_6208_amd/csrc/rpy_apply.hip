@@ -114,7 +114,7 @@ template <typename T> constexpr int symv_nz() { return sizeof(T) == 8 ? 4 : 2; }
 
 template <typename T, int M, bool CACHED, int NW = symv_waves<T, M>()>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(M >= 3 ? 2 : 1, 8))) void k_symv6(int N, int n3, int n3pad, int rhs_cap, int j0,
-                                               int nsf, int flip, int nm1, int fold,
+                                               int nsf, int flip, int hot, int nm1, int fold,
                                                const SfCol *__restrict__ cols,
                                                const KCoef *__restrict__ kcoef,
                                                const double2 *__restrict__ axt,
@@ -139,135 +139,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(M >= 3 
     constexpr bool HOIST = P6<T>::hoist && NW == 4;
     const int ord = bid - nsf;
     const int t = flip ? ntl - 1 - ord : ord;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int g = lane >> 4, q = lane & 15;
-    // BF16 rows of several vectors are small: all four of a lane's rows
-    // are loaded before any arithmetic (more bytes in flight per wave;
-    // 34.1 against 37.4 us at N = 4000 for one vector, before it moved to two
-    // waves).  FP64 rows of one-vector products, and the BF16 rows of the
-    // two-wave form, are loaded one row ahead, each while the previous one
-    // is used (FP64: 67.2 against 69.2 us at N = 4000, at two waves per SIMD
-    // instead of three); FP32 rows and the rows of several vectors one at a
-    // time (hoisting them costs occupancy: FP32 46.9 against 43.8 us).  The
-    // tile's address needs only t, so the first row is loaded before the
-    // vector loads, which wait on the tile's (I, J) (FP32 one-vector steps
-    // 577 -> 582 per second; all four hoisted BF16 rows issued there lose:
-    // 32.2 -> 33.1 us).
-    const T *tile = tiles + (size_t)t * TILE6;
-    typename P6<T>::raw_t rw[NIT][6];
-    constexpr bool PF = !HOIST && M == 1 && (sizeof(T) == 8 || NW < 4);   // rows one ahead
-    if constexpr (!HOIST) {
-#pragma unroll
-        for (int c = 0; c < 6; ++c)
-            rw[0][c] = P6<T>::template raw<CACHED>(tile + (size_t)(4 * w + g) * 6 * TB + c * TB, q);
-    }
-    const int2 ij = tile_ij[t];
-    const int I = ij.x, J = ij.y;
-    // the vector loads of x_I (for LDS) and x_J (registers) all go out
-    // before the first LDS store, which waits for them
-    constexpr int NSX = (M * TS + NT - 1) / NT;
-    double sxv[NSX];
-#pragma unroll
-    for (int u = 0; u < NSX; ++u) {
-        const int e = threadIdx.x + NT * u, j = e / TS, row = I * TS + e % TS;
-        sxv[u] = e < M * TS && row < n3 ? v[(size_t)(j0 + j) * n3 + row] : 0.0;
-    }
-    double xj[M][4][3];
-#pragma unroll
-    for (int j = 0; j < M; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const int col = J * TS + 3 * P6<T>::col(q, e) + c;
-                xj[j][e][c] = col < n3 ? v[(size_t)(j0 + j) * n3 + col] : 0.0;
-            }
-#pragma unroll
-    for (int u = 0; u < NSX; ++u) {
-        const int e = threadIdx.x + NT * u;
-        if (e < M * TS) sx[e / TS][e % TS] = sxv[u];
-    }
-    double cacc[M][4][3];
-#pragma unroll
-    for (int j = 0; j < M; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) cacc[j][e][0] = cacc[j][e][1] = cacc[j][e][2] = 0.0;
-    __syncthreads();
-    const bool offd = I != J;
-    if constexpr (HOIST) {
-#pragma unroll
-        for (int it = 0; it < NIT; ++it)
-#pragma unroll
-            for (int c = 0; c < 6; ++c)
-                rw[it][c] = P6<T>::template raw<CACHED>(
-                    tile + (size_t)(RPI * it + 4 * w + g) * 6 * TB + c * TB, q);
-    }
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int i = RPI * it + 4 * w + g;
-        double b[6][4];
-        if constexpr (PF) {
-            if (it + 1 < NIT) {
-#pragma unroll
-                for (int c = 0; c < 6; ++c)
-                    rw[it + 1][c] = P6<T>::template raw<CACHED>(
-                        tile + (size_t)(i + RPI) * 6 * TB + c * TB, q);
-            }
-            // compiler-only barrier: keeps the next row's loads ahead of this
-            // row's arithmetic
-            __asm__ volatile("" ::: "memory");
-        } else if constexpr (!HOIST) {
-            if (it > 0) {
-#pragma unroll
-                for (int c = 0; c < 6; ++c)
-                    rw[it][c] = P6<T>::template raw<CACHED>(tile + (size_t)i * 6 * TB + c * TB, q);
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < 6; ++c) P6<T>::cvt(rw[it][c], b[c]);
-#pragma unroll
-        for (int j = 0; j < M; ++j) {
-            double r0 = 0.0, r1 = 0.0, r2 = 0.0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const double x0 = xj[j][e][0], x1 = xj[j][e][1], x2 = xj[j][e][2];
-                r0 += b[0][e] * x0 + b[1][e] * x1 + b[2][e] * x2;
-                r1 += b[1][e] * x0 + b[3][e] * x1 + b[4][e] * x2;
-                r2 += b[2][e] * x0 + b[4][e] * x1 + b[5][e] * x2;
-            }
-            const double r = sum16x3(r0, r1, r2, q);
-            if (q < 3) part[((size_t)J * rhs_cap + j0 + j) * n3pad + I * TS + 3 * i + q] = r;
-            if (offd) {
-                const double y0 = sx[j][3 * i], y1 = sx[j][3 * i + 1], y2 = sx[j][3 * i + 2];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    cacc[j][e][0] += b[0][e] * y0 + b[1][e] * y1 + b[2][e] * y2;
-                    cacc[j][e][1] += b[1][e] * y0 + b[3][e] * y1 + b[4][e] * y2;
-                    cacc[j][e][2] += b[2][e] * y0 + b[4][e] * y1 + b[5][e] * y2;
-                }
-            }
-        }
-    }
-    if (!offd) return;
-    // combine the 4 row groups of a wave, then the 4 waves through LDS
-#pragma unroll
-    for (int j = 0; j < M; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                double s = cacc[j][e][c];
-                s += __shfl_xor(s, 16);
-                s += __shfl_xor(s, 32);
-                if (g == 0) scol[w][j][3 * P6<T>::col(q, e) + c] = s;
-            }
-    __syncthreads();
-    for (int e = threadIdx.x; e < M * TS; e += blockDim.x) {
-        const int j = e / TS, cidx = e % TS;
-        double s = scol[0][j][cidx];
-#pragma unroll
-        for (int w2 = 1; w2 < NW; ++w2) s += scol[w2][j][cidx];
-        part[((size_t)I * rhs_cap + j0 + j) * n3pad + J * TS + cidx] = s;
+    if constexpr (CACHED) {
+        constexpr bool HOT = true;
+#include "rpy_symv_tile.inc"
+    } else if (((long)ord + 1) * hot / ntl != (long)ord * hot / ntl) {
+        // one of the `hot` tiles of a larger array, spread evenly over it
+        constexpr bool HOT = true;
+#include "rpy_symv_tile.inc"
+    } else {
+        constexpr bool HOT = false;
+#include "rpy_symv_tile.inc"
     }
 }
 
@@ -286,10 +167,11 @@ static void symv_launch(const Ctx &c, const T *tiles, const double *v, int j0, h
     const size_t lds = symv_lds<T, M>(c);
     // Allocating loads, with the tile order reversed on every other launch,
     // for arrays that fit the Infinity Cache (each product then starts on the
-    // tiles the previous one read last); otherwise non-temporal loads in
-    // stored order, which keep the stream from evicting the rest.
+    // tiles the previous one read last); otherwise stored order, allocating
+    // loads for as many tiles as fit and non-temporal ones, which do not evict them, for the rest.
     const size_t bytes = (size_t)c.ntiles * TILE6 * sizeof(T);
     const bool cached = bytes <= TILE_CACHE_BYTES;
+    const int hot = cached || !own_tiles<T>(c) ? 0 : (int)(TILE_CACHE_BYTES / (TILE6 * sizeof(T)));
     const int flip = cached ? (int)(c.symv_calls++ & 1u) : 0;
     // when profiled, the dispatch itself records the start and end events,
     // so that they time the kernel alone (null events: a plain launch)
@@ -298,12 +180,12 @@ static void symv_launch(const Ctx &c, const T *tiles, const double *v, int j0, h
     if (cached)
         hipExtLaunchKernelGGL((k_symv6<T, M, true>), dim3(nsf + c.ntiles), dim3(64 * symv_waves<T, M>()),
                               (uint32_t)lds, s, e0, e1, 0u, c.N, c.n3, c.n3pad, c.rhs_cap, j0, nsf,
-                              flip, c.nmax + 1, c.fold, cols.d, c.kcoef, c.axt, c.fold ? c.tkf : c.tk, c.tile_ij,
+                              flip, hot, c.nmax + 1, c.fold, cols.d, c.kcoef, c.axt, c.fold ? c.tkf : c.tk, c.tile_ij,
                               tiles, v, c.part, c.gate);
     else
         hipExtLaunchKernelGGL((k_symv6<T, M, false>), dim3(nsf + c.ntiles), dim3(64 * symv_waves<T, M>()),
                               (uint32_t)lds, s, e0, e1, 0u, c.N, c.n3, c.n3pad, c.rhs_cap, j0, nsf,
-                              flip, c.nmax + 1, c.fold, cols.d, c.kcoef, c.axt, c.fold ? c.tkf : c.tk, c.tile_ij,
+                              flip, hot, c.nmax + 1, c.fold, cols.d, c.kcoef, c.axt, c.fold ? c.tkf : c.tk, c.tile_ij,
                               tiles, v, c.part, c.gate);
 }
 

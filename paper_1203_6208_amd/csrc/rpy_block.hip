@@ -33,6 +33,8 @@
 // only D is rounded) for BF16 tiles.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "rpy_internal.h"
 
 namespace rpy {
@@ -205,7 +207,7 @@ template <typename T> struct alignas(32) BlkLds {
 // FP32: at most 128 VGPRs, two workgroups per compute unit (132 leave one: 64.4
 // against 60.0 us at N = 4000).
 template <typename T, bool CACHED>
-__global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1, 8))) void k_block_tiles(int ntiles, int npad, int n3pad,
+__global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1, 8))) void k_block_tiles(int ntiles, int hot, int npad, int n3pad,
                                                      const int2 *__restrict__ tile_ij,
                                                      const T *tiles,
                                                      const typename BK<T>::x_t *__restrict__ xs,
@@ -251,12 +253,14 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_
             xr[u] = *reinterpret_cast<const u4v *>(xs + o);
         }
     };
+    auto tile_products = [&](auto hot_tiles) {
+    constexpr bool HOT = decltype(hot_tiles)::value;
     Stripe<T> ring[3];
     int t = blockIdx.x;
     if (t < ntiles) {
         if (XAHEAD) fetch_x(tile_ij[t]);
-        load_stripe<T, CACHED>(tiles, t, 0, row, g, h, ring[0]);
-        load_stripe<T, CACHED>(tiles, t, 1, row, g, h, ring[1]);
+        load_stripe<T, HOT>(tiles, t, 0, row, g, h, ring[0]);
+        load_stripe<T, HOT>(tiles, t, 1, row, g, h, ring[1]);
     }
     for (; t < ntiles; t += step) {
         const int2 ij = tile_ij[t];
@@ -278,8 +282,8 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int c = 0; c < 6; ++c) {
             // two planes ahead; planes 4 and 5 fetch planes 0 and 1 of the next tile
-            if (c + 2 < 6) load_stripe<T, CACHED>(tiles, t, c + 2, row, g, h, ring[(c + 2) % 3]);
-            else if (tn < ntiles) load_stripe<T, CACHED>(tiles, tn, c - 4, row, g, h, ring[(c + 2) % 3]);
+            if (c + 2 < 6) load_stripe<T, HOT>(tiles, t, c + 2, row, g, h, ring[(c + 2) % 3]);
+            else if (tn < ntiles) load_stripe<T, HOT>(tiles, tn, c - 4, row, g, h, ring[(c + 2) % 3]);
             if (XAHEAD && c == 2 && tn < ntiles) fetch_x(ijn);
             __asm__ volatile("" ::: "memory");
             const Stripe<T> &st = ring[c % 3];
@@ -401,6 +405,11 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_
             }
         }
     }
+    };
+    if constexpr (CACHED) tile_products(std::true_type{});
+    // `hot` workgroups of a larger array's, spread evenly over them
+    else if (((int)blockIdx.x + 1) * hot / step != (int)blockIdx.x * hot / step) tile_products(std::true_type{});
+    else tile_products(std::false_type{});
 }
 
 // Tile arrays that fit the Infinity Cache (TILE_CACHE_BYTES) are read with
@@ -435,18 +444,20 @@ static void block_tiles_launch(const Ctx &c, const T *tiles, hipStream_t s)
     const int cap = cached ? block_grid<T, true>(c) : block_grid<T, false>(c);
     const int grid = c.ntiles < cap ? c.ntiles : cap;
     const int npad = c.nbt * TB;
+    // of a larger array the tiles of some workgroups, about as much as the cache holds
+    const int hot = cached || !own_tiles<T>(c) ? 0 : (int)((double)grid * TILE_CACHE_BYTES / ((double)c.ntiles * TILE6 * sizeof(T)));
     typedef typename BK<T>::x_t X;
     typedef typename BK<T>::part_t P;
     hipEvent_t e0 = c.prof_ev0, e1 = c.prof_ev1;
     c.prof_ev0 = c.prof_ev1 = nullptr;
     if (cached)
         hipExtLaunchKernelGGL((block_kernel<T, true>()), dim3(grid), dim3(64 * BK<T>::NWAVE), 0, s, e0, e1, 0u,
-                              c.ntiles, npad, c.n3pad, c.tile_ij, tiles,
+                              c.ntiles, hot, npad, c.n3pad, c.tile_ij, tiles,
                               reinterpret_cast<const X *>(c.xpk), reinterpret_cast<P *>(c.bpart),
                               c.gate);
     else
         hipExtLaunchKernelGGL((block_kernel<T, false>()), dim3(grid), dim3(64 * BK<T>::NWAVE), 0, s, e0, e1, 0u,
-                              c.ntiles, npad, c.n3pad, c.tile_ij, tiles,
+                              c.ntiles, hot, npad, c.n3pad, c.tile_ij, tiles,
                               reinterpret_cast<const X *>(c.xpk), reinterpret_cast<P *>(c.bpart),
                               c.gate);
 }

@@ -34,11 +34,12 @@ constexpr int TILE6 = 6 * TB * TB;   // packed FP64 tile: 6 planes per bead row
 // Tile arrays up to TILE_CACHE_BYTES are read with allocating loads and stay
 // in the 256 MB Infinity Cache from one product to the next (measured at
 // N = 4000: FP32 tiles, 192 MB, 44.1 -> 39.2 us; BF16, 96 MB, 33.9 -> 30.6
-// us).  Larger arrays stream with non-temporal loads in stored order, which
-// keeps the rest of the product's data (partials, vectors, T_k) cached: for
-// the FP64 tiles at N = 4000 (384 MB) allocating loads with the tile order
-// reversed on every other launch read part of the array from the cache, but
-// the step runs faster without them (254.0 against 251.5 steps/s).
+// us).  Of a larger array, tiles of this size, spread evenly over it, are read with
+// allocating loads and are found there by every product, the rest with
+// non-temporal ones, which keep it there (FP64 tiles at N = 4000, 396 MB: one vector
+// 67.9 -> 60.0 us, three 92 -> 82, sixteen 128 -> 122; all allocating, in stored order 75.8, in
+// alternating order 65.8) -- where it is the array of the context's own precision; the
+// FP64 tiles beside an FP32 or BF16 copy, read once per step, leave the cache to the copy.
 constexpr size_t TILE_CACHE_BYTES = (size_t)200 << 20;
 constexpr int NSER = 20;        // terms of the small-r series of S(r)
 constexpr double XSER = 0.75;   // use the series for alpha*r below this
@@ -620,6 +621,10 @@ struct EpiArgs {
     double *ds;            // dS [m][3N]
     double *tpart;
 };
+template <typename T> inline bool own_tiles(const Ctx &c)
+{
+    return c.lowp == (sizeof(T) == 8 ? RPY_PREC_F64 : sizeof(T) == 4 ? RPY_PREC_F32 : RPY_PREC_BF16);
+}
 void launch_symv(const Ctx &c, int prec, const double *v, int j0, int mc, hipStream_t s);
 // Block product D.V for 5 <= m <= 16 vectors (c.block): the tile product on
 // the matrix cores from the packed planes of precision `prec` (FP64 or FP32

@@ -33,3 +33,17 @@ def test_block_edges(size, m):
         got = f(a, v)
         want = torch.cat([f(b, v[j:j + 4]) for j in range(0, m, 4)])
         assert (got - want).abs().max().item() <= 1e-12 * want.abs().max().item()
+
+
+def test_tile_array_past_the_cache():
+    """FP64 tiles of more than the part of the cache they may keep (some tiles read
+    with allocating loads, the rest without), against a context whose FP32 copy
+    has the cache: the loads differ, the arithmetic does not."""
+    w = inputs.Workload("hot", 50, 59, 1.0, seed=56)   # 2950 beads: 47 x 48 / 2 tiles of 196 KB, 222 MB
+    pos = _cuda(w.positions())
+    a, b = rpy.context_for(w, max_rhs=16), rpy.context_for(w, lowp="f32", max_rhs=16)
+    a.build(pos)
+    b.build(pos)
+    for m in (1, 2, 3, 4, 7, 16):
+        v = _cuda(np.random.default_rng(m).standard_normal((m, w.n, 3)))
+        assert torch.equal(a.apply(v), b.apply(v)), m
