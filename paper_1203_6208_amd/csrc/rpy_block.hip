@@ -189,6 +189,9 @@ template <typename T> struct alignas(32) BlkLds {
     T pb[2][TB * BK<T>::PLD];
 };
 
+// First tile of workgroup w of g when nt tiles are dealt in contiguous parts.
+__host__ __device__ inline int run_start(int w, int nt, int g) { return (int)((long)w * nt / g); }
+
 // Workgroup b (4 or 8 waves) takes the stored tiles b, b + gridDim.x, ... (a
 // persistent loop, so that the plane loads run ahead across tiles).  Wave w
 // (row group r = w % 4, half h = w / 4) owns the bead rows 16 r .. 16 r + 15
@@ -228,7 +231,13 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_
     const int rg = w & 3, h = w >> 2;
     const int n = lane & 15, g = lane >> 4;
     const int row = 16 * rg + n;   // this lane's bead row of a plane stripe (column of P^T)
-    const int step = gridDim.x;
+    // FP64: the tiles [t0, t1) in stored order, whose row products are summed in registers along
+    // a row I and written once per run (slot J of its last tile); FP32, BF16: b, b + gridDim.x, ...,
+    // each tile's row product on its own (FP32 sums end with the tile)
+    constexpr bool RUN = sizeof(T) == 8;
+    const int step = RUN ? 1 : gridDim.x;
+    const int t0 = RUN ? run_start(blockIdx.x, ntiles, gridDim.x) : blockIdx.x;
+    const int t1 = RUN ? run_start(blockIdx.x + 1, ntiles, gridDim.x) : ntiles;
     // The vectors of J (row product), then of I (column product), in pieces of 16
     // bytes, loaded during the previous tile: N = 2000 FP64 48.8 -> 45.3 us, BF16 17.4 -> 15.4.
     // FP32 tiles load them at the tile's start: their registers would cost the second
@@ -256,13 +265,16 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_
     auto tile_products = [&](auto hot_tiles) {
     constexpr bool HOT = decltype(hot_tiles)::value;
     Stripe<T> ring[3];
-    int t = blockIdx.x;
-    if (t < ntiles) {
+    int t = t0;
+    A dacc[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) dacc[a] = A{};
+    if (t < t1) {
         if (XAHEAD) fetch_x(tile_ij[t]);
         load_stripe<T, HOT>(tiles, t, 0, row, g, h, ring[0]);
         load_stripe<T, HOT>(tiles, t, 1, row, g, h, ring[1]);
     }
-    for (; t < ntiles; t += step) {
+    for (; t < t1; t += step) {
         const int2 ij = tile_ij[t];
         const int I = ij.x, J = ij.y;
         const bool offd = I != J;
@@ -273,18 +285,19 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_
             const int q = threadIdx.x + 64 * NW * u;
             reinterpret_cast<u4v *>(q < NC ? L.xj : L.xi)[q < NC ? q : q - NC] = xr[u];
         }
-        A dacc[3], tacc[3];
+        A tacc[3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) dacc[a] = tacc[a] = A{};
+        for (int a = 0; a < 3; ++a) tacc[a] = A{};
         __syncthreads();
         const int tn = t + step;   // the tile whose vectors and first planes are loaded meanwhile
         const int2 ijn = tile_ij[min(tn, ntiles - 1)];
+        const bool flush = !RUN || tn >= t1 || ijn.x != I;   // the row product ends with this tile
 #pragma unroll
         for (int c = 0; c < 6; ++c) {
             // two planes ahead; planes 4 and 5 fetch planes 0 and 1 of the next tile
             if (c + 2 < 6) load_stripe<T, HOT>(tiles, t, c + 2, row, g, h, ring[(c + 2) % 3]);
-            else if (tn < ntiles) load_stripe<T, HOT>(tiles, tn, c - 4, row, g, h, ring[(c + 2) % 3]);
-            if (XAHEAD && c == 2 && tn < ntiles) fetch_x(ijn);
+            else if (tn < t1) load_stripe<T, HOT>(tiles, tn, c - 4, row, g, h, ring[(c + 2) % 3]);
+            if (XAHEAD && c == 2 && tn < t1) fetch_x(ijn);
             __asm__ volatile("" ::: "memory");
             const Stripe<T> &st = ring[c % 3];
             const int a = plane_a(c), b = plane_b(c);
@@ -377,7 +390,7 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_
             if (h == 1) {
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    hbuf[(rg * 6 + a) * 64 + lane] = dacc[a];
+                    if (flush) hbuf[(rg * 6 + a) * 64 + lane] = dacc[a];
                     hbuf[(rg * 6 + 3 + a) * 64 + lane] = tacc[a];
                 }
             }
@@ -385,7 +398,7 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_
             if (h == 0) {
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    dacc[a] = dacc[a] + hbuf[(rg * 6 + a) * 64 + lane];
+                    if (flush) dacc[a] = dacc[a] + hbuf[(rg * 6 + a) * 64 + lane];
                     tacc[a] = tacc[a] + hbuf[(rg * 6 + 3 + a) * 64 + lane];
                 }
             }
@@ -399,16 +412,19 @@ __global__ __launch_bounds__(64 * BK<T>::NWAVE) __attribute__((amdgpu_waves_per_
                 const int bead = 16 * rg + K::orow(g, e);
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    pd[(size_t)(3 * bead + a) * 16] = dacc[a][e];
+                    if (flush) pd[(size_t)(3 * bead + a) * 16] = dacc[a][e];
                     if (offd) pt[(size_t)(3 * bead + a) * 16] = tacc[a][e];
                 }
             }
         }
+        if (flush)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) dacc[a] = A{};
     }
     };
     if constexpr (CACHED) tile_products(std::true_type{});
     // `hot` workgroups of a larger array's, spread evenly over them
-    else if (((int)blockIdx.x + 1) * hot / step != (int)blockIdx.x * hot / step) tile_products(std::true_type{});
+    else if (((int)blockIdx.x + 1) * hot / (int)gridDim.x != (int)blockIdx.x * hot / (int)gridDim.x) tile_products(std::true_type{});
     else tile_products(std::false_type{});
 }
 
@@ -432,17 +448,29 @@ template <typename T, bool CACHED> static int block_grid(const Ctx &c)
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, block_kernel<T, CACHED>(), 64 * BK<T>::NWAVE, 0) !=
             hipSuccess ||
         cus < 1 || per < 1)
-        return 256;   // not cached: asked again next time
-    g = cus * per;
+        g = 256;   // kept as well: the partial sums have to know the tile product's grid
+    else
+        g = cus * per;
     return g;
+}
+
+template <typename T> static int block_tiles_grid(const Ctx &c)
+{
+    const bool cached = (size_t)c.ntiles * TILE6 * sizeof(T) <= TILE_CACHE_BYTES;
+    const int cap = cached ? block_grid<T, true>(c) : block_grid<T, false>(c);
+    return c.ntiles < cap ? c.ntiles : cap;
+}
+static int block_tiles_grid(const Ctx &c, int prec)
+{
+    return prec == RPY_PREC_BF16 ? block_tiles_grid<uint16_t>(c)
+           : prec == RPY_PREC_F32 ? block_tiles_grid<float>(c) : block_tiles_grid<double>(c);
 }
 
 template <typename T>
 static void block_tiles_launch(const Ctx &c, const T *tiles, hipStream_t s)
 {
     const bool cached = (size_t)c.ntiles * TILE6 * sizeof(T) <= TILE_CACHE_BYTES;
-    const int cap = cached ? block_grid<T, true>(c) : block_grid<T, false>(c);
-    const int grid = c.ntiles < cap ? c.ntiles : cap;
+    const int grid = block_tiles_grid<T>(c);
     const int npad = c.nbt * TB;
     // of a larger array the tiles of some workgroups, about as much as the cache holds
     const int hot = cached || !own_tiles<T>(c) ? 0 : (int)((double)grid * TILE_CACHE_BYTES / ((double)c.ntiles * TILE6 * sizeof(T)));
@@ -536,38 +564,69 @@ struct SfLd {
 // thread issues the loads of PS_BATCH slots at once, sums them as a pairwise
 // tree and adds the batches in K order, in FP64, into ypart[j][row].  This
 // HBM stream overlaps the matrix-core work.
+// FP64 partials of the row products are written once per run of tiles (k_block_tiles on
+// `grid` workgroups): the slots of row tile I are K < I and, from K = I on, the last
+// tile of each run; a batch's slots are found by its first threads.  N = 4000: the
+// tile product writes and this reads 56 instead of 97 MB, 121.8 -> 119.5 and 35.7 -> 31.1 us.
 constexpr int PS_BATCH = 32;
+__device__ inline int run_slot(int i, int I, int nbt, int nt, int grid)
+{
+    if (i < I) return i;
+    const int base = I * nbt - I * (I - 1) / 2, end = base + nbt - I;   // tiles of row I: [base, end)
+    // workgroup of the row's first tile, then the (i - I)-th after it
+    int w = (int)((long)base * grid / nt);
+    while (run_start(w + 1, nt, grid) <= base) ++w;
+    return I + min(run_start(w + 1 + i - I, nt, grid), end) - 1 - base;
+}
+__device__ inline int run_slots(int I, int nbt, int nt, int grid)
+{
+    const int base = I * nbt - I * (I - 1) / 2, end = base + nbt - I;
+    int w = (int)((long)base * grid / nt), z = (int)((long)(end - 1) * grid / nt);
+    while (run_start(w + 1, nt, grid) <= base) ++w;
+    while (run_start(z + 1, nt, grid) <= end - 1) ++z;
+    return I + z - w + 1;
+}
 template <typename P>
-__device__ inline void block_part_sum(int b, int n3, int n3pad, int m, int nslot,
+__device__ inline void block_part_sum(int b, int n3, int n3pad, int m, int nslot, int nt, int grid,
                                       const P *__restrict__ part, double *__restrict__ ypart)
 {
+    constexpr bool RUN = sizeof(P) == 8;
+    __shared__ int slots[PS_BATCH];
+    if (16 * b >= n3) return;
     const int row = 16 * b + (threadIdx.x >> 4), j = threadIdx.x & 15;
-    if (row >= n3 || j >= m) return;
-    const P *pp = part + (size_t)row * BLOCK_RHS + j;
+    const int I = 16 * b / TS;
+    const bool live = row < n3 && j < m;
+    const P *pp = part + (size_t)min(row, n3 - 1) * BLOCK_RHS + j;
     const size_t ks = (size_t)n3pad * BLOCK_RHS;
+    const int ns = RUN ? run_slots(I, nslot, nt, grid) : nslot;
     double y = 0.0;
-    for (int K = 0; K < nslot; K += PS_BATCH) {
-        // branch-free: a slot past nslot re-reads the last one and is zeroed
+    for (int K = 0; K < ns; K += PS_BATCH) {
+        if constexpr (RUN) {
+            __syncthreads();
+            if (threadIdx.x < PS_BATCH) slots[threadIdx.x] = run_slot(min(K + (int)threadIdx.x, ns - 1), I, nslot, nt, grid);
+            __syncthreads();
+        }
+        // branch-free: a slot past the last re-reads it and is zeroed
         // after the loads (a conditional load would wait at every join)
         P raw[PS_BATCH];
 #pragma unroll
-        for (int u = 0; u < PS_BATCH; ++u) raw[u] = pp[(size_t)min(K + u, nslot - 1) * ks];
+        for (int u = 0; u < PS_BATCH; ++u) raw[u] = pp[(size_t)(RUN ? slots[u] : min(K + u, ns - 1)) * ks];
         double q[PS_BATCH];
 #pragma unroll
-        for (int u = 0; u < PS_BATCH; ++u) q[u] = K + u < nslot ? (double)raw[u] : 0.0;
+        for (int u = 0; u < PS_BATCH; ++u) q[u] = K + u < ns ? (double)raw[u] : 0.0;
 #pragma unroll
         for (int h = PS_BATCH / 2; h >= 1; h >>= 1)
 #pragma unroll
             for (int u = 0; u < h; ++u) q[u] += q[u + h];
         y += q[0];
     }
-    ypart[(size_t)j * n3 + row] = y;
+    if (live) ypart[(size_t)j * n3 + row] = y;
 }
 
 template <int U>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(U > 8 ? 4 : 3, 8))) void k_block_sf(int nk, int nk16, int nq, int cq, int nkb,
                                                   int N, int n3, int n3pad, int m, int nslot,
-                                                  const double2 *eph, const double *vpk,
+                                                  int nt, int grid, const double2 *eph, const double *vpk,
                                                   double *sfpart,
                                                   const void *__restrict__ part, int part64,
                                                   double *__restrict__ ypart,
@@ -578,9 +637,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(U > 8 ? 4 :
     if ((int)blockIdx.x >= nkb) {
         const int b = (blockIdx.x - nkb) + blockIdx.y * (gridDim.x - nkb);
         if (part64)
-            block_part_sum(b, n3, n3pad, m, nslot, reinterpret_cast<const double *>(part), ypart);
+            block_part_sum(b, n3, n3pad, m, nslot, nt, grid, reinterpret_cast<const double *>(part), ypart);
         else
-            block_part_sum(b, n3, n3pad, m, nslot, reinterpret_cast<const float *>(part), ypart);
+            block_part_sum(b, n3, n3pad, m, nslot, nt, grid, reinterpret_cast<const float *>(part), ypart);
         return;
     }
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -706,10 +765,11 @@ void launch_block_sf(const Ctx &c, int m, int prec, hipStream_t s)
     // workgroups per grid row (npg = groups of 16 rows)
     const int npg = (c.n3 + 15) / 16;
     const int px = (npg + c.nchb - 1) / c.nchb;
+    const int grid = block_tiles_grid(c, prec);   // of the tile product before
 #define RPY_BSF(U)                                                                              \
     hipLaunchKernelGGL(k_block_sf<U>, dim3(nkb + px, c.nchb), dim3(64 * SF_WAVES), 0, s, c.nk,  \
-                       (c.nk + 15) / 16 * 16, nq, cq, nkb, c.N, c.n3, c.n3pad, m, c.nbt, c.eph, \
-                       c.vpk, c.sfpart, (const void *)c.bpart, prec == RPY_PREC_F64 ? 1 : 0,    \
+                       (c.nk + 15) / 16 * 16, nq, cq, nkb, c.N, c.n3, c.n3pad, m, c.nbt, c.ntiles, \
+                       grid, c.eph, c.vpk, c.sfpart, (const void *)c.bpart, prec == RPY_PREC_F64 ? 1 : 0,    \
                        c.ypart, c.gate)
     if (cq <= SF_U[0] * SF_WAVES) RPY_BSF(SF_U[0]);
     else RPY_BSF(SF_U[1]);

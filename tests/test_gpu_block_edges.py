@@ -47,3 +47,21 @@ def test_tile_array_past_the_cache():
     for m in (1, 2, 3, 4, 7, 16):
         v = _cuda(np.random.default_rng(m).standard_normal((m, w.n, 3)))
         assert torch.equal(a.apply(v), b.apply(v)), m
+
+
+@pytest.mark.parametrize("size", [(20, 50), (23, 59), (30, 61), (43, 47)])
+def test_runs_of_tiles(size):
+    """FP64 row products summed over a workgroup's run of tiles: tile counts below,
+    around and above the workgroups (136, 253, 435 and 528 tiles on 256), runs that
+    end inside, at the end of and beyond a row, against the vector-unit path."""
+    w = inputs.Workload("runs", *size, 1.0, seed=57)
+    pos = _cuda(w.positions())
+    a, b = rpy.context_for(w, max_rhs=16), rpy.context_for(w, lowp="f32", max_rhs=4)
+    a.build(pos)
+    b.build(pos)
+    for m in (5, 16):
+        v = _cuda(np.random.default_rng(m).standard_normal((m, w.n, 3)))
+        got = a.apply(v)
+        want = torch.cat([b.apply(v[j:j + 4]) for j in range(0, m, 4)])
+        assert (got - want).abs().max().item() <= 1e-12 * want.abs().max().item()
+        assert torch.equal(got, a.apply(v))
