@@ -230,9 +230,9 @@ void launch_sf(const Ctx &c, const double *v, int m, int fold, hipStream_t s)
 }
 
 // ------------------------------------- reciprocal back-projection + epilogue
-// Workgroup: 16 beads x 64 slices (16 waves; lane = bead (low 4 bits) and
-// sub-slice (high 2 bits); slice u = 4 wave + sub).  Slice u owns the wave
-// vectors [u nk/64, (u+1) nk/64) and the tile columns K = u, u+64, ...:
+// Workgroup: B beads x S = 1024 / B slices (16 waves; lane = bead (low bits) and
+// sub-slice (high bits); slice u = (64 / B) wave + sub).  Slice u owns the wave
+// vectors [u nk/S, (u+1) nk/S) and the tile columns K = u, u+S, ...:
 //   y_u = sum_K part[K][j][3 nu + c] + sum_k cos(k.r_nu) Tc_k + sin(k.r_nu) Ts_k
 // with k.r_nu = 2 pi n.s_nu.  The wave vectors are sorted by (n_x, n_y) and
 // then n_z, so inside a run of equal (n_x, n_y) the phase advances by
@@ -294,8 +294,12 @@ __device__ __forceinline__ void epi_entry(const EpiArgs &f, size_t o, double yy,
     tb2 = v0 * f.ddw[o];
 }
 
-constexpr int EPI_BEADS = 16;
-constexpr int EPI_SLICES = 64;
+// B = 8 while one workgroup per compute unit covers the box (the wave-vector loop is a
+// chain of LDS reads, half as long as with 16), else 16.  Product of one vector on BF16 tiles:
+// N = 800 14.2 against 15.4 us, 2000 16.6 against 17.8; N = 2100 18.0 against 19.2 with 8 and
+// 20.8 with 32; three vectors N = 2000 37.8 against 39.9, N = 2100 41.5 against 48.7.
+constexpr int EPI_B8_MAX = 2048;
+static int epi_beads(int N) { return N <= EPI_B8_MAX ? 8 : 16; }
 // When `staged` (nk <= 1024, at most epi_stage_per<M>() x 1024 values of tk,
 // and the tables fit the workgroup's LDS), the wave vectors and this
 // launch's 6 M values of tk per k are copied to LDS once per workgroup --
@@ -304,8 +308,7 @@ constexpr int EPI_SLICES = 64;
 // the slack entries, so no write is conditional).  The per-thread counts
 // cover the 618 half-space wave vectors of alpha L = 6 for 1-4 vectors.
 template <int M> constexpr int epi_stage_per() { return M == 1 ? 6 : M == 2 ? 8 : M == 3 ? 11 : 15; }
-constexpr size_t EPI_RED_BYTES = sizeof(double) * 16 * 3 * EPI_BEADS;   // static `red`
-template <int M>
+template <int M, int B>
 __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, int nbt, int nk,
                                                      int nmax, int rhs_cap, int j0, int staged,
                                                      const KVec *kvec,
@@ -314,25 +317,27 @@ __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, i
                                                      const double *tk_g, EpiArgs f,
                                                      const int *__restrict__ gate)
 {
-    __shared__ double red[16][3][EPI_BEADS];
+    constexpr int S = 1024 / B;   // slices
+    static_assert(3 * B <= 64, "the entries are lanes of the first wave");
+    __shared__ double red[16][3][B];
     extern __shared__ double lds[];
     if (gate && *gate) return;
     const int nm1 = nmax + 1;
-    double2 *tabs = reinterpret_cast<double2 *>(lds);          // [EPI_BEADS][3 nm1]
-    double *stage = lds + 2 * EPI_BEADS * 3 * nm1;
+    double2 *tabs = reinterpret_cast<double2 *>(lds);          // [B][3 nm1]
+    double *stage = lds + 2 * B * 3 * nm1;
     // Loads that do not depend on the staged tables are issued first: the
-    // bead's tile-column partials and, for the 3 EPI_BEADS threads that apply
+    // bead's tile-column partials and, for the 3 B threads that apply
     // the epilogue, the recurrence operands.
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int bl = lane & 15, sub = lane >> 4;
-    const int u = 4 * w + sub;
-    const int nu = blockIdx.x * EPI_BEADS + bl;
+    const int bl = lane % B, sub = lane / B;
+    const int u = 64 / B * w + sub;
+    const int nu = blockIdx.x * B + bl;
     const bool live = nu < N;
     double y[M][3];
 #pragma unroll
     for (int j = 0; j < M; ++j) y[j][0] = y[j][1] = y[j][2] = 0.0;
     if (live) {
-        for (int K = u; K < nbt; K += EPI_SLICES) {
+        for (int K = u; K < nbt; K += S) {
 #pragma unroll
             for (int j = 0; j < M; ++j) {
                 const double *pp = part + ((size_t)K * rhs_cap + j0 + j) * n3pad + 3 * nu;
@@ -343,8 +348,8 @@ __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, i
         }
     }
     const int eb = (int)threadIdx.x / 3, ec = (int)threadIdx.x % 3;
-    const int ebead = blockIdx.x * EPI_BEADS + eb;
-    const bool eth = threadIdx.x < 3 * EPI_BEADS && ebead < N;
+    const int ebead = blockIdx.x * B + eb;
+    const bool eth = threadIdx.x < 3 * B && ebead < N;
     double pv[M], pv2[M], pa[M];
 #pragma unroll
     for (int j = 0; j < M; ++j) {
@@ -355,9 +360,9 @@ __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, i
         pa[j] = eth && (f.mode == EPI_CHEB_NEXT || f.mode == EPI_ADJ) ? f.acc[o] : 0.0;
     }
     // the phase tables e^{i 2 pi j s_a} of the workgroup's beads (zero past N)
-    const int ntab = EPI_BEADS * 3 * nm1;
-    const size_t tab0 = (size_t)blockIdx.x * EPI_BEADS * 3 * nm1;
-    const int nlive = min(EPI_BEADS, N - (int)blockIdx.x * EPI_BEADS) * 3 * nm1;
+    const int ntab = B * 3 * nm1;
+    const size_t tab0 = (size_t)blockIdx.x * B * 3 * nm1;
+    const int nlive = min(B, N - (int)blockIdx.x * B) * 3 * nm1;
     for (int e = threadIdx.x; e < ntab; e += blockDim.x)
         tabs[e] = e < nlive ? etab[tab0 + e] : make_double2(0.0, 0.0);
     if (staged) {
@@ -378,7 +383,7 @@ __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, i
         for (int i = 0; i < SP; ++i) td[min((int)threadIdx.x + 1024 * i, ntk)] = tv[i];
     }
     __syncthreads();
-    const int klo = (int)((long)u * nk / EPI_SLICES), khi = (int)((long)(u + 1) * nk / EPI_SLICES);
+    const int klo = (int)((long)u * nk / S), khi = (int)((long)(u + 1) * nk / S);
     const double2 *tb = tabs + bl * 3 * nm1;
     const double2 ez = nm1 > 1 ? tb[2 * nm1 + 1] : make_double2(1.0, 0.0);   // e^{i 2 pi s_z}
     const double ezr = ez.x, ezi = ez.y;
@@ -422,8 +427,8 @@ __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, i
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             double v = y[j][c];
-            v += __shfl_xor(v, 16);
-            v += __shfl_xor(v, 32);
+#pragma unroll
+            for (int x = B; x <= 32; x <<= 1) v += __shfl_xor(v, x);
             if (sub == 0) red[w][c][bl] = v;
         }
         __syncthreads();
@@ -435,7 +440,7 @@ __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, i
             epi_entry(f, (size_t)(j0 + j) * n3 + 3 * (size_t)ebead + ec, yy, pv[j], pv2[j], pa[j], trial,
                       ta, tb2);
         }
-        if (trial && w == 0) {   // the 3 EPI_BEADS entries are lanes of the first wave
+        if (trial && w == 0) {   // the 3 B entries are lanes of the first wave
 #pragma unroll
             for (int o2 = 32; o2 >= 1; o2 >>= 1) {
                 ta += __shfl_xor(ta, o2);
@@ -465,7 +470,7 @@ __global__ __launch_bounds__(1024) void k_kspace_epi(int N, int n3, int n3pad, i
 // the 618 wave vectors of alpha L = 6 the staged form stays ahead: 7.2 against 9.5 us at
 // N = 2000, 8.2 against 10.0 us at N = 4000.
 constexpr int COL_BEADS = 64;
-static_assert(3 * COL_BEADS / 64 <= COL_BEADS / EPI_BEADS, "trial_chunks covers both");
+static_assert(3 * COL_BEADS / 64 <= 8, "trial_chunks covers this form");
 constexpr int COL_TRIAL = 3 * COL_BEADS / 64;   // waves that hold entries
 __global__ __launch_bounds__(1024) void k_kspace_cols(int N, int n3, int n3pad, int nbt, int nm1,
                                                       int rhs_cap,
@@ -563,23 +568,30 @@ __global__ __launch_bounds__(1024) void k_kspace_cols(int N, int n3, int n3pad, 
 
 void launch_kspace_epi(const Ctx &c, const EpiArgs &f, hipStream_t s)
 {
-    const dim3 g((c.N + EPI_BEADS - 1) / EPI_BEADS), b(1024);
+    const dim3 b(1024);
     if (c.fold) {
         hipLaunchKernelGGL(k_kspace_cols, dim3((c.N + COL_BEADS - 1) / COL_BEADS, f.m), b, 0, s, c.N,
                            c.n3, c.n3pad, c.nslot, c.nmax + 1, c.rhs_cap, c.fold_split, c.fold_cols,
                            c.axt, c.part, c.tkf, f, c.gate);
         return;
     }
-    const size_t tabs = sizeof(double) * 2 * EPI_BEADS * 3 * (size_t)(c.nmax + 1);
+    const int beads = epi_beads(c.N);
+    const dim3 g((c.N + beads - 1) / beads);
+    const size_t tabs = sizeof(double) * 2 * beads * 3 * (size_t)(c.nmax + 1);
+    const size_t red = sizeof(double) * 16 * 3 * beads;   // static
+#define RPY_EPI(MC, B)                                                                          \
+    hipLaunchKernelGGL((k_kspace_epi<MC, B>), g, b, tabs + (staged ? lds : 0), s, c.N, c.n3,    \
+                       c.n3pad, c.nslot, c.nk, c.nmax, c.rhs_cap, j0, staged, c.kvec, c.etab,   \
+                       c.part, c.tk, f, c.gate)
     RPY_RHS_GROUPS(f.m, {
         const size_t lds = sizeof(double) * ((size_t)c.nk * (2 + 6 * MC) + 3);
         const int staged = c.nk <= 1024 &&
                            (size_t)c.nk * 6 * MC <= (size_t)1024 * epi_stage_per<MC>() &&
-                           tabs + lds + EPI_RED_BYTES <= (size_t)c.lds_max;
-        hipLaunchKernelGGL(k_kspace_epi<MC>, g, b, tabs + (staged ? lds : 0), s, c.N, c.n3,
-                           c.n3pad, c.nslot, c.nk, c.nmax, c.rhs_cap, j0, staged, c.kvec, c.etab,
-                           c.part, c.tk, f, c.gate);
+                           tabs + lds + red <= (size_t)c.lds_max;
+        if (beads == 8) RPY_EPI(MC, 8);
+        else RPY_EPI(MC, 16);
     });
+#undef RPY_EPI
 }
 
 // ------------------------------------------------- Chebyshev coefficients
@@ -809,7 +821,9 @@ void launch_trial(const Ctx &c, int m, int n, int nmax, double tol, size_t ps,
 
 int epi_trial_chunks(const Ctx &c)
 {
-    return c.fold ? (c.N + COL_BEADS - 1) / COL_BEADS * COL_TRIAL : (c.N + EPI_BEADS - 1) / EPI_BEADS;
+    if (c.fold) return (c.N + COL_BEADS - 1) / COL_BEADS * COL_TRIAL;
+    const int b = epi_beads(c.N);
+    return (c.N + b - 1) / b;   // its workgroups
 }
 
 void launch_trial_check(const Ctx &c, int m, int nchunk, int n, int nmax, double tol, double *e_f,
@@ -821,7 +835,7 @@ void launch_trial_check(const Ctx &c, int m, int nchunk, int n, int nmax, double
 
 int trial_chunks(int N)
 {
-    const int a = (3 * N + 255) / 256, b = (N + COL_BEADS - 1) / COL_BEADS * (COL_BEADS / EPI_BEADS);
+    const int a = (3 * N + 255) / 256, b = (N + COL_BEADS - 1) / COL_BEADS * 8;   // of any form: at most one per 8 beads
     const int r = N <= ROWS_MAX ? rows_trial_chunks(N) : 0;
     return a > b ? (a > r ? a : r) : (b > r ? b : r);
 }

@@ -99,3 +99,22 @@ def test_back_projection_by_columns(size, lma):
         assert n == n_o
         assert np.abs(ds.cpu().numpy().reshape(m, -1) - want).max() <= TOL * np.abs(want).max()
     ctx.close()
+
+
+@pytest.mark.parametrize("size", [(32, 64), (3, 683), (41, 51)])
+def test_back_projection_groups(size):
+    """Eight beads per workgroup up to 2048 beads, 16 above: products and adaptive
+    series (whose trials' partial sums are per workgroup) of one and three
+    vectors against the block path of five, which has workgroups of its own."""
+    w = inputs.Workload("groups", *size, 1.0, seed=94)
+    pos = torch.from_numpy(w.positions()).cuda()
+    a = rpy.context_for(w, lowp="bf16", max_rhs=5, cheb_keep=64)
+    a.build(pos)
+    v = torch.from_numpy(np.random.default_rng(6).standard_normal((5, w.n, 3))).cuda()
+    want, (ws, wf, wn) = a.apply(v), a.sqrt_adaptive(v, 0.04, 40.0, 1e-2, 64)
+    for m in (1, 3):
+        got = a.apply(v[:m])
+        assert (got - want[:m]).abs().max().item() <= TOL * want.abs().max().item()
+        gs, gf, gn = a.sqrt_adaptive(v[:m], 0.04, 40.0, 1e-2, 64, n_start=wn)
+        assert gn == wn
+        assert (gs - ws[:m]).abs().max().item() <= TOL * ws.abs().max().item()
