@@ -580,7 +580,7 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
         (c.grad && ((rc = dalloc(&c.wgrad, te)) ||
                     (rc = dalloc(&c.xy, (size_t)c.cheb_keep * 2 * nv)) ||
                     (rc = dalloc(&c.gpart, (size_t)c.nbt * c.n3pad)) ||
-                    (rc = dalloc(&c.gk, nv)) || (rc = dalloc(&c.mur, 3 * nv)))) ||
+                    (rc = dalloc(&c.gk, grad_parts(c.N) * nv)) || (rc = dalloc(&c.mur, 3 * nv)))) ||
         (rc = dalloc(&c.cell_start, 2 * ncells_cap + 1)) || (rc = dalloc(&c.cell_beads, nv))) {
         rpy_destroy(x);
         return rc;

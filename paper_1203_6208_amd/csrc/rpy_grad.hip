@@ -240,91 +240,81 @@ void launch_grad_real(const Ctx &c, hipStream_t s)
 
 // ------------------------------------------------ reciprocal-space gradient
 // Per bead l: the reciprocal term above for the nq pairs whose T_k are in
-// tk[k][2 qq + (0: x, 1: y)][6].  Workgroup: 4 beads x 64 wave-vector slices
-// (lane = bead (low 2 bits) and 16 slices, 4 waves; phases by the n_z
-// recursion as in the product's back-projection); slices are combined in a
-// fixed order (xor tree over the lanes of a bead, then the 4 waves); gk =
-// (or +=, accumulate) the result.
-constexpr int GK_BEADS = 4;
-constexpr int GK_SLICES = 64;
+// tk[k][2 qq + (0: x, 1: y)][6].  Lane = bead; the wave vectors are cut into GK_WAVES
+// gridDim.y slices, one per wave, so that T_k (96 values for 8 pairs) is the same for all
+// lanes and comes through the scalar cache into the multiply-adds; the phase is the
+// product of the bead's three axis phases.  The waves are added in order; gk[blockIdx.y] = (or
+// +=, accumulate) the result, and k_grad_sum adds the gridDim.y parts.
+// Bound by the FP64 multiply-adds (18 per pair and wave vector) and the scalar loads'
+// latency: with one workgroup per compute unit and a pair's T_k at a time 30.6 us for eight
+// pairs at N = 2000; four beads and 64 slices per workgroup, T_k through vector loads of
+// 16 slices at a time, 35 us.  Two reverse steps there: 4.38 -> 4.25 ms.
+constexpr int GK_WAVES = 8;
 constexpr int GK_QMAX = 8;
-__global__ __launch_bounds__(256) void k_grad_kspace(int N, int n3, int nk, int rhs_cap, int nq,
-                                                      double twopi_L, int accumulate,
-                                                      const KVec *__restrict__ kvec,
-                                                      const double *__restrict__ sfr,
-                                                      const double *__restrict__ xy,
-                                                      const double *__restrict__ tk,
-                                                      double *__restrict__ gk)
+__global__ __launch_bounds__(64 * GK_WAVES) void k_grad_kspace(int N, int n3, int nk, int nm1,
+                                                               int rhs_cap, int nq, double twopi_L,
+                                                               int accumulate,
+                                                               const KVec *__restrict__ kvec,
+                                                               const double2 *__restrict__ axt,
+                                                               const double *__restrict__ xy,
+                                                               const double *__restrict__ tk,
+                                                               double *__restrict__ gk)
 {
-    __shared__ double red[4][3][GK_BEADS];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int bl = lane & 3, sub = lane >> 2;
-    const int u = 16 * w + sub;   // slice 0 .. 63
-    const int nu = blockIdx.x * GK_BEADS + bl;
-    const bool live = nu < N;
+    __shared__ double red[GK_WAVES][3][64];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int u = blockIdx.y * GK_WAVES + w, U = gridDim.y * GK_WAVES;
+    const int nu = min((int)blockIdx.x * 64 + lane, N - 1);
     double xv[GK_QMAX][3], yv[GK_QMAX][3];
 #pragma unroll
     for (int q = 0; q < GK_QMAX; ++q)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const bool ok = live && q < nq;
-            xv[q][c] = ok ? xy[(size_t)(2 * q) * n3 + 3 * nu + c] : 0.0;
-            yv[q][c] = ok ? xy[(size_t)(2 * q + 1) * n3 + 3 * nu + c] : 0.0;
+            xv[q][c] = q < nq ? xy[(size_t)(2 * q) * n3 + 3 * (size_t)nu + c] : 0.0;
+            yv[q][c] = q < nq ? xy[(size_t)(2 * q + 1) * n3 + 3 * (size_t)nu + c] : 0.0;
         }
+    const int klo = (int)((long)u * nk / U), khi = (int)((long)(u + 1) * nk / U);
     double acc[3] = {0.0, 0.0, 0.0};
-    if (live) {
-        const double sx = sfr[3 * nu], sy = sfr[3 * nu + 1], sz = sfr[3 * nu + 2];
-        const int klo = (int)((long)u * nk / GK_SLICES),
-                  khi = (int)((long)(u + 1) * nk / GK_SLICES);
-        double ezr, ezi;
-        sincospi(2.0 * sz, &ezi, &ezr);
-        double cs = 1.0, sn = 0.0;
-        int px = -(1 << 30), py = 0, pz = 0;
-        for (int k = klo; k < khi; ++k) {
-            const KVec kv = kvec[k];
-            if (kv.nx == px && kv.ny == py && kv.nz == pz + 1) {
-                const double c2 = cs * ezr - sn * ezi;
-                sn = cs * ezi + sn * ezr;
-                cs = c2;
-            } else {
-                sincospi(2.0 * (kv.nx * sx + kv.ny * sy + kv.nz * sz), &sn, &cs);
-            }
-            px = kv.nx;
-            py = kv.ny;
-            pz = kv.nz;
-            const double *tt = tk + (size_t)k * rhs_cap * 6;
-            double sk = 0.0;
+    for (int k = klo; k < khi; ++k) {
+        const KVec kv = kvec[k];
+        const double2 ex = axt[(size_t)kv.nx * N + nu], ey = axt[(size_t)(nm1 + abs(kv.ny)) * N + nu],
+                      ez = axt[(size_t)(2 * nm1 + abs(kv.nz)) * N + nu];
+        const double eyi = kv.ny < 0 ? -ey.y : ey.y, ezi = kv.nz < 0 ? -ez.y : ez.y;
+        const double er = ex.x * ey.x - ex.y * eyi, ei = ex.x * eyi + ex.y * ey.x;
+        const double cs = er * ez.x - ei * ezi, sn = er * ezi + ei * ez.x;
+        const double *tt = tk + (size_t)k * rhs_cap * 6;
+        double sk = 0.0;
+        // two pairs' T_k at a time (those of a pair past the last, whose x and y are
+        // zero, from the last)
 #pragma unroll
-            for (int q = 0; q < GK_QMAX; ++q) {
-                if (q < nq) {
-                    const double *tx = tt + 12 * q, *ty = tx + 6;
+        for (int q0 = 0; q0 < GK_QMAX; q0 += 2) {
+            double t[2][12];
 #pragma unroll
-                    for (int c = 0; c < 3; ++c)
-                        sk += xv[q][c] * (sn * ty[c] - cs * ty[3 + c]) +
-                              yv[q][c] * (sn * tx[c] - cs * tx[3 + c]);
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int c = 0; c < 12; ++c) t[p][c] = tt[12 * min(q0 + p, nq - 1) + c];
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    sk = fma(xv[q0 + p][c], fma(sn, t[p][6 + c], -cs * t[p][9 + c]), sk);
+                    sk = fma(yv[q0 + p][c], fma(sn, t[p][c], -cs * t[p][3 + c]), sk);
                 }
-            }
-            acc[0] -= sk * (twopi_L * kv.nx);
-            acc[1] -= sk * (twopi_L * kv.ny);
-            acc[2] -= sk * (twopi_L * kv.nz);
         }
+        acc[0] -= sk * (twopi_L * kv.nx);
+        acc[1] -= sk * (twopi_L * kv.ny);
+        acc[2] -= sk * (twopi_L * kv.nz);
     }
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        double v = acc[c];
-#pragma unroll
-        for (int o = 4; o <= 32; o <<= 1) v += __shfl_xor(v, o);
-        if (sub == 0) red[w][c][bl] = v;
-    }
+    for (int c = 0; c < 3; ++c) red[w][c][lane] = acc[c];
     __syncthreads();
-    if (threadIdx.x < 3 * GK_BEADS) {
+    if (threadIdx.x < 3 * 64) {
         const int b = threadIdx.x / 3, c = threadIdx.x % 3;
-        const int bead = blockIdx.x * GK_BEADS + b;
+        const int bead = blockIdx.x * 64 + b;
         if (bead < N) {
             double s = 0.0;
 #pragma unroll
-            for (int ww = 0; ww < 4; ++ww) s += red[ww][c][b];
-            const size_t o = 3 * (size_t)bead + c;
+            for (int ww = 0; ww < GK_WAVES; ++ww) s += red[ww][c][b];
+            const size_t o = (size_t)blockIdx.y * n3 + 3 * (size_t)bead + c;
             gk[o] = accumulate ? gk[o] + s : s;
         }
     }
@@ -332,26 +322,27 @@ __global__ __launch_bounds__(256) void k_grad_kspace(int N, int n3, int nk, int 
 
 void launch_grad_kspace(const Ctx &c, const double *xy, int nq, int accumulate, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_grad_kspace, dim3((c.N + GK_BEADS - 1) / GK_BEADS), dim3(256), 0, s, c.N,
-                       c.n3, c.nk, c.rhs_cap, nq, 2.0 * M_PI / c.L, accumulate, c.kvec, c.sfr, xy,
-                       c.tk, c.gk);
+    hipLaunchKernelGGL(k_grad_kspace, dim3((c.N + 63) / 64, grad_parts(c.N)), dim3(64 * GK_WAVES), 0, s,
+                       c.N, c.n3, c.nk, c.nmax + 1, c.rhs_cap, nq, 2.0 * M_PI / c.L, accumulate,
+                       c.kvec, c.axt, xy, c.tk, c.gk);
 }
 
-// gpos[3 l + c] = sum over the tile-column slots K (ascending) + reciprocal part.
-__global__ void k_grad_sum(int n3, int n3pad, int nbt, const double *__restrict__ gpart,
+// gpos[3 l + c] = sum over the tile-column slots K (ascending) + the parts of the reciprocal part.
+__global__ void k_grad_sum(int n3, int n3pad, int nbt, int parts, const double *__restrict__ gpart,
                            const double *__restrict__ gk, double *__restrict__ gpos)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n3) return;
-    double s = 0.0;
+    double s = 0.0, r = 0.0;
     for (int K = 0; K < nbt; ++K) s += gpart[(size_t)K * n3pad + i];
-    gpos[i] = s + gk[i];
+    for (int p = 0; p < parts; ++p) r += gk[(size_t)p * n3 + i];
+    gpos[i] = s + r;
 }
 
 void launch_grad_sum(const Ctx &c, double *gpos, hipStream_t s)
 {
     hipLaunchKernelGGL(k_grad_sum, dim3((c.n3 + 255) / 256), dim3(256), 0, s, c.n3, c.n3pad, c.nbt,
-                       c.gpart, c.gk, gpos);
+                       grad_parts(c.N), c.gpart, c.gk, gpos);
 }
 
 }  // namespace rpy

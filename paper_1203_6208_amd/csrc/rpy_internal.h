@@ -502,7 +502,7 @@ struct Ctx {
     double *wgrad = nullptr;     // [ntiles][TS*TS] W = sum_q x_q y_q^T + y_q x_q^T, stored tiles
     double *xy = nullptr;        // [cheb_keep][2][3N] adjoint pairs (x_q, y_q)
     double *gpart = nullptr;     // [nbt][n3pad] real-space gradient partials per tile column
-    double *gk = nullptr;        // [3N] reciprocal-space gradient
+    double *gk = nullptr;        // [grad_parts][3N] reciprocal-space gradient
     double *mur = nullptr;       // [3][3N] adjoint vectors mu_p (ring)
     // cell list for excluded volume
     int ncell;                   // cells per side (0: no cell list)
@@ -684,6 +684,12 @@ void launch_grad_pairs(const Ctx &c, int P, const double *g, const double *F, co
                        size_t ps, hipStream_t s);
 void launch_grad_wtiles(const Ctx &c, int nq, hipStream_t s);
 void launch_grad_real(const Ctx &c, hipStream_t s);
+// parts of the reciprocal gradient: two workgroups of 64 beads for every compute unit
+inline int grad_parts(int N)
+{
+    const int p = 512 / ((N + 63) / 64);
+    return p < 1 ? 1 : p > 16 ? 16 : p;
+}
 void launch_grad_kspace(const Ctx &c, const double *xy, int nq, int accumulate, hipStream_t s);
 void launch_grad_sum(const Ctx &c, double *gpos, hipStream_t s);
 // step
