@@ -59,8 +59,8 @@ struct rpy_ctx {
 // waits.  So while a device has such a context and any other that
 // runs series, their series kernels are ordered one after the other, by an event
 // recorded behind each; the calls around them overlap as before.  With one
-// context, or small boxes only (64 workgroups each, at most four hardware queues), nothing is
-// recorded.
+// context, or small boxes only (64 workgroups each or 128 that share a compute unit two by two, at
+// most four hardware queues), nothing is recorded.
 struct SeriesGate {
     std::mutex m;
     int all = 0, big = 0;

@@ -15,8 +15,8 @@
 // atomic accesses at device scope.  Two slots suffice: a workgroup writes V_{p+2}
 // after it has read all of V_{p+1}, so every workgroup has read all of V_p by then.
 //
-// The wait needs all workgroups on the device at once (one per 8 beads, 64 at
-// most; past 512 beads one per 4, 256 at most, which the host keeps from starting
+// The wait needs all workgroups on the device at once (64 or, adaptive, 128 at most; past
+// 512 beads one per 4 beads, 256 at most, which the host keeps from starting
 // beside another).  They are, unless enough other kernels run at the same time that
 // some are only partly resident; so every wait is bounded: a workgroup that has
 // waited for its limit raises a flag, all of them leave, and the finishing
@@ -28,13 +28,17 @@
 namespace rpy {
 
 // Bead rows per workgroup (B), waves per row (WPR), column blocks of 128 per wave
-// (NB; 24 registers each): (8, 1, 4) up to SERIES_SMALL beads, else (SR_B, SR_WPR, SR_NBW).
+// (NB; 24 registers each): up to SERIES_SMALL beads (8, 1, 4) for a fixed order and (4, 2, 2)
+// for the adaptive one, else (SR_B, SR_WPR, SR_NBW).
+// Series of 20 terms, N = 100 / 400: (8, 1, 4) 45.9 / 53.1 us, (4, 2, 2) 47.6 / 53.7, (4, 1, 4)
+// 54.8 / 63.0, (8, 2, 2) 55.0 / 61.6; adaptive to 33 terms: 85.7 / 122.0, 80.8 / 99.0 (the trials'
+// sums beside the row in half the registers), 93.5 / 122.6, 93.8 / 105.9.
 // N = 1000, per term: (4, 4, 2) 4.8 us; (4, 2, 4) 8.6 and (8, 2, 4) 8.2, whose
 // rows spill; (8, 1, 8) 13.3.
 constexpr int SR_SMALL = SERIES_SMALL;
 constexpr int SR_B = 4, SR_WPR = 4, SR_NBW = 2;
 static_assert(SR_WPR * SR_NBW * 128 == SERIES_MAX, "a row in registers");
-static_assert((SERIES_MAX + SR_B - 1) / SR_B <= SERIES_GROUPS && SR_SMALL / 8 <= SERIES_GROUPS,
+static_assert((SERIES_MAX + SR_B - 1) / SR_B <= SERIES_GROUPS && SR_SMALL / 4 <= SERIES_GROUPS,
               "workgroups in the partial sums");
 typedef double sr2 __attribute__((ext_vector_type(2)));
 typedef unsigned long long word_t;
@@ -131,8 +135,11 @@ __device__ inline bool settles(double a, double b, int n, int nmax, double tol, 
     return (ef > 0.0 ? ef : 0.0) < tol || n >= nmax;   // as k_trial_check
 }
 
-template <int B, int WPR, int NB>
-__global__ __launch_bounds__(64 * B * WPR) void k_series(SeriesArgs a)
+// WEU: waves per SIMD at least.  (4, 2, 2) takes 157 VGPRs, one workgroup per compute unit; past
+// 256 beads it is kept to 128 (a few spills: N = 400 adaptive 99.0 against 94.2 us), two per
+// compute unit, so that four such kernels (one per hardware queue) are resident together.
+template <int B, int WPR, int NB, int WEU = 1>
+__global__ __launch_bounds__(64 * B * WPR) __attribute__((amdgpu_waves_per_eu(WEU, 8))) void k_series(SeriesArgs a)
 {
     constexpr int NT = 64 * B * WPR, X = 3 * 128 * NB * WPR, NW = (X + NT - 1) / NT;
     static_assert(2 * SERIES_GROUPS <= NT, "a thread per partial sum");
@@ -448,7 +455,11 @@ void launch_series_coeffs(const Ctx &c, int n0, int n1, int explicit_, double dm
 
 void launch_series(const SeriesArgs &a, hipStream_t s)
 {
-    if (a.N <= SR_SMALL)
+    if (a.N <= SR_SMALL / 2 && a.st)
+        hipLaunchKernelGGL((k_series<4, 2, 2>), dim3((a.N + 3) / 4), dim3(512), 0, s, a);
+    else if (a.N <= SR_SMALL && a.st)
+        hipLaunchKernelGGL((k_series<4, 2, 2, 4>), dim3((a.N + 3) / 4), dim3(512), 0, s, a);
+    else if (a.N <= SR_SMALL)
         hipLaunchKernelGGL((k_series<8, 1, 4>), dim3((a.N + 7) / 8), dim3(512), 0, s, a);
     else
         hipLaunchKernelGGL((k_series<SR_B, SR_WPR, SR_NBW>), dim3((a.N + SR_B - 1) / SR_B),

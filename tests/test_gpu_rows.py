@@ -258,3 +258,37 @@ def test_larger_series_on_streams():
         jobs[0] = (w, jobs[0][1], rpy.context_for(w))
     for x, y in zip(*res):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("size", [(1, 255), (8, 32), (1, 257), (3, 127), (32, 16)])
+def test_adaptive_series_workgroups(size):
+    """Adaptive series on four rows per workgroup (two waves per row), around the
+    256 beads where its register limit changes: orders and sums as by products of
+    tiles, on one context after a fixed order, and four contexts on four
+    streams as one after the other."""
+    w, pos, a, b = _pair(*size, cheb_keep=100)
+    a.build(pos)
+    b.build(pos)
+    v = _vec(w, 1) * 0.03
+    for n, tol in ((7, 1e-2), (30, 1e-3), (2, 1e-1)):
+        _close(a.sqrt_apply(v, n, 0.04, 40.0), b.sqrt_apply(v, n, 0.04, 40.0))
+        x, y = (c.sqrt_adaptive(v, 0.04, 40.0, tol, 90, allow_etol=True) for c in (a, b))
+        assert x[2] == y[2]
+        _close(x[0], y[0])
+        assert abs(x[1].item() ** 2 - y[1].item() ** 2) < 1e-12
+    ctxs = [rpy.context_for(w, cheb_keep=100) for _ in range(4)]
+    streams = [torch.cuda.Stream() for _ in ctxs]
+    bp = rpy.make_bd_params(dt=1e-3, n_cheb=0, d_min=0.04, d_max=40.0, tol=1e-2, n_max=60)
+    res = []
+    for together in (False, True):
+        ps = [pos.clone() for _ in ctxs]
+        torch.cuda.synchronize()
+        for step in range(12):
+            for k, (c, s) in enumerate(zip(ctxs, streams)):
+                c.step(ps[k], bp, seed=k, step=step, stream=s)
+                if not together:
+                    s.synchronize()
+        torch.cuda.synchronize()
+        res.append(ps)
+    for x, y in zip(*res):
+        assert torch.equal(x, y)
