@@ -3,7 +3,7 @@
 // (rpy_rows.hip).
 //
 // Such a product is a few microseconds of work behind four of launch.  Here a
-// term takes 2.0 us at N = 100, with the trials of the adaptive order 3.0
+// term takes 2.0 us at N = 100, with the trials of the adaptive order 2.5
 // at N = 400, and 4.8 at N = 1000 (one launch per term: 3.9, 5.6 plus the check of each
 // order, and 12.3),
 // bound by the round trip of the new vector through memory:
