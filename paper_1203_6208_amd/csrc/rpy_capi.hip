@@ -33,8 +33,10 @@ struct rpy_ctx {
     double *Bv[2] = {nullptr, nullptr};  // [max_rhs][3N] Chebyshev vectors
     double *ddw = nullptr;    // [max_rhs][3N] D.dW
     double *acc = nullptr;    // [max_rhs][3N] scratch accumulator
-    // the phase matrix c.eph is valid for wrap generation eph_gen
-    uint64_t wrap_gen = 1, eph_gen = 0;
+    // the phase matrix c.eph is valid for wrap generation eph_gen, inside capture
+    // cap_id for cap_eph_gen
+    uint64_t wrap_gen = 1, eph_gen = 0, cap_eph_gen = 0;
+    unsigned long long cap = 0, cap_id = 0;   // capture this call is part of (0: none), the last one
     // with c.drow the stored tiles and the rows are each formed when a product
     // needs them; they hold D of the wrap generations tiles_gen and rows_gen.
     // captured: some call has been captured into a graph, whose replays this
@@ -684,6 +686,26 @@ struct ProfScope {
     }
 };
 
+// At the start of a call: the capture its stream is in.  What a capture forms has not
+// run, and what a replay forms is not seen here: inside a capture only what that
+// capture formed counts, and once some call was captured an eager call forms the phases
+// anew.
+static void begin_call(rpy_ctx *x, hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (hipStreamGetCaptureInfo(s, &st, &id) != hipSuccess) {
+        (void)hipGetLastError();
+        st = hipStreamCaptureStatusNone;
+    }
+    x->cap = st == hipStreamCaptureStatusNone ? 0 : id ? id : ~0ull;
+    if (x->cap && x->cap != x->cap_id) {
+        x->cap_id = x->cap;
+        x->cap_eph_gen = 0;
+    }
+    if (!x->cap && x->cap_id) x->eph_gen = 0;
+}
+
 // Whether products of `m` vectors, about `products` of them on the present
 // positions, go by rows (rpy_rows.hip).  Forming the rows costs more than the
 // tiles by the octant sums, 10 us at N = 400 and 80 at N = 1400; a product by
@@ -704,10 +726,13 @@ static bool use_rows(rpy_ctx *x, int m, int products, hipStream_t s)
 }
 
 // D of the present positions in the form that about `products` products of m
-// vectors are to use, unless it is there already.
-static void form_tensor(rpy_ctx *x, int products, hipStream_t s, int m = 1)
+// vectors are to use, unless it is there already.  moved: the call has set new
+// positions.
+static void form_tensor(rpy_ctx *x, int products, hipStream_t s, int m, bool moved)
 {
     const Ctx &c = x->c;
+    begin_call(x, s);
+    if (!moved && !c.drow) return;
     const bool rows = use_rows(x, m, products, s);
     // by rows as well where only they are formed and the products can use them
     if (rows ? x->rows_gen == x->wrap_gen : c.drow && x->tiles_gen == x->wrap_gen) return;
@@ -738,7 +763,7 @@ extern "C" int rpy_ewald_build(rpy_ctx *x, const double *pos, void *stream)
     if (!x || !pos) return RPY_EINVAL;
     launch_wrap_tables(x->c, pos, S(stream));
     ++x->wrap_gen;
-    form_tensor(x, 1, S(stream));
+    form_tensor(x, 1, S(stream), 1, true);
     return check_launch("rpy_ewald_build");
 }
 
@@ -781,9 +806,10 @@ static void product(rpy_ctx *x, const double *v, int m, int prec, const EpiArgs 
         }
         {
             ProfScope ps(x, RPY_PROF_KSPACE, s);
-            if (x->eph_gen != x->wrap_gen) {   // positions changed since the last phases
+            uint64_t &gen = x->cap ? x->cap_eph_gen : x->eph_gen;
+            if (gen != x->wrap_gen) {   // positions changed since the last phases
                 launch_block_phases(c, s);
-                x->eph_gen = x->wrap_gen;
+                gen = x->wrap_gen;
             }
             launch_block_sf(c, m, prec, s);
         }
@@ -816,7 +842,7 @@ extern "C" int rpy_apply(rpy_ctx *x, const double *v, double *out, int m, int pr
     f.mode = EPI_APPLY;
     f.m = m;
     f.vout = out;
-    if (x->c.drow) form_tensor(x, 1, S(stream), m);
+    form_tensor(x, 1, S(stream), m, false);
     product(x, v, m, prec, f, S(stream));
     return check_launch("rpy_apply");
 }
@@ -1009,7 +1035,7 @@ extern "C" int chebyshev_sqrt_apply(rpy_ctx *x, const double *dw, double *out, i
         snprintf(g_err, sizeof g_err, "the adaptive order needs cheb_keep >= n_cheb");
         return RPY_EINVAL;
     }
-    if (c.drow) form_tensor(x, n_cheb - 1, s, m);
+    form_tensor(x, n_cheb - 1, s, m, false);
     if (tol > 0) {
         if (by_series(x, m, n_cheb)) {
             series_explicit(x, dw, out, adapt_first(0, d_min, d_max, n_cheb), n_cheb, d_min, d_max,
@@ -1139,7 +1165,7 @@ extern "C" int rpy_lanczos_bounds(rpy_ctx *x, int n_iter, uint64_t seed, const d
     const Ctx &c = x->c;
     const int n3 = c.n3;
     double *qa = x->Bv[0], *qb = x->Bv[1], *w = x->acc;
-    if (c.drow) form_tensor(x, n_iter, s);
+    form_tensor(x, n_iter, s, 1, false);
     if (!start) {
         launch_noise(x->dW, n3, seed, 0, 1.0, s);
         start = x->dW;
@@ -1190,7 +1216,7 @@ extern "C" int chebyshev_sqrt_adaptive(rpy_ctx *x, const double *dw, double *out
         return RPY_EINVAL;
     hipStream_t s = S(stream);
     Ctx &c = x->c;
-    if (c.drow) form_tensor(x, n_max - 1, s, m);
+    form_tensor(x, n_max - 1, s, m, false);
     const int floor_n = n_start >= 2 ? n_start : 0;
     if (by_series(x, m, n_max)) {
         series_explicit(x, dw, out, adapt_first(floor_n, d_min, d_max, n_max), n_max, d_min, d_max,
@@ -1253,7 +1279,7 @@ extern "C" int rpy_u_forward(rpy_ctx *x, const double *pos, const double *F, con
     const size_t nv = (size_t)c.n3;
     launch_wrap_tables(c, pos, s);
     ++x->wrap_gen;
-    form_tensor(x, n_cheb, s);
+    form_tensor(x, n_cheb, s, 1, true);
     EpiArgs f{};
     f.mode = EPI_APPLY;
     f.m = 1;
@@ -1286,7 +1312,7 @@ extern "C" int rpy_u_vjp(rpy_ctx *x, const double *pos, const double *F, const d
     const size_t nv = (size_t)c.n3;
     launch_wrap_tables(c, pos, s);
     ++x->wrap_gen;
-    form_tensor(x, n_cheb, s);
+    form_tensor(x, n_cheb, s, 1, true);
     launch_cheb_coeffs(c, n_cheb, RPY_BOUNDS_EXPLICIT, 0.0, d_min, d_max, nullptr, s);
     size_t ps = nv;
     if (!vh) {   // recompute V_0 .. V_{n_cheb-1}
@@ -1355,7 +1381,7 @@ extern "C" int rpy_bounds(rpy_ctx *x, int rule, double C, double *d_min, double 
     f.mode = EPI_APPLY;
     f.m = m;
     f.vout = x->Y + nv;
-    if (c.drow) form_tensor(x, 1, s, m);
+    form_tensor(x, 1, s, m, false);
     product(x, v, m, RPY_PREC_F64, f, s);
     launch_cheb_coeffs(c, 2, rule, C, 0, 0, x->Y + nv, s);
     int rc = check_launch("rpy_bounds");
@@ -1494,7 +1520,7 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
         ev_forces(x, c.rt, bp->ev_zstar, bp->ev_dstar, bp->ev_rcut, x->F, x->side);
         HIP_TRY(hipEventRecord(x->join, x->side));
     }
-    form_tensor(x, nmax, s);
+    form_tensor(x, nmax, s, 1, true);
     if (ev) HIP_TRY(hipStreamWaitEvent(s, x->join, 0));
     // the drift product: F, then U+ (paper and dilute rules) and U- (dilute),
     // then dW; D.F lands in Y, D.U+ in Y + nv, D.dW last
@@ -1620,7 +1646,7 @@ extern "C" int rpy_real_space_dense(rpy_ctx *x, double *out, void *stream)
         snprintf(g_err, sizeof g_err, "the low-memory form stores no real-space matrix");
         return RPY_EINVAL;
     }
-    if (x->c.drow) form_tensor(x, 1, S(stream), MAX_RHS);   // the tiles hold the real-space part
+    form_tensor(x, 1, S(stream), MAX_RHS, false);   // the tiles hold the real-space part
     launch_dense_copy(x->c, out, S(stream));
     return check_launch("rpy_real_space_dense");
 }
