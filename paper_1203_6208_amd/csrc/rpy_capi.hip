@@ -43,6 +43,7 @@ struct rpy_ctx {
     // bookkeeping does not see -- from then on the context uses the tiles only
     uint64_t tiles_gen = 0, rows_gen = 0;
     bool captured = false;
+    bool rows = false;        // the products of the present call go by rows
     // series kernel: number of its next call's first term, bound of its waits
     // (10 ms; a wait is microseconds unless the kernel is not fully resident)
     uint32_t series_epoch = 1;
@@ -726,17 +727,19 @@ static bool use_rows(rpy_ctx *x, int m, int products, hipStream_t s)
 }
 
 // D of the present positions in the form that about `products` products of m
-// vectors are to use, unless it is there already.  moved: the call has set new
-// positions.
+// vectors are to use, unless it is there already.  The form follows from the box, m and
+// products alone: with the form another call has left, a product's bits would depend on
+// the calls before it.  (So a build of more than ROWS_EAGER beads and then a series form
+// both: the tiles belong to the build, 10 to 20 us at 257 to 1024 beads.)  moved: the call
+// has set new positions.
 static void form_tensor(rpy_ctx *x, int products, hipStream_t s, int m, bool moved)
 {
     const Ctx &c = x->c;
     begin_call(x, s);
     if (!moved && !c.drow) return;
     const bool rows = use_rows(x, m, products, s);
-    // by rows as well where only they are formed and the products can use them
+    x->rows = rows;
     if (rows ? x->rows_gen == x->wrap_gen : c.drow && x->tiles_gen == x->wrap_gen) return;
-    if (!rows && m <= 4 && c.drow && !x->captured && x->rows_gen == x->wrap_gen) return;
     ProfScope ps(x, RPY_PROF_BUILD, s);
     if (rows) {
         launch_build_rows(c, s);
@@ -752,11 +755,8 @@ static void form_tensor(rpy_ctx *x, int products, hipStream_t s, int m, bool mov
     }
 }
 
-// Whether a product of m vectors runs by rows now.
-static bool by_rows(const rpy_ctx *x, int m)
-{
-    return x->c.drow && m <= 4 && !x->captured && x->rows_gen == x->wrap_gen;
-}
+// Whether a product of m vectors of this call runs by rows.
+static bool by_rows(const rpy_ctx *x, int m) { return x->rows && m <= 4; }
 
 extern "C" int rpy_ewald_build(rpy_ctx *x, const double *pos, void *stream)
 {
