@@ -22,6 +22,10 @@ struct Prof {
     int n[RPY_PROF_KINDS] = {};
 };
 
+// Forms of D of a set of positions: the stored tiles, the complete tensor by rows
+// (c.drow), the phase matrix of the block product (c.eph).
+enum Form { TILES = 0, ROWS = 1, PHASES = 2, FORMS = 3 };
+
 struct rpy_ctx {
     Ctx c;
     Prof prof;
@@ -33,16 +37,10 @@ struct rpy_ctx {
     double *Bv[2] = {nullptr, nullptr};  // [max_rhs][3N] Chebyshev vectors
     double *ddw = nullptr;    // [max_rhs][3N] D.dW
     double *acc = nullptr;    // [max_rhs][3N] scratch accumulator
-    // the phase matrix c.eph is valid for wrap generation eph_gen, inside capture
-    // cap_id for cap_eph_gen
-    uint64_t wrap_gen = 1, eph_gen = 0, cap_eph_gen = 0;
+    // generation of the positions, and the one each form of D holds: of eager calls (gen)
+    // and inside capture cap_id (cap_gen)
+    uint64_t wrap_gen = 1, gen[FORMS] = {}, cap_gen[FORMS] = {};
     unsigned long long cap = 0, cap_id = 0;   // capture this call is part of (0: none), the last one
-    // with c.drow the stored tiles and the rows are each formed when a product
-    // needs them; they hold D of the wrap generations tiles_gen and rows_gen.
-    // captured: some call has been captured into a graph, whose replays this
-    // bookkeeping does not see -- from then on the context uses the tiles only
-    uint64_t tiles_gen = 0, rows_gen = 0;
-    bool captured = false;
     bool rows = false;        // the products of the present call go by rows
     // series kernel: number of its next call's first term, bound of its waits
     // (10 ms; a wait is microseconds unless the kernel is not fully resident)
@@ -687,10 +685,20 @@ struct ProfScope {
     }
 };
 
+// Products by rows (rpy_rows.hip) of up to 4 vectors.  Forming the rows costs more than the
+// tiles by the octant sums, 10 us at N = 400 and 80 at N = 1400; a product by
+// rows saves 10 and 6 us.  Up to ROWS_EAGER beads they pay from the first.
+constexpr int ROWS_EAGER = 256;
+constexpr int ROWS_PRODUCTS = 8;
+
+// The form that every call which sets positions leaves behind.
+static Form primary(const Ctx &c) { return c.drow && c.N <= ROWS_EAGER ? ROWS : TILES; }
+
 // At the start of a call: the capture its stream is in.  What a capture forms has not
-// run, and what a replay forms is not seen here: inside a capture only what that
-// capture formed counts, and once some call was captured an eager call forms the phases
-// anew.
+// run, and what a replay forms is not seen here.  Inside a capture a form counts if the
+// same capture has formed it, the primary one also if an eager call has: every
+// later call that sets positions, captured or not, forms that anew.  Once some call was
+// captured an eager call trusts the primary form and forms the others itself.
 static void begin_call(rpy_ctx *x, hipStream_t s)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
@@ -702,28 +710,38 @@ static void begin_call(rpy_ctx *x, hipStream_t s)
     x->cap = st == hipStreamCaptureStatusNone ? 0 : id ? id : ~0ull;
     if (x->cap && x->cap != x->cap_id) {
         x->cap_id = x->cap;
-        x->cap_eph_gen = 0;
+        for (uint64_t &g : x->cap_gen) g = 0;
     }
-    if (!x->cap && x->cap_id) x->eph_gen = 0;
+    if (!x->cap && x->cap_id)
+        for (int f = 0; f < FORMS; ++f)
+            if (f != primary(x->c)) x->gen[f] = 0;
 }
 
-// Whether products of `m` vectors, about `products` of them on the present
-// positions, go by rows (rpy_rows.hip).  Forming the rows costs more than the
-// tiles by the octant sums, 10 us at N = 400 and 80 at N = 1400; a product by
-// rows saves 10 and 6 us.  Up to ROWS_EAGER beads they pay from the first.
-constexpr int ROWS_EAGER = 256;
-constexpr int ROWS_PRODUCTS = 8;
-static bool use_rows(rpy_ctx *x, int m, int products, hipStream_t s)
+// Whether form f has to be formed for the present positions; it then counts as formed.
+static bool stale(rpy_ctx *x, Form f)
+{
+    if (x->cap && f == primary(x->c) && x->gen[f] == x->wrap_gen) return false;
+    uint64_t &g = x->cap ? x->cap_gen[f] : x->gen[f];
+    if (g == x->wrap_gen) return false;
+    g = x->wrap_gen;
+    return true;
+}
+
+static void form(rpy_ctx *x, Form f, hipStream_t s)
+{
+    if (!stale(x, f)) return;
+    ProfScope ps(x, RPY_PROF_BUILD, s);
+    if (f == ROWS) launch_build_rows(x->c, s);
+    else launch_build_tiles(x->c, s);
+}
+
+// Whether a call with about `products` products of m vectors goes by rows.
+static bool use_rows(const rpy_ctx *x, int m, int products)
 {
     const Ctx &c = x->c;
-    if (!c.drow) return false;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        x->captured = true;
-    }
-    if (st != hipStreamCaptureStatusNone) x->captured = true;
-    return !x->captured && m <= 4 && (c.N <= ROWS_EAGER || products >= ROWS_PRODUCTS);
+    if (!c.drow || m > 4) return false;
+    if (x->cap) return primary(c) == ROWS;
+    return c.N <= ROWS_EAGER || products >= ROWS_PRODUCTS;
 }
 
 // D of the present positions in the form that about `products` products of m
@@ -731,28 +749,13 @@ static bool use_rows(rpy_ctx *x, int m, int products, hipStream_t s)
 // products alone: with the form another call has left, a product's bits would depend on
 // the calls before it.  (So a build of more than ROWS_EAGER beads and then a series form
 // both: the tiles belong to the build, 10 to 20 us at 257 to 1024 beads.)  moved: the call
-// has set new positions.
+// has set new positions (and called begin_call).
 static void form_tensor(rpy_ctx *x, int products, hipStream_t s, int m, bool moved)
 {
-    const Ctx &c = x->c;
-    begin_call(x, s);
-    if (!moved && !c.drow) return;
-    const bool rows = use_rows(x, m, products, s);
-    x->rows = rows;
-    if (rows ? x->rows_gen == x->wrap_gen : c.drow && x->tiles_gen == x->wrap_gen) return;
-    ProfScope ps(x, RPY_PROF_BUILD, s);
-    if (rows) {
-        launch_build_rows(c, s);
-        x->rows_gen = x->wrap_gen;
-    } else {
-        launch_build_tiles(c, s);
-        // a captured build has not run: later calls form the tiles again
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        if (c.drow && (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone))
-            (void)hipGetLastError();
-        else
-            x->tiles_gen = x->wrap_gen;
-    }
+    if (!moved) begin_call(x, s);
+    x->rows = use_rows(x, m, products);
+    if (moved && x->cap_id) form(x, primary(x->c), s);   // what captured products read
+    if (moved || x->c.drow) form(x, x->rows ? ROWS : TILES, s);
 }
 
 // Whether a product of m vectors of this call runs by rows.
@@ -761,6 +764,7 @@ static bool by_rows(const rpy_ctx *x, int m) { return x->rows && m <= 4; }
 extern "C" int rpy_ewald_build(rpy_ctx *x, const double *pos, void *stream)
 {
     if (!x || !pos) return RPY_EINVAL;
+    begin_call(x, S(stream));
     launch_wrap_tables(x->c, pos, S(stream));
     ++x->wrap_gen;
     form_tensor(x, 1, S(stream), 1, true);
@@ -806,11 +810,7 @@ static void product(rpy_ctx *x, const double *v, int m, int prec, const EpiArgs 
         }
         {
             ProfScope ps(x, RPY_PROF_KSPACE, s);
-            uint64_t &gen = x->cap ? x->cap_eph_gen : x->eph_gen;
-            if (gen != x->wrap_gen) {   // positions changed since the last phases
-                launch_block_phases(c, s);
-                gen = x->wrap_gen;
-            }
+            if (stale(x, PHASES)) launch_block_phases(c, s);
             launch_block_sf(c, m, prec, s);
         }
         ProfScope ps(x, RPY_PROF_EPI, s);
@@ -877,10 +877,11 @@ static void cheb_run(rpy_ctx *x, const double *dw, double *out, int m, int n_che
     }
 }
 
-// Whether the series of one vector up to order nmax runs in one launch.
+// Whether the series of one vector up to order nmax runs in one launch (whose words
+// carry numbers given here, so not one that is replayed).
 static bool by_series(const rpy_ctx *x, int m, int nmax)
 {
-    return x->c.series && m == 1 && nmax <= SERIES_ORDERS && by_rows(x, 1);
+    return x->c.series && !x->cap && m == 1 && nmax <= SERIES_ORDERS && by_rows(x, 1);
 }
 
 // The arguments of such a series on V_0 = dw into out, n terms or, with st,
@@ -1277,6 +1278,7 @@ extern "C" int rpy_u_forward(rpy_ctx *x, const double *pos, const double *F, con
     hipStream_t s = S(stream);
     Ctx &c = x->c;
     const size_t nv = (size_t)c.n3;
+    begin_call(x, s);
     launch_wrap_tables(c, pos, s);
     ++x->wrap_gen;
     form_tensor(x, n_cheb, s, 1, true);
@@ -1310,6 +1312,7 @@ extern "C" int rpy_u_vjp(rpy_ctx *x, const double *pos, const double *F, const d
     }
     hipStream_t s = S(stream);
     const size_t nv = (size_t)c.n3;
+    begin_call(x, s);
     launch_wrap_tables(c, pos, s);
     ++x->wrap_gen;
     form_tensor(x, n_cheb, s, 1, true);
@@ -1484,6 +1487,7 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
     if (rc) return rc;
     hipStream_t s = S(stream);
     const size_t nv = (size_t)c.n3;
+    begin_call(x, s);
     const int floor_n = adapt ? (bp->n_cheb >= 2 ? bp->n_cheb : 0) : -1;
     const int nmax = adapt ? bp->n_max : bp->n_cheb;
     // The first Chebyshev product rides with the drift product: one FP64
@@ -1502,7 +1506,7 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
     pre.sdt = sqrt(bp->dt);
     // an explicit interval's coefficients, where the series kernel will take them
     const bool coef = c.series && rule == RPY_BOUNDS_EXPLICIT && nmax <= SERIES_ORDERS &&
-                      use_rows(x, 1, nmax, s);
+                      !x->cap && use_rows(x, 1, nmax);
     if (coef) {
         const int n0 = adapt ? adapt_first(floor_n, bp->d_min, bp->d_max, nmax) : nmax;
         pre.coef = series_coef_args(c, n0, 1, bp->d_min, bp->d_max, adapt ? c.adapt : nullptr);
