@@ -519,7 +519,8 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
     const size_t mv = (size_t)c.rhs_cap * nv;
     std::vector<int> roff;
     std::vector<double> rwk;
-    const bool rows = !c.lma && c.lowp == RPY_PREC_F64 && c.N <= ROWS_MAX &&
+    const bool rows = !c.lma && c.lowp == RPY_PREC_F64 &&
+                      c.N <= (c.nk > FOLD_MIN_NK ? ROWS_MAX : SERIES_MAX) &&
                       make_rows_weights(c, roff, rwk);
     c.row_ld = (c.N + 127) / 128 * 128;
     const bool series = rows && c.N <= SERIES_MAX;
@@ -685,11 +686,18 @@ struct ProfScope {
     }
 };
 
-// Products by rows (rpy_rows.hip) of up to 4 vectors.  Forming the rows costs more than the
-// tiles by the octant sums, 10 us at N = 400 and 80 at N = 1400; a product by
-// rows saves 10 and 6 us.  Up to ROWS_EAGER beads they pay from the first.
+// Products by rows (rpy_rows.hip) of up to 4 vectors.  Forming the rows costs 21 us at
+// N = 400 and 62 at N = 1000 (106 with 1398 wave vectors); a term of one vector
+// then takes 2.4 and 4.9 us (series kernel) and a product of 2, 3, 4 vectors 8.5, 11, 14 and
+// 14.6, 17.8, 20.9 us, by tiles 12.7 and 14.3, 18.5, 24, 31 and 22, 27, 37.  So they pay, formed
+// beside the tiles of a build, from 2 products on at N = 400 and from 4 to 9 at
+// N = 1024; up to ROWS_EAGER beads from the first.  Past 1024 beads there is no series
+// kernel and a product by rows takes what one by tiles does (N = 1100: 16 and 16, 22 and 22
+// us; N = 1536: 24 and 19, 47 and 41 for four vectors), except with more wave vectors than the
+// back-projection stages: 16 and 27 us at N = 1100, 17.2 and 27.7 at N = 1280, for 156 us of
+// forming the rows, paid back by 15 products there and by 20 to 26 at N = 1400.
 constexpr int ROWS_EAGER = 256;
-constexpr int ROWS_PRODUCTS = 8;
+constexpr int ROWS_PRODUCTS = 8, ROWS_PRODUCTS_LARGE = 16;
 
 // The form that every call which sets positions leaves behind.
 static Form primary(const Ctx &c) { return c.drow && c.N <= ROWS_EAGER ? ROWS : TILES; }
@@ -741,7 +749,7 @@ static bool use_rows(const rpy_ctx *x, int m, int products)
     const Ctx &c = x->c;
     if (!c.drow || m > 4) return false;
     if (x->cap) return primary(c) == ROWS;
-    return c.N <= ROWS_EAGER || products >= ROWS_PRODUCTS;
+    return c.N <= ROWS_EAGER || products >= (c.N <= SERIES_MAX ? ROWS_PRODUCTS : ROWS_PRODUCTS_LARGE);
 }
 
 // D of the present positions in the form that about `products` products of m

@@ -449,7 +449,8 @@ struct Ctx {
     double *d64 = nullptr;       // [ntiles][TILE6], packed symmetric blocks
     float *p32 = nullptr;        // [ntiles][TILE6] packed planes, lowp FP32
     uint16_t *p16 = nullptr;     // [ntiles][TILE6] packed planes, lowp BF16
-    // complete tensor by rows (rpy_rows.hip; FP64 contexts of at most ROWS_MAX beads)
+    // complete tensor by rows (rpy_rows.hip; FP64 contexts of at most
+    // ROWS_MAX beads)
     int row_ld = 0;              // columns stored per plane of a row
     double *drow = nullptr;      // [N][6][row_ld]
     int *row_off = nullptr;      // octant weights of the reciprocal sum: first chunk per n_x (in smooth)
@@ -542,7 +543,7 @@ void launch_build_tiles(const Ctx &c, hipStream_t s);
 void launch_dense_copy(const Ctx &c, double *out, hipStream_t s);
 // complete tensor by rows (rpy_rows.hip): the build from the wrapped positions
 // and phase tables, and a product of up to 4 vectors with its epilogue
-constexpr int ROWS_MAX = 1536;   // beads
+constexpr int ROWS_MAX = 1280;   // beads (SERIES_MAX up to FOLD_MIN_NK wave vectors: use_rows says why)
 constexpr int rows_nz(int nmax) { return nmax <= 6 ? 7 : 9; }
 bool make_rows_weights(const Ctx &c, std::vector<int> &off, std::vector<double> &w);
 void launch_build_rows(const Ctx &c, hipStream_t s);

@@ -143,7 +143,7 @@ __device__ inline void recip_block(int nmax, int n2max, int x0,
 // in a fixed order.  Off the diagonal the mirrored blocks (equal, every pair
 // block being symmetric and even) go out as well, as runs of R columns.
 // Bounded by its multiply-adds, 1834 per pair at |n|^2 <= 44 and 3714 at 77:
-// 100 us at N = 1400 (39 TFLOP/s), 113 us at N = 1000 with the larger set.
+// 62 us at N = 1000 and 106 us there with the larger set (35 TFLOP/s).
 template <int NP, int NF, int NZ, int G, int KS>
 __global__ __launch_bounds__(256) void k_build_rows(int N, int nmax, int n2max, int ld,
                                                     const int2 *__restrict__ tile_ij,
@@ -299,8 +299,10 @@ void launch_build_rows(const Ctx &c, hipStream_t s)
 // are combined by a fixed xor tree that leaves component c in lane c, then the
 // waves of a row in order.
 // One vector, per product with its recurrence step: N = 100 3.8 us, 400 5.6,
-// 1000 11.4 (48 MB), 1400 19.8 (94 MB), against 15.5, 15.9, 24 (at 618 wave
-// vectors) and 26 us in two launches by tiles.
+// 1000 11.4 (48 MB), against 15.5, 15.9 and 24 us (at 618 wave vectors) in two launches by
+// tiles.  As many vectors per launch as stage in the workgroup's LDS (24 ld bytes each, all
+// four up to 1280 beads): with 64 KiB of it three vectors at N = 1000 take 26 instead of 17.8 us, four
+// at N = 1280 47 instead of 35.
 // flip: workgroups in reverse order (keeping blockIdx mod 8, the XCD), so that
 // a product starts on the rows its XCD's L2 read last.
 constexpr int ROW_U = 4;
@@ -463,9 +465,8 @@ void launch_row_product(const Ctx &c, const double *v, const EpiArgs &f, hipStre
 {
     static_assert(ROWS_MAX <= 3 * 128 * ROW_U, "a row is at most three waves");
     for (int j0 = 0; j0 < f.m;) {
-        // as many vectors per launch as stage in 64 KiB of LDS (24 ld bytes each)
         int mc = f.m - j0 < 4 ? f.m - j0 : 4;
-        while (mc > 1 && (size_t)24 * c.row_ld * mc > 65536 - 1024) --mc;
+        while (mc > 1 && (size_t)24 * c.row_ld * mc > (size_t)c.lds_max - 2048) --mc;   // static LDS below 2 KiB
         if (mc == 4) row_launch<4>(c, j0, v, f, s);
         else if (mc == 3) row_launch<3>(c, j0, v, f, s);
         else if (mc == 2) row_launch<2>(c, j0, v, f, s);
