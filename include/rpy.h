@@ -386,6 +386,16 @@ enum {
 int rpy_profile_enable(rpy_ctx *c, int cap);
 int rpy_profile_read(rpy_ctx *c, int kind, int64_t *count, double *total_ms);
 
+/* FP64 boxes of at most 1024 beads run the Chebyshev series of one vector (of at most 128
+ * terms, outside graph capture) in one launch whose workgroups wait for each other.  A wait that is not answered
+ * within 10 ms -- the launch was only partly resident beside other work on the
+ * GPU -- makes one workgroup run that series again alone: the same result, later.
+ * rpy_series_stats: how many series since the last read ran that way (HOST output;
+ * synchronises the stream and resets the count).  rpy_series_wait: the bound of a wait in
+ * units of 10 ns (default 1000000; negative: no wait is granted, for tests). */
+int rpy_series_stats(rpy_ctx *c, int64_t *alone, void *stream);
+void rpy_series_wait(rpy_ctx *c, int64_t ticks);
+
 /* Number of wave vectors in the half-space set used per product. */
 int rpy_num_kvectors(const rpy_ctx *c);
 

@@ -524,7 +524,7 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
                       make_rows_weights(c, roff, rwk);
     c.row_ld = (c.N + 127) / 128 * 128;
     const bool series = rows && c.N <= SERIES_MAX;
-    // coefficients, ring, vector words, partial-sum words, record, flag
+    // coefficients, ring, vector words, partial-sum words, record, flag and count
     constexpr size_t SW = 2 * 2 * 3 * SERIES_MAX, SP = 2 * 2 * 2 * SERIES_GROUPS;
     constexpr size_t SC = (SERIES_ORDERS + 1) * SERIES_ORDERS, SR = 3 * 3 * SERIES_MAX;
     constexpr size_t SERIES_DOUBLES = SC + SR + SW + SP + 2 + 1;
@@ -923,9 +923,21 @@ static SeriesArgs series_args(rpy_ctx *x, const double *dw, double *out, int n, 
     return a;
 }
 
-// For tests: the bound of the series kernel's waits, in 100 MHz ticks (negative:
-// every wait gives up at once, so that the finishing kernel runs the series).
 extern "C" void rpy_series_wait(rpy_ctx *x, int64_t ticks) { x->series_limit = ticks; }
+
+extern "C" int rpy_series_stats(rpy_ctx *x, int64_t *alone, void *stream)
+{
+    if (!x || !alone) return RPY_EINVAL;
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    int n = 0;
+    if (x->c.series) {
+        HIP_TRY(hipMemcpyAsync(&n, x->c.series_abort + 1, sizeof n, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        if (n) HIP_TRY(hipMemset(x->c.series_abort + 1, 0, sizeof n));
+    }
+    *alone = n;
+    return RPY_OK;
+}
 
 // First order of an adaptive call as the device computes it from the
 // interval (eq. nint, rounded half away from zero) or the caller's start.

@@ -461,7 +461,7 @@ struct Ctx {
     double *series_ring = nullptr;   // [3][3 SERIES_MAX]
     unsigned long long *series_words = nullptr, *series_part = nullptr;
     struct SeriesRec *series_rec = nullptr;
-    int *series_abort = nullptr;
+    int *series_abort = nullptr;       // [2] some wait ran out; series the finishing kernel ran
     double *part = nullptr;      // [nbt][rhs_cap][n3pad] tile-column partials
     // block products (5 to 16 vectors on the matrix cores, any tile precision)
     bool block = false;          // enabled: stored tiles and max_rhs >= BLOCK_MIN_RHS
@@ -574,7 +574,7 @@ struct SeriesArgs {
     unsigned long long *words, *part;   // the vectors and partial sums in flight
     uint32_t epoch;           // first of the numbers this call marks its words with
     long long limit;          // bound of a wait (100 MHz ticks)
-    int *abort_flag;
+    int *abort_flag;          // [2] raised by a wait that ran out; series run by the finishing kernel
     SeriesRec *rec;
     double *vh;               // for the finishing kernel alone: terms at vh + p ps
     size_t ps;

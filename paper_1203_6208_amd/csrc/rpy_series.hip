@@ -421,7 +421,10 @@ __global__ __launch_bounds__(SF_NT) void k_series_finish(SeriesArgs a, double *p
     }
     if (threadIdx.x == 0) {
         if (e_f) *e_f = ef;
-        if (redo) *a.abort_flag = 0;
+        if (redo) {
+            a.abort_flag[0] = 0;
+            ++a.abort_flag[1];
+        }
         if (adapt) {
             AdaptState *st = a.st;
             const bool ok = (ef > 0.0 ? ef : 0.0) < a.tol;

@@ -70,6 +70,8 @@ _SIG = {
     "rpy_philox4x32_10": (_i, [_v, _v, ctypes.c_int64, _v]),
     "rpy_host_pair_block": (_i, [_P(RpyParams), _P(_d), _i, _P(_d)]),
     "rpy_num_kvectors": (_i, [_v]),
+    "rpy_series_stats": (_i, [_v, _P(ctypes.c_int64), _v]),
+    "rpy_series_wait": (None, [_v, ctypes.c_int64]),
     "rpy_profile_enable": (_i, [_v, _i]),
     "rpy_profile_read": (_i, [_v, _i, _P(ctypes.c_int64), _P(_d)]),
     "rpy_strerror": (ctypes.c_char_p, [_i]),
@@ -182,6 +184,19 @@ def rpy_order_stats(ctx, stream=None):
     _check(_lib.rpy_order_stats(ctx, ctypes.byref(calls), ctypes.byref(mean), ctypes.byref(mx),
                                 ctypes.byref(missed), _stream(stream)), "rpy_order_stats")
     return calls.value, mean.value, mx.value, missed.value
+
+
+def rpy_series_stats(ctx, stream=None) -> int:
+    """Series since the last read that one workgroup ran alone, because a wait of the
+    one-launch series was not answered in time."""
+    n = ctypes.c_int64()
+    _check(_lib.rpy_series_stats(ctx, ctypes.byref(n), _stream(stream)), "rpy_series_stats")
+    return n.value
+
+
+def rpy_series_wait(ctx, ticks: int) -> None:
+    """Bound of a wait of the one-launch series, in units of 10 ns (negative: none)."""
+    _lib.rpy_series_wait(ctx, int(ticks))
 
 
 def rpy_lanczos_bounds(ctx, n_iter: int, seed: int = 0, start: torch.Tensor = None,
