@@ -360,6 +360,11 @@ int rpy_philox4x32_10(const uint32_t *ctr_key, uint32_t *out, int64_t n,
 int rpy_host_pair_block(const rpy_params *p, const double *d, int self,
                         double *out);
 
+/* Host-only helper for tests: whether a box of n_beads may run the one-launch series on a device
+ * of `cus` compute units that hold `per_cu` of its workgroups each.  0: no (one launch per product);
+ * 1: not beside another series; 2: beside three others. */
+int rpy_host_series_use(int n_beads, int adaptive, int per_cu, int cus);
+
 /* Kernel timing for measurement.  rpy_profile_enable(c, cap) creates, once,
  * cap HIP event pairs per kernel class and from then on records a pair around
  * every launch of that class on the caller's stream (cap = 0 stops
@@ -387,7 +392,8 @@ int rpy_profile_enable(rpy_ctx *c, int cap);
 int rpy_profile_read(rpy_ctx *c, int kind, int64_t *count, double *total_ms);
 
 /* FP64 boxes of at most 1024 beads run the Chebyshev series of one vector (of at most 128
- * terms, outside graph capture) in one launch whose workgroups wait for each other.  A wait that is not answered
+ * terms, outside graph capture) in one launch whose workgroups wait for each other, where the device
+ * holds them all at once.  A wait that is not answered
  * within 10 ms -- the launch was only partly resident beside other work on the
  * GPU -- makes one workgroup run that series again alone: the same result, later.
  * rpy_series_stats: how many series since the last read ran that way (HOST output;

@@ -47,6 +47,8 @@ struct rpy_ctx {
     uint32_t series_epoch = 1;
     long long series_limit = 1000000;
     int series_dev = -1;      // device whose SeriesGate this context is counted in
+    SeriesUse series_use[2] = {SERIES_OFF, SERIES_OFF};   // of fixed and adaptive orders
+    bool series_big() const { return series_use[0] == SERIES_ORDERED || series_use[1] == SERIES_ORDERED; }
     // bd_step runs the excluded-volume forces on a second stream (default
     // priority) beside the tile build: fork after the wrap, join before the
     // drift product
@@ -54,9 +56,9 @@ struct rpy_ctx {
     hipEvent_t fork = nullptr, join = nullptr;
 };
 
-// The series kernel of a box past SERIES_SMALL beads takes nearly every compute
-// unit, and two of them (or one and a small one) started together from two
-// streams could each become resident in part and wait for the bound of their
+// A series kernel that leaves no room for three more (SERIES_ORDERED: a box past SERIES_SMALL
+// beads takes nearly every compute unit) and another one, started together from two
+// streams, could each become resident in part and wait for the bound of their
 // waits.  So while a device has such a context and any other that
 // runs series, their series kernels are ordered one after the other, by an event
 // recorded behind each; the calls around them overlap as before.  With one
@@ -86,7 +88,7 @@ static hipError_t gate_enter(rpy_ctx *x)   // before the device synchronisation 
     }
     x->series_dev = dev;
     ++g.all;
-    g.big += x->c.N > SERIES_SMALL;
+    g.big += x->series_big();
     return hipSuccess;
 }
 
@@ -95,7 +97,7 @@ static void gate_leave(rpy_ctx *x)   // after the device synchronisation of rpy_
     if (x->series_dev < 0) return;
     SeriesGate &g = g_gate[x->series_dev];
     std::lock_guard<std::mutex> lock(g.m);
-    g.big -= x->c.N > SERIES_SMALL;
+    g.big -= x->series_big();
     if (--g.all == 0) {
         (void)hipEventDestroy(g.ev);
         g.ev = nullptr;
@@ -523,7 +525,18 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
                       c.N <= (c.nk > FOLD_MIN_NK ? ROWS_MAX : SERIES_MAX) &&
                       make_rows_weights(c, roff, rwk);
     c.row_ld = (c.N + 127) / 128 * 128;
-    const bool series = rows && c.N <= SERIES_MAX;
+    bool series = rows && c.N <= SERIES_MAX;
+    if (series) {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+            (void)hipGetLastError();
+            cus = 0;
+        }
+        for (int a = 0; a < (c.cheb_keep ? 2 : 1); ++a)
+            x->series_use[a] = series_use(series_groups(c.N, a), series_per_cu(c.N, a), cus);
+        series = x->series_use[0] != SERIES_OFF || x->series_use[1] != SERIES_OFF;
+    }
     // coefficients, ring, vector words, partial-sum words, record, flag and count
     constexpr size_t SW = 2 * 2 * 3 * SERIES_MAX, SP = 2 * 2 * 2 * SERIES_GROUPS;
     constexpr size_t SC = (SERIES_ORDERS + 1) * SERIES_ORDERS, SR = 3 * 3 * SERIES_MAX;
@@ -887,9 +900,10 @@ static void cheb_run(rpy_ctx *x, const double *dw, double *out, int m, int n_che
 
 // Whether the series of one vector up to order nmax runs in one launch (whose words
 // carry numbers given here, so not one that is replayed).
-static bool by_series(const rpy_ctx *x, int m, int nmax)
+static bool by_series(const rpy_ctx *x, int m, int nmax, bool adaptive)
 {
-    return x->c.series && !x->cap && m == 1 && nmax <= SERIES_ORDERS && by_rows(x, 1);
+    return x->series_use[adaptive] != SERIES_OFF && !x->cap && m == 1 && nmax <= SERIES_ORDERS &&
+           by_rows(x, 1);
 }
 
 // The arguments of such a series on V_0 = dw into out, n terms or, with st,
@@ -1058,7 +1072,7 @@ extern "C" int chebyshev_sqrt_apply(rpy_ctx *x, const double *dw, double *out, i
     }
     form_tensor(x, n_cheb - 1, s, m, false);
     if (tol > 0) {
-        if (by_series(x, m, n_cheb)) {
+        if (by_series(x, m, n_cheb, true)) {
             series_explicit(x, dw, out, adapt_first(0, d_min, d_max, n_cheb), n_cheb, d_min, d_max,
                             tol, e_f, s);
             int rc = check_launch("chebyshev_sqrt_apply");
@@ -1072,7 +1086,7 @@ extern "C" int chebyshev_sqrt_apply(rpy_ctx *x, const double *dw, double *out, i
         if (rc || !n_used) return rc;
         return adapt_result(x, n_used, s);
     }
-    if (by_series(x, m, n_cheb)) {
+    if (by_series(x, m, n_cheb, false)) {
         series_explicit(x, dw, out, n_cheb, n_cheb, d_min, d_max, 0.0, e_f, s);
         if (n_used) *n_used = n_cheb;
         return check_launch("chebyshev_sqrt_apply");
@@ -1239,7 +1253,7 @@ extern "C" int chebyshev_sqrt_adaptive(rpy_ctx *x, const double *dw, double *out
     Ctx &c = x->c;
     form_tensor(x, n_max - 1, s, m, false);
     const int floor_n = n_start >= 2 ? n_start : 0;
-    if (by_series(x, m, n_max)) {
+    if (by_series(x, m, n_max, true)) {
         series_explicit(x, dw, out, adapt_first(floor_n, d_min, d_max, n_max), n_max, d_min, d_max,
                         tol, e_f, s);
         int rc = check_launch("chebyshev_sqrt_adaptive");
@@ -1525,8 +1539,8 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
     pre.step = step;
     pre.sdt = sqrt(bp->dt);
     // an explicit interval's coefficients, where the series kernel will take them
-    const bool coef = c.series && rule == RPY_BOUNDS_EXPLICIT && nmax <= SERIES_ORDERS &&
-                      !x->cap && use_rows(x, 1, nmax);
+    x->rows = use_rows(x, 1, nmax);
+    const bool series = by_series(x, 1, nmax, adapt), coef = series && rule == RPY_BOUNDS_EXPLICIT;
     if (coef) {
         const int n0 = adapt ? adapt_first(floor_n, bp->d_min, bp->d_max, nmax) : nmax;
         pre.coef = series_coef_args(c, n0, 1, bp->d_min, bp->d_max, adapt ? c.adapt : nullptr);
@@ -1549,7 +1563,6 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
     // the drift product: F, then U+ (paper and dilute rules) and U- (dilute),
     // then dW; D.F lands in Y, D.U+ in Y + nv, D.dW last
     const int nb = rule == RPY_BOUNDS_PAPER ? 1 : rule == RPY_BOUNDS_DILUTE ? 2 : 0;
-    const bool series = by_series(x, 1, nmax);
     if (coef) {
         // the interval needs no product: drift, series and update in two launches
         AdaptState *st = adapt ? c.adapt : nullptr;
@@ -1710,6 +1723,11 @@ extern "C" int rpy_host_pair_block(const rpy_params *p, const double *d, int sel
     const double v[9] = {b[0], b[1], b[2], b[1], b[3], b[4], b[2], b[4], b[5]};
     memcpy(out, v, sizeof v);
     return RPY_OK;
+}
+
+extern "C" int rpy_host_series_use(int n_beads, int adaptive, int per_cu, int cus)
+{
+    return n_beads < 1 || n_beads > SERIES_MAX ? 0 : series_use(series_groups(n_beads, adaptive != 0), per_cu, cus);
 }
 
 extern "C" int rpy_profile_enable(rpy_ctx *x, int cap)

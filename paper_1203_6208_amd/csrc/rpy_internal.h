@@ -552,7 +552,7 @@ void launch_row_product(const Ctx &c, const double *v, const EpiArgs &f, hipStre
 int rows_trial_chunks(int N);    // its partial sums of a trial per vector
 // The Chebyshev series of one vector in one launch (rpy_series.hip).
 constexpr int SERIES_MAX = 1024;     // beads
-constexpr int SERIES_SMALL = 512;    // up to this many take eight beads per workgroup
+constexpr int SERIES_SMALL = 512;    // up to this many take (8, 1, 4) or, adaptive, (4, 2, 2) of rpy_series.hip
 constexpr int SERIES_GROUPS = 256;   // workgroups at most
 constexpr int SERIES_ORDERS = 128;   // largest order
 struct SeriesRec {
@@ -589,6 +589,19 @@ CoefArgs series_coef_args(const Ctx &c, int n0, int explicit_, double dmin, doub
 void launch_series_coeffs(const Ctx &c, int n0, int n1, int explicit_, double dmin, double dmax,
                           AdaptState *st, hipStream_t s);
 void launch_series(const SeriesArgs &a, hipStream_t s);
+// Workgroups of the series kernel of N beads, and how many of them a compute unit holds (0: not
+// known).
+int series_groups(int N, bool adaptive);
+int series_per_cu(int N, bool adaptive);
+// Whether the series kernel may run: its workgroups wait for each other, so the device has to hold
+// all of them at once.  SERIES_FREE: four such kernels, one per hardware queue, as well;
+// SERIES_ORDERED: not beside another series kernel.
+enum SeriesUse { SERIES_OFF = 0, SERIES_ORDERED = 1, SERIES_FREE = 2 };
+inline SeriesUse series_use(int groups, int per_cu, int cus)
+{
+    const long held = (long)per_cu * cus;
+    return held < groups ? SERIES_OFF : held < 4l * groups ? SERIES_ORDERED : SERIES_FREE;
+}
 void launch_series_finish(const SeriesArgs &a, double *pos, double dt4, double *drift, double *noise,
                           double *e_f, hipStream_t s);
 // products: the tile-product kernel also computes tk of its input; the final

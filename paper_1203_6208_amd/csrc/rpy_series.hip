@@ -16,8 +16,10 @@
 // after it has read all of V_{p+1}, so every workgroup has read all of V_p by then.
 //
 // The wait needs all workgroups on the device at once (64 or, adaptive, 128 at most; past
-// 512 beads one per 4 beads, 256 at most, which the host keeps from starting
-// beside another).  They are, unless enough other kernels run at the same time that
+// 512 beads one per 4 beads, 256 at most).  rpy_create checks that the device holds them
+// (series_use), and the host keeps those that nearly fill it from starting beside another.
+// So they are, unless enough other kernels (or series of another process) run at the same time, or
+// the stream may use only a part of the compute units, that
 // some are only partly resident; so every wait is bounded: a workgroup that has
 // waited for its limit raises a flag, all of them leave, and the finishing
 // kernel, one workgroup that waits for nobody, then runs the series alone.
@@ -456,17 +458,40 @@ void launch_series_coeffs(const Ctx &c, int n0, int n1, int explicit_, double dm
                        series_coef_args(c, n0, explicit_, dmin, dmax, st));
 }
 
+struct SeriesForm {
+    void (*kernel)(SeriesArgs);
+    int rows, threads;
+};
+
+static SeriesForm series_form(int N, bool adaptive)
+{
+    if (N > SR_SMALL) return {k_series<SR_B, SR_WPR, SR_NBW>, SR_B, 64 * SR_B * SR_WPR};
+    if (!adaptive) return {k_series<8, 1, 4>, 8, 512};
+    return {N <= SR_SMALL / 2 ? k_series<4, 2, 2> : k_series<4, 2, 2, 4>, 4, 512};
+}
+
+int series_groups(int N, bool adaptive)
+{
+    const int r = series_form(N, adaptive).rows;
+    return (N + r - 1) / r;
+}
+
+int series_per_cu(int N, bool adaptive)
+{
+    const SeriesForm f = series_form(N, adaptive);
+    int per = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void *>(f.kernel),
+                                                     f.threads, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return per;
+}
+
 void launch_series(const SeriesArgs &a, hipStream_t s)
 {
-    if (a.N <= SR_SMALL / 2 && a.st)
-        hipLaunchKernelGGL((k_series<4, 2, 2>), dim3((a.N + 3) / 4), dim3(512), 0, s, a);
-    else if (a.N <= SR_SMALL && a.st)
-        hipLaunchKernelGGL((k_series<4, 2, 2, 4>), dim3((a.N + 3) / 4), dim3(512), 0, s, a);
-    else if (a.N <= SR_SMALL)
-        hipLaunchKernelGGL((k_series<8, 1, 4>), dim3((a.N + 7) / 8), dim3(512), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_series<SR_B, SR_WPR, SR_NBW>), dim3((a.N + SR_B - 1) / SR_B),
-                           dim3(64 * SR_B * SR_WPR), 0, s, a);
+    const SeriesForm f = series_form(a.N, a.st != nullptr);
+    hipLaunchKernelGGL(f.kernel, dim3((a.N + f.rows - 1) / f.rows), dim3(f.threads), 0, s, a);
 }
 
 void launch_series_finish(const SeriesArgs &a, double *pos, double dt4, double *drift, double *noise,

@@ -69,6 +69,7 @@ _SIG = {
     "rpy_gaussian_noise": (_i, [_v, ctypes.c_int64, ctypes.c_uint64, ctypes.c_uint64, _d, _v]),
     "rpy_philox4x32_10": (_i, [_v, _v, ctypes.c_int64, _v]),
     "rpy_host_pair_block": (_i, [_P(RpyParams), _P(_d), _i, _P(_d)]),
+    "rpy_host_series_use": (_i, [_i, _i, _i, _i]),
     "rpy_num_kvectors": (_i, [_v]),
     "rpy_series_stats": (_i, [_v, _P(ctypes.c_int64), _v]),
     "rpy_series_wait": (None, [_v, ctypes.c_int64]),
