@@ -92,16 +92,31 @@ __device__ inline bool take(const word_t *src, int q, int stride, int n, uint32_
     }
 }
 
+// The arithmetic below is written with its fused operations spelled out, so that the finishing
+// kernel, which runs a series again alone, rounds as the series kernel does.
+
 // y += the lane's two columns of a column block times their vector entries x.
 __device__ inline void row_block(const sr2 (&d)[6], const double *x, double &y0, double &y1, double &y2)
 {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const double x0 = x[3 * q], x1 = x[3 * q + 1], x2 = x[3 * q + 2];
-        y0 += d[0][q] * x0 + d[1][q] * x1 + d[2][q] * x2;
-        y1 += d[1][q] * x0 + d[3][q] * x1 + d[4][q] * x2;
-        y2 += d[2][q] * x0 + d[4][q] * x1 + d[5][q] * x2;
+        y0 += fma(d[2][q], x2, fma(d[1][q], x1, d[0][q] * x0));
+        y1 += fma(d[4][q], x2, fma(d[3][q], x1, d[1][q] * x0));
+        y2 += fma(d[5][q], x2, fma(d[4][q], x1, d[2][q] * x0));
     }
+}
+
+// V_1 = Y V_0 and V_p = 2 Y V_{p-1} - V_{p-2} from y = D V.
+__device__ inline double cheb_one(double ya, double yb, double y, double v) { return fma(ya, y, -(yb * v)); }
+__device__ inline double cheb_next(double ya, double yb, double y, double v, double vp)
+{
+    return fma(2.0, cheb_one(ya, yb, y, v), -vp);
+}
+// The sum of a fixed order, from its first two terms.
+__device__ inline double cheb_sum2(const double *ct, double v0, double v1)
+{
+    return fma(ct[1], v1, 0.5 * ct[0] * v0);
 }
 
 // A wave's part of its row's product with its columns x of the staged vector:
@@ -124,11 +139,30 @@ __device__ inline double trial_sum(const double (&h)[2][3], int n, const double 
     for (int s = 0; s < 2; ++s) {
         const int q = 64 * s + lane;
         const double c = q < n ? (q ? ct[q] : 0.5 * ct[0]) : 0.0;
-        t0 += c * h[s][0];
-        t1 += c * h[s][1];
-        t2 += c * h[s][2];
+        t0 = fma(c, h[s][0], t0);
+        t1 = fma(c, h[s][1], t1);
+        t2 = fma(c, h[s][2], t2);
     }
     return wave_sum3(t0, t1, t2, lane);
+}
+
+// The sum of a row's three entries (lanes 0 .. 2).
+__device__ inline double row_sum(double q) { return __shfl(q, 0) + __shfl(q, 1) + __shfl(q, 2); }
+
+// The two sums over G workgroups from their parts pr (zero past the last), in every lane.
+__device__ inline void group_sums(const double *pr, int G, int lane, double &sa, double &sb)
+{
+    sa = pr[2 * lane];
+    sb = pr[2 * lane + 1];
+    for (int g = 64; g < G; g += 64) {
+        sa += pr[2 * (g + lane)];
+        sb += pr[2 * (g + lane) + 1];
+    }
+#pragma unroll
+    for (int x = 32; x >= 1; x >>= 1) {
+        sa += __shfl_xor(sa, x);
+        sb += __shfl_xor(sb, x);
+    }
 }
 
 __device__ inline bool settles(double a, double b, int n, int nmax, double tol, double &ef)
@@ -192,7 +226,7 @@ __global__ __launch_bounds__(64 * B * WPR) __attribute__((amdgpu_waves_per_eu(WE
         if (eth) a.ud[o] = f;
     }
     if (!a.have_ddw && eth) a.ddw[o] = dd;
-    double vp = v0, v = ya * dd - yb * v0;   // V_0, V_1
+    double vp = v0, v = cheb_one(ya, yb, dd, v0);   // V_0, V_1
     if (eth && nmax > 2) put(a.words + 2 * o, v, a.epoch + 1);
     __syncthreads();
     for (int z = threadIdx.x; z < X; z += NT) sx[1][z] = 0.0;   // zero past 3N
@@ -210,9 +244,7 @@ __global__ __launch_bounds__(64 * B * WPR) __attribute__((amdgpu_waves_per_eu(WE
     };
     // this workgroup's share of dS.dS and dW.D dW, to every workgroup
     auto share = [&](double s, uint32_t ep) {
-        const double q = eth ? s * s : 0.0, t = eth ? v0 * dd : 0.0;
-        const double q3 = __shfl(q, 0) + __shfl(q, 1) + __shfl(q, 2);
-        const double r3 = __shfl(t, 0) + __shfl(t, 1) + __shfl(t, 2);
+        const double q3 = row_sum(eth ? s * s : 0.0), r3 = row_sum(eth ? v0 * dd : 0.0);
         if (lane == 0 && h0 == 0) {
             tred[r][0] = q3;
             tred[r][1] = r3;
@@ -234,17 +266,7 @@ __global__ __launch_bounds__(64 * B * WPR) __attribute__((amdgpu_waves_per_eu(WE
                          a.limit);
         if (threadIdx.x < 2 * SERIES_GROUPS) pr[threadIdx.x] = (int)threadIdx.x < 2 * G ? z[0] : 0.0;
         if (__syncthreads_or(!ok)) return false;
-        sa = pr[2 * lane];
-        sb = pr[2 * lane + 1];
-        for (int g = 64; g < G; g += 64) {
-            sa += pr[2 * (g + lane)];
-            sb += pr[2 * (g + lane) + 1];
-        }
-#pragma unroll
-        for (int x = 32; x >= 1; x >>= 1) {
-            sa += __shfl_xor(sa, x);
-            sb += __shfl_xor(sb, x);
-        }
+        group_sums(pr, G, lane, sa, sb);
         return true;
     };
     if (adapt) {
@@ -255,7 +277,7 @@ __global__ __launch_bounds__(64 * B * WPR) __attribute__((amdgpu_waves_per_eu(WE
             share(t, a.epoch + 2);
         }
     } else {
-        acc = 0.5 * ct[0] * v0 + ct[1] * v;
+        acc = cheb_sum2(ct, v0, v);
     }
     int n = 2;   // order of the last trial
     bool done = false;
@@ -271,7 +293,7 @@ __global__ __launch_bounds__(64 * B * WPR) __attribute__((amdgpu_waves_per_eu(WE
             if ((int)threadIdx.x + NT * k < n3) x[threadIdx.x + NT * k] = z[k];
         if (__syncthreads_or(!ok)) return;
         const double y = dot(p & 1, 0);
-        const double vn = 2.0 * (ya * y - yb * v) - vp;
+        const double vn = cheb_next(ya, yb, y, v, vp);
         if (adapt && p >= nst) {   // the trial of order p, formed before this product
             double sa, sb;
             if (!collect(a.epoch + p, sa, sb)) return;
@@ -290,7 +312,7 @@ __global__ __launch_bounds__(64 * B * WPR) __attribute__((amdgpu_waves_per_eu(WE
                 share(t, a.epoch + p + 1);
             }
         } else {
-            acc += ct[p] * v;
+            acc = fma(ct[p], v, acc);
         }
     }
     if (adapt && !done) {   // the trial of the largest order
@@ -315,100 +337,117 @@ __global__ __launch_bounds__(64 * B * WPR) __attribute__((amdgpu_waves_per_eu(WE
 }
 
 // One workgroup.  If the series above gave up, all of it again, alone: the rows
-// from memory, the terms in vh (adaptive order: all; else a ring of three).
+// from memory, a row per wave with the sums split as there (B rows per workgroup, WPR waves per
+// row, NB column blocks per wave), so that the result is the same to the bit; the terms in vh
+// (adaptive order: all; else a ring of three).
 // Then what follows the series: the adaptive state as k_trial_check leaves it,
 // E_f, the Euler update and the copies of drift and noise.
 constexpr int SF_NT = 1024;
+template <int B, int WPR, int NB>
 __global__ __launch_bounds__(SF_NT) void k_series_finish(SeriesArgs a, double *pos, double dt4,
                                                          double *drift, double *noise, double *e_f)
 {
     __shared__ double sx[3 * SERIES_MAX];
-    __shared__ double red[2][SF_NT / 64];
+    __shared__ double rsum[SERIES_MAX][2], pr[2 * SERIES_GROUPS];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, n3 = 3 * a.N;
     const bool adapt = a.st != nullptr;
     int n = a.rec->n;
     double ef = a.rec->ef;
     const bool redo = *a.abort_flag != 0;   // uniform
     if (redo) {
-        const int nb = a.ld / 128, nmax = a.n, nst = adapt ? a.st->n_start : 0;
+        const int nmax = a.n, nst = adapt ? a.st->n_start : 0, G = (a.N + B - 1) / B;
         const double ya = a.scal[2], yb = a.scal[3];
-        // y = D x for the vector x in memory, into memory
-        auto product = [&](const double *x, double *y) {
+        // every row's product with the vector x in memory: use(o, y) in the lanes of its
+        // entries o
+        auto product = [&](const double *x, auto use) {
             __syncthreads();
             for (int z = threadIdx.x; z < 3 * SERIES_MAX; z += SF_NT) sx[z] = z < n3 ? x[z] : 0.0;
             __syncthreads();
             for (int i = w; i < a.N; i += SF_NT / 64) {
-                const double *row = a.drow + (size_t)i * 6 * a.ld + 2 * lane;
-                double y0 = 0.0, y1 = 0.0, y2 = 0.0;
-                for (int u = 0; u < nb; ++u) {
-                    sr2 d[6];
+                double y = 0.0;
+#pragma unroll 1
+                for (int h = 0; h < WPR; ++h) {
+                    const double *row = a.drow + (size_t)i * 6 * a.ld + 128 * NB * h + 2 * lane;
+                    const int nb = min(max(a.ld / 128 - NB * h, 0), NB);
+                    double y0 = 0.0, y1 = 0.0, y2 = 0.0;
+#pragma unroll 1
+                    for (int u = 0; u < nb; ++u) {
+                        sr2 d[6];
 #pragma unroll
-                    for (int e = 0; e < 6; ++e)
-                        d[e] = *reinterpret_cast<const sr2 *>(row + (size_t)e * a.ld + 128 * u);
-                    row_block(d, sx + 6 * (lane + 64 * u), y0, y1, y2);
+                        for (int e = 0; e < 6; ++e)
+                            d[e] = *reinterpret_cast<const sr2 *>(row + (size_t)e * a.ld + 128 * u);
+                        row_block(d, sx + 3 * 128 * NB * h + 6 * (lane + 64 * u), y0, y1, y2);
+                    }
+                    const double s = wave_sum3(y0, y1, y2, lane);
+                    y = h ? y + s : s;
                 }
-                const double s = wave_sum3(y0, y1, y2, lane);
-                if (lane < 3) y[3 * i + lane] = s;
+                if (lane < 3) use(3 * i + lane, y);
             }
             __syncthreads();
         };
-        auto sums = [&](double &sa, double &sb) {   // out.out and dW.D dW
-            double p = 0.0, q = 0.0;
-            for (int z = threadIdx.x; z < n3; z += SF_NT) {
-                p += a.out[z] * a.out[z];
-                q += a.dw[z] * a.ddw[z];
-            }
-#pragma unroll
-            for (int x = 32; x >= 1; x >>= 1) {
-                p += __shfl_xor(p, x);
-                q += __shfl_xor(q, x);
-            }
-            if (lane == 0) {
-                red[0][w] = p;
-                red[1][w] = q;
+        // out.out and dW.D dW
+        auto sums = [&](double &sa, double &sb) {
+            for (int i = w; i < a.N; i += SF_NT / 64) {
+                const int o = 3 * i + min(lane, 2);
+                const double s = a.out[o], v0 = a.dw[o], dd = a.ddw[o];
+                const double q3 = row_sum(lane < 3 ? s * s : 0.0), r3 = row_sum(lane < 3 ? v0 * dd : 0.0);
+                if (lane == 0) {
+                    rsum[i][0] = q3;
+                    rsum[i][1] = r3;
+                }
             }
             __syncthreads();
-            sa = sb = 0.0;
-            for (int k = 0; k < SF_NT / 64; ++k) {
-                sa += red[0][k];
-                sb += red[1][k];
+            if (threadIdx.x < 2 * SERIES_GROUPS) {
+                const int g = threadIdx.x >> 1, c = threadIdx.x & 1;
+                double z = 0.0;
+                if (g < G) {
+                    z = rsum[g * B][c];
+                    for (int k = 1; k < B; ++k) z += g * B + k < a.N ? rsum[g * B + k][c] : 0.0;
+                }
+                pr[threadIdx.x] = z;
             }
+            __syncthreads();
+            group_sums(pr, G, lane, sa, sb);
             __syncthreads();
         };
         auto term = [&](int p) { return a.vh + (size_t)(adapt ? p : p % 3) * a.ps; };
-        if (!a.have_ddw) product(a.dw, a.ddw);
-        if (a.F) product(a.F, a.ud);
+        if (!a.have_ddw) product(a.dw, [&](int o, double y) { a.ddw[o] = y; });
+        if (a.F) product(a.F, [&](int o, double y) { a.ud[o] = y; });
         for (int z = threadIdx.x; z < n3; z += SF_NT) {
-            term(0)[z] = a.dw[z];
-            term(1)[z] = ya * a.ddw[z] - yb * a.dw[z];
-            if (!adapt) a.out[z] = 0.5 * a.coef[0] * a.dw[z] + a.coef[1] * term(1)[z];
+            const double v0 = a.dw[z], v1 = cheb_one(ya, yb, a.ddw[z], v0);
+            term(0)[z] = v0;
+            term(1)[z] = v1;
+            if (!adapt) a.out[z] = cheb_sum2(a.coef, v0, v1);
         }
         bool done = false;
+        ef = 0.0;
         for (int p = 1; p < nmax && !done; ++p) {
-            if (p > 1) {
-                product(term(p - 1), term(p));
-                for (int z = threadIdx.x; z < n3; z += SF_NT) {
-                    const double v = 2.0 * (ya * term(p)[z] - yb * term(p - 1)[z]) - term(p - 2)[z];
-                    term(p)[z] = v;
-                    if (!adapt) a.out[z] += a.coef[p] * v;
-                }
-            }
+            if (p > 1)
+                product(term(p - 1), [&](int o, double y) {
+                    const double v = cheb_next(ya, yb, y, term(p - 1)[o], term(p - 2)[o]);
+                    term(p)[o] = v;
+                    if (!adapt) a.out[o] = fma(a.coef[p], v, a.out[o]);
+                });
             n = p + 1;
-            if (adapt && n >= nst) {
-                const double *ct = a.coef + (size_t)n * SERIES_ORDERS;
-                for (int z = threadIdx.x; z < n3; z += SF_NT) {
-                    double s = 0.5 * ct[0] * term(0)[z];
-                    for (int q = 1; q < n; ++q) s += ct[q] * term(q)[z];
-                    a.out[z] = s;
-                }
-                __syncthreads();
-                double sa, sb;
-                sums(sa, sb);
-                done = settles(sa, sb, n, nmax, a.tol, ef);
-            }
-        }
-        if (!adapt) {
+            if (!adapt || n < nst) continue;
             __syncthreads();
+            for (int i = w; i < a.N; i += SF_NT / 64) {
+                double h[2][3];
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        h[s][c] = 64 * s + lane < n ? term(64 * s + lane)[3 * i + c] : 0.0;
+                const double t = trial_sum(h, n, a.coef + (size_t)n * SERIES_ORDERS, lane);
+                if (lane < 3) a.out[3 * i + lane] = t;
+            }
+            __syncthreads();
+            double sa, sb;
+            sums(sa, sb);
+            done = settles(sa, sb, n, nmax, a.tol, ef);
+        }
+        __syncthreads();
+        if (!adapt && a.want_ef) {
             double sa, sb;
             sums(sa, sb);
             settles(sa, sb, 0, 1, 0.0, ef);
@@ -460,14 +499,16 @@ void launch_series_coeffs(const Ctx &c, int n0, int n1, int explicit_, double dm
 
 struct SeriesForm {
     void (*kernel)(SeriesArgs);
+    void (*finish)(SeriesArgs, double *, double, double *, double *, double *);
     int rows, threads;
 };
 
 static SeriesForm series_form(int N, bool adaptive)
 {
-    if (N > SR_SMALL) return {k_series<SR_B, SR_WPR, SR_NBW>, SR_B, 64 * SR_B * SR_WPR};
-    if (!adaptive) return {k_series<8, 1, 4>, 8, 512};
-    return {N <= SR_SMALL / 2 ? k_series<4, 2, 2> : k_series<4, 2, 2, 4>, 4, 512};
+    if (N > SR_SMALL)
+        return {k_series<SR_B, SR_WPR, SR_NBW>, k_series_finish<SR_B, SR_WPR, SR_NBW>, SR_B, 64 * SR_B * SR_WPR};
+    if (!adaptive) return {k_series<8, 1, 4>, k_series_finish<8, 1, 4>, 8, 512};
+    return {N <= SR_SMALL / 2 ? k_series<4, 2, 2> : k_series<4, 2, 2, 4>, k_series_finish<4, 2, 2>, 4, 512};
 }
 
 int series_groups(int N, bool adaptive)
@@ -497,7 +538,8 @@ void launch_series(const SeriesArgs &a, hipStream_t s)
 void launch_series_finish(const SeriesArgs &a, double *pos, double dt4, double *drift, double *noise,
                           double *e_f, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_series_finish, dim3(1), dim3(SF_NT), 0, s, a, pos, dt4, drift, noise, e_f);
+    hipLaunchKernelGGL(series_form(a.N, a.st != nullptr).finish, dim3(1), dim3(SF_NT), 0, s, a, pos, dt4, drift,
+                       noise, e_f);
 }
 
 }  // namespace rpy

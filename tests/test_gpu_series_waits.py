@@ -39,3 +39,41 @@ def test_count(size):
         a.sqrt_adaptive(v, 0.04, 40.0, 1e-2, 60)
         assert rpy.rpy_series_stats(a.handle) == want
         assert rpy.rpy_series_stats(a.handle) == 0
+
+
+@pytest.mark.parametrize("size", SIZES)
+def test_alone_same_bits(size):
+    """With every wait denied: the same bits as the series kernel, of every output, at the
+    edges of its workgroups and column blocks, for fixed and adaptive orders and for steps
+    of every rule."""
+    w, pos, a = _setup(size)
+    b = rpy.context_for(w, cheb_keep=140)
+    rpy.rpy_series_wait(b.handle, -1)
+    v = _vec(w)
+    for c in (a, b):
+        c.build(pos)
+    # the product rules only where they bracket the spectrum (else the series diverges)
+    hi = 1.1 * a.lanczos_bounds(min(40, 3 * w.n), margin=0.0)[1]
+    for n in (2, 3, 4, 17, 65, 128):
+        for x, y in zip(*(c.sqrt_apply(v, n, 0.04, 40.0, want_ef=True) for c in (a, b))):
+            assert torch.equal(x, y)
+        assert torch.equal(*(c.sqrt_apply(v, n, 0.04, 40.0) for c in (a, b)))
+    for tol, start, nmax in ((1e-2, 0, 64), (1e-3, 2, 100), (1e-14, 3, 7), (1e-2, 0, 2), (1e-6, 30, 128)):
+        x, y = (c.sqrt_adaptive(v, 0.04, 40.0, tol, nmax, n_start=start, allow_etol=True) for c in (a, b))
+        assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1]) and x[2] == y[2]
+    assert a.order_stats() == b.order_stats()
+    assert a.status() == b.status()
+    for kw in (dict(n_cheb=2, d_min=0.04, d_max=40.0), dict(n_cheb=20, d_min=0.04, d_max=40.0),
+               dict(n_cheb=20, bounds_rule=rpy.BOUNDS_PAPER, bounds_C=60.0),
+               dict(n_cheb=0, d_min=0.04, d_max=40.0, tol=1e-2, n_max=60),
+               dict(n_cheb=0, bounds_rule=rpy.BOUNDS_PAPER, bounds_C=60.0, tol=1e-2, n_max=100)):
+        if "bounds_rule" in kw and a.bounds(60.0)[1] < hi:
+            continue
+        bp = rpy.make_bd_params(dt=1e-3, **kw)
+        p, q = pos.clone(), pos.clone()
+        for step in range(3):
+            x, y = (c.step(r, bp, seed=3, step=step, want=step != 1) for c, r in ((a, p), (b, q)))
+            for s, t in zip(x or (), y or ()):
+                assert torch.equal(s, t)
+        assert torch.equal(p, q)
+    assert rpy.rpy_series_stats(a.handle) == 0 and rpy.rpy_series_stats(b.handle) > 20
