@@ -68,7 +68,6 @@ struct SeriesGate {
     std::mutex m;
     int all = 0, big = 0;
     hipEvent_t ev = nullptr;
-    hipStream_t last = nullptr;
     bool set = false;
 };
 constexpr int GATE_DEVICES = 64;
@@ -110,12 +109,11 @@ static void run_series(rpy_ctx *x, const SeriesArgs &a, hipStream_t s)
     SeriesGate &g = g_gate[x->series_dev];
     std::lock_guard<std::mutex> lock(g.m);
     const bool order = g.big > 0 && g.all > 1;
-    if (order && g.set && g.last != s) (void)hipStreamWaitEvent(s, g.ev, 0);
+    // also behind one of the same handle: that of the per-thread default stream names another
+    // stream in every thread, and a handle can be given out again
+    if (order && g.set) (void)hipStreamWaitEvent(s, g.ev, 0);
     launch_series(a, s);
-    if (order) {
-        g.set = hipEventRecord(g.ev, s) == hipSuccess;
-        g.last = s;
-    }
+    if (order) g.set = hipEventRecord(g.ev, s) == hipSuccess;
 }
 
 static thread_local char g_err[256];

@@ -77,3 +77,43 @@ def test_alone_same_bits(size):
                 assert torch.equal(s, t)
         assert torch.equal(p, q)
     assert rpy.rpy_series_stats(a.handle) == 0 and rpy.rpy_series_stats(b.handle) > 20
+
+
+def test_threads_on_the_per_thread_stream():
+    """Four large boxes in four threads, each on its own per-thread default stream (one handle
+    value for all): their series are ordered, no wait runs out.  The threads live until the
+    device is idle, since that stream ends with its thread."""
+    class PerThread:
+        cuda_stream = 2   # hipStreamPerThread
+
+    n = 4
+    jobs = [_setup((40, 25)) for _ in range(n)]
+    v = _vec(jobs[0][0])
+    outs = [torch.empty_like(v) for _ in jobs]
+    for _, pos, c in jobs:
+        c.build(pos)
+    want = jobs[0][2].sqrt_apply(v, 128, 0.03, 40.0)
+    start, idle = threading.Barrier(n + 1), threading.Event()
+    enqueued = threading.Barrier(n + 1)
+    torch.cuda.synchronize()
+
+    def run(k):
+        start.wait()
+        for i in range(150):
+            rpy.chebyshev_sqrt_apply(jobs[k][2].handle, v, outs[k], 1, 128 - (i + k) % 3, 0.03, 40.0, stream=PerThread)
+        rpy.chebyshev_sqrt_apply(jobs[k][2].handle, v, outs[k], 1, 128, 0.03, 40.0, stream=PerThread)
+        enqueued.wait()
+        idle.wait()
+
+    th = [threading.Thread(target=run, args=(k,)) for k in range(n)]
+    for t in th:
+        t.start()
+    start.wait()
+    enqueued.wait()
+    torch.cuda.synchronize()
+    idle.set()
+    for t in th:
+        t.join()
+    for o in outs:
+        assert torch.equal(o, want)
+    assert [rpy.rpy_series_stats(c.handle) for _, _, c in jobs] == [0] * n
