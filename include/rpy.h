@@ -398,9 +398,12 @@ int rpy_profile_read(rpy_ctx *c, int kind, int64_t *count, double *total_ms);
  * GPU -- makes one workgroup run that series again alone: the same result, later.
  * rpy_series_stats: how many series since the last read ran that way (HOST output;
  * synchronises the stream and resets the count).  rpy_series_wait: the bound of a wait in
- * units of 10 ns (default 1000000; negative: no wait is granted, for tests). */
+ * units of 10 ns (default 1000000; negative: no wait is granted, for tests).
+ * rpy_series_number: the number of the next series' first term (they count through all 32 bits and
+ * then start again), larger than any before, for tests. */
 int rpy_series_stats(rpy_ctx *c, int64_t *alone, void *stream);
 void rpy_series_wait(rpy_ctx *c, int64_t ticks);
+void rpy_series_number(rpy_ctx *c, uint32_t first);
 
 /* Number of wave vectors in the half-space set used per product. */
 int rpy_num_kvectors(const rpy_ctx *c);

@@ -907,9 +907,16 @@ static bool by_series(const rpy_ctx *x, int m, int nmax, bool adaptive)
 // The arguments of such a series on V_0 = dw into out, n terms or, with st,
 // orders up to n.
 static SeriesArgs series_args(rpy_ctx *x, const double *dw, double *out, int n, AdaptState *st,
-                              double tol)
+                              double tol, hipStream_t s)
 {
     const Ctx &c = x->c;
+    // once in 2^32 terms (some hours of steps) the numbers start again at 1: words left from
+    // before, and those never written (0), must not carry one of them
+    if (x->series_epoch > UINT32_MAX - ((uint32_t)n + 2)) {
+        launch_fill(reinterpret_cast<double *>(c.series_words), 0.0,
+                    (size_t)(reinterpret_cast<unsigned long long *>(c.series_rec) - c.series_words), s);
+        x->series_epoch = 1;
+    }
     SeriesArgs a{};
     a.N = c.N;
     a.ld = c.row_ld;
@@ -936,6 +943,8 @@ static SeriesArgs series_args(rpy_ctx *x, const double *dw, double *out, int n, 
 }
 
 extern "C" void rpy_series_wait(rpy_ctx *x, int64_t ticks) { x->series_limit = ticks; }
+
+extern "C" void rpy_series_number(rpy_ctx *x, uint32_t first) { x->series_epoch = first ? first : 1; }
 
 extern "C" int rpy_series_stats(rpy_ctx *x, int64_t *alone, void *stream)
 {
@@ -1045,7 +1054,7 @@ static void series_explicit(rpy_ctx *x, const double *dw, double *out, int n0, i
     const Ctx &c = x->c;
     AdaptState *st = tol > 0 ? c.adapt : nullptr;
     launch_series_coeffs(c, n0, n, 1, d_min, d_max, st, s);
-    SeriesArgs a = series_args(x, dw, out, n, st, tol);
+    SeriesArgs a = series_args(x, dw, out, n, st, tol, s);
     a.want_ef = e_f != nullptr;
     {
         ProfScope ps(x, RPY_PROF_SYMV, s);
@@ -1564,7 +1573,7 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
     if (coef) {
         // the interval needs no product: drift, series and update in two launches
         AdaptState *st = adapt ? c.adapt : nullptr;
-        SeriesArgs a = series_args(x, w, x->dS, nmax, st, bp->tol);
+        SeriesArgs a = series_args(x, w, x->dS, nmax, st, bp->tol, s);
         a.F = x->F;
         a.want_ef = e_f != nullptr;
         {
@@ -1609,7 +1618,7 @@ extern "C" int bd_step(rpy_ctx *x, double *pos, const bd_params *bp, const doubl
         }
         if (series) {
             if (adapt) launch_series_coeffs(c, host_first, nmax, 0, 0.0, 0.0, c.adapt, s);
-            SeriesArgs a = series_args(x, w, x->dS, nmax, adapt ? c.adapt : nullptr, bp->tol);
+            SeriesArgs a = series_args(x, w, x->dS, nmax, adapt ? c.adapt : nullptr, bp->tol, s);
             a.have_ddw = 1;
             a.ddw = x->Y + (1 + nb) * nv;
             if (!adapt) a.coef = c.scal + 8;

@@ -73,6 +73,7 @@ _SIG = {
     "rpy_num_kvectors": (_i, [_v]),
     "rpy_series_stats": (_i, [_v, _P(ctypes.c_int64), _v]),
     "rpy_series_wait": (None, [_v, ctypes.c_int64]),
+    "rpy_series_number": (None, [_v, ctypes.c_uint32]),
     "rpy_profile_enable": (_i, [_v, _i]),
     "rpy_profile_read": (_i, [_v, _i, _P(ctypes.c_int64), _P(_d)]),
     "rpy_strerror": (ctypes.c_char_p, [_i]),

@@ -117,3 +117,28 @@ def test_threads_on_the_per_thread_stream():
     for o in outs:
         assert torch.equal(o, want)
     assert [rpy.rpy_series_stats(c.handle) for _, _, c in jobs] == [0] * n
+
+
+@pytest.mark.parametrize("size", [(10, 10), (32, 16), (40, 25)])
+def test_numbers_start_again(size):
+    """Where the terms' numbers run out of 32 bits, in every position of a call: no word of an
+    earlier call, and no word never written, is taken for one of this."""
+    w, pos, a = _setup(size)
+    v = _vec(w)
+    a.build(pos)
+    want = a.sqrt_apply(v, 9, 0.04, 40.0, want_ef=True)
+    ad = a.sqrt_adaptive(v, 0.04, 40.0, 1e-2, 60, n_start=2)
+    for back in range(1, 16):
+        # each time a new context: the words of the sums are still unwritten there
+        c = rpy.context_for(w, cheb_keep=140)
+        c.build(pos)
+        assert torch.equal(c.sqrt_apply(v, 9, 0.04, 40.0), want[0])
+        rpy._lib.rpy_series_number(c.handle, 2 ** 32 - back)
+        x = c.sqrt_apply(v, 9, 0.04, 40.0, want_ef=True)
+        assert torch.equal(x[0], want[0]) and torch.equal(x[1], want[1])
+        rpy._lib.rpy_series_number(c.handle, 2 ** 32 - back)
+        x = c.sqrt_adaptive(v, 0.04, 40.0, 1e-2, 60, n_start=2)
+        assert torch.equal(x[0], ad[0]) and torch.equal(x[1], ad[1]) and x[2] == ad[2]
+        assert torch.equal(c.sqrt_apply(v, 9, 0.04, 40.0), want[0])
+        assert rpy.rpy_series_stats(c.handle) == 0
+        c.close()
