@@ -81,12 +81,18 @@ __global__ void k_cell_fill(int N, double L, int nc, const double *__restrict__ 
     beads[start[c] + slot] = nu;
 }
 
-// Count, scan and fill by one workgroup with the counters in LDS, for at most CELL_ONE_N
-// beads in CELL_ONE_CELLS cells, in place of four launches, whose atomics on few addresses take
-// longer than all of this when the cells are few: low-memory step of N = 16000 (64 cells)
-// 10.46 -> 10.34 ms, two steps of the differentiation at N = 2000 4.27 -> 4.24 ms, the BF16
-// step of N = 2010 695 -> 687 us.
-constexpr int CELL_ONE_N = 32768, CELL_ONE_CELLS = 4096;
+// Count, scan and fill by one workgroup with the counters in LDS, in place of four launches,
+// whose atomics on few addresses take longer than all of this when the cells are few.  One
+// compute unit's scattered writes set the limits: forces of N beads in nc^3 cells, us, four
+// launches against this: N = 1000 60 -> 50 (nc = 4), 44 -> 37 (16); 6000 748 -> 706, 63 -> 61;
+// 8000 89.2 -> 84.8 (8), 64.9 -> 65.3 (16); 16000 192.5 -> 185.9 (8), 110.9 -> 112.9 (10),
+// 77.7 -> 84.8 (16); 32000 415 -> 410 (8), 315 -> 318 (9), 104 -> 125 (16).
+constexpr int CELL_ONE_N = 32768, CELL_ONE_CELLS = 4096;   // beads in at most CELL_FEW cells; LDS counters
+constexpr int CELL_MANY_N = 6144, CELL_FEW = 512;          // beads in more cells
+static bool cell_one(int N, int ncells)
+{
+    return ncells <= CELL_ONE_CELLS && N <= (ncells <= CELL_FEW ? CELL_ONE_N : CELL_MANY_N);
+}
 __global__ __launch_bounds__(1024) void k_cell_one(int N, double L, int nc, const double *__restrict__ rt,
                                                    int *__restrict__ start, int *__restrict__ beads)
 {
@@ -165,7 +171,7 @@ void launch_cell_list_into(int N, double L, int nc, const double *rt, int *start
 {
     if (nc < 3) return;
     const int ncells = nc * nc * nc;
-    if (N <= CELL_ONE_N && ncells <= CELL_ONE_CELLS) {
+    if (cell_one(N, ncells)) {
         hipLaunchKernelGGL(k_cell_one, dim3(1), dim3(1024), 0, s, N, L, nc, rt, start, beads);
         hipLaunchKernelGGL(k_cell_sort, dim3(ncells), dim3(256), 0, s, start, beads);
         return;
