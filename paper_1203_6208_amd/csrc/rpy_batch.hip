@@ -42,8 +42,8 @@ struct BoxDev {
 template <int TBB>
 __global__ void k_bwrap(int G, int nm1, const int *__restrict__ tile_box,
                         const BoxDev *__restrict__ boxes, const double *__restrict__ pos,
-                        double *__restrict__ rt, double *__restrict__ sfr,
-                        double2 *__restrict__ etab, int *__restrict__ flags)
+                        double *__restrict__ rt, double2 *__restrict__ etab,
+                        int *__restrict__ flags)
 {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= G) return;
@@ -59,7 +59,6 @@ __global__ void k_bwrap(int G, int nm1, const int *__restrict__ tile_box,
         double s = r / d.L;
         s = s - floor(s);
         rt[3 * (size_t)g + i] = d.L * s;
-        sfr[3 * (size_t)g + i] = s;
         double2 *tab = etab + (size_t)(3 * g + i) * nm1;
         for (int j = 0; j < nm1; ++j) {
             double sn, cs;
@@ -904,7 +903,7 @@ struct rpy_batch {
     int smooth_np = 0;            // terms of the polynomial pair form (0: erfc / exp form)
     bool smooth_single = true;    // one moved image component at most, in every box
     double *smooth = nullptr;     // [nbox][2 SMOOTH_MAX]
-    double *rt = nullptr, *sfr = nullptr;   // [G][3]
+    double *rt = nullptr;         // [G][3]
     double2 *etab = nullptr;      // [G][3][nmax + 1]
     double *d64 = nullptr;        // [nstor][6 TBB^2] packed planes
     float *d32 = nullptr;
@@ -961,7 +960,7 @@ extern "C" void rpy_batch_destroy(rpy_batch *b)
     if (b->cs) (void)hipStreamDestroy(b->cs);
     void *bufs[] = {b->boxes, b->tile_box, b->stor, b->chains, b->kvec, b->runs, b->krun,
                     b->kcoef, b->smooth, b->rt,
-                    b->sfr, b->etab, b->d64, b->d32, b->part, b->sfpart, b->tk, b->scal,
+                    b->etab, b->d64, b->d32, b->part, b->sfpart, b->tk, b->scal,
                     b->work, b->flags, b->stepc};
     for (void *p : bufs)
         if (p) (void)hipFree(p);
@@ -1107,7 +1106,6 @@ extern "C" int rpy_batch_create(rpy_batch **out, const rpy_params *bp, int nbox,
         (rc = balloc(&b->kvec, b->nk)) || (rc = balloc(&b->runs, runs.size())) ||
         (rc = balloc(&b->krun, b->nk)) || (rc = balloc(&b->kcoef, kc.size())) ||
         (rc = balloc(&b->smooth, smooth.size())) || (rc = balloc(&b->rt, G3)) ||
-        (rc = balloc(&b->sfr, G3)) ||
         (rc = balloc(&b->etab, G3 * (nmax + 1))) || (rc = balloc(&b->d64, te)) ||
         (lowp == RPY_PREC_F32 && (rc = balloc(&b->d32, te))) ||
         (rc = balloc(&b->part, (size_t)b->maxnbt * BRC * G3)) ||
@@ -1194,7 +1192,7 @@ template <int TBB> static void bwrap_build(rpy_batch *b, const double *pos, hipS
 {
     const unsigned gg = (unsigned)((b->G + 255) / 256);
     hipLaunchKernelGGL(k_bwrap<TBB>, dim3(gg), dim3(256), 0, s, b->G, b->nmax + 1, b->tile_box,
-                       b->boxes, pos, b->rt, b->sfr, b->etab, b->flags);
+                       b->boxes, pos, b->rt, b->etab, b->flags);
     if (b->smooth_np) {
         if (b->lowp == RPY_PREC_F32) bbuild_smooth<TBB, 1>(b, s);
         else bbuild_smooth<TBB, 0>(b, s);

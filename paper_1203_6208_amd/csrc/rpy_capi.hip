@@ -378,7 +378,7 @@ extern "C" void rpy_destroy(rpy_ctx *x)
     void *bufs[] = {c.rt, c.rt_ev, c.smooth, c.eph, c.etab, c.tile_ij, c.d64,
                     c.p32, c.p16, c.drow, c.series, c.part, c.xpk, c.ypart,
                     c.vpk, c.bpart, c.tkm,
-                    c.sfpart, c.tk, c.sfr, c.work, c.scal, c.red, c.flags, c.cell_start, c.lanc,
+                    c.sfpart, c.tk, c.work, c.scal, c.red, c.flags, c.cell_start, c.lanc,
                     c.adapt, c.tpart,
                     c.vhist, c.wgrad, c.xy, c.gpart, c.gk, c.mur,
                     c.lma_start, c.lma_beads, c.rt_sorted, c.v_sorted,
@@ -583,8 +583,7 @@ extern "C" int rpy_create(rpy_ctx **out, const rpy_params *p)
                      (rc = dalloc(&c.eph, (size_t)(c.N + 3) / 4 * ((c.nk + 15) / 16 * 16) * 4)))) ||
         (rc = dalloc(&c.sfpart, sfpart_elems(c))) ||
         (rc = dalloc(&c.tk, (size_t)6 * c.rhs_cap * (c.nk + (c.fold ? 2 * npair : 0)))) ||
-        (rc = dalloc(&c.sfr, nv)) ||
-        (rc = dalloc(&c.work, c.work_elems)) || (rc = dalloc(&c.scal, 8 + MAX_NCHEB)) ||
+                (rc = dalloc(&c.work, c.work_elems)) || (rc = dalloc(&c.scal, 8 + MAX_NCHEB)) ||
         (rc = dalloc(&c.red, 64)) || (rc = dalloc(&c.flags, 4)) ||
         (rc = dalloc(&c.lanc, 2 * MAX_LANCZOS)) ||
         (rc = dalloc(&c.adapt, 1)) ||
@@ -801,8 +800,8 @@ static bool prec_ok(const Ctx &c, int prec)
 // (whose structure-factor workgroups also write T_k of v), then the
 // reciprocal back-projection + epilogue.  With 5..16 vectors the block path
 // runs instead: matrix-core tile product, FP64 matrix-core structure factors
-// and back-projection.  The low-memory form: the matrix-free real-space
-// product, structure-factor partials, their reduction, the back-projection.
+// and back-projection; by rows of D, one launch.  The low-memory form: the matrix-free
+// real-space product, T_k of v, the back-projection.
 // prepacked: v is the output of the previous product of the same series,
 // whose block epilogue (f.pack) already wrote it in the packed layouts.
 static void product(rpy_ctx *x, const double *v, int m, int prec, const EpiArgs &f,
@@ -1440,7 +1439,6 @@ extern "C" int rpy_bounds(rpy_ctx *x, int rule, double C, double *d_min, double 
     return fl ? RPY_ENONFINITE : RPY_OK;
 }
 
-// Springs plus excluded volume; `rt` holds the wrapped positions of `pos`.
 // F += the excluded-volume forces at the wrapped positions rt.
 static void ev_forces(rpy_ctx *x, const double *rt, double zstar, double dstar, double rcut, double *F,
                       hipStream_t s)

@@ -46,7 +46,6 @@ constexpr double XSER = 0.75;   // use the series for alpha*r below this
 constexpr int MAX_RHS = 16;
 constexpr int MAX_NCHEB = 512;
 constexpr int MAX_LANCZOS = 2048;
-constexpr int KSLICE = 16;      // wave-vector / tile-column slices of the back-projection
 constexpr int SF_BEADS = 64;    // beads per structure-factor partial
 
 // ---------------------------------------------------------------- pair terms
@@ -433,7 +432,6 @@ struct Ctx {
     // device buffers
     double *rt = nullptr;        // wrapped positions [N][3] of the built D
     double *rt_ev = nullptr;     // wrapped positions for stand-alone force calls
-    double *sfr = nullptr;       // fractional coordinates s = r/L - floor(r/L) [N][3]
     double2 *etab = nullptr;     // phases [N][3][nmax+1]
     double2 *axt = nullptr;      // the same phases bead-contiguous, [3 (nmax + 1)][N] (behind etab)
     SfCols sf2, sf4;             // columns of wave vectors (rpy_sf.h), cut after 2 and after 4 n_z
@@ -527,13 +525,13 @@ struct WrapArgs {
     int N, nmax;
     double L;
     const double *pos;
-    double *rt, *sfr;
+    double *rt;
     double2 *etab, *axt;
     int *flags;
 };
 inline WrapArgs wrap_args(const Ctx &c, const double *pos)
 {
-    return {c.N, c.nmax, c.L, pos, c.rt, c.sfr, c.etab, c.axt, c.flags};
+    return {c.N, c.nmax, c.L, pos, c.rt, c.etab, c.axt, c.flags};
 }
 inline int wrap_threads(const Ctx &c) { return c.n3 * (c.nmax + 1); }
 void launch_wrap_tables(const Ctx &c, const double *pos, hipStream_t s);

@@ -21,10 +21,7 @@ __device__ inline void wrap_entry(const WrapArgs &a, int t)
     }
     double s = r / a.L;
     s = s - floor(s);
-    if (j == 0) {
-        a.rt[3 * (size_t)nu + i] = a.L * s;
-        a.sfr[3 * (size_t)nu + i] = s;
-    }
+    if (j == 0) a.rt[3 * (size_t)nu + i] = a.L * s;
     double sn, cs;
     sincospi(2.0 * j * s, &sn, &cs);
     const double2 p = make_double2(cs, sn);

@@ -10,8 +10,8 @@
 // every wave keeps its bead row of D in registers for the whole series, and the
 // workgroups pass each new vector to each other through memory: every double
 // travels as two 8-byte words that carry half of it and the number of the
-// term, so a reader polls the words themselves until all of them are of the
-// term it waits for -- no barrier, no fence, no separate flag, only relaxed
+// term (the flag-in-data words of low-latency collective protocols), so a reader polls
+// the words themselves until all of them are of the term it waits for -- no barrier, no fence, no separate flag, only relaxed
 // atomic accesses at device scope.  Two slots suffice: a workgroup writes V_{p+2}
 // after it has read all of V_{p+1}, so every workgroup has read all of V_p by then.
 //
