@@ -186,7 +186,8 @@ PairConst make_pair_const(double L, double a, double alpha, double rc)
 // the closed form above.
 static void smooth_exact(long double u, long double v[4])
 {
-    const long double x = sqrtl(u), isp = 1.0L / sqrtl(acosl(-1.0L));
+    static const long double isp = 1.0L / sqrtl(acosl(-1.0L));
+    const long double x = sqrtl(u);
     if (x < 0.75L) {
         long double un = 1, fact = 1;   // u^n, n!
         v[0] = v[1] = v[2] = v[3] = 0;
@@ -213,24 +214,39 @@ static void smooth_exact(long double u, long double v[4])
 SmoothBasis::SmoothBasis(double um_) : um(um_)
 {
     constexpr int NN = SMOOTH_NN;
-    long double cs[4 * NN], c[4][NN];   // cos(pi i / (2 NN)), one period
-    for (int i = 0; i < 4 * NN; ++i) cs[i] = cosl(acosl(-1.0L) * i / (2 * NN));
+    static const struct Cosines {   // cos(pi i / (2 NN)), one period
+        long double v[4 * NN];
+        Cosines()
+        {
+            const long double pi = acosl(-1.0L);
+            for (int i = 0; i < 4 * NN; ++i) v[i] = cosl(pi * i / (2 * NN));
+        }
+    } cosines;
+    const long double *cs = cosines.v;
+    long double c[4][NN];
     for (int j = 0; j < NN; ++j) {
         long double v[4];
         smooth_exact(0.5L * um * (cs[2 * j + 1] + 1), v);
         for (int w = 0; w < 4; ++w) f[w][j] = v[w];
     }
-    for (int w = 0; w < 4; ++w)
-        for (int k = 0; k < NN; ++k) {
-            long double s = 0;
-            for (int j = 0; j < NN; ++j) s += f[w][j] * cs[k * (2 * j + 1) % (4 * NN)];
-            c[w][k] = (k ? 2.0L : 1.0L) * s / NN;
+    for (int k = 0; k < NN; ++k) {
+        long double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+        for (int j = 0, i = k; j < NN; ++j) {   // i = k (2 j + 1) within the period
+            s0 += f[0][j] * cs[i];
+            s1 += f[1][j] * cs[i];
+            s2 += f[2][j] * cs[i];
+            s3 += f[3][j] * cs[i];
+            i += 2 * k;
+            if (i >= 4 * NN) i -= 4 * NN;
         }
+        const long double s[4] = {s0, s1, s2, s3};
+        for (int w = 0; w < 4; ++w) c[w][k] = (k ? 2.0L : 1.0L) * s[w] / NN;
+    }
     // powers of z from the Chebyshev polynomials T_k = 2 z T_{k-1} - T_{k-2}
     long double t0[SMOOTH_MAX] = {1}, t1[SMOOTH_MAX] = {0, 1}, m[4][SMOOTH_MAX] = {};
     for (int k = 0; k < SMOOTH_MAX; ++k) {
         for (int w = 0; w < 4; ++w)
-            for (int i = 0; i <= k; ++i) m[w][i] += c[w][k] * t0[i];
+            for (int i = k & 1; i <= k; i += 2) m[w][i] += c[w][k] * t0[i];   // T_k is even or odd
         long double t2[SMOOTH_MAX];
         for (int i = 0; i < SMOOTH_MAX; ++i) t2[i] = (i ? 2 * t1[i - 1] : 0) - t0[i];
         memcpy(t0, t1, sizeof t0);
