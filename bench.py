@@ -189,7 +189,7 @@ def profile_pass(st, rpy, steps, torch):
     out = {}
     names = {rpy.PROF_SYMV: "tile_product", rpy.PROF_SYMV_MULTI: "tile_product_2_to_4_vectors",
              rpy.PROF_BUILD: "tile_build", rpy.PROF_KSPACE: "sf_reduce",
-             rpy.PROF_EPI: "kspace_epilogue", rpy.PROF_OTHER: "forces_noise_side_stream"}
+             rpy.PROF_EPI: "kspace_epilogue", rpy.PROF_OTHER: "prelude"}
     for k, nm in names.items():
         n, ms = rpy.rpy_profile_read(ctx.handle, k)
         out[nm] = {"launches": n, "total_ms": ms, "avg_us": 1e3 * ms / max(n, 1)}
@@ -894,6 +894,23 @@ def measured_traffic(t=TRAFFIC, key=None):
     return t["bytes_per_launch"] if key is None else t["bytes_per_launch"][key]
 
 
+REPORTS = ("step_configurations", "kernels", "forms", "eigen")
+
+
+def compact(line: dict) -> dict:
+    """The line as printed, which has to fit the 16 KB of output that a harness may keep: of
+    the reports beside the headline the per-state tables (on stderr) are left out and
+    floats are given to six digits; everything else is whole."""
+    def short(x):
+        if isinstance(x, dict):
+            return {k: len(v) if k == "states" and isinstance(v, list) else short(v) for k, v in x.items()}
+        if isinstance(x, list):
+            return [short(v) for v in x]
+        return float(f"{x:.6g}") if isinstance(x, float) else x
+
+    return {k: short(v) if k in REPORTS else v for k, v in line.items()}
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -976,8 +993,7 @@ def main():
     if studies:
         torch.cuda.empty_cache()
         eigen["scaling_with_N"] = eigen_scaling(torch, rpy, inputs)
-        print(f"# eigen scaling {json.dumps(eigen['scaling_with_N']['fit'])}", file=sys.stderr,
-              flush=True)
+        print(f"# eigen scaling {json.dumps(eigen['scaling_with_N'])}", file=sys.stderr, flush=True)
         forms["theta_statics"] = theta_statics(torch, rpy, inputs, steps=args.theta_steps)
         print(f"# theta statics {json.dumps(forms['theta_statics'])}", file=sys.stderr,
               flush=True)
@@ -1022,7 +1038,7 @@ def main():
     }
     if otab is not None:
         line["oracle_table"] = otab
-    print(json.dumps(line))
+    print(json.dumps(compact(line)))
 
 
 if __name__ == "__main__":
