@@ -9,13 +9,12 @@ namespace rpy {
 // The tables of one bead, axis and index per thread (wrap_entry).
 __global__ void k_wrap_tables(WrapArgs a)
 {
-    wrap_entry(a, blockIdx.x * blockDim.x + threadIdx.x);
+    wrap_entry(a, blockIdx.x);
 }
 
 void launch_wrap_tables(const Ctx &c, const double *pos, hipStream_t s)
 {
-    const int bs = 256, n = wrap_threads(c);
-    hipLaunchKernelGGL(k_wrap_tables, dim3((n + bs - 1) / bs), dim3(bs), 0, s, wrap_args(c, pos));
+    hipLaunchKernelGGL(k_wrap_tables, dim3(wrap_groups(c)), dim3(256), 0, s, wrap_args(c, pos));
 }
 
 // Wrapped positions only; a non-finite coordinate raises flags[0] as above.

@@ -533,7 +533,7 @@ inline WrapArgs wrap_args(const Ctx &c, const double *pos)
 {
     return {c.N, c.nmax, c.L, pos, c.rt, c.etab, c.axt, c.flags};
 }
-inline int wrap_threads(const Ctx &c) { return c.n3 * (c.nmax + 1); }
+inline int wrap_groups(const Ctx &c) { return 3 * (c.nmax + 1) * ((c.N - 1) / 256 + 1); }
 void launch_wrap_tables(const Ctx &c, const double *pos, hipStream_t s);
 // wrapped positions only (into `rt`), for forces of positions other than D's
 void launch_wrap_positions(const Ctx &c, const double *pos, double *rt, hipStream_t s);

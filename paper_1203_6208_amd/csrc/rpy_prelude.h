@@ -5,15 +5,16 @@
 
 namespace rpy {
 
-// Thread t = e N + nu, e = axis (nmax + 1) + j: the phase e^{i 2 pi j s} (s = r/L
+// Workgroup b (256 threads) of wrap_groups: 256 beads of entry e = axis (nmax + 1) + j, the
+// phase e^{i 2 pi j s} (s = r/L
 // wrapped) by bead (etab) and bead-contiguous (axt); with j = 0 the wrapped position
 // rt = L (r/L - floor(r/L)).  A non-finite coordinate raises flags[0] and is
 // replaced by 0 so that every later kernel still runs on finite data.
-__device__ inline void wrap_entry(const WrapArgs &a, int t)
+__device__ inline void wrap_entry(const WrapArgs &a, int b)
 {
-    const int nm1 = a.nmax + 1;
-    if (t >= 3 * nm1 * a.N) return;
-    const int e = t / a.N, nu = t - e * a.N, i = e / nm1, j = e - i * nm1;
+    const int nm1 = a.nmax + 1, nb = (a.N - 1) / 256 + 1, e = b / nb;
+    const int nu = 256 * (b - e * nb) + threadIdx.x, i = e / nm1, j = e - i * nm1;
+    if (nu >= a.N) return;
     double r = a.pos[3 * (size_t)nu + i];
     if (!isfinite(r)) {
         if (j == 0) atomicOr(a.flags, 1);

@@ -439,7 +439,7 @@ __global__ __launch_bounds__(256) void k_prelude(PreludeArgs a)
     }
     b -= a.ncoef;
     if (b < a.bwrap) {
-        wrap_entry(a.wrap, b * 256 + threadIdx.x);
+        wrap_entry(a.wrap, b);
         return;
     }
     b -= a.bwrap;
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(256) void k_prelude(PreludeArgs a)
 
 void launch_prelude(const Ctx &c, PreludeArgs a, hipStream_t s)
 {
-    a.bwrap = (wrap_threads(c) + 255) / 256;
+    a.bwrap = wrap_groups(c);
     a.bnoise = (c.n3 + 1023) / 1024;
     hipLaunchKernelGGL(k_prelude, dim3(a.ncoef + a.bwrap + a.bnoise + (c.N + 255) / 256), dim3(256), 0, s,
                        a);
