@@ -101,9 +101,9 @@ __device__ inline void row_block(const sr2 (&d)[6], const double *x, double &y0,
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const double x0 = x[3 * q], x1 = x[3 * q + 1], x2 = x[3 * q + 2];
-        y0 += fma(d[2][q], x2, fma(d[1][q], x1, d[0][q] * x0));
-        y1 += fma(d[4][q], x2, fma(d[3][q], x1, d[1][q] * x0));
-        y2 += fma(d[5][q], x2, fma(d[4][q], x1, d[2][q] * x0));
+        y0 = fma(d[2][q], x2, fma(d[1][q], x1, fma(d[0][q], x0, y0)));
+        y1 = fma(d[4][q], x2, fma(d[3][q], x1, fma(d[1][q], x0, y1)));
+        y2 = fma(d[5][q], x2, fma(d[4][q], x1, fma(d[2][q], x0, y2)));
     }
 }
 
