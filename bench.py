@@ -42,21 +42,21 @@ HBM_PEAK_GBS = 8000.0
 # what the L2 fetches over the fabric, Infinity-Cache hits included.  Valid only for the
 # kernel source they were measured on (sha256 of the kernel's source files);
 # otherwise reported as null.
-TRAFFIC = {"src_sha256": "d7edc8f726eca2d70bb3b1691d65729860931f0c40ad8578ec34293254da54ca",
+TRAFFIC = {"src_sha256": "9006521277a21008e3df4990e9c1a5f8e1882b6b363c770c4348abc5b4d76ef2",
            "files": ("rpy_apply.hip", "rpy_symv_tile.inc", "rpy_sf.h", "rpy_internal.h"),
-           "bytes_per_launch": 413235405}
+           "bytes_per_launch": 412863319}
 # The matrix-core tile kernel (k_block_tiles) of a 16-vector product: tile and
 # vector reads plus the per-run (FP64) or per-tile partial sums it writes.
-TRAFFIC_BLOCK = {"src_sha256": "d4be3253b895d4750875a4c735c0adca985788c578e5753a5e731b6b8ef9e326",
+TRAFFIC_BLOCK = {"src_sha256": "79b976812f28ba0dcc0e19c878d1fec14d3ad8e074c6a342bc53fc44ae10c879",
                  "files": ("rpy_block.hip", "rpy_internal.h"),
-                 "bytes_per_launch": {"f64": 445821133 + 55590912,
-                                      "f32": 217495552 + 48772915,
-                                      "bf16": 107513651 + 48771277}}
+                 "bytes_per_launch": {"f64": 446045428 + 55590912,
+                                      "f32": 217432443 + 48772996,
+                                      "bf16": 107464309 + 48771225}}
 # The batched FP32 tile product over the 256-box ensemble (k_bsymv<64, float, 1>),
 # same calibration (FETCH x 2.0, WRITE x 1.0).
-TRAFFIC_BATCH = {"src_sha256": "d96563c43991de205e5e8591bb63e0c4e653cc5435510297fb1597e8436471fb",
+TRAFFIC_BATCH = {"src_sha256": "b4d126142dbb6a90850e9ef61e231b19fd9acb896ab695918ab0ba73f7bc5050",
                  "files": ("rpy_batch.hip", "rpy_sf.h", "rpy_internal.h"),
-                 "bytes_per_launch": 4843232666}
+                 "bytes_per_launch": 4845545320}
 METRIC = "BD steps/s at N=4000 (Ewald-RPY D·F + Chebyshev √D·dW) vs plain FP64"
 BOUNDS_C = 60.0   # C of the paper's bound rule; chosen so that d_min < lambda_min here
 TOL_EF = 1e-2     # E_f tolerance of the headline's adaptive order

@@ -20,7 +20,10 @@
  *    on the device; it is reported by the next synchronising call
  *    (rpy_status, rpy_bounds) as RPY_ENONFINITE.
  *  - A context is not thread-safe: calls on one context must be ordered on a
- *    single stream by the caller.  Distinct contexts are independent.
+ *    single stream by the caller.  Distinct contexts are independent: their calls may run
+ *    at the same time from several threads and streams.  (On one device the one-launch series,
+ *    rpy_series_stats, of a box that needs most of its compute units waits, by an event, for
+ *    those of other contexts.)
  */
 #ifndef RPY_H
 #define RPY_H
@@ -88,7 +91,12 @@ typedef struct {
                           stored (upper tiles, the 6 distinct entries of
                           each symmetric 3 x 3 bead-pair block: about
                           3N(N+1) doubles, read by every product of any
-                          number of vectors).
+                          number of vectors).  With lowp = FP64 and at most 1024
+                          beads (1280 with more than 1024 wave vectors) also
+                          the complete D by bead rows, reciprocal part included: 6 N
+                          doubles per bead row (N rounded up to a multiple
+                          of 128), 49 MB at N = 1000, read by products of 1 to 4
+                          vectors where that is the faster form (rpy_apply).
                           1: low-memory form (section "Low memory
                           algorithm"): nothing of size N^2 is stored; every
                           product recomputes the real-space sum over a cell
@@ -124,7 +132,9 @@ void rpy_destroy(rpy_ctx *c);
  * into the context's symmetric tile storage (plus the low-precision copy if
  * lowp is set).  The reciprocal-space part is applied per product
  * (rpy_apply), as in the paper's high-memory algorithm (section "Optimisation
- * of each Euler time step"). */
+ * of each Euler time step").  FP64 boxes of at most 256 beads: the complete D by bead rows
+ * instead, the reciprocal part added to every block; the tiles are then written by
+ * the first call that reads them. */
 int rpy_ewald_build(rpy_ctx *c, const double *pos, void *stream);
 
 /* out = D . v for m right-hand sides (v, out: device [m][N][3], not
@@ -137,8 +147,18 @@ int rpy_ewald_build(rpy_ctx *c, const double *pos, void *stream);
  * accumulation inside each 64-bead tile, BF16 tiles likewise (the vectors
  * enter as a hi + lo BF16 pair, so only D is rounded to BF16); the
  * reciprocal sum and the sums over tiles stay FP64.  Results are
- * deterministic run to run.  Errors: RPY_EINVAL (m outside 1..max_rhs, prec
- * not built, null pointers). */
+ * deterministic run to run.
+ * FP64 boxes that keep D by rows (rpy_params): products of 1 to 4 vectors read the rows in
+ * calls of at most 256 beads, in calls that make at least 8 products (a square root of 9 terms, a step of 8,
+ * Lanczos), and past 1024 beads at least 16; others read the tiles.  The form follows from the
+ * box, m and the call's number of products, not from earlier calls, so the same call on the same
+ * positions gives the same bits.  The two forms agree to rounding (1e-12).
+ * Graph capture: any call that does not synchronise may be captured.  A captured call with 1 to 4
+ * vectors reads the rows up to 256 beads, else the tiles, and never runs the one-launch series
+ * (rpy_series_stats), so a replayed step agrees with an eager one to rounding, not to
+ * the bit.  A graph of products works on the positions last set before its replay, by an eager
+ * call or by a replay; eager calls give the same bits whether or not others were captured.
+ * Errors: RPY_EINVAL (m outside 1..max_rhs, prec not built, null pointers). */
 int rpy_apply(rpy_ctx *c, const double *v, double *out, int m, int prec,
               void *stream);
 
@@ -229,7 +249,7 @@ int chebyshev_sqrt_adaptive(rpy_ctx *c, const double *dw, double *out, int m,
  * rpy_status, and rpy_order_stats reports the orders used.
  * prec selects the arithmetic of the Chebyshev products from V_1 on; the
  * drift, the bounds and the first product D.dW (taken in the same FP64 pass
- * over D as D.F, and reused by E_f) always use FP64.  The forces and the device noise run on a second
+ * over D as D.F, and reused by E_f) always use FP64.  The excluded-volume forces run on a second
  * stream owned by the context, forked from `stream` after the wrap and
  * joined back before the drift product (event record / wait, no host
  * synchronisation), so that they overlap the tile build; everything the call
@@ -391,11 +411,13 @@ enum {
 int rpy_profile_enable(rpy_ctx *c, int cap);
 int rpy_profile_read(rpy_ctx *c, int kind, int64_t *count, double *total_ms);
 
-/* FP64 boxes of at most 1024 beads run the Chebyshev series of one vector (of at most 128
- * terms, outside graph capture) in one launch whose workgroups wait for each other, where the device
- * holds them all at once.  A wait that is not answered
- * within 10 ms -- the launch was only partly resident beside other work on the
- * GPU -- makes one workgroup run that series again alone: the same result, later.
+/* FP64 boxes of at most 1024 beads that go by rows (rpy_apply) run the Chebyshev series of one
+ * vector in one launch whose workgroups wait for each other, if its largest order (n_cheb, with an
+ * adaptive order n_max) is at most 128, the wave vectors have |n_i| <= 8, the call is not captured and the
+ * device holds all the workgroups at once; else one launch per product.  A wait that is not answered
+ * within 10 ms -- the launch was only partly resident: beside long kernels of other streams or
+ * the series of another process, or on a stream that may use only a part of the compute units --
+ * makes one workgroup run that series again alone: the same bits, later.
  * rpy_series_stats: how many series since the last read ran that way (HOST output;
  * synchronises the stream and resets the count).  rpy_series_wait: the bound of a wait in
  * units of 10 ns (default 1000000; negative: no wait is granted, for tests).

@@ -969,7 +969,7 @@ extern "C" int rpy_series_stats(rpy_ctx *x, int64_t *alone, void *stream)
     if (x->c.series) {
         HIP_TRY(hipMemcpyAsync(&n, x->c.series_abort + 1, sizeof n, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
-        if (n) HIP_TRY(hipMemset(x->c.series_abort + 1, 0, sizeof n));
+        if (n) HIP_TRY(hipMemsetAsync(x->c.series_abort + 1, 0, sizeof n, s));
     }
     *alone = n;
     return RPY_OK;

@@ -4,7 +4,9 @@
 //   r >= 2a : M1 = Omega_A(r) - S(x^2)          (eq. M1)
 //   r <  2a : M1 + M* = Omega_B(r) - S(x^2)     (eq. cor5)
 // so one polynomial in r^2 per coefficient serves every image, and the only
-// special function left is 1/sqrt(r^2).
+// special function left is 1/sqrt(r^2).  Near r_c a block is the small difference of two terms
+// of order a/r: its entries are accurate to the rounding of those (1e-17 of the largest
+// entries of D), not to their own size as with erfc.
 #pragma once
 
 #include "rpy_internal.h"
