@@ -898,7 +898,7 @@ REPORTS = ("step_configurations", "kernels", "forms", "eigen")
 
 
 def compact(line: dict) -> dict:
-    """The line as printed, which has to fit the 16 KB of output that a harness may keep: of
+    """The line as printed, short enough to be whole where output is cut at 16 KB: of
     the reports beside the headline the per-state tables (on stderr) are left out and
     floats are given to six digits; everything else is whole."""
     def short(x):
